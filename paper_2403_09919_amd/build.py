@@ -1,9 +1,11 @@
-"""Builds the HIP library (librd.so) for gfx950 with hipcc, in-tree."""
+"""Builds the HIP library (librd.so) for gfx950 with hipcc and the Python extension that calls it
+(_rdcall.so, host code against torch's headers) with g++, both in-tree."""
 from __future__ import annotations
 
 import os
 import subprocess
 import sys
+import sysconfig
 from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
@@ -11,6 +13,7 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "librd.so")
+CALL = os.path.join(HERE, "_rdcall.so")
 SOURCES = ["rd_api.hip", "rd_dedup.hip", "rd_tree_attn.hip", "rd_tree_attn_bf16.hip",
            "rd_tree_attn_f16.hip", "rd_tree_attn_paged.hip", "rd_tree_attn_rope_bf16.hip", "rd_tree_attn_rope_f16.hip", "rd_tree_attn_f32.hip", "rd_accept.hip", "rd_accept_sample.hip", "rd_commit.hip", "rd_rope.hip", "rd_draft.hip"]
 # -packed-fp32-ops is switched off for device code on purpose (hipcc's host pass does not
@@ -32,18 +35,28 @@ def _run(cmd, verbose):
 
 
 def build(verbose: bool = False, extra_flags=()) -> str:
-    """Compile every kernel source and link paper_2403_09919_amd/librd.so (always recompiles)."""
+    """Compile every source and link paper_2403_09919_amd/librd.so and _rdcall.so (always recompiles)."""
     hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
     os.makedirs(OBJ, exist_ok=True)
     inc = ["-I", os.path.join(ROOT, "include"), "-I", CSRC]
     objs = [os.path.join(OBJ, s.replace(".hip", ".o")) for s in SOURCES]
     jobs = [[hipcc, *FLAGS, *extra_flags, *inc, "-c", os.path.join(CSRC, s), "-o", o]
             for s, o in zip(SOURCES, objs)]
+    import torch
+    call_obj = os.path.join(OBJ, "rd_call.o")
+    troot = os.path.dirname(torch.__file__)
+    jobs.append(["g++", "-O2", "-std=c++17", "-fPIC", "-D__HIP_PLATFORM_AMD__", "-DUSE_ROCM", "-Wall", *inc[:2],
+                 "-isystem", os.path.join(troot, "include"), "-isystem", os.path.join(os.path.dirname(os.path.dirname(hipcc)), "include"),
+                 "-isystem", sysconfig.get_paths()["include"], "-c", os.path.join(CSRC, "rd_call.cpp"), "-o", call_obj])
     with ThreadPoolExecutor(max_workers=min(8, len(jobs))) as ex:
         list(ex.map(lambda c: _run(c, verbose), jobs))
     tmp = LIB + ".tmp%d" % os.getpid()
-    _run([hipcc, "--offload-arch=gfx950", "-shared", "-fPIC", *objs, "-o", tmp], verbose)
+    _run([hipcc, "--offload-arch=gfx950", "-shared", "-fPIC", "-Wl,-soname,librd.so", *objs, "-o", tmp], verbose)
     os.replace(tmp, LIB)
+    tmp = CALL + ".tmp%d" % os.getpid()
+    _run(["g++", "-shared", "-fPIC", call_obj, LIB, "-L" + os.path.join(troot, "lib"), "-ltorch_python", "-lc10", "-lc10_hip",
+          "-ltorch_cpu", "-Wl,-rpath,$ORIGIN", "-o", tmp], verbose)
+    os.replace(tmp, CALL)
     return LIB
 
 
