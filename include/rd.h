@@ -340,7 +340,7 @@ int rd_commit(const void *k_new, const void *v_new, const int32_t *accepted_idx,
  * For b, h, packed row p < n_packed[b], pos = position_ids[b][p] clamped to [0, max_pos-1], i < D/2:
  *     y[i]       = x[i] * cos_tab[pos][i] - x[i + D/2] * sin_tab[pos][i]
  *     y[i + D/2] = x[i + D/2] * cos_tab[pos][i] + x[i] * sin_tab[pos][i]
- * ("rotate half" pairing), computed in fp32 with every product rounded before the sum, rounded once
+ * ("rotate half" pairing), computed in fp32 (sine products rounded, cosine products by fused multiply-add), rounded once
  * to the storage type, in place.  Rows p >= n_packed[b] are left untouched.
  *
  *   q, k_new : [B,H,N,D], element type by `dt` (any of the three), 32-byte aligned; either may be

@@ -1,17 +1,15 @@
-// Pieces shared by the bf16 (MFMA) and fp32 tree-attention kernels: the split plan, the
-// partial-result workspace layout and the in-kernel combine done by the last workgroup
-// of a (sequence, head) to finish.
+// Pieces shared by the tree-attention kernels: the launch plans and the exchange in which the last
+// workgroup of a (sequence, head) to finish learns that it is.
 //
-// Work decomposition (flash-decoding style).  The keys a packed row may see are the
-// context keys 0..ctx_len-1 plus the packed keys allowed by its mask row (Sec. 3.3).  For
-// each (sequence, head) the context keys are cut into S contiguous ranges and the packed
-// keys form one more range; one workgroup per range computes, for all packed rows at once,
-// a partial softmax state (running max m, sum l, unnormalised output O) and stores it in
-// the workspace.  The workgroup that finishes last for that (sequence, head) — found with
-// a device-scope counter — merges the S+1 partials, normalises and writes the output, so
-// the whole operation is a single launch.
+// Work decomposition (flash-decoding style).  The keys a packed row may see are the context keys
+// 0..ctx_len-1 plus the packed keys allowed by its mask row (Sec. 3.3).  The keys of a (sequence, head) are cut
+// into ranges, one workgroup each; it computes, for all packed rows (or a group of them) at once, a partial softmax
+// state (running max m, sum l, unnormalised output O).  A head with one range is written out directly; else
+// the state goes to the workspace and the workgroup that finishes last for that head -- found with a device-scope
+// counter -- merges the partials, normalises and writes the output, so the whole operation is a single launch.
 #pragma once
 #include "rd_internal.h"
+#include <math.h>
 
 namespace rd {
 
@@ -19,91 +17,119 @@ constexpr int kAttnThreads = 256;
 constexpr int kBlockKeys = 128;   // keys handled per workgroup iteration
 
 struct AttnPlan {
-    int waves;         // waves per workgroup of the bf16 kernel (4 or 8); a block is 32*waves keys
-    int S;             // context splits per (sequence, head)
-    int fuse_tree;     // 1: the packed keys are the last block of the last context range, not a range of their own
-    int n_part;        // workgroups (and partial results) per head: S, or S + 1 with a separate packed-key range
+    int waves;         // matrix-core kernel: waves per workgroup (4 or 8); a block is 32*waves keys
+    int S;             // workgroups per (sequence, head); fp32 kernel: context ranges, one more workgroup takes the packed keys
     int rows_pad;      // packed rows padded to a multiple of 16 (fp32 kernel's partial layout)
-    int rg_tiles;      // bf16 kernel: 16-row tiles of packed rows per workgroup (a row group)
-    int n_rg;          // bf16 kernel: row groups per (sequence, head); 1 unless N is large
+    int rg_tiles;      // matrix-core kernel: 16-row tiles of packed rows per workgroup (a row group)
+    int n_rg;          // ... row groups per (sequence, head); 1 unless N is large
     size_t counters_bytes;
-    size_t partial_floats;   // floats per partial: m[rows_pad] + l[rows_pad] + O[rows_pad][D]
     size_t total_bytes;
 };
 
-// How many context splits per (sequence, head), and whether the packed keys ride on the last
-// context range.  Measured behaviour of the kernel on MI355X that the estimate encodes:
-//   * a compute unit streams K/V through this kernel at about 27 GB/s whether it holds one
-//     workgroup or two, so the blocks of the workgroups that share a compute unit add up; the
-//     launch as a whole cannot exceed about 5.5 TB/s;
-//   * workgroups beyond the resident capacity (`slots`) start only as earlier ones retire;
-//   * more than one workgroup per head costs a merge: about 3 us of latency plus the partial
-//     results written and read back once (at roughly 4 TB/s).
-// Long ranges (four blocks or more) take the packed keys as one more block; a head with a single
-// such range needs no workspace traffic at all.  S minimises the estimated time.
-static inline AttnPlan attn_plan(int B, int H, int N, int D, int Cmax, size_t elem_bytes)
+// Plan of the matrix-core kernel (rd_tree_attn_mfma.h), for contexts of up to Cmax keys: waves per workgroup, rows
+// per workgroup and workgroups per head, from an estimate of the launch time.  Lengths are upper bounds and the
+// packed rows are not known at all here (distinct prefixes are taken to be 0.6 of the candidates' tokens); the kernel
+// deals its tiles to the workgroups from the lengths it finds.  Measured on MI355X, us, at D = 128 (D = 64: blocks take 0.6 of it):
+//   * a workgroup is 1.0 (eight waves) or 1.2 (four) plus 2.0 + 0.5 r or 1.15 + 0.3 r per block, r = row tiles with
+//     packed rows; at five row tiles K comes in operand order, 0.3 more per block of eight waves;
+//   * one eight-wave workgroup fills a compute unit, two of four waves do; more start as those retire;
+//   * the workgroups that run at one time share 5.0 (eight waves) or 5.25 TB/s, a compute unit gets 28 GB/s at most,
+//     and one with two workgroups takes twice as long as one with one (the rest of the chip then idles, which leaves
+//     the others more: half of that is counted); latency and bandwidth overlap in part (root of the sum of squares);
+//   * more than one range per head adds a merge: 1.5, and the partial results written and read back, the reading by
+//     one compute unit at 50 GB/s.
+// Beams of more than 80 packed rows are cut into row groups, as equal as whole tiles allow; every group walks the
+// head's keys, and workgroups of groups that turn out empty go to the others.
+static inline AttnPlan attn_plan_make(int B, int H, int N, int D, int Cmax)
 {
-    AttnPlan p;
+    constexpr int kMaxTilesPerGroup = 5, kWideTilesPerGroup = 4;    // as instantiated
     const long long BH = (long long)B * H;
-    const double kv_bytes = 2.0 * (double)BH * Cmax * D * (double)elem_bytes;
-    const bool small = kv_bytes < 64e6;          // latency-bound: few blocks per range
-    // Packed rows per workgroup: all of them while they fit the register budget (5 row tiles at
-    // D = 128, 8 at D = 64); wider beams are cut into row groups of 3 (4) tiles, each a workgroup
-    // of its own per key range (K/V are then re-read per group, from L2 mostly).
     const int nq_all = (N + 15) / 16;
-    static const int tiles_env = env_int("RD_ATTN_ROWTILES", 0);       // tuning: largest single group
-    int nq_max = D == 128 ? 5 : 8;
-    const int nq_grp = D == 128 ? 3 : 4;
-    if (tiles_env >= nq_grp && tiles_env <= nq_max) nq_max = tiles_env;
-    const int nq = elem_bytes == 2 ? (nq_all <= nq_max ? nq_all : nq_grp) : nq_all;
-    const int n_rg = elem_bytes == 2 ? (nq_all + nq - 1) / nq : 1;
-    // Waves per workgroup: eight for small working sets, and also when the heads (and row groups) alone come
-    // to one workgroup per compute unit (129..256 of them) over contexts long enough to take the packed keys
-    // along: such a launch has no second workgroup per compute unit to overlap with, and eight waves keep
-    // 128 KB of loads in flight per compute unit instead of 64 KB.
-    static const int waves_env = env_int("RD_ATTN_WAVES", 0);
-    const long long units = BH * n_rg;
-    const bool one_per_cu = units > 128 && units <= 256 && (Cmax + 255) / 256 >= 4;
-    p.waves = (elem_bytes == 2 && D == 128 && (small || one_per_cu)) ? 8 : 4;
-    if (waves_env == 4 || (waves_env == 8 && elem_bytes == 2 && D == 128)) p.waves = waves_env;
-    const int block_keys = elem_bytes == 2 ? 32 * p.waves : kBlockKeys;
-    const int nblk = (Cmax + block_keys - 1) / block_keys;
-    const long long slots = (elem_bytes == 2 && p.waves == 4 && nq <= 5) ? 512 : 256;
-    const bool can_fuse = elem_bytes == 2;
-    const double blk_bytes = 2.0 * block_keys * D * (double)elem_bytes;      // K and V of one block of one head
-    const double t_blk = blk_bytes / 27e9;
+    const double rows = 0.6 * N, scale = D == 128 ? 1.0 : 0.6;
+    const int tiles = (Cmax + 31) / 32 + ((int)rows + 31) / 32;
+    static const int waves_env = env_int("RD_ATTN_WAVES", 0), forced = env_int("RD_ATTN_SPLITS", 0);
+    AttnPlan best = {};
+    double best_T = 1e30;
+    for (int waves = 8; waves >= 4; waves -= 4) {
+        if (waves_env && waves != waves_env) continue;
+        int n_rg = (nq_all + kMaxTilesPerGroup - 1) / kMaxTilesPerGroup;
+        const int nq = N > 32 * waves ? kWideTilesPerGroup : (nq_all + n_rg - 1) / n_rg;
+        n_rg = (nq_all + nq - 1) / nq;
+        int n_act = (int)((rows + 16 * nq - 1) / (16 * nq));
+        n_act = n_act < 1 ? 1 : n_act;
+        double r = n_act > 1 ? nq : (rows + 15) / 16;
+        r = r < 1 ? 1 : (r > nq ? nq : r);
+        const int nblk = tiles > waves ? (tiles + waves - 1) / waves : 1;
+        const double t_blk = scale * (waves == 8 ? 2.0 + 0.5 * r + (nq > 4 ? 0.3 : 0.0) : 1.15 + 0.3 * r);
+        const double t_wg = waves == 8 ? 1.0 : 1.2, rate = waves == 8 ? 5.0e6 : 5.25e6;
+        const long long slots = waves == 8 ? 256 : 512;
+        const double part = r * 16 * (2 + D) * sizeof(float);
+        for (int S = n_rg; S <= 64 * n_rg && S <= nblk * n_rg; ++S) {
+            const int ranges = S / n_act, per = (nblk + ranges - 1) / ranges, n_part = (nblk + per - 1) / per;
+            const double t_lat = t_wg + per * t_blk, bytes = (double)(per * waves < tiles ? per * waves : tiles) * 32 * D * 4 / n_act;
+            const long long wgs = (BH + 7) / 8 * 8 * S, full = wgs / slots, rest = wgs % slots;
+            auto round = [&](long long n) {
+                const long long per_cu = (n + 255) / 256;
+                const double sharing = ((n < 256 ? n : 256) + (double)n / per_cu) / 2;
+                const double t_bw = per_cu * bytes / (rate / sharing < 28e3 ? rate / sharing : 28e3);
+                return sqrt(t_lat * t_lat + t_bw * t_bw);
+            };
+            double T = full * round(slots) + (rest ? round(rest) : 0.0);
+            if (n_part > 1) T += 1.5 + n_part * part / 50e3 + 2.0 * (double)BH * n_act * n_part * part / 4e6;
+            const bool take = forced > 0 ? S == (forced < n_rg ? n_rg : (forced < nblk * n_rg ? forced : nblk * n_rg)) : T < best_T * (1 - 1e-9);
+            if (take) {
+                best_T = T;
+                best.waves = waves;
+                best.S = S;
+                best.rg_tiles = nq;
+                best.n_rg = n_rg;
+                best.counters_bytes = ((size_t)BH * n_rg * sizeof(unsigned long long) + 255) / 256 * 256;
+                best.total_bytes = best.counters_bytes + (S > 1 ? (size_t)BH * S * (size_t)(nq * 16 * (2 + D)) * sizeof(float) : 0);
+            }
+        }
+    }
+    best.rows_pad = nq_all * 16;
+    return best;
+}
+
+// The search takes up to some microseconds; a program calls with the same few shapes, so each thread keeps its last plan.
+static inline AttnPlan attn_plan(int B, int H, int N, int D, int Cmax)
+{
+    static thread_local int key[5] = {0, 0, 0, 0, -1};
+    static thread_local AttnPlan plan;
+    if (key[0] != B || key[1] != H || key[2] != N || key[3] != D || key[4] != Cmax) {
+        plan = attn_plan_make(B, H, N, D, Cmax);
+        key[0] = B; key[1] = H; key[2] = N; key[3] = D; key[4] = Cmax;
+    }
+    return plan;
+}
+
+// Plan of the fp32 kernel: context ranges per head, estimated as above from what it does (27 GB/s per compute unit).
+static inline AttnPlan attn_plan_f32(int B, int H, int N, int D, int Cmax)
+{
+    AttnPlan p = {};
+    const long long BH = (long long)B * H;
+    const int nblk = (Cmax + kBlockKeys - 1) / kBlockKeys, rows_pad = (N + 15) / 16 * 16;
+    const double blk_bytes = 2.0 * kBlockKeys * D * sizeof(float), t_blk = blk_bytes / 27e9;
     const double t_hbm = (double)BH * nblk * blk_bytes / 5.5e12;
-    const double part_bytes = (double)nq * 16 * (2 + D) * sizeof(float);
+    const double part_bytes = (double)rows_pad * (2 + D) * sizeof(float);
     int best_S = 1;
     double best_T = 1e30;
     for (int S = 1; S <= nblk && S <= 64; ++S) {
         const int per = (nblk + S - 1) / S;
-        const bool fuse = can_fuse && per >= 4;
-        const int n_part = S + (fuse ? 0 : 1);
-        const long long wg = BH * S * n_rg;
-        const long long rounds = wg <= slots ? (wg + 255) / 256 : (wg + slots - 1) / slots * (slots / 256);
-        double T = (double)rounds * (per + (fuse ? 1 : 0)) * t_blk;
+        const long long rounds = (BH * S + 255) / 256;
+        double T = (double)rounds * per * t_blk;
         if (T < t_hbm) T = t_hbm;
-        if (n_part > 1) T += 3e-6 + 2.0 * (double)BH * n_rg * n_part * part_bytes / 4e12;
+        T += 3e-6 + 2.0 * (double)BH * (S + 1) * part_bytes / 4e12;
         if (T < best_T * (1.0 - 1e-9)) { best_T = T; best_S = S; }
     }
-    if (p.waves == 8 && one_per_cu && !small) best_S = 1;     // the heads fill the compute units by themselves
-    static const int forced = env_int("RD_ATTN_SPLITS", 0);
-    if (forced > 0) best_S = forced < nblk ? forced : (nblk > 0 ? nblk : 1);
+    p.waves = 4;
     p.S = best_S;
-    static const int fuse_env = env_int("RD_ATTN_FUSE", -1);
-    p.fuse_tree = (can_fuse && nblk > 0 && (nblk + p.S - 1) / p.S >= 4) ? 1 : 0;
-    if (fuse_env >= 0 && can_fuse && nblk > 0) p.fuse_tree = fuse_env ? 1 : 0;
-    p.n_part = p.S + (p.fuse_tree ? 0 : 1);
-    p.rows_pad = (N + 15) / 16 * 16;
-    p.rg_tiles = nq;
-    p.n_rg = n_rg;
-    p.counters_bytes = ((size_t)BH * n_rg * sizeof(unsigned long long) + 255) / 256 * 256;
-    // floats per partial: fp32 kernel m[rows_pad] + l[rows_pad] + O[rows_pad][D] per (b,h,part);
-    // bf16 kernel the same for the rows of one group, per (b,h,group,part)
-    p.partial_floats = elem_bytes == 2 ? (size_t)nq * 16 * (2 + D) : (size_t)p.rows_pad * (2 + D);
-    p.total_bytes = p.counters_bytes +
-                    (p.n_part > 1 ? (size_t)BH * n_rg * p.n_part * p.partial_floats * sizeof(float) : 0);
+    p.rows_pad = rows_pad;
+    p.rg_tiles = 1;
+    p.n_rg = 1;
+    p.counters_bytes = ((size_t)BH * sizeof(unsigned long long) + 255) / 256 * 256;
+    p.total_bytes = p.counters_bytes + (size_t)BH * (p.S + 1) * (size_t)rows_pad * (2 + D) * sizeof(float);
     return p;
 }
 
@@ -117,9 +143,7 @@ struct AttnArgs {
     unsigned long long *counters;
     float *partials;
     int B, H, N, Cmax, S, words, rows_pad;
-    int n_rg;      // row groups per (sequence, head) (bf16 kernel; each is NQ*16 rows of the template)
-    int fuse_tree; // 1: packed keys walked by the workgroup of the last context range (see AttnPlan)
-    int xcd_remap; // 1: workgroup i serves XCD i%8's share of the heads (needs B*H % 8 == 0)
+    int n_rg;      // row groups per (sequence, head) (matrix-core kernel; each is NQ*16 rows of the template)
     float scale_log2e;
     // rotary embedding fused into the call (rd_tree_attn_rope); unused (null) otherwise
     const int32_t *position_ids;   // [B, N]

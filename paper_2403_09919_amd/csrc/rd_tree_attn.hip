@@ -24,7 +24,7 @@ static int attn_check_shape(int B, int H, int N, int D, int Cmax, rd_dtype dt)
 extern "C" size_t rd_tree_attn_workspace(int B, int H, int N, int D, int Cmax, rd_dtype dt)
 {
     if (attn_check_shape(B, H, N, D, Cmax, dt) != RD_OK) return 0;
-    return rd::attn_plan(B, H, N, D, Cmax, dt == RD_F32 ? 4 : 2).total_bytes;
+    return (dt == RD_F32 ? rd::attn_plan_f32(B, H, N, D, Cmax) : rd::attn_plan(B, H, N, D, Cmax)).total_bytes;
 }
 
 // Dense entry points: `plan_ctx` is the context length the launch plan is made for (the cache's
@@ -43,7 +43,7 @@ static int tree_attn_dense(const void *q, const void *k_cache, const void *v_cac
     if (!rd_aligned(q, 16) || !rd_aligned(k_cache, 16) || !rd_aligned(v_cache, 16) || !rd_aligned(k_new, 16) ||
         !rd_aligned(v_new, 16) || !rd_aligned(out, 16) || !rd_aligned(tree_mask_bits, 8))
         return RD_ERR_INVALID_ARG;
-    const rd::AttnPlan plan = rd::attn_plan(B, H, N, D, plan_ctx, dt == RD_F32 ? 4 : 2);
+    const rd::AttnPlan plan = dt == RD_F32 ? rd::attn_plan_f32(B, H, N, D, plan_ctx) : rd::attn_plan(B, H, N, D, plan_ctx);
     if (!workspace || !rd_aligned(workspace, 256) || workspace_bytes < plan.total_bytes) return RD_ERR_WORKSPACE;
 
     rd::AttnArgs a;
@@ -53,8 +53,6 @@ static int tree_attn_dense(const void *q, const void *k_cache, const void *v_cac
     a.partials = reinterpret_cast<float *>(static_cast<unsigned char *>(workspace) + plan.counters_bytes);
     a.B = B; a.H = H; a.N = N; a.Cmax = Cmax; a.S = plan.S; a.words = (N + 63) / 64; a.rows_pad = plan.rows_pad;
     a.scale_log2e = scale * 1.44269504088896340736f;
-    a.xcd_remap = (((long long)B * H) % 8 == 0) ? 1 : 0;
-    a.fuse_tree = plan.fuse_tree;
     a.n_rg = plan.n_rg;
     a.block_table = nullptr; a.page_size = 0; a.max_pages = 0; a.n_pages = 0;
     a.position_ids = nullptr; a.cos_tab = nullptr; a.sin_tab = nullptr; a.max_pos = 0; a.k_rot = nullptr;
@@ -97,7 +95,7 @@ static int paged_check_shape(int B, int H, int N, int D, int page_size, int max_
 extern "C" size_t rd_tree_attn_paged_workspace(int B, int H, int N, int D, int page_size, int max_pages, rd_dtype dt)
 {
     if (paged_check_shape(B, H, N, D, page_size, max_pages, 1, dt) != RD_OK) return 0;
-    return rd::attn_plan(B, H, N, D, page_size * max_pages, 2).total_bytes;
+    return rd::attn_plan(B, H, N, D, page_size * max_pages).total_bytes;
 }
 
 extern "C" int rd_tree_attn_paged(const void *q, const void *k_pages, const void *v_pages,
@@ -115,7 +113,7 @@ extern "C" int rd_tree_attn_paged(const void *q, const void *k_pages, const void
         !rd_aligned(v_new, 16) || !rd_aligned(out, 16) || !rd_aligned(tree_mask_bits, 8) || !rd_aligned(block_table, 4))
         return RD_ERR_INVALID_ARG;
     const int Cmax = page_size * max_pages;
-    const rd::AttnPlan plan = rd::attn_plan(B, H, N, D, Cmax, 2);
+    const rd::AttnPlan plan = rd::attn_plan(B, H, N, D, Cmax);
     if (!workspace || !rd_aligned(workspace, 256) || workspace_bytes < plan.total_bytes) return RD_ERR_WORKSPACE;
 
     rd::AttnArgs a;
@@ -126,8 +124,6 @@ extern "C" int rd_tree_attn_paged(const void *q, const void *k_pages, const void
     a.partials = reinterpret_cast<float *>(static_cast<unsigned char *>(workspace) + plan.counters_bytes);
     a.B = B; a.H = H; a.N = N; a.Cmax = Cmax; a.S = plan.S; a.words = (N + 63) / 64; a.rows_pad = plan.rows_pad;
     a.scale_log2e = scale * 1.44269504088896340736f;
-    a.xcd_remap = (((long long)B * H) % 8 == 0) ? 1 : 0;
-    a.fuse_tree = plan.fuse_tree;
     a.n_rg = plan.n_rg;
     a.position_ids = nullptr; a.cos_tab = nullptr; a.sin_tab = nullptr; a.max_pos = 0; a.k_rot = nullptr;
     return rd::tree_attn_paged(a, D, plan.waves, plan.rg_tiles, dt == RD_F16, (hipStream_t)stream);
@@ -153,7 +149,7 @@ extern "C" int rd_tree_attn_rope(const void *q, const void *k_cache, const void 
         !rd_aligned(cos_tab, 4) || !rd_aligned(sin_tab, 4) || !rd_aligned(position_ids, 4))
         return RD_ERR_INVALID_ARG;
     if (k_new_rot == k_new || k_new_rot == q) return RD_ERR_INVALID_ARG;    // other workgroups still read the unrotated rows
-    const rd::AttnPlan plan = rd::attn_plan(B, H, N, D, Cmax, 2);
+    const rd::AttnPlan plan = rd::attn_plan(B, H, N, D, Cmax);
     if (!workspace || !rd_aligned(workspace, 256) || workspace_bytes < plan.total_bytes) return RD_ERR_WORKSPACE;
 
     rd::AttnArgs a;
@@ -163,8 +159,6 @@ extern "C" int rd_tree_attn_rope(const void *q, const void *k_cache, const void 
     a.partials = reinterpret_cast<float *>(static_cast<unsigned char *>(workspace) + plan.counters_bytes);
     a.B = B; a.H = H; a.N = N; a.Cmax = Cmax; a.S = plan.S; a.words = (N + 63) / 64; a.rows_pad = plan.rows_pad;
     a.scale_log2e = scale * 1.44269504088896340736f;
-    a.xcd_remap = (((long long)B * H) % 8 == 0) ? 1 : 0;
-    a.fuse_tree = plan.fuse_tree;
     a.n_rg = plan.n_rg;
     a.block_table = nullptr; a.page_size = 0; a.max_pages = 0; a.n_pages = 0;
     a.position_ids = position_ids; a.cos_tab = cos_tab; a.sin_tab = sin_tab; a.max_pos = max_pos; a.k_rot = k_new_rot;

@@ -1,6 +1,25 @@
-// Tree-masked attention on the gfx950 matrix cores for 16-bit K/V (bf16 or fp16): the kernel
-// template and its dispatch, instantiated once per element type (rd_tree_attn_bf16.hip,
-// rd_tree_attn_f16.hip).  The design is described at the top of rd_tree_attn_bf16.hip.
+// Tree-masked attention of the packed candidates against the KV cache (Sec. 3.3, 3.4) on the gfx950 matrix cores
+// for 16-bit K/V (bf16 or fp16): a split-key flash kernel, its template and dispatch, instantiated per element
+// type, cache layout and rotation (rd_tree_attn_bf16.hip, _f16, _paged, _rope_bf16, _rope_f16).
+//
+// A key range is a sequence of 32-key tiles, the context's first, then the packed keys'; a block is NW of them, one
+// per wave.  Per block a wave
+//   * has K of its tile in registers as the A operand of S^T = K Q^T and Q there too as the B operand;
+//   * takes the softmax of its 32 keys and leaves the probabilities in LDS as its lanes hold them (keys of a tile
+//     taken as 4g+i, 16+4g+i: that is the B-operand order of the next product), beside its V tile;
+//   * after one barrier adds up its own d-tiles of O^T = V^T P^T over all the block's tiles; V^T (eight keys of one
+//     column per lane) comes from the row-major V tiles by transpose reads.
+// The next block's K and V are in flight meanwhile.
+//
+// What bounds it.  Long contexts in large batches: HBM (38.6 us for 201 MB of K and V at B=8, H=32, C=1536, 5.2 TB/s).
+// Everything else: latency -- loads in operand order (see stage_k), and per block the LDS traffic, the vector
+// arithmetic of the softmax and the matrix products, which two waves per SIMD in step overlap badly.  Hence: one
+// barrier where the data is ready and one where it is free, no exchange of maxima in between (kSlack); tiles of the
+// context and of the tree in one sequence, so that a short context and its tree are one block and one workgroup;
+// no more workgroups per head than the lengths at hand need (n_part).  Against the kernel it replaced, whose waves
+// met at three barriers per block and whose packed keys were a workgroup of their own at short contexts, us per
+// launch: H=8, C=87, 20 packed rows 9.4 -> 5.3; B=11, H=40, C=180 31.2 -> 13.1; B=20, H=26, C=300, D=64 29.3 -> 19.3;
+// B=6, H=40, C=700, 96 packed rows 56.6 -> 36.8; B=8, H=32, C=1536 41.9 -> 39.2; B=16, H=52, C=2048 190 -> 190.
 #pragma once
 #include "rd_attn_common.h"
 #include <type_traits>
@@ -39,10 +58,9 @@ struct Geo {
     static constexpr int kTileBytes = kTileKeys * kRowBytes;
     static constexpr int kKSteps = D / 32;                 // MFMA k-steps of the QK^T contraction
     static constexpr int kDTiles = D / 16;
-    static constexpr int kDTilesPerWave = kDTiles / 4;
 };
 
-// LDS placement of 16-byte chunk c of row `row`: K and Q tiles are read by 16 lanes holding 16
+// LDS placement of 16-byte chunk c of row `row`: K tiles are read by 16 lanes holding 16
 // different rows and one chunk index, V tiles by transpose reads that touch 8 rows x 2 adjacent
 // chunks per half-wave; each gets the XOR pattern that spreads its readers over all banks.
 template <int D> __device__ __forceinline__ int kswz(int row, int c) { return c ^ (row & (Geo<D>::kChunks - 1)); }
@@ -54,7 +72,7 @@ template <int D> __device__ __forceinline__ int vswz(int row, int c)
 __device__ __forceinline__ uint4 ldg16(const void *p) { return *reinterpret_cast<const uint4 *>(p); }
 
 // Synchronisation that orders LDS traffic only.  __syncthreads() also waits for every global
-// load in flight, which would drain the K/V prefetch at each of the three barriers per block.
+// load in flight, which would drain the K/V prefetch at each of the barriers per block.
 __device__ __forceinline__ void lds_barrier()
 {
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
@@ -69,8 +87,6 @@ __device__ __forceinline__ void wave_lds_sync()
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
 
-// NW = waves per workgroup (4 or 8).  A block is 32*NW keys; eight waves halve the number of
-// sequential blocks of a range, which is what counts when a range is only one or two blocks long.
 // max / sum over the four lanes l, l^16, l^32, l^48 (the four 8-key groups of a score tile
 // column) with the gfx950 lane-swap instructions: each gives a lane the pair {x[l], x[l^k]}.
 __device__ __forceinline__ float quad_max(float x)
@@ -89,8 +105,8 @@ __device__ __forceinline__ float quad_sum(float x)
 }
 
 // Rotary embedding of eight elements ("rotate half": element i pairs with element i + D/2), in the
-// arithmetic of rd_rope: fp32, every product rounded before the sum, one rounding to the storage
-// type.  `x` is this lane's 16-byte chunk, `partner` the chunk D/2 elements away in the same row,
+// arithmetic of rd_rope: fp32, the partner's product rounded, then one fused multiply-add, one rounding to
+// the storage type.  `x` is this lane's 16-byte chunk, `partner` the chunk D/2 elements away in the same row,
 // cs / sn the cosines and sines of the eight pairs; `low`: x is the lower half of the pairs.
 template <typename T>
 __device__ __forceinline__ uint4 rope8(uint4 x, uint4 partner, const float (&cs)[8], const float (&sn)[8], bool low)
@@ -101,630 +117,639 @@ __device__ __forceinline__ uint4 rope8(uint4 x, uint4 partner, const float (&cs)
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
         const float a = (float)xv[i], b = (float)pv[i];
-        const float xc = __fmul_rn(a, cs[i]), ps = __fmul_rn(b, sn[i]);
-        float r = low ? __fsub_rn(xc, ps) : __fadd_rn(xc, ps);
+        float ps = b * sn[i];
+        asm volatile("" : "+v"(ps));              // an fp32 product, then one fused multiply-add
+        float r = __builtin_fmaf(a, cs[i], low ? -ps : ps);
         asm volatile("" : "+v"(r));               // an fp32 sum, then one rounding (as rd_rope does)
         y[i] = (T)r;
     }
     return __builtin_bit_cast(uint4, y);
 }
 
-// TB = packed-key blocks the launch can need: ceil(N / block keys).  1 for all but the widest beams;
-// the mask words of every such block are fetched up front, so the common case should not pay for three.
+// Row tiles (16 packed rows) of a workgroup at most: what registers and LDS hold.
+constexpr int kMaxTiles = 5;
+constexpr int kGroupTiles = 4;      // ... where beams have more packed keys than a block holds
+
+// Whether K is fetched as whole rows and turned into operand order through LDS (16 keys at a time, 32 KB for eight
+// waves), or fetched in operand order (lane = key r16 x 16-byte chunk 4t+g).  In operand order the 16 lanes of a row
+// touch 16 cache lines, which costs about 1 us per 64 KB: eight-wave workgroups, chosen where there are too few to
+// fill the chip, are bound by that (17.3 against 19.0 us at H=32, C=1024 in one workgroup per head).  With two
+// four-wave workgroups per compute unit the other one's work covers it (B=11, H=40, C=180: 13.1 us, 15.2 staged), and
+// with five row tiles the LDS is not there.
+template <int D, int NQ, int NW> constexpr bool stage_k() { return NW == 8 && NQ <= 4; }
+
+// NW = waves per workgroup (4 or 8); NQ = row tiles; TB = packed-key tiles a wave can meet (1 for all but the widest
+// beams: the mask words of all of them are fetched up front).
 // PAGED: the context keys and values live in fixed-size pages found through a block table
 // (a.block_table, a.page_size, a.max_pages) instead of one dense [B,H,Cmax,D] tensor.
 // ROPE: q and k_new arrive unrotated; the kernel applies the rotary embedding at a.position_ids
 // to the query rows as it brings them into LDS and to the packed-key tiles as it walks them.
-template <typename T, int D, int NQ, int NW, int TB, bool PAGED, bool ROPE = false>
+template <typename T, int D, int NQ, int NW, int TB, bool PAGED, bool ROPE>
 __global__ __launch_bounds__(NW * 64, 2) void rd_tree_attn_mfma_kernel(AttnArgs a)
 {
     using G = Geo<D>;
     using vec8 = typename Elem<T>::vec8;
-    constexpr int kThreads = NW * 64;
-    constexpr int kBlock = NW * G::kTileKeys;                   // keys per block
+    constexpr int KS = G::kKSteps;
+    constexpr int DT = G::kDTiles;
     constexpr int kRows = NQ * 16;
-    constexpr int kDTW = G::kDTiles / NW;                       // d-tiles of the output owned by a wave
-    static_assert(kDTW >= 1, "more waves than output d-tiles");
-    constexpr int kPF = kRows * (2 + D);                        // floats per partial
+    constexpr int JW = DT >= NW ? DT / NW : 1;                  // d-tiles of the output a wave owns
+    constexpr int RW = DT >= NW ? 1 : NW / DT;                  // waves that share d-tiles and divide the row tiles
+    constexpr int QW = (NQ + RW - 1) / RW;                      // row tiles of a wave's output
+    constexpr int kPF = kRows * 2 + DT * NQ * 256;              // floats per partial: (m,l) per row, then fragments
+    constexpr bool kStageK = stage_k<D, NQ, NW>();
+    constexpr bool kQReg = NQ * KS <= 8;                       // Q operands stay in registers
+    constexpr int kMLStride = NW * 8 + 16;                      // bytes per row of the tiles' (maximum, sum) table
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-    unsigned char *sQ = smem;                                   // [kRows][kRowBytes]
-    unsigned char *sKV = sQ + kRows * G::kRowBytes;             // NW tiles [32][kRowBytes]
-    unsigned char *sP = sKV + NW * G::kTileBytes;               // [NW kt][NQ][64 lanes] x 16 B
-    float *sM = reinterpret_cast<float *>(sP + NW * NQ * 64 * 16);  // [NW waves][kRows]
-    uint32_t *sVis = reinterpret_cast<uint32_t *>(sM + NW * kRows);   // [NW waves][NQ][64 lanes]
+    unsigned char *sQ = smem;                                   // [NQ][KS][64 lanes] x 16 B, B-operand order
+    unsigned char *sV = sQ + NQ * KS * 1024;                    // [NW] V tiles
+    unsigned char *sP = sV + NW * G::kTileBytes;                // [NW][NQ][64 lanes] x 16 B
+    unsigned char *sML = sP + NW * NQ * 1024;                   // [kRows] x [NW] (maximum, sum)
+
+    constexpr bool kVisInLds = NQ > 4;                          // the visibility bytes: registers, or LDS where those are short
+    int *sMoved = reinterpret_cast<int *>(sML + kRows * kMLStride);             // [NW] a reference moved in the wave's tile
+    unsigned char *sVis = reinterpret_cast<unsigned char *>(sMoved + NW);       // [TB][NW][NQ][64 lanes]
+    unsigned char *sK = sVis;                                   // [NW] half K tiles (kernels without sVis)
+    constexpr float kSlack = 8.f;                               // exponents may exceed their reference by this much
 
     const int tid = threadIdx.x;
     const int lane = tid & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);     // wave-uniform, kept in a scalar register
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int r16 = lane & 15;
     const int g = lane >> 4;
     RD_TR(0);
 
-    // ---- which (sequence, head, key range) -------------------------------------------------------
-    // Workgroups are dealt round-robin to the 8 XCDs; when the head count allows, all ranges of a
-    // head go to one XCD so that Q and the partial results stay in that XCD's L2.  Within an XCD
-    // the long context ranges come first and the short packed-key ranges last, so that the
-    // compute units are filled with long-running workgroups from the start.
-    // The packed keys are either a range of their own (split == S, one more workgroup per head) or,
-    // when the context ranges are long (a.fuse_tree), one more block at the end of the last context
-    // range; with a single context range the head then has one workgroup and needs no merge.
-    const int n_part = a.S + (a.fuse_tree ? 0 : 1);
-    // Work items are (head, key range, row group); the row groups of one key range are neighbours
-    // in launch order so that they stream the same K/V at the same time (one reads HBM, the others L2).
+    // ---- which (sequence, head), which of its a.S workgroups.  Workgroups are dealt round-robin to the 8 XCDs; all of
+    // a head's go to one of them, whose L2 then serves Q, K/V shared by row groups and the partial results (merging
+    // partials past the L2 takes about twice as long).  Head numbers past the end fill up the last eight.
+    const int k = (int)(blockIdx.x >> 3);
+    const int hl = a.S == 1 ? k : k / a.S;
+    const int r_wg = k - hl * a.S;
+    const int bh = hl * 8 + (int)(blockIdx.x & 7);
+    if (bh >= a.B * a.H) return;
+    const int b = a.B == 1 ? 0 : bh / a.H;
     const int n_rg = a.n_rg;
-    int bh, split, rg;
-    {
-        const int xcd = a.xcd_remap ? (int)(blockIdx.x & 7) : 0;
-        const int k = a.xcd_remap ? (int)(blockIdx.x >> 3) : (int)blockIdx.x;
-        const int heads_here = a.xcd_remap ? (a.B * a.H) >> 3 : a.B * a.H;    // heads served by this XCD
-        const int per_head = a.S * n_rg;
-        const int n_ctx = heads_here * per_head;
-        int hl;
-        if (k < n_ctx) {
-            hl = k / per_head;
-            const int r = k - hl * per_head;
-            split = r / n_rg;
-            rg = r - split * n_rg;
-        } else {
-            const int r = k - n_ctx;
-            hl = r / n_rg;
-            rg = r - hl * n_rg;
-            split = a.S;
-        }
-        bh = a.xcd_remap ? hl * 8 + xcd : hl;
-    }
-    const int b = bh / a.H;
     const int C = clampi(a.ctx_len[b], 0, a.Cmax);
     const int P_all = clampi(a.n_packed[b], 0, a.N);
-    // This workgroup's rows are row0 .. row0 + kRows - 1 of the packed rows; P of them are real.
-    // A packed row p sees no packed key beyond itself (the mask is lower triangular), so the group
-    // needs the packed keys [0, tree_end) only.
+    // Row groups that hold packed rows share the head's workgroups evenly (a.S >= n_rg); a workgroup is
+    // (row group rg, key range split).  Output rows of the other groups are zero.
+    const int n_act = n_rg == 1 ? 1 : max((P_all + kRows - 1) / kRows, 1);
+    const int ranges = n_act == 1 ? a.S : a.S / n_act;
+    const int split = n_act == 1 ? r_wg : r_wg / n_act;
+    const int rg = r_wg - split * n_act;
+    if (n_rg > 1) {
+        T *z = static_cast<T *>(a.out) + (size_t)bh * a.N * D;
+        for (int i = n_act * kRows * D + (r_wg * NW * 64 + tid) * 8; i < a.N * D; i += a.S * NW * 64 * 8)
+            *reinterpret_cast<uint4 *>(z + i) = make_uint4(0, 0, 0, 0);
+    }
+    if (split >= ranges) return;
     const int row0 = rg * kRows;
+    const int Ng = min(kRows, a.N - row0);                      // rows of `out` this group owns
+
+    // ---- Q and (rotary embedding) the positions of its rows: neither needs the scalars below.  Fragment
+    // (row tile, k-step) of the staged Q is one lane-ordered 1 KB; a wave brings in every NW-th.  With the
+    // rotation a wave takes k-steps t and t + KS/2 together: they hold a lane's pairs.
+    constexpr int kQFrags = ROPE ? NQ * KS / 2 : NQ * KS;
+    constexpr int kQPer = (kQFrags + NW - 1) / NW;
+    const unsigned char *Qb = static_cast<const unsigned char *>(a.q) + ((size_t)bh * a.N + row0) * G::kRowBytes;
+    uint4 qreg[kQPer], qreg2[ROPE ? kQPer : 1];
+    int qpos[ROPE ? kQPer : 1];
+#pragma unroll
+    for (int i = 0; i < kQPer; ++i) {
+        const int f = min(wave + NW * i, kQFrags - 1);
+        const int qt = ROPE ? f / (KS / 2) : f / KS, t = ROPE ? f % (KS / 2) : f % KS;
+        const int row = min(qt * 16 + r16, Ng - 1);
+        if constexpr (ROPE) qpos[i] = a.position_ids[(size_t)b * a.N + row0 + row];
+        qreg[i] = ldg16(Qb + row * G::kRowBytes + (4 * t + g) * 16);
+        if constexpr (ROPE) qreg2[i] = ldg16(Qb + row * G::kRowBytes + (4 * (t + KS / 2) + g) * 16);
+    }
+
     const int P = clampi(P_all - row0, 0, kRows);
-    const int Ng = min(kRows, a.N - row0);                 // rows of `out` this group owns
+    // a packed row sees no packed key beyond itself (the mask is lower triangular)
     const int tree_end = min(P_all, row0 + kRows);
 
-    // Blocks this workgroup walks: nA blocks of context keys [k_begin, k_end), then nB blocks of
-    // packed keys [0, tree_end).  All of this is wave-uniform.  A group without real rows walks nothing.
-    int k_begin = 0, k_end = 0;
-    if (split < a.S && P > 0) ctx_range(C, a.S, split, kBlock, &k_begin, &k_end);
-    const bool has_tree = (split == a.S) || (a.fuse_tree && split == a.S - 1);
-    const int nA = (k_end - k_begin + kBlock - 1) / kBlock;
-    const int nB = (has_tree && P > 0) ? (tree_end + kBlock - 1) / kBlock : 0;
-    const int nb = nA + nB;
-    const unsigned char *Qb = static_cast<const unsigned char *>(a.q) + ((size_t)bh * a.N + row0) * G::kRowBytes;
-    // dense cache: this head's rows; paged cache: the page pool (the head is picked inside a page)
-    const unsigned char *Kc = static_cast<const unsigned char *>(a.k_cache) + (PAGED ? 0 : (size_t)bh * a.Cmax * G::kRowBytes);
-    const unsigned char *Vc = static_cast<const unsigned char *>(a.v_cache) + (PAGED ? 0 : (size_t)bh * a.Cmax * G::kRowBytes);
-    const unsigned char *Kn = static_cast<const unsigned char *>(a.k_new) + (size_t)bh * a.N * G::kRowBytes;
-    const unsigned char *Vn = static_cast<const unsigned char *>(a.v_new) + (size_t)bh * a.N * G::kRowBytes;
-    // ---- all first loads, without branches so that the waits on them stay exact --------------------
-    // Order: Q and the tree-mask words (they gate the first score tile), then K, then V.
-    constexpr int kQRowsPerPass = kThreads / G::kChunks;
-    constexpr int kQPasses = (kRows + kQRowsPerPass - 1) / kQRowsPerPass;
-    uint4 qreg[kQPasses];
+    // ---- this workgroup's tiles.  The tiles of a head are dealt in whole blocks of NW to as few of its
+    // `ranges` workgroups as cover them; the others have nothing to do and nobody waits for them.
+    const int nA = (C + 31) >> 5;
+    const int nT = P > 0 ? nA + ((tree_end + 31) >> 5) : 0;
+    const int nblk = (nT + NW - 1) / NW;
+    const int per = ranges == 1 ? max(nblk, 1) : max((nblk + ranges - 1) / ranges, 1);
+    const int n_part = ranges == 1 ? 1 : max((nblk + per - 1) / per, 1);
+    if (split >= n_part) return;
+    const int tile_begin = split * per * NW;
+    const int tile_end = min(nT, tile_begin + per * NW);
+    const int nb = (tile_end - tile_begin + NW - 1) / NW;       // blocks
+    const int head = bh - b * a.H;
+    // context rows (paged: the pool), and how far from them the packed rows lie: addresses as numbers, because
+    // a choice between two captured pointers makes the compiler keep everything that is captured in memory
+    const uintptr_t Kc = reinterpret_cast<uintptr_t>(a.k_cache) + (PAGED ? 0 : (size_t)bh * a.Cmax * G::kRowBytes);
+    const uintptr_t Vc = reinterpret_cast<uintptr_t>(a.v_cache) + (PAGED ? 0 : (size_t)bh * a.Cmax * G::kRowBytes);
+    const uintptr_t Kn = reinterpret_cast<uintptr_t>(a.k_new) + (size_t)bh * a.N * G::kRowBytes - Kc;
+    const uintptr_t Vn = reinterpret_cast<uintptr_t>(a.v_new) + (size_t)bh * a.N * G::kRowBytes - Vc;
+
+    const int t_first = tile_begin + wave;
+    // this wave's first packed-key tile (it may lie past the end)
+    const int tree_first = t_first >= nA ? t_first : t_first + (nA - t_first + NW - 1) / NW * NW;
+
+    // Rows past the end of a tile's keys are redirected to its last key (their probabilities are zero).
+    auto page_of = [&](int tile) __attribute__((always_inline)) {               // wave-uniform scalar load
+        const int pg = min(tile * 32 / a.page_size, a.max_pages - 1);
+        return clampi(a.block_table[(size_t)b * a.max_pages + pg], 0, a.n_pages - 1);
+    };
+    int pid = 0;              // page of the tile that is fetched next (paged context tiles only)
+    auto tile_off = [&](int tile, bool tree) __attribute__((always_inline)) -> size_t {   // of the tile's first key
+        const uint32_t dense = (uint32_t)(tile - (tree ? nA : 0)) * 32;
+        if (!PAGED) return (size_t)dense * G::kRowBytes;
+        const size_t paged = ((size_t)pid * a.H + head) * a.page_size + (uint32_t)(tile * 32) % (uint32_t)a.page_size;
+        return (tree ? dense : paged) * G::kRowBytes;
+    };
+    auto tile_keys = [&](int tile, bool tree) __attribute__((always_inline)) {
+        return min(32, tree ? tree_end - (tile - nA) * 32 : C - tile * 32);
+    };
+    vec8 kreg[2][KS], vreg[G::kLoads];                          // (native vectors stay in registers)
+    typedef const __attribute__((address_space(1))) vec8 gvec8;   // an address made from a number is a global one
+    auto load_k = [&](uintptr_t p, int keys, int ln) __attribute__((always_inline)) {
+        if constexpr (kStageK) {          // whole rows
+            const uint32_t off0 = (uint32_t)ln * 16, last = (uint32_t)(keys - 1) * G::kRowBytes + (ln % G::kChunks) * 16;
 #pragma unroll
-    for (int i = 0; i < kQPasses; ++i) {
-        const int row = min(i * kQRowsPerPass + tid / G::kChunks, P - 1);    // rows >= P are zeroed below
-        qreg[i] = ldg16(Qb + max(row, 0) * G::kRowBytes + (tid % G::kChunks) * 16);
-    }
-    // rotary embedding of the query rows: the partner chunk, and the cosines / sines of the row's position
-    constexpr int kHalfChunks = G::kChunks / 2;
-    uint4 qpart[ROPE ? kQPasses : 1];
-    float qcs[ROPE ? kQPasses : 1][8], qsn[ROPE ? kQPasses : 1][8];
+            for (int s = 0; s < 2 * KS; ++s) kreg[s / KS][s % KS] = *(gvec8 *)(p + min(off0 + s * 1024u, last));
+        } else {                          // operand order
+#pragma unroll
+            for (int mt = 0; mt < 2; ++mt) {
+                const uint32_t off = (uint32_t)min(mt * 16 + (ln & 15), keys - 1) * G::kRowBytes + (ln >> 4) * 16;
+#pragma unroll
+                for (int t = 0; t < KS; ++t) kreg[mt][t] = *(gvec8 *)(p + off + t * 64);
+            }
+        }
+    };
+    auto load_v = [&](uintptr_t p, int keys, int ln) __attribute__((always_inline)) {
+        const uint32_t off0 = (uint32_t)ln * 16, last = (uint32_t)(keys - 1) * G::kRowBytes + (ln % G::kChunks) * 16;
+#pragma unroll
+        for (int s = 0; s < G::kLoads; ++s) vreg[s] = *(gvec8 *)(p + min(off0 + s * 1024u, last));
+    };
+
+    // ---- rotary embedding of Q: cosines and sines are fetched ahead of K and V, as the wait on them is
+    // a wait on everything fetched before
+    float qcs[ROPE ? kQPer : 1][8], qsn[ROPE ? kQPer : 1][8];
     if constexpr (ROPE) {
 #pragma unroll
-        for (int i = 0; i < kQPasses; ++i) {
-            const int row = max(min(i * kQRowsPerPass + tid / G::kChunks, P - 1), 0);
-            const int chunk = tid % G::kChunks;
-            qpart[i] = ldg16(Qb + row * G::kRowBytes + (chunk ^ kHalfChunks) * 16);
-            const int pos = clampi(a.position_ids[(size_t)b * a.N + row0 + row], 0, a.max_pos - 1);
-            const float *ct = a.cos_tab + (size_t)pos * (D / 2) + (chunk & (kHalfChunks - 1)) * 8;
-            const float *st = a.sin_tab + (size_t)pos * (D / 2) + (chunk & (kHalfChunks - 1)) * 8;
+        for (int i = 0; i < kQPer; ++i) {
+            const int f = min(wave + NW * i, kQFrags - 1), t = f % (KS / 2);
+            const size_t o = (size_t)clampi(qpos[i], 0, a.max_pos - 1) * (D / 2) + (4 * t + g) * 8;
 #pragma unroll
-            for (int e = 0; e < 8; ++e) { qcs[i][e] = ct[e]; qsn[i][e] = st[e]; }
+            for (int e = 0; e < 8; ++e) { qcs[i][e] = a.cos_tab[o + e]; qsn[i][e] = a.sin_tab[o + e]; }
         }
     }
-    // Visibility of this wave's 32 keys, in each packed-key block, for the packed rows this lane
-    // scores (row row0 + 16*qt + r16).  Context keys are visible to every row; packed keys per the
-    // tree mask: in packed-key block t wave w holds keys 32*(t*NW + w) .. +31, i.e. one half of mask
-    // word (t*NW + w)/2.  (Loaded by every workgroup; those without a packed-key block ignore it.)
-    constexpr int kTreeBlocks = TB;
-    static_assert(TB * kBlock < RD_MAX_N + kBlock, "more packed-key blocks than the largest N has");
-    uint64_t mword[kTreeBlocks][NQ];
+    // visibility words of the wave's packed-key tiles, and (rotation) the positions of the first one's keys
+    uint64_t mword[TB][NQ];
+    int kpos[2] = {0, 0};
 #pragma unroll
-    for (int t = 0; t < kTreeBlocks; ++t) {
-        const int word = min((t * NW + wave) >> 1, a.words - 1);
+    for (int t = 0; t < TB; ++t) {
+        const int word = min((tree_first - nA + t * NW) >> 1, a.words - 1);
 #pragma unroll
         for (int qt = 0; qt < NQ; ++qt)
             mword[t][qt] = a.mask_bits[((size_t)b * a.N + min(row0 + qt * 16 + r16, a.N - 1)) * a.words + word];
     }
+    if constexpr (ROPE) {
+#pragma unroll
+        for (int mt = 0; mt < 2; ++mt)
+            kpos[mt] = a.position_ids[(size_t)b * a.N + clampi((tree_first - nA) * 32 + mt * 16 + r16, 0, max(tree_end - 1, 0))];
+    }
+    // K and V of this wave's tile of a block.  A wave whose turn falls past the end takes the last tile again
+    // (masked: no branch around the loads, which would turn every wait into a wait for all of them); a
+    // workgroup without tiles reads the first tile there is and ignores it.
+    auto fetch = [&](int tile, int ln, auto which_k, auto which_v) __attribute__((always_inline)) {
+        const int tl = max(min(tile, tile_end - 1), 0);
+        const bool tree = tl >= nA;
+        const size_t off = tile_off(tl, tree);
+        const int keys = max(tile_keys(tl, tree), 1);
+        if (decltype(which_k)::value) load_k(Kc + off + (tree ? Kn : 0), keys, ln);
+        if (decltype(which_v)::value) load_v(Vc + off + (tree ? Vn : 0), keys, ln);
+    };
+    auto next_page = [&](int tile) __attribute__((always_inline)) {             // looked up one block ahead
+        if (PAGED) {
+            const int tl = max(min(tile, tile_end - 1), 0);
+            if (tl < nA) pid = page_of(tl);
+        }
+    };
+    next_page(t_first);
+    fetch(t_first, lane, std::true_type{}, std::true_type{});
+    next_page(t_first + NW);
 
-    // This wave's slice of a block: coalesced 16-byte loads into registers; a wave-wide load
-    // covers 1 KB of consecutive rows.  Rows past the end of the range are redirected to the last
-    // valid row (their scores are masked and their probabilities are zero), so the loads carry no
-    // predicate.
-    uint4 kreg[G::kLoads], vreg[G::kLoads];
-    const int ld_row = lane / G::kChunks;
-    const int ld_chunk = lane % G::kChunks;
-    auto load_tile = [&](const unsigned char *base, int key0, int end, uint4 (&reg)[G::kLoads]) __attribute__((always_inline)) {
-        const uint32_t off0 = (uint32_t)(key0 + wave * G::kTileKeys + ld_row) * G::kRowBytes + ld_chunk * 16;
-        const uint32_t last_off = (uint32_t)(end - 1) * G::kRowBytes + ld_chunk * 16;
+    // ---- Q -> LDS
 #pragma unroll
-        for (int s = 0; s < G::kLoads; ++s) reg[s] = ldg16(base + min(off0 + s * 1024u, last_off));
-    };
-    // Paged cache: a tile (32 keys, never straddling a page because page_size % 32 == 0) is
-    // addressed through the page of its first key.  Tiles beyond the end of the range are
-    // redirected to the last tile that holds a key, rows beyond the end to the tile's last valid
-    // row.  The page id of the tile to prefetch is itself fetched one iteration earlier, so the
-    // scalar load's latency is off the critical path.
-    const int head = bh - b * a.H;
-    auto ctx_tile_first = [&](int key0, int end) __attribute__((always_inline)) {   // first key of this wave's (redirected) tile
-        return min(key0 + wave * G::kTileKeys, ((end - 1) >> 5) << 5);
-    };
-    auto page_of = [&](int t0) __attribute__((always_inline)) {                 // wave-uniform scalar load
-        const int pg = min(t0 / a.page_size, a.max_pages - 1);
-        return clampi(a.block_table[(size_t)b * a.max_pages + pg], 0, a.n_pages - 1);
-    };
-    auto load_tile_paged = [&](const unsigned char *pages, int pid, int t0, int end, uint4 (&reg)[G::kLoads]) __attribute__((always_inline)) {
-        const unsigned char *base = pages + (((size_t)pid * a.H + head) * a.page_size + (t0 % a.page_size)) * G::kRowBytes;
-        const uint32_t off0 = (uint32_t)ld_row * G::kRowBytes + ld_chunk * 16;
-        const uint32_t last_off = (uint32_t)(min(G::kTileKeys, end - t0) - 1) * G::kRowBytes + ld_chunk * 16;
-#pragma unroll
-        for (int s = 0; s < G::kLoads; ++s) reg[s] = ldg16(base + min(off0 + s * 1024u, last_off));
-    };
-    int pid_next = 0;         // page of this wave's tile in the block after the current one (paged context only)
-    {   // first block; a workgroup with no block at all reads (and ignores) the first row of Q
-        const bool ctx = nA > 0;
-        if (PAGED && ctx) {
-            const int t0 = ctx_tile_first(k_begin, k_end);
-            const int pid = page_of(t0);
-            load_tile_paged(Kc, pid, t0, k_end, kreg);
-            load_tile_paged(Vc, pid, t0, k_end, vreg);
-            if (nA > 1) pid_next = page_of(ctx_tile_first(k_begin + kBlock, k_end));
-        } else {
-            const unsigned char *kb = nb == 0 ? Qb : (ctx ? Kc : Kn);
-            const unsigned char *vb = nb == 0 ? Qb : (ctx ? Vc : Vn);
-            const int key0 = ctx ? k_begin : 0;
-            const int end = nb == 0 ? 1 : (ctx ? k_end : tree_end);
-            load_tile(kb, key0, end, kreg);
-            load_tile(vb, key0, end, vreg);
+    for (int i = 0; i < kQPer; ++i) {
+        const int f = wave + NW * i;
+        if (f < kQFrags) {
+            const int qt = ROPE ? f / (KS / 2) : f / KS, t = ROPE ? f % (KS / 2) : f % KS;
+            const bool real = qt * 16 + r16 < P;
+            uint4 lo = qreg[i];
+            if constexpr (ROPE) {
+                lo = rope8<T>(qreg[i], qreg2[i], qcs[i], qsn[i], true);
+                uint4 hi = rope8<T>(qreg2[i], qreg[i], qcs[i], qsn[i], false);
+                *reinterpret_cast<uint4 *>(sQ + ((qt * KS + t + KS / 2) * 64 + lane) * 16) = real ? hi : make_uint4(0, 0, 0, 0);
+            }
+            *reinterpret_cast<uint4 *>(sQ + ((qt * KS + t) * 64 + lane) * 16) = real ? lo : make_uint4(0, 0, 0, 0);
         }
     }
-
-    // Visibility of this wave's packed keys (used in the packed-key blocks only).  Of a tile's 32
-    // keys this lane scores only the eight with index 4g+i and 16+4g+i, so one byte per block is
-    // all it keeps: bit 4*mt+i of byte t (row tile qt) = key 16*mt+4g+i of packed-key block t is
-    // visible to row 16*qt+r16.
-    // With up to three row tiles the bytes stay in registers.  The larger variants are short of
-    // registers: there the bytes are parked in LDS (each lane reads back only what it wrote),
-    // because a register that is first used inside the block loop but refilled from scratch memory
-    // makes the compiler wait for it, and with it for the K/V tiles in flight, in every iteration.
-    constexpr bool kVisInLds = NQ > 3;
+    // element (mt, i) of a lane's scores of the t-th packed-key tile = key 16*mt+4g+i: bit 4*mt+i of byte t
     uint32_t vis[NQ];
-    static_assert(kTreeBlocks <= 4, "one byte per packed-key block");
 #pragma unroll
     for (int qt = 0; qt < NQ; ++qt) {
         uint32_t packed = 0;
-        if (qt * 16 + r16 < P) {
 #pragma unroll
-            for (int t = 0; t < kTreeBlocks; ++t) {
-                if (((t * NW + wave) >> 1) < a.words) {
-                    const uint32_t v32 = (uint32_t)(mword[t][qt] >> ((wave & 1) * 32));
-                    packed |= (((v32 >> (4 * g)) & 0xfu) | (((v32 >> (16 + 4 * g)) & 0xfu) << 4)) << (8 * t);
-                }
-            }
+        for (int t = 0; t < TB; ++t) {
+            const uint32_t v32 = (uint32_t)(mword[t][qt] >> (((tree_first - nA + t * NW) & 1) * 32));
+            packed |= (((v32 >> (4 * g)) & 0xfu) | (((v32 >> (16 + 4 * g)) & 0xfu) << 4)) << (8 * t);
         }
-        if (kVisInLds) {
-            sVis[(wave * NQ + qt) * 64 + lane] = packed;
-            vis[qt] = 0;
-        } else {
-            asm volatile("" : "+v"(packed));          // computed here, not sunk into the loop's masked path
-            vis[qt] = packed;
-        }
+        vis[qt] = qt * 16 + r16 < P ? packed : 0u;
+        if (kVisInLds) {                               // (a lane reads back what it wrote)
+#pragma unroll
+            for (int t = 0; t < TB; ++t) sVis[((t * NW + wave) * NQ + qt) * 64 + lane] = (unsigned char)(vis[qt] >> (8 * t));
+        } else asm volatile("" : "+v"(vis[qt]));         // computed here, not sunk into the loop's masked path
     }
 
-#pragma unroll
-    for (int i = 0; i < kQPasses; ++i) {
-        const int row = i * kQRowsPerPass + tid / G::kChunks;
-        if (row < kRows)
-            *reinterpret_cast<uint4 *>(sQ + row * G::kRowBytes + kswz<D>(row, tid % G::kChunks) * 16) =
-                (row < P) ? (ROPE ? rope8<T>(qreg[i], qpart[i], qcs[i], qsn[i], (tid % G::kChunks) < kHalfChunks) : qreg[i])
-                          : make_uint4(0, 0, 0, 0);
-    }
-
-    float m_run[NQ], l_run[NQ];
-    f32x4 oacc[kDTW][NQ];
-#pragma unroll
-    for (int qt = 0; qt < NQ; ++qt) {
-        m_run[qt] = -INFINITY;
-        l_run[qt] = 0.f;
-#pragma unroll
-        for (int j = 0; j < kDTW; ++j) oacc[j][qt] = f32x4{0.f, 0.f, 0.f, 0.f};
-    }
-
-    unsigned char *my_tile = sKV + wave * G::kTileBytes;
-    // Lane-constant LDS offsets.  The XOR swizzles make the offset of load s / k-step t / d-tile dt
-    // the XOR of one lane-dependent value with a compile-time constant, so one register serves each
-    // family instead of one per member.
-    const int k_base = ld_row * G::kRowBytes + kswz<D>(ld_row, ld_chunk) * 16;
-    const int v_base = ld_row * G::kRowBytes + vswz<D>(ld_row, ld_chunk) * 16;
-    auto k_wr = [&](int s) __attribute__((always_inline)) {    // row s*kRowsPerLoad + ld_row, K swizzle
-        return s * 1024 + (k_base ^ (((s * G::kRowsPerLoad) & (G::kChunks - 1)) * 16));
+    // this wave's part of the output: row tiles RW*i + q_first, d-tiles j_first ..
+    const int j_first = RW > 1 ? wave % DT : wave * JW, q_first = RW > 1 ? wave / DT : 0;
+    unsigned char *my_tile = sV + wave * G::kTileBytes;
+    auto v_wr = [&](int s, int ln) __attribute__((always_inline)) {
+        const int row = ln / G::kChunks, base = row * G::kRowBytes + vswz<D>(row, ln % G::kChunks) * 16;
+        return s * 1024 + (base ^ (((s * G::kRowsPerLoad) & (G::kChunks / 2 - 1)) * 32));
     };
-    auto v_wr = [&](int s) __attribute__((always_inline)) {    // same row, V swizzle
-        return s * 1024 + (v_base ^ (((s * G::kRowsPerLoad) & (G::kChunks / 2 - 1)) * 32));
-    };
-    const int kq_base = r16 * G::kRowBytes + kswz<D>(r16, g) * 16;
-    auto kq_rd = [&](int t) __attribute__((always_inline)) {   // row r16, chunk 4t+g (rows 16+r16, 16qt+r16 add constants)
-        return kq_base ^ (((4 * t) & (G::kChunks - 1)) * 16);
-    };
-    const int vt_row = 4 * g + (r16 >> 2);
-    const int vt_base = vt_row * G::kRowBytes + vswz<D>(vt_row, (r16 & 3) >> 1) * 16 + (r16 & 1) * 8;
-    auto vt_rd = [&](int dt) __attribute__((always_inline)) {  // transpose-read address of rows 4g+(r16>>2), d-tile dt
-        return vt_base ^ ((dt & (G::kChunks / 2 - 1)) * 32);
+    auto vt_rd = [&](int dt, int ln) __attribute__((always_inline)) {
+        const int r = ln & 15, row = 4 * (ln >> 4) + (r >> 2);
+        const int base = row * G::kRowBytes + vswz<D>(row, (r & 3) >> 1) * 16 + (r & 1) * 8;
+        return base ^ ((dt & (G::kChunks / 2 - 1)) * 32);
     };
 
-    lds_barrier();        // Q visible to all waves
+    lds_barrier();            // Q visible to all waves
     RD_TR(1);
 
-    const int nqt = (P + 15) >> 4;            // row tiles that hold packed rows; the others are skipped
+    // rows -> operand order, 16 keys at a time through the wave's own piece of LDS
+    auto turn_k = [&](int ln) __attribute__((always_inline)) {
+        if constexpr (kStageK) {
+            unsigned char *st = sK + wave * (16 * G::kRowBytes);
+            const int row = ln / G::kChunks, wr = row * G::kRowBytes + kswz<D>(row, ln % G::kChunks) * 16;
+            const int rd = (ln & 15) * G::kRowBytes + kswz<D>(ln & 15, ln >> 4) * 16;
+#pragma unroll
+            for (int mt = 0; mt < 2; ++mt) {
+#pragma unroll
+                for (int s = 0; s < KS; ++s)
+                    *reinterpret_cast<vec8 *>(st + s * 1024 + (wr ^ (((s * G::kRowsPerLoad) & (G::kChunks - 1)) * 16))) = kreg[mt][s];
+                wave_lds_sync();
+#pragma unroll
+                for (int t = 0; t < KS; ++t) kreg[mt][t] = *reinterpret_cast<const vec8 *>(st + (rd ^ ((4 * t & (G::kChunks - 1)) * 16)));
+                wave_lds_sync();
+            }
+        }
+    };
+
+    const int nqt = (P + 15) >> 4;
     const float c_abs = fabsf(a.scale_log2e);
     const bool c_neg = a.scale_log2e < 0.f;
 
-    // The block loop is instantiated twice: for all row tiles, and for the lower half when the
-    // packed rows fit there (a padded tile costs as much as a real one, and branches around it
-    // would stop the compiler from overlapping LDS reads with the matrix instructions); the
-    // five-tile kernel, whose full loop is short of registers, has a third for four tiles.
-    auto block_loop = [&](auto nqa_tag) __attribute__((always_inline)) {
+    // One block; `more`: there is another one, whose K and V are fetched here.
+    auto block_step = [&](auto nqa_tag, auto more_tag, int ib, const vec8 (&qf)[kQReg ? NQ : 1][KS], auto &m_ref, auto &l_own, auto &oacc, auto &m_out, auto &l_out) __attribute__((always_inline)) {
         constexpr int NQA = decltype(nqa_tag)::value;
-        for (int ib = 0; ib < nb; ++ib) {
-            // this block and the one to prefetch: tensors, first key, end of the key range.  After
-            // the last block the prefetch repeats it (issued and ignored).
-            const bool cur_tree = ib >= nA;
-            const int cur_key0 = cur_tree ? (ib - nA) * kBlock : k_begin + ib * kBlock;
-            const int cur_end = cur_tree ? tree_end : k_end;
-            const int inext = ib + 1 < nb ? ib + 1 : ib;
-            const bool next_tree = inext >= nA;
-            const unsigned char *next_kb = next_tree ? Kn : Kc;
-            const unsigned char *next_vb = next_tree ? Vn : Vc;
-            const int next_key0 = next_tree ? (inext - nA) * kBlock : k_begin + inext * kBlock;
-            const int next_end = next_tree ? tree_end : k_end;
-            const int tile0 = cur_key0 + wave * G::kTileKeys;
-            // Lane ids re-read through an opaque copy: the LDS addresses derived from them are then
-            // recomputed in each iteration (one or two ALU operations) instead of being kept in
-            // registers across the loop, where the larger variants would park them in scratch memory
-            // and wait for ALL loads in flight on every reload.
-            int r16_l = r16, lane_l = lane;
-            asm volatile("" : "+v"(r16_l), "+v"(lane_l));
-
-            // K registers -> own LDS tile (K swizzle); then fetch the next block's K.  The prefetch
-            // is issued after the last block too (and ignored): a branch around it would make the
-            // compiler wait for all loads in flight wherever it waits for one of them.
-            if constexpr (ROPE) {
-                if (cur_tree) {
-                    // packed keys: rotate at the key's position.  The partner chunk of the same row sits
-                    // kHalfChunks lanes away; rows past the end were redirected to the last packed key and
-                    // take its position.  The rotated rows also go to a.k_rot (what a cache stores).
-                    const int chunk = lane_l % G::kChunks;
+        constexpr bool more = decltype(more_tag)::value;
+        // lane numbers through an opaque copy: addresses derived from them are made anew in each block (one or two
+        // operations) and not kept in registers across the loop, where the larger instances would park them in
+        // scratch memory and wait for ALL loads in flight on every reload
+        int lane = tid & 63;
+        if (NQA * JW >= 3) asm volatile("" : "+v"(lane));
+        const int r16 = lane & 15, g = lane >> 4;
+        const int tile = t_first + ib * NW;
+        const bool tree = tile >= nA;
+        turn_k(lane);
+        if constexpr (ROPE) {
+            if (tree && tile < tile_end) {       // packed keys: rotated here; the rotated rows also go to a.k_rot (what a cache stores)
 #pragma unroll
-                    for (int s = 0; s < G::kLoads; ++s) {
-                        const int key = tile0 + lane_l / G::kChunks + s * G::kRowsPerLoad;
-                        const int key_eff = min(key, tree_end - 1);
-                        uint4 pr;
-                        pr.x = __shfl_xor(kreg[s].x, kHalfChunks, 64); pr.y = __shfl_xor(kreg[s].y, kHalfChunks, 64);
-                        pr.z = __shfl_xor(kreg[s].z, kHalfChunks, 64); pr.w = __shfl_xor(kreg[s].w, kHalfChunks, 64);
-                        const int pos = clampi(a.position_ids[(size_t)b * a.N + key_eff], 0, a.max_pos - 1);
-                        const float *ct = a.cos_tab + (size_t)pos * (D / 2) + (chunk & (kHalfChunks - 1)) * 8;
-                        const float *st = a.sin_tab + (size_t)pos * (D / 2) + (chunk & (kHalfChunks - 1)) * 8;
+                for (int mt = 0; mt < 2; ++mt) {
+                    const int key = (tile - nA) * 32 + mt * 16 + r16;
+                    int pos = kpos[mt];
+                    if (tile != tree_first) pos = a.position_ids[(size_t)b * a.N + min(key, tree_end - 1)];
+                    const size_t o = (size_t)clampi(pos, 0, a.max_pos - 1) * (D / 2) + g * 8;
+#pragma unroll
+                    for (int t = 0; t < KS / 2; ++t) {
                         float cs[8], sn[8];
 #pragma unroll
-                        for (int e = 0; e < 8; ++e) { cs[e] = ct[e]; sn[e] = st[e]; }
-                        kreg[s] = rope8<T>(kreg[s], pr, cs, sn, chunk < kHalfChunks);
-                        if (a.k_rot != nullptr && key < tree_end)
-                            *reinterpret_cast<uint4 *>(static_cast<unsigned char *>(a.k_rot) + ((size_t)bh * a.N + key) * G::kRowBytes + chunk * 16) = kreg[s];
-                    }
-                }
-            }
-#pragma unroll
-            for (int s = 0; s < G::kLoads; ++s) *reinterpret_cast<uint4 *>(my_tile + k_wr(s)) = kreg[s];
-            int pid_cur_next = 0, t0_next = 0;
-            if (PAGED && !next_tree) {
-                // page of the tile fetched now (looked up one iteration ago), and the lookup for the
-                // block after it
-                pid_cur_next = pid_next;
-                t0_next = ctx_tile_first(next_key0, next_end);
-                if (inext + 1 < nA) pid_next = page_of(ctx_tile_first(next_key0 + kBlock, next_end));
-                load_tile_paged(Kc, pid_cur_next, t0_next, next_end, kreg);
-            } else {
-                load_tile(next_kb, next_key0, next_end, kreg);
-            }
-            wave_lds_sync();
-
-            // S^T tile pair: keys (16 mt + r) x packed rows (16 qt + c), raw (unscaled) scores
-            f32x4 sacc[2][NQA];
-#pragma unroll
-            for (int qt = 0; qt < NQA; ++qt) {
-                sacc[0][qt] = f32x4{0.f, 0.f, 0.f, 0.f};
-                sacc[1][qt] = f32x4{0.f, 0.f, 0.f, 0.f};
-            }
-#pragma unroll
-            for (int t = 0; t < G::kKSteps; ++t) {
-                const vec8 a0 = *reinterpret_cast<const vec8 *>(my_tile + kq_rd(t));
-                const vec8 a1 = *reinterpret_cast<const vec8 *>(my_tile + kq_rd(t) + 16 * G::kRowBytes);
-#pragma unroll
-                for (int qt = 0; qt < NQA; ++qt) {
-                    {
-                        const vec8 bq = *reinterpret_cast<const vec8 *>(sQ + kq_rd(t) + qt * 16 * G::kRowBytes);
-                        sacc[0][qt] = Elem<T>::mfma(a0, bq, sacc[0][qt]);
-                        sacc[1][qt] = Elem<T>::mfma(a1, bq, sacc[1][qt]);
-                    }
-                }
-            }
-            if (ib == 0) RD_TR(8);
-
-            // per-row maximum over this wave's 32 keys, in log2 units (score * scale * log2 e).  An
-            // interior context tile keeps the raw scores (the scale is folded into the exponent
-            // later); a tile with masked or out-of-range keys is scaled here and its dead entries
-            // set to -inf.
-            const int rem = cur_end - tile0;                       // keys of this tile inside the range
-            const bool plain = !cur_tree && rem >= G::kTileKeys && !c_neg;
-            if (plain) {
-#pragma unroll
-                for (int qt = 0; qt < NQA; ++qt) {
-                    {
-                        float tmax = fmaxf(fmaxf(fmaxf(sacc[0][qt][0], sacc[0][qt][1]), fmaxf(sacc[0][qt][2], sacc[0][qt][3])),
-                                           fmaxf(fmaxf(sacc[1][qt][0], sacc[1][qt][1]), fmaxf(sacc[1][qt][2], sacc[1][qt][3])));
-                        tmax = quad_max(tmax) * c_abs;
-                        if (g == 0) sM[(qt * 16 + r16_l) * NW + wave] = tmax;
-                    }
-                }
-            } else {
-                const uint32_t tail = rem >= 32 ? 0xffffffffu : (rem <= 0 ? 0u : ((1u << rem) - 1u));
-                const uint32_t tail8 = ((tail >> (4 * g)) & 0xfu) | (((tail >> (16 + 4 * g)) & 0xfu) << 4);
-                const int tsh = cur_tree ? 8 * (ib - nA) : 0;
-#pragma unroll
-                for (int qt = 0; qt < NQA; ++qt) {
-                    {
-                        // element (mt, i) at bit 4 mt + i; context keys are all visible
-                        const uint32_t vq = kVisInLds ? sVis[(wave * NQ + qt) * 64 + lane_l] : vis[qt];
-                        const uint32_t bits = (cur_tree ? (vq >> tsh) : 0xffu) & tail8;
-                        float tmax = -INFINITY;
-#pragma unroll
-                        for (int mt = 0; mt < 2; ++mt)
-#pragma unroll
-                            for (int i = 0; i < 4; ++i) {
-                                const float sv = ((bits >> (4 * mt + i)) & 1u) ? sacc[mt][qt][i] * a.scale_log2e : -INFINITY;
-                                sacc[mt][qt][i] = sv;
-                                tmax = fmaxf(tmax, sv);
-                            }
-                        tmax = quad_max(tmax);
-                        if (g == 0) sM[(qt * 16 + r16_l) * NW + wave] = tmax;
-                    }
-                }
-            }
-
-            lds_barrier();        // (A) tile maxima of all waves visible
-            if (ib == 0) RD_TR(9);
-
-            // V registers -> own LDS tile (V swizzle), replacing K which this wave has consumed
-#pragma unroll
-            for (int s = 0; s < G::kLoads; ++s) *reinterpret_cast<uint4 *>(my_tile + v_wr(s)) = vreg[s];
-            if (PAGED && !next_tree) load_tile_paged(Vc, pid_cur_next, t0_next, next_end, vreg);
-            else load_tile(next_vb, next_key0, next_end, vreg);
-
-            // online softmax with the block-wide maximum; P^T to LDS in B-operand layout
-#pragma unroll
-            for (int qt = 0; qt < NQA; ++qt) {
-                {
-                    const f32x4 *pm = reinterpret_cast<const f32x4 *>(sM + (qt * 16 + r16_l) * NW);
-                    f32x4 mv = pm[0];
-                    if (NW == 8) {
-                        const f32x4 mv2 = pm[1];
-                        mv[0] = fmaxf(mv[0], mv2[0]); mv[1] = fmaxf(mv[1], mv2[1]);
-                        mv[2] = fmaxf(mv[2], mv2[2]); mv[3] = fmaxf(mv[3], mv2[3]);
-                    }
-                    const float mb = fmaxf(fmaxf(mv[0], mv[1]), fmaxf(mv[2], mv[3]));
-                    const float m_new = fmaxf(m_run[qt], mb);
-                    const float m_safe = (m_new == -INFINITY) ? 0.f : m_new;
-                    const float alpha = __builtin_amdgcn_exp2f(m_run[qt] - m_safe);
-                    m_run[qt] = m_new;
-                    float psum = 0.f;
-                    vec8 pb;
-#pragma unroll
-                    for (int mt = 0; mt < 2; ++mt)
-#pragma unroll
-                        for (int i = 0; i < 4; ++i) {
-                            const float e = plain ? __builtin_fmaf(sacc[mt][qt][i], c_abs, -m_safe) : sacc[mt][qt][i] - m_safe;
-                            const float pv = __builtin_amdgcn_exp2f(e);
-                            psum += pv;
-                            pb[4 * mt + i] = (T)pv;
+                        for (int e = 0; e < 8; ++e) { cs[e] = a.cos_tab[o + t * 32 + e]; sn[e] = a.sin_tab[o + t * 32 + e]; }
+                        const uint4 lo = __builtin_bit_cast(uint4, kreg[mt][t]), hi = __builtin_bit_cast(uint4, kreg[mt][t + KS / 2]);
+                        kreg[mt][t] = __builtin_bit_cast(vec8, rope8<T>(lo, hi, cs, sn, true));
+                        kreg[mt][t + KS / 2] = __builtin_bit_cast(vec8, rope8<T>(hi, lo, cs, sn, false));
+                        if (a.k_rot != nullptr && key < tree_end) {
+                            unsigned char *kr = static_cast<unsigned char *>(a.k_rot) + ((size_t)bh * a.N + key) * G::kRowBytes + (4 * t + g) * 16;
+                            *reinterpret_cast<vec8 *>(kr) = kreg[mt][t];
+                            *reinterpret_cast<vec8 *>(kr + D) = kreg[mt][t + KS / 2];
                         }
-                    l_run[qt] = l_run[qt] * alpha + psum;
-                    *reinterpret_cast<vec8 *>(sP + ((wave * NQ + qt) * 64 + lane_l) * 16) = pb;
-                    if (__builtin_amdgcn_ballot_w64(alpha != 1.0f) != 0) {      // the maximum moved for some row
-#pragma unroll
-                        for (int j = 0; j < kDTW; ++j) oacc[j][qt] *= alpha;
                     }
                 }
             }
-            lds_barrier();        // (B) V tiles and P^T of all waves visible
-            if (ib == 0) RD_TR(10);
+        }
+        f32x4 sacc[2][NQA];
+#pragma unroll
+        for (int qt = 0; qt < NQA; ++qt) sacc[0][qt] = sacc[1][qt] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int t = 0; t < KS; ++t) {
+            const vec8 a0 = kreg[0][t], a1 = kreg[1][t];
+#pragma unroll
+            for (int qt = 0; qt < NQA; ++qt) {
+                const vec8 bq = kQReg ? qf[kQReg ? qt : 0][t] : *reinterpret_cast<const vec8 *>(sQ + ((qt * KS + t) * 64 + lane) * 16);
+                sacc[0][qt] = Elem<T>::mfma(a0, bq, sacc[0][qt]);
+                sacc[1][qt] = Elem<T>::mfma(a1, bq, sacc[1][qt]);
+            }
+        }
+        if (NQA * JW > 3) __builtin_amdgcn_sched_barrier(0);      // K's registers are read before they are fetched again
+        if (more) fetch(tile + NW, lane, std::true_type{}, std::false_type{});
 
-            // O^T += V^T P^T over the block's key tiles, for this wave's d-tiles.  Key tiles beyond
-            // the range were not loaded (their P^T is zero); only the last block of a range can have them.
-            auto pv_tile = [&](int kt) __attribute__((always_inline)) {
-                const unsigned char *vt = sKV + kt * G::kTileBytes;
-                vec8 aV[kDTW];
+        // softmax in log2 units.  An interior context tile keeps the raw scores (the scale is folded into
+        // the exponent); a tile with masked or missing keys is scaled here and its dead entries set to -inf.
+        const int rem = tile < tile_end ? tile_keys(tile, tree) : 0;
+        const bool plain = !tree && rem >= 32 && !c_neg;
+        float mx[NQA];
+        if (plain) {
 #pragma unroll
-                for (int j = 0; j < kDTW; ++j) {
-                    const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4 *)(vt + vt_rd(wave * kDTW + j)));
-                    const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4 *)(vt + vt_rd(wave * kDTW + j) + 16 * G::kRowBytes));
-                    aV[j] = __builtin_bit_cast(vec8, (s16x8)__builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+            for (int qt = 0; qt < NQA; ++qt)
+                mx[qt] = quad_max(fmaxf(fmaxf(fmaxf(sacc[0][qt][0], sacc[0][qt][1]), fmaxf(sacc[0][qt][2], sacc[0][qt][3])),
+                                        fmaxf(fmaxf(sacc[1][qt][0], sacc[1][qt][1]), fmaxf(sacc[1][qt][2], sacc[1][qt][3])))) * c_abs;
+        } else {
+            const uint32_t tail = rem >= 32 ? 0xffffffffu : (rem <= 0 ? 0u : ((1u << rem) - 1u));
+            const uint32_t tail8 = ((tail >> (4 * g)) & 0xfu) | (((tail >> (16 + 4 * g)) & 0xfu) << 4);
+            const int tb = tree ? (tile - tree_first) / NW : 0;
+#pragma unroll
+            for (int qt = 0; qt < NQA; ++qt) {
+                const uint32_t vq = kVisInLds ? sVis[((tb * NW + wave) * NQ + qt) * 64 + lane] : vis[qt] >> (8 * tb);
+                const uint32_t bits = (tree ? vq : 0xffu) & tail8;
+                float tmax = -INFINITY;
+#pragma unroll
+                for (int mt = 0; mt < 2; ++mt)
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) {
+                        const float sv = ((bits >> (4 * mt + i)) & 1u) ? sacc[mt][qt][i] * a.scale_log2e : -INFINITY;
+                        sacc[mt][qt][i] = sv;
+                        tmax = fmaxf(tmax, sv);
+                    }
+                mx[qt] = quad_max(tmax);
+            }
+        }
+        const float c_fold = plain ? c_abs : 1.0f;
+        // Reference of the exponents: the workgroup's running one, or this tile's maximum in rows where it lies
+        // more than 2^kSlack above that.  Rows seldom move once the first block is in, and while none does
+        // (`moved`, agreed through LDS) the products add up without a factor.
+        float ref[NQA], psum[NQA];
+        vec8 pb[NQA];
+        bool moved = false;
+#pragma unroll
+        for (int qt = 0; qt < NQA; ++qt) {
+            const bool up = mx[qt] > m_ref[qt] + kSlack;
+            moved |= __builtin_amdgcn_ballot_w64(up) != 0;
+            ref[qt] = up ? mx[qt] : m_ref[qt];
+            const float m_safe = (ref[qt] == -INFINITY) ? 0.f : ref[qt];
+            float sum = 0.f;
+#pragma unroll
+            for (int mt = 0; mt < 2; ++mt)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const float pv = __builtin_amdgcn_exp2f(__builtin_fmaf(sacc[mt][qt][i], c_fold, -m_safe));
+                    sum += pv;
+                    pb[qt][4 * mt + i] = (T)pv;
                 }
+            psum[qt] = sum;
+            // the last block's table also carries the waves' sums
+            if (!more) psum[qt] = quad_sum(l_own[qt] * __builtin_amdgcn_exp2f(m_ref[qt] - m_safe) + sum);
+        }
+        if (ib > 0) lds_barrier();        // the block before is read
 #pragma unroll
-                for (int qt = 0; qt < NQA; ++qt) {
-                    const vec8 pB = *reinterpret_cast<const vec8 *>(sP + ((kt * NQ + qt) * 64 + lane) * 16);
+        for (int qt = 0; qt < NQA; ++qt)
+            *reinterpret_cast<vec8 *>(sP + ((wave * NQ + qt) * 64 + lane) * 16) = pb[qt];
+        if (!more || moved) {
 #pragma unroll
-                    for (int j = 0; j < kDTW; ++j)
-                        oacc[j][qt] = Elem<T>::mfma(aV[j], pB, oacc[j][qt]);
+            for (int qt = 0; qt < NQA; ++qt)
+                if (g == 0) *reinterpret_cast<float2 *>(sML + (qt * 16 + r16) * kMLStride + wave * 8) = make_float2(ref[qt], psum[qt]);
+        }
+        if (more && lane == 0) sMoved[wave] = moved ? 1 : 0;
+#pragma unroll
+        for (int s = 0; s < G::kLoads; ++s) *reinterpret_cast<vec8 *>(my_tile + v_wr(s, lane)) = vreg[s];
+        if (NQA * JW > 3) __builtin_amdgcn_sched_barrier(0);
+        if (more) {
+            fetch(tile + NW, lane, std::false_type{}, std::true_type{});
+            next_page(tile + 2 * NW);
+        }
+        lds_barrier();                    // tiles, probabilities and references of all waves visible
+
+        constexpr int QWA = (NQA + RW - 1) / RW;
+        auto row_tile = [&](int i) __attribute__((always_inline)) { return RW == 1 ? i : min(RW * i + q_first, NQA - 1); };
+        auto v_frag = [&](int kt, int j) __attribute__((always_inline)) {
+            const unsigned char *vt = sV + kt * G::kTileBytes + vt_rd(j_first + j, lane);
+            const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4 *)vt);
+            const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4 *)(vt + 16 * G::kRowBytes));
+            return __builtin_bit_cast(vec8, (s16x8)__builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+        };
+        auto p_frag = [&](int kt, int qt) __attribute__((always_inline)) { return *reinterpret_cast<const vec8 *>(sP + ((kt * NQ + qt) * 64 + lane) * 16); };
+        uint32_t any = 1;
+        int4 mv[NW / 4];
+        if (more) {
+            any = 0;
+#pragma unroll
+            for (int w = 0; w < NW / 4; ++w) {
+                mv[w] = *reinterpret_cast<const int4 *>(sMoved + 4 * w);
+                any |= mv[w].x | mv[w].y | mv[w].z | mv[w].w;
+            }
+            any = __builtin_amdgcn_readfirstlane(any);
+        }
+        if (any == 0) {
+#pragma unroll
+            for (int qt = 0; qt < NQA; ++qt) l_own[qt] += psum[qt];
+#pragma unroll
+            for (int kt = 0; kt < NW; ++kt) {
+                vec8 aV[JW];
+#pragma unroll
+                for (int j = 0; j < JW; ++j) aV[j] = v_frag(kt, j);
+#pragma unroll
+                for (int i = 0; i < QWA; ++i) {
+                    const vec8 pB = p_frag(kt, row_tile(i));
+#pragma unroll
+                    for (int j = 0; j < JW; ++j) oacc[i][j] = Elem<T>::mfma(aV[j], pB, oacc[i][j]);
+                }
+                if (NQA * JW > 2) __builtin_amdgcn_sched_barrier(0);
+            }
+            return;
+        }
+        // some row's reference moves (or the sums are due): products scaled by 2^(tile reference - new reference)
+        constexpr int QP = QWA * JW > 3 ? (QWA + 1) / 2 : QWA;       // row tiles per pass over V: the factors of more of them do not fit
+        const int n_here = tile_end - (tile - wave);            // tiles of this block (those past the end hold zeros)
+        float m_new[NQA];
+#pragma unroll
+        for (int i0 = 0; i0 < QWA; i0 += QP) {
+            float fac[QP][NW];
+#pragma unroll
+            for (int i = 0; i < QP; ++i) {
+                if (i0 + i >= QWA) continue;
+                const int qt = row_tile(i0 + i);
+                float m_old = m_ref[RW == 1 ? i0 + i : 0];
+                if (RW > 1) {
+#pragma unroll
+                    for (int q = 1; q < NQA; ++q) m_old = q == qt ? m_ref[q] : m_old;
+                }
+                f32x4 ml[NW / 2];
+#pragma unroll
+                for (int w = 0; w < NW / 2; ++w) ml[w] = *reinterpret_cast<const f32x4 *>(sML + (qt * 16 + r16) * kMLStride + w * 16);
+                float m = m_old;
+#pragma unroll
+                for (int w = 0; w < NW; ++w) {
+                    if (more) {
+                        const int f = w % 4 == 0 ? mv[w / 4].x : w % 4 == 1 ? mv[w / 4].y : w % 4 == 2 ? mv[w / 4].z : mv[w / 4].w;
+                        ml[w / 2][2 * (w & 1)] = f ? ml[w / 2][2 * (w & 1)] : m_old;
+                    }
+                    m = fmaxf(m, ml[w / 2][2 * (w & 1)]);
+                }
+                const float m_safe = (m == -INFINITY) ? 0.f : m;
+                float l = 0.f;
+#pragma unroll
+                for (int w = 0; w < NW; ++w) {
+                    fac[i][w] = __builtin_amdgcn_exp2f(ml[w / 2][2 * (w & 1)] - m_safe);
+                    if (!more) l += fac[i][w] * ml[w / 2][2 * (w & 1) + 1];
+                }
+                const float alpha = __builtin_amdgcn_exp2f(m_old - m_safe);
+#pragma unroll
+                for (int j = 0; j < JW; ++j) oacc[i0 + i][j] *= alpha;
+                if (!more) { m_out[i0 + i] = m; l_out[i0 + i] = l; }
+                if (RW == 1) m_new[i0 + i] = m;
+            }
+            auto pv_tile = [&](int kt) __attribute__((always_inline)) {
+                vec8 aV[JW];
+#pragma unroll
+                for (int j = 0; j < JW; ++j) aV[j] = v_frag(kt, j);
+#pragma unroll
+                for (int i = 0; i < QP; ++i) {
+                    if (i0 + i >= QWA) continue;
+                    const vec8 pB = p_frag(kt, row_tile(i0 + i));
+#pragma unroll
+                    for (int j = 0; j < JW; ++j)
+                        oacc[i0 + i][j] += fac[i][kt] * Elem<T>::mfma(aV[j], pB, f32x4{0.f, 0.f, 0.f, 0.f});
                 }
             };
-            if (cur_key0 + kBlock <= cur_end) {
 #pragma unroll
-                for (int kt = 0; kt < NW; ++kt) pv_tile(kt);
-            } else {
-#pragma unroll 1
-                for (int kt = 0; cur_key0 + kt * G::kTileKeys < cur_end; ++kt) pv_tile(kt);
+            for (int kt = 0; kt < NW / 2; ++kt) { pv_tile(kt); __builtin_amdgcn_sched_barrier(0); }
+            if (n_here > NW / 2) {
+#pragma unroll
+                for (int kt = NW / 2; kt < NW; ++kt) { pv_tile(kt); __builtin_amdgcn_sched_barrier(0); }
             }
-            lds_barrier();        // (C) tiles and P^T free for the next block
-            if (ib == 0) RD_TR(2);
+        }
+        if (more) {
+#pragma unroll
+            for (int qt = 0; qt < NQA; ++qt) {
+                float m = m_ref[qt];
+                if (RW == 1) {
+                    m = m_new[qt];
+                } else {
+#pragma unroll
+                    for (int w = 0; w < NW; ++w) {
+                        const int f = w % 4 == 0 ? mv[w / 4].x : w % 4 == 1 ? mv[w / 4].y : w % 4 == 2 ? mv[w / 4].z : mv[w / 4].w;
+                        const float r = *reinterpret_cast<const float *>(sML + (qt * 16 + r16) * kMLStride + w * 8);
+                        m = fmaxf(m, f ? r : -INFINITY);
+                    }
+                }
+                const float m_safe = (m == -INFINITY) ? 0.f : m;
+                l_own[qt] = l_own[qt] * __builtin_amdgcn_exp2f(m_ref[qt] - m_safe) + psum[qt] * __builtin_amdgcn_exp2f(ref[qt] - m_safe);
+                m_ref[qt] = m;
+            }
         }
     };
-    constexpr int kHalf = (NQ + 1) / 2;
-    if (NQ > 1 && nqt <= kHalf) block_loop(std::integral_constant<int, kHalf>{});
-    else if (NQ == 5 && nqt == 4) block_loop(std::integral_constant<int, NQ == 5 ? 4 : NQ>{});   // five tiles spill; four do not
-    else block_loop(std::integral_constant<int, NQ>{});
-    RD_TR(3);
-
-    // ---- a head served by this workgroup alone: normalise and write the output -------------------
-    if (n_part == 1) {
-        float *sL1 = sM;          // [kRows][NW]
+    T *outp = static_cast<T *>(a.out) + ((size_t)bh * a.N + row0) * D;
+    auto put = [&](int i, f32x4 (&o)[JW], float l) __attribute__((always_inline)) {
+        const int qt = RW * i + q_first, row = qt * 16 + r16;
+        if (qt < NQ && row < Ng) {
+            const bool keep = row < P;                          // rows beyond the packed count are zero
+            const float inv = keep ? 1.0f / l : 0.f;
 #pragma unroll
-        for (int qt = 0; qt < NQ; ++qt) {
-            const float l = quad_sum(l_run[qt]);
-            if (g == 0) sL1[(qt * 16 + r16) * NW + wave] = l;
-        }
-        lds_barrier();
-        T *outp = static_cast<T *>(a.out) + ((size_t)bh * a.N + row0) * D;
+            for (int j = 0; j < JW; ++j) {
+                f32x4 y;
 #pragma unroll
-        for (int qt = 0; qt < NQ; ++qt) {
-            const int qrow = qt * 16 + r16;
-            if (qrow < Ng) {
-                float lsum = sL1[qrow * NW];
-#pragma unroll
-                for (int w = 1; w < NW; ++w) lsum += sL1[qrow * NW + w];
-                const bool keep = qrow < P;                               // rows beyond the packed count are zero
-                const float inv = keep ? 1.0f / lsum : 0.f;
-#pragma unroll
-                for (int j = 0; j < kDTW; ++j) {
-                    const f32x4 o = oacc[j][qt];
-                    store_out4(outp + (size_t)qrow * D + (wave * kDTW + j) * 16 + 4 * g, keep ? o[0] * inv : 0.f,
-                               keep ? o[1] * inv : 0.f, keep ? o[2] * inv : 0.f, keep ? o[3] * inv : 0.f);
+                for (int e = 0; e < 4; ++e) {
+                    float v = keep ? o[j][e] * inv : 0.f;
+                    asm volatile("" : "+v"(v));                 // an fp32 product, then one rounding, in every instance
+                    y[e] = v;
                 }
+                store_out4(outp + (size_t)row * D + (j_first + j) * 16 + 4 * g, y[0], y[1], y[2], y[3]);
             }
         }
+    };
+    auto finish = [&](auto nqa_tag, auto &m_run, auto &l_run, auto &oacc) __attribute__((always_inline)) {
+    constexpr int QWA = (decltype(nqa_tag)::value + RW - 1) / RW;      // row tiles that can hold packed rows; the rest of the output is zero
+    if (n_part == 1) {        // the head's only workgroup
+#pragma unroll
+        for (int i = 0; i < QW; ++i) put(i, oacc[i < QWA ? i : 0], l_run[i < QWA ? i : 0]);
         RD_TR(6);
         return;
     }
 
-    // ---- partial state of this key range -> workspace ------------------------------------------
-    // Layout of one partial: (m, l) pairs [kRows][2], then the output accumulators exactly as the
-    // lanes hold them, [wave][d-tile j][row tile qt][lane][4 floats], so that every wave store
-    // (and the merge's loads) covers 1 KB of contiguous memory.
-    const size_t unit = (size_t)bh * n_rg + rg;                    // (head, row group): one merge each
-    float *part = a.partials + (unit * n_part + split) * kPF;
-    const int frag_off = 2 * kRows + wave * kDTW * NQ * 256 + lane * 4;    // + (j*NQ + qt)*256
-    float *sL = sM;           // reuse: [NW waves][kRows]
+    // ---- partial state -> workspace; the last workgroup of this head (and row group) merges -----------
+    // Layout of one partial: (m, l) per row, then the fragments [row tile][d-tile][64 lanes][4], so that
+    // every wave store and load covers 1 KB.
+    const size_t unit = (size_t)bh * n_rg + rg;
+    float *part = a.partials + ((size_t)bh * a.S + split * n_act + rg) * kPF;
+    auto frag = [&](int i, int j) __attribute__((always_inline)) { return 2 * kRows + (((RW * i + q_first) * DT + j_first + j) * 64 + lane) * 4; };
+    auto real = [&](int i) __attribute__((always_inline)) { return RW * i + q_first < NQ && (RW * i + q_first) * 16 + r16 < P; };
 #pragma unroll
-    for (int qt = 0; qt < NQ; ++qt) {
-        const float l = quad_sum(l_run[qt]);
-        if (g == 0) sL[(qt * 16 + r16) * NW + wave] = l;
-    }
+    for (int i = 0; i < QWA; ++i) {
+        if (real(i)) {
+            if (j_first == 0 && g == 0) st_dev2(part + 2 * ((RW * i + q_first) * 16 + r16), m_run[i], l_run[i]);
 #pragma unroll
-    for (int qt = 0; qt < NQ; ++qt) {
-        if (qt * 16 + r16 < P) {                        // lanes whose row is padding neither store nor (in the merge) load
-#pragma unroll
-            for (int j = 0; j < kDTW; ++j) {
-                const f32x4 o = oacc[j][qt];
-                st_dev4(part + frag_off + (j * NQ + qt) * 256, o[0], o[1], o[2], o[3]);
-            }
+            for (int j = 0; j < JW; ++j) st_dev4(part + frag(i, j), oacc[i][j][0], oacc[i][j][1], oacc[i][j][2], oacc[i][j][3]);
         }
     }
-    lds_barrier();
-    if (wave == 0 && g == 0) {
-#pragma unroll
-        for (int qt = 0; qt < NQ; ++qt) {
-            const int qrow = qt * 16 + r16;
-            float lsum = sL[qrow * NW];
-#pragma unroll
-            for (int w = 1; w < NW; ++w) lsum += sL[qrow * NW + w];
-            st_dev2(part + 2 * qrow, m_run[qt], lsum);
-        }
-    }
-
-    // ---- last workgroup of this (sequence, head) merges and writes the output ---------------------
-    // With the XCD-aligned mapping every producer of this head ran on this XCD, so their
-    // write-through stores also updated this XCD's L2 and plain (cached, 16-byte) loads see them.
     RD_TR(4);
     const int last = arrive_is_last(a.counters + unit, (uint32_t)n_part);
     RD_TR(5);
     if (last == kNotLast) return;
     const bool cached = (last == kLastClean);
-    RD_TR(11);
-#ifdef RD_TRACE
-    if (tid == 0 && rd_trace_buf) rd_trace_buf[(size_t)blockIdx.x * 16 + 13] = 1000 + last * 10 + xcc_id();
-#endif
-
-    // Merge: out[q] = sum_s 2^(m_s - M) O_s[q] / sum_s 2^(m_s - M) l_s[q], M = max_s m_s (log2
-    // units).  Each thread merges the accumulator fragments it would own itself, two row tiles at
-    // a time; the loads of up to kChunk partials for both are issued together, then consumed (the
-    // read of a head's partials by one compute unit is what this phase costs, so it should be a
-    // single round trip whenever the partials are few).
-    constexpr int kChunk = 6;
-    const float *hp = a.partials + unit * n_part * kPF;
-    T *outp = static_cast<T *>(a.out) + ((size_t)bh * a.N + row0) * D;
-    const int nqt_out = (Ng + 15) >> 4;
-#pragma unroll 1
-    for (int qt0 = 0; qt0 < nqt_out; qt0 += 2) {
-        float M[2], den[2];
-        f32x4 acc[2][kDTW];
+    constexpr int kChunk = 6;                                   // partials whose loads are in flight together
+    constexpr int kPair = QWA < 2 || JW > 1 ? 1 : 2;                       // row tiles merged together
+    const float *hp = a.partials + ((size_t)bh * a.S + rg) * kPF;
 #pragma unroll
-        for (int u = 0; u < 2; ++u) {
+    for (int i0 = 0; i0 < QW; i0 += kPair) {
+        float M[kPair], den[kPair];
+        f32x4 acc[kPair][JW];
+#pragma unroll
+        for (int u = 0; u < kPair; ++u) {
             M[u] = -INFINITY;
             den[u] = 0.f;
 #pragma unroll
-            for (int j = 0; j < kDTW; ++j) acc[u][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+            for (int j = 0; j < JW; ++j) acc[u][j] = f32x4{0.f, 0.f, 0.f, 0.f};
         }
-        if (qt0 < nqt) {
-            const bool two = qt0 + 1 < nqt;                                     // uniform
+        if (i0 < QWA && (RW * i0 + q_first) * 16 < P) {
 #pragma unroll 1
             for (int s0 = 0; s0 < n_part; s0 += kChunk) {
-                float2 ml[2][kChunk];
-                f32x4 f[2][kChunk][kDTW];
+                float2 ml[kPair][kChunk];
+                f32x4 fr[kPair][kChunk][JW];
 #pragma unroll
                 for (int c = 0; c < kChunk; ++c) {
-                    const bool have = s0 + c < n_part;                          // uniform
-                    const float *ps = hp + (size_t)(s0 + c) * kPF;
+                    const bool have = s0 + c < n_part;          // uniform
+                    const float *ps = hp + (size_t)(s0 + c) * n_act * kPF;
 #pragma unroll
-                    for (int u = 0; u < 2; ++u) {
-                        ml[u][c] = make_float2(-INFINITY, 0.f);                 // absent: weight 2^-inf = 0
+                    for (int u = 0; u < kPair; ++u) {
+                        ml[u][c] = make_float2(-INFINITY, 0.f); // absent: weight 2^-inf = 0
 #pragma unroll
-                        for (int j = 0; j < kDTW; ++j) f[u][c][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-                        if (have && (u == 0 || two) && (qt0 + u) * 16 + r16 < P) {
-                            const int qt = qt0 + u;
-                            const float *pm = ps + 2 * (qt * 16 + r16);
-                            const float *pf = ps + frag_off + qt * 256;
+                        for (int j = 0; j < JW; ++j) fr[u][c][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+                        if (have && i0 + u < QWA && real(i0 + u)) {
+                            const float *pm = ps + 2 * ((RW * (i0 + u) + q_first) * 16 + r16);
                             if (cached) {
                                 ml[u][c] = *reinterpret_cast<const float2 *>(pm);
 #pragma unroll
-                                for (int j = 0; j < kDTW; ++j)
-                                    f[u][c][j] = *reinterpret_cast<const f32x4 *>(pf + j * NQ * 256);
+                                for (int j = 0; j < JW; ++j) fr[u][c][j] = *reinterpret_cast<const f32x4 *>(ps + frag(i0 + u, j));
                             } else {
                                 ml[u][c] = ld_dev2(pm);
 #pragma unroll
-                                for (int j = 0; j < kDTW; ++j) {
-                                    const float2 lo = ld_dev2(pf + j * NQ * 256);
-                                    const float2 hi = ld_dev2(pf + j * NQ * 256 + 2);
-                                    f[u][c][j] = f32x4{lo.x, lo.y, hi.x, hi.y};
+                                for (int j = 0; j < JW; ++j) {
+                                    const float2 lo = ld_dev2(ps + frag(i0 + u, j)), hi = ld_dev2(ps + frag(i0 + u, j) + 2);
+                                    fr[u][c][j] = f32x4{lo.x, lo.y, hi.x, hi.y};
                                 }
                             }
                         }
                     }
                 }
-                if (qt0 == 0 && s0 == 0) RD_TR(12);
 #pragma unroll
-                for (int u = 0; u < 2; ++u) {
+                for (int u = 0; u < kPair; ++u) {
                     float Mn = M[u];
 #pragma unroll
                     for (int c = 0; c < kChunk; ++c) Mn = fmaxf(Mn, ml[u][c].x);
@@ -732,69 +757,88 @@ __global__ __launch_bounds__(NW * 64, 2) void rd_tree_attn_mfma_kernel(AttnArgs 
                     const float resc = __builtin_amdgcn_exp2f(M[u] - Ms);
                     den[u] *= resc;
 #pragma unroll
-                    for (int j = 0; j < kDTW; ++j) acc[u][j] *= resc;
+                    for (int j = 0; j < JW; ++j) acc[u][j] *= resc;
 #pragma unroll
                     for (int c = 0; c < kChunk; ++c) {
-                        const float w = __builtin_amdgcn_exp2f(ml[u][c].x - Ms);     // 0 for an empty or absent range
+                        const float w = __builtin_amdgcn_exp2f(ml[u][c].x - Ms);
                         den[u] += w * ml[u][c].y;
 #pragma unroll
-                        for (int j = 0; j < kDTW; ++j) acc[u][j] += w * f[u][c][j];
+                        for (int j = 0; j < JW; ++j) acc[u][j] += w * fr[u][c][j];
                     }
                     M[u] = Mn;
                 }
             }
         }
-        if (qt0 == 0) RD_TR(7);
+        RD_TR(7);
 #pragma unroll
-        for (int u = 0; u < 2; ++u) {
-            const int qrow = (qt0 + u) * 16 + r16;
-            if (qrow < Ng) {
-                const bool keep = qrow < P;                               // rows beyond the packed count are zero
-                const float inv = keep ? 1.0f / den[u] : 0.f;
-#pragma unroll
-                for (int j = 0; j < kDTW; ++j) {
-                    const int d0 = (wave * kDTW + j) * 16 + 4 * g;
-                    store_out4(outp + (size_t)qrow * D + d0, keep ? acc[u][j][0] * inv : 0.f, keep ? acc[u][j][1] * inv : 0.f,
-                               keep ? acc[u][j][2] * inv : 0.f, keep ? acc[u][j][3] * inv : 0.f);
-                }
-            }
-        }
+        for (int u = 0; u < kPair; ++u)
+            if (i0 + u < QW) put(i0 + u, acc[u], den[u]);
     }
     if (tid == 0) a.counters[unit] = 0;   // leave the workspace ready for the next call
     RD_TR(6);
+    };
+
+    // Loop and epilogue are instantiated for all row tiles and for the lower half (a padded row tile costs as
+    // much as a real one); the last block, which fetches nothing, is a step of its own.
+    auto walk = [&](auto nqa_tag) __attribute__((always_inline)) {
+        constexpr int NQA = decltype(nqa_tag)::value;
+        constexpr int QWA = (NQA + RW - 1) / RW;
+        float m_ref[NQA], l_own[NQA];     // exponents' reference of every row; this wave's share of the sums (lane partials)
+        float m_run[QWA], l_run[QWA];     // in the end: reference and sum of the rows this wave writes
+        f32x4 oacc[QWA][JW];
+#pragma unroll
+        for (int qt = 0; qt < NQA; ++qt) { m_ref[qt] = -INFINITY; l_own[qt] = 0.f; }
+#pragma unroll
+        for (int i = 0; i < QWA; ++i) {
+            m_run[i] = -INFINITY;
+            l_run[i] = 0.f;
+#pragma unroll
+            for (int j = 0; j < JW; ++j) oacc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+        }
+        vec8 qf[kQReg ? NQ : 1][KS];
+        if constexpr (kQReg) {
+#pragma unroll
+            for (int qt = 0; qt < NQA; ++qt)
+#pragma unroll
+                for (int t = 0; t < KS; ++t) qf[qt][t] = *reinterpret_cast<const vec8 *>(sQ + ((qt * KS + t) * 64 + lane) * 16);
+        }
+        for (int ib = 0; ib + 1 < nb; ++ib) block_step(nqa_tag, std::true_type{}, ib, qf, m_ref, l_own, oacc, m_run, l_run);
+        if (nb > 0) block_step(nqa_tag, std::false_type{}, nb - 1, qf, m_ref, l_own, oacc, m_run, l_run);
+        RD_TR(3);
+        finish(nqa_tag, m_run, l_run, oacc);
+    };
+    constexpr int kHalf = (NQ + 1) / 2;
+    if (NQ > 1 && nqt <= kHalf) walk(std::integral_constant<int, kHalf>{});
+    else walk(std::integral_constant<int, NQ>{});
+
 }
 
-template <int D, int NQ, int NW>
-static size_t mfma_smem_bytes()
+template <int D, int NQ, int NW, int TB>
+static constexpr size_t mfma_smem_bytes()
 {
-    return (size_t)NQ * 16 * Geo<D>::kRowBytes + NW * Geo<D>::kTileBytes + (size_t)NW * NQ * 64 * 16 +
-           (size_t)NW * NQ * 16 * sizeof(float) + (size_t)NW * NQ * 64 * sizeof(uint32_t);
+    return (size_t)NQ * Geo<D>::kKSteps * 1024 + (size_t)NW * Geo<D>::kTileBytes + (size_t)NW * NQ * 1024 + (size_t)NQ * 16 * (NW * 8 + 16) + NW * sizeof(int) +
+           (NQ > 4 ? (size_t)TB * NW * NQ * 64 : 0) + (stage_k<D, NQ, NW>() ? (size_t)NW * 16 * Geo<D>::kRowBytes : 0);
 }
 
-template <typename T, int D, int NQ, int NW, int TB, bool PAGED, bool ROPE = false>
+template <typename T, int D, int NQ, int NW, int TB, bool PAGED, bool ROPE>
 static int launch_mfma(const AttnArgs &a, hipStream_t stream)
 {
-    const size_t smem = mfma_smem_bytes<D, NQ, NW>();
+    constexpr size_t smem = mfma_smem_bytes<D, NQ, NW, TB>();
+    static_assert(smem <= 160 * 1024, "LDS of a compute unit");
     static std::atomic<unsigned long long> configured{0};
-    const int st = ensure_dynamic_lds(reinterpret_cast<const void *>(&rd_tree_attn_mfma_kernel<T, D, NQ, NW, TB, PAGED, ROPE>), smem,
-                                      configured);
+    const int st = ensure_dynamic_lds(reinterpret_cast<const void *>(&rd_tree_attn_mfma_kernel<T, D, NQ, NW, TB, PAGED, ROPE>), smem, configured);
     if (st != RD_OK) return st;
-    const size_t wgs = (size_t)a.B * a.H * (a.S + (a.fuse_tree ? 0 : 1)) * a.n_rg;
+    const size_t wgs = ((size_t)a.B * a.H + 7) / 8 * 8 * a.S;
     if (wgs > 0x7fffffffull) return RD_ERR_UNSUPPORTED;
-    const unsigned grid = (unsigned)wgs;
-    hipLaunchKernelGGL((rd_tree_attn_mfma_kernel<T, D, NQ, NW, TB, PAGED, ROPE>), dim3(grid), dim3(NW * 64), smem, stream, a);
+    hipLaunchKernelGGL((rd_tree_attn_mfma_kernel<T, D, NQ, NW, TB, PAGED, ROPE>), dim3((unsigned)wgs), dim3(NW * 64), smem, stream, a);
     return rd_check_launch();
 }
 
-// rg_tiles = 16-row tiles per workgroup (the template's NQ); D = 128 kernels exist for 1..5 tiles,
-// D = 64 kernels for 1..8 (the plan never asks for more).  Beams with more packed keys than one
-// block (N > 32*NW) only occur with row groups, i.e. with kGroupTiles tiles.
-template <typename T, int D, int NW, bool PAGED, bool ROPE = false>
+template <typename T, int D, int NW, bool PAGED, bool ROPE>
 static int dispatch_nq(const AttnArgs &a, int rg_tiles, hipStream_t stream)
 {
-    constexpr int kGroupTiles = D == 128 ? 3 : 4;
-    const int tb = (a.N + 32 * NW - 1) / (32 * NW);
-    if (tb > 1) {
+    const int tb = ((a.N + 31) / 32 + NW - 1) / NW;             // packed-key tiles a wave can meet
+    if (tb > 1) {                                               // (N > 32 NW: the largest row groups)
         if (rg_tiles != kGroupTiles) return RD_ERR_UNSUPPORTED;
         if (tb == 2) return launch_mfma<T, D, kGroupTiles, NW, 2, PAGED, ROPE>(a, stream);
         if constexpr (NW == 4) {
@@ -808,26 +852,16 @@ static int dispatch_nq(const AttnArgs &a, int rg_tiles, hipStream_t stream)
     case 3: return launch_mfma<T, D, 3, NW, 1, PAGED, ROPE>(a, stream);
     case 4: return launch_mfma<T, D, 4, NW, 1, PAGED, ROPE>(a, stream);
     case 5: return launch_mfma<T, D, 5, NW, 1, PAGED, ROPE>(a, stream);
-    default: break;
+    default: return RD_ERR_UNSUPPORTED;
     }
-    if constexpr (D == 64) {
-        switch (rg_tiles) {
-        case 6: return launch_mfma<T, 64, 6, NW, 1, PAGED, ROPE>(a, stream);
-        case 7: return launch_mfma<T, 64, 7, NW, 1, PAGED, ROPE>(a, stream);
-        case 8: return launch_mfma<T, 64, 8, NW, 1, PAGED, ROPE>(a, stream);
-        default: break;
-        }
-    }
-    return RD_ERR_UNSUPPORTED;
 }
 
 template <typename T, bool PAGED, bool ROPE = false>
 static int tree_attn_mfma(const AttnArgs &a, int D, int waves, int rg_tiles, hipStream_t stream)
 {
     if (D == 128)
-        return waves == 8 ? dispatch_nq<T, 128, 8, PAGED, ROPE>(a, rg_tiles, stream)
-                          : dispatch_nq<T, 128, 4, PAGED, ROPE>(a, rg_tiles, stream);
-    return dispatch_nq<T, 64, 4, PAGED, ROPE>(a, rg_tiles, stream);
+        return waves == 8 ? dispatch_nq<T, 128, 8, PAGED, ROPE>(a, rg_tiles, stream) : dispatch_nq<T, 128, 4, PAGED, ROPE>(a, rg_tiles, stream);
+    return waves == 8 ? dispatch_nq<T, 64, 8, PAGED, ROPE>(a, rg_tiles, stream) : dispatch_nq<T, 64, 4, PAGED, ROPE>(a, rg_tiles, stream);
 }
 
 }  // namespace rd

@@ -145,6 +145,40 @@ def test_shapes(rd, dtype, D, W, L):
     full_check(rd, t, dtype, what="shapes")
 
 
+@pytest.mark.parametrize("dtype", ["bf16", "f16", "f32"])
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("B,H,W,L,ctx", [(2, 8, 3, 4, (700, 1100)), (1, 3, 8, 5, (1500,)), (3, 2, 12, 6, (40, 513, 900)), (1, 2, 40, 6, (800,))])
+def test_scores_that_rise(rd, dtype, D, B, H, W, L, ctx):
+    """Softmax references that move block after block: keys that grow along the context (and, in the second half of
+    the heads, a few late keys far above the rest), so that earlier blocks' sums are rescaled, for some rows only."""
+    announce("attn rising scores dtype=%s D=%d B=%d H=%d W=%d L=%d" % (dtype, D, B, H, W, L))
+    t = make_case(B, H, D, W, L, ctx, dtype, seed=D + W, poison=False)
+    Cmax = max(ctx)
+    k = synth.to_f64(t["k_cache"], dtype)
+    rise = np.linspace(0.05, 4.0, Cmax)[None, None, :, None]
+    k[:, :H // 2 + 1] *= rise
+    k[:, H // 2 + 1:, ::97] *= 6.0
+    if dtype == "bf16":
+        t["k_cache"] = host(torch.from_numpy(k).to(torch.bfloat16))
+    else:
+        t["k_cache"] = k.astype(np.float16 if dtype == "f16" else np.float32)
+    full_check(rd, t, dtype, scale=0.5, what="rising")
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f16"])
+@pytest.mark.parametrize("D,B,H,W,L,Cmax", [(128, 3, 3, 8, 5, 4000), (64, 2, 5, 3, 4, 6000), (128, 1, 2, 30, 6, 3000), (128, 1, 9, 70, 5, 2500)])
+def test_live_contexts_far_below_capacity(rd, dtype, D, B, H, W, L, Cmax):
+    """Plans with many workgroups per head, contexts that leave most of them without keys, head counts that do not
+    divide by the XCDs."""
+    announce("attn far below capacity dtype=%s D=%d B=%d H=%d W=%d L=%d" % (dtype, D, B, H, W, L))
+    for ctx in ([0, 33, 250][:B], [Cmax, 31, 700][:B]):
+        ctx = np.asarray(ctx, np.int32)
+        t = dict(ctx_len=ctx, beams=synth.make_beams(B, W, L, 9, 3, "uniform"))
+        t["q"], t["k_new"], t["v_new"] = synth.make_qkv_new(B, H, W * L, D, dtype, 4)
+        t["k_cache"], t["v_cache"] = synth.make_kv_cache(B, H, Cmax, D, dtype, 5, ctx, True)
+        full_check(rd, t, dtype, what="below capacity")
+
+
 @pytest.mark.parametrize("dtype", ["bf16", "f32", "f16"])
 def test_degenerate_beams_and_scales(rd, dtype):
     announce("attn degenerate beams dtype=%s" % dtype)
