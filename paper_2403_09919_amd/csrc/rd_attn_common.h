@@ -13,15 +13,11 @@
 
 namespace rd {
 
-constexpr int kAttnThreads = 256;
-constexpr int kBlockKeys = 128;   // keys handled per workgroup iteration
-
 struct AttnPlan {
-    int waves;         // matrix-core kernel: waves per workgroup (4 or 8); a block is 32*waves keys
-    int S;             // workgroups per (sequence, head); fp32 kernel: context ranges, one more workgroup takes the packed keys
-    int rows_pad;      // packed rows padded to a multiple of 16 (fp32 kernel's partial layout)
-    int rg_tiles;      // matrix-core kernel: 16-row tiles of packed rows per workgroup (a row group)
-    int n_rg;          // ... row groups per (sequence, head); 1 unless N is large
+    int waves;         // waves per workgroup (4 or 8); a block is a tile of keys per wave
+    int S;             // workgroups per (sequence, head)
+    int rg_tiles;      // 16-row tiles of packed rows per workgroup (a row group)
+    int n_rg;          // row groups per (sequence, head); 1 unless N is large
     size_t counters_bytes;
     size_t total_bytes;
 };
@@ -84,53 +80,59 @@ static inline AttnPlan attn_plan_make(int B, int H, int N, int D, int Cmax)
                 best.rg_tiles = nq;
                 best.n_rg = n_rg;
                 best.counters_bytes = ((size_t)BH * n_rg * sizeof(unsigned long long) + 255) / 256 * 256;
-                best.total_bytes = best.counters_bytes + (S > 1 ? (size_t)BH * S * (size_t)(nq * 16 * (2 + D)) * sizeof(float) : 0);
+                best.total_bytes = best.counters_bytes + (S > 1 ? ((size_t)BH * S * (size_t)(nq * 16 * (2 + D)) * sizeof(float) + 255) / 256 * 256 : 0);
             }
         }
     }
-    best.rows_pad = nq_all * 16;
+    return best;
+}
+
+// Plan of the fp32 kernel (rd_tree_attn_f32.hip; row groups of one tile): workgroups per head, estimated as above.  A
+// workgroup is eight waves of 16-key tiles; a block of 128 keys takes 3.0 us (D = 128) or half of that, a compute
+// unit reads 40 GB/s, the chip 5 TB/s.
+static inline AttnPlan attn_plan_make_f32(int B, int H, int N, int D, int Cmax)
+{
+    AttnPlan best = {};
+    const long long BH = (long long)B * H;
+    static const int forced = env_int("RD_ATTN_SPLITS", 0);
+    const double rows = 0.6 * N, t_blk = D == 128 ? 3.0 : 1.5, part = 16.0 * (2 + D) * sizeof(float);
+    const int tiles = (Cmax + 15) / 16 + ((int)rows + 15) / 16, nblk = tiles > 8 ? (tiles + 7) / 8 : 1;
+    const int n_rg = (N + 15) / 16, n_act = rows > 16 ? (int)((rows + 15) / 16) : 1;
+    double best_T = 1e30;
+    for (int S = n_rg; S <= 64 * n_rg && S <= nblk * n_rg; ++S) {
+        const int ranges = S / n_act, per = (nblk + ranges - 1) / ranges, n_part = (nblk + per - 1) / per;
+        const double t_lat = 1.5 + per * t_blk, bytes = (double)(per * 8 < tiles ? per * 8 : tiles) * 16 * D * 8;
+        const long long wgs = (BH + 7) / 8 * 8 * S, full = wgs / 256, rest = wgs % 256;
+        auto round = [&](long long n) {
+            const double t_bw = bytes / (5e6 / n < 40e3 ? 5e6 / n : 40e3);
+            return sqrt(t_lat * t_lat + t_bw * t_bw);
+        };
+        double T = full * round(256) + (rest ? round(rest) : 0.0);
+        if (n_part > 1) T += 1.5 + n_part * part / 50e3 + 2.0 * (double)BH * n_act * n_part * part / 4e6;
+        const bool take = forced > 0 ? S == (forced < n_rg ? n_rg : (forced < nblk * n_rg ? forced : nblk * n_rg)) : T < best_T * (1 - 1e-9);
+        if (take) {
+            best_T = T;
+            best.waves = 8;
+            best.S = S;
+            best.rg_tiles = 1;
+            best.n_rg = n_rg;
+            best.counters_bytes = ((size_t)BH * n_rg * sizeof(unsigned long long) + 255) / 256 * 256;
+            best.total_bytes = best.counters_bytes + ((size_t)BH * (S > 2 ? S : 2) * (size_t)(16 * (2 + D)) * sizeof(float) + 255) / 256 * 256;
+        }
+    }
     return best;
 }
 
 // The search takes up to some microseconds; a program calls with the same few shapes, so each thread keeps its last plan.
-static inline AttnPlan attn_plan(int B, int H, int N, int D, int Cmax)
+static inline AttnPlan attn_plan(int B, int H, int N, int D, int Cmax, bool f32 = false)
 {
-    static thread_local int key[5] = {0, 0, 0, 0, -1};
+    static thread_local int key[6] = {0, 0, 0, 0, -1, 0};
     static thread_local AttnPlan plan;
-    if (key[0] != B || key[1] != H || key[2] != N || key[3] != D || key[4] != Cmax) {
-        plan = attn_plan_make(B, H, N, D, Cmax);
-        key[0] = B; key[1] = H; key[2] = N; key[3] = D; key[4] = Cmax;
+    if (key[0] != B || key[1] != H || key[2] != N || key[3] != D || key[4] != Cmax || key[5] != (int)f32) {
+        plan = f32 ? attn_plan_make_f32(B, H, N, D, Cmax) : attn_plan_make(B, H, N, D, Cmax);
+        key[0] = B; key[1] = H; key[2] = N; key[3] = D; key[4] = Cmax; key[5] = (int)f32;
     }
     return plan;
-}
-
-// Plan of the fp32 kernel: context ranges per head, estimated as above from what it does (27 GB/s per compute unit).
-static inline AttnPlan attn_plan_f32(int B, int H, int N, int D, int Cmax)
-{
-    AttnPlan p = {};
-    const long long BH = (long long)B * H;
-    const int nblk = (Cmax + kBlockKeys - 1) / kBlockKeys, rows_pad = (N + 15) / 16 * 16;
-    const double blk_bytes = 2.0 * kBlockKeys * D * sizeof(float), t_blk = blk_bytes / 27e9;
-    const double t_hbm = (double)BH * nblk * blk_bytes / 5.5e12;
-    const double part_bytes = (double)rows_pad * (2 + D) * sizeof(float);
-    int best_S = 1;
-    double best_T = 1e30;
-    for (int S = 1; S <= nblk && S <= 64; ++S) {
-        const int per = (nblk + S - 1) / S;
-        const long long rounds = (BH * S + 255) / 256;
-        double T = (double)rounds * per * t_blk;
-        if (T < t_hbm) T = t_hbm;
-        T += 3e-6 + 2.0 * (double)BH * (S + 1) * part_bytes / 4e12;
-        if (T < best_T * (1.0 - 1e-9)) { best_T = T; best_S = S; }
-    }
-    p.waves = 4;
-    p.S = best_S;
-    p.rows_pad = rows_pad;
-    p.rg_tiles = 1;
-    p.n_rg = 1;
-    p.counters_bytes = ((size_t)BH * sizeof(unsigned long long) + 255) / 256 * 256;
-    p.total_bytes = p.counters_bytes + (size_t)BH * (p.S + 1) * (size_t)rows_pad * (2 + D) * sizeof(float);
-    return p;
 }
 
 struct AttnArgs {
@@ -142,8 +144,8 @@ struct AttnArgs {
     void *out;
     unsigned long long *counters;
     float *partials;
-    int B, H, N, Cmax, S, words, rows_pad;
-    int n_rg;      // row groups per (sequence, head) (matrix-core kernel; each is NQ*16 rows of the template)
+    int B, H, N, Cmax, S, words;
+    int n_rg;      // row groups per (sequence, head) (each is NQ*16 rows of the kernel's template)
     float scale_log2e;
     // rotary embedding fused into the call (rd_tree_attn_rope); unused (null) otherwise
     const int32_t *position_ids;   // [B, N]
@@ -154,22 +156,6 @@ struct AttnArgs {
 
 __device__ __forceinline__ int clampi(int x, int lo, int hi) { return x < lo ? lo : (x > hi ? hi : x); }
 
-// Context key range [k_begin, k_end) of split s out of S for a context of C keys: whole
-// blocks of block_keys keys, spread as evenly as whole blocks allow.
-__device__ __forceinline__ void ctx_range(int C, int S, int s, int block_keys, int *k_begin, int *k_end)
-{
-    const int nblk = (C + block_keys - 1) / block_keys;
-    const int per = (nblk + S - 1) / S;
-    const int kb = s * per * block_keys;
-    *k_begin = kb < C ? kb : C;
-    const int ke = kb + per * block_keys;
-    *k_end = ke < C ? ke : C;
-}
-
-__device__ __forceinline__ void store_out4(float *dst, float a, float b, float c, float d)
-{
-    *reinterpret_cast<float4 *>(dst) = make_float4(a, b, c, d);
-}
 __device__ __forceinline__ void store_out4(__bf16 *dst, float a, float b, float c, float d)
 {
     typedef __attribute__((ext_vector_type(4))) __bf16 bf16x4;
@@ -216,41 +202,6 @@ __device__ __forceinline__ int arrive_is_last(unsigned long long *counter, uint3
     __syncthreads();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");   // later loads stay after the counter update
     return (int)s_last;
-}
-
-// Merge of the S+1 partial softmax states of one (sequence, head) and final store:
-// out[p] = sum_s 2^(m_s - M) O_s[p] / sum_s 2^(m_s - M) l_s[p] with M = max_s m_s (scores
-// are kept in log2 units).  Rows p >= P are written as zero.  Run by one workgroup.
-template <int D, typename OutT>
-__device__ __forceinline__ void combine_partials(const float *part /* first partial of this head */,
-                                                 int n_part, size_t partial_floats, int rows_pad,
-                                                 int P, int N, OutT *out /* [N][D] of this head */)
-{
-    constexpr int kVecPerRow = D / 4;
-    constexpr int kRowsPerPass = kAttnThreads / kVecPerRow;
-    const int tid = threadIdx.x;
-    const int v = tid % kVecPerRow;
-    for (int p = tid / kVecPerRow; p < N; p += kRowsPerPass) {
-        float a0 = 0.f, a1 = 0.f, a2 = 0.f, a3 = 0.f;
-        if (p < P) {
-            float M = -INFINITY;
-            for (int s = 0; s < n_part; ++s) M = fmaxf(M, ld_dev(part + s * partial_floats + p));
-            float denom = 0.f;
-            for (int s = 0; s < n_part; ++s) {
-                const float *ps = part + s * partial_floats;
-                const float m = ld_dev(ps + p);
-                if (m == -INFINITY) continue;          // that range held no visible key for row p
-                const float w = __builtin_amdgcn_exp2f(m - M);
-                denom += w * ld_dev(ps + rows_pad + p);
-                const float *po = ps + 2 * rows_pad + (size_t)p * D + 4 * v;
-                const float2 o01 = ld_dev2(po), o23 = ld_dev2(po + 2);
-                a0 += w * o01.x; a1 += w * o01.y; a2 += w * o23.x; a3 += w * o23.y;
-            }
-            const float inv = 1.0f / denom;
-            a0 *= inv; a1 *= inv; a2 *= inv; a3 *= inv;
-        }
-        store_out4(out + (size_t)p * D + 4 * v, a0, a1, a2, a3);
-    }
 }
 
 }  // namespace rd

@@ -24,7 +24,7 @@ static int attn_check_shape(int B, int H, int N, int D, int Cmax, rd_dtype dt)
 extern "C" size_t rd_tree_attn_workspace(int B, int H, int N, int D, int Cmax, rd_dtype dt)
 {
     if (attn_check_shape(B, H, N, D, Cmax, dt) != RD_OK) return 0;
-    return (dt == RD_F32 ? rd::attn_plan_f32(B, H, N, D, Cmax) : rd::attn_plan(B, H, N, D, Cmax)).total_bytes;
+    return rd::attn_plan(B, H, N, D, Cmax, dt == RD_F32).total_bytes;
 }
 
 // Dense entry points: `plan_ctx` is the context length the launch plan is made for (the cache's
@@ -43,7 +43,7 @@ static int tree_attn_dense(const void *q, const void *k_cache, const void *v_cac
     if (!rd_aligned(q, 16) || !rd_aligned(k_cache, 16) || !rd_aligned(v_cache, 16) || !rd_aligned(k_new, 16) ||
         !rd_aligned(v_new, 16) || !rd_aligned(out, 16) || !rd_aligned(tree_mask_bits, 8))
         return RD_ERR_INVALID_ARG;
-    const rd::AttnPlan plan = dt == RD_F32 ? rd::attn_plan_f32(B, H, N, D, plan_ctx) : rd::attn_plan(B, H, N, D, plan_ctx);
+    const rd::AttnPlan plan = rd::attn_plan(B, H, N, D, plan_ctx, dt == RD_F32);
     if (!workspace || !rd_aligned(workspace, 256) || workspace_bytes < plan.total_bytes) return RD_ERR_WORKSPACE;
 
     rd::AttnArgs a;
@@ -51,7 +51,7 @@ static int tree_attn_dense(const void *q, const void *k_cache, const void *v_cac
     a.ctx_len = ctx_len; a.n_packed = n_packed; a.mask_bits = tree_mask_bits; a.out = out;
     a.counters = static_cast<unsigned long long *>(workspace);
     a.partials = reinterpret_cast<float *>(static_cast<unsigned char *>(workspace) + plan.counters_bytes);
-    a.B = B; a.H = H; a.N = N; a.Cmax = Cmax; a.S = plan.S; a.words = (N + 63) / 64; a.rows_pad = plan.rows_pad;
+    a.B = B; a.H = H; a.N = N; a.Cmax = Cmax; a.S = plan.S; a.words = (N + 63) / 64;
     a.scale_log2e = scale * 1.44269504088896340736f;
     a.n_rg = plan.n_rg;
     a.block_table = nullptr; a.page_size = 0; a.max_pages = 0; a.n_pages = 0;
@@ -122,7 +122,7 @@ extern "C" int rd_tree_attn_paged(const void *q, const void *k_pages, const void
     a.block_table = block_table; a.page_size = page_size; a.max_pages = max_pages; a.n_pages = n_pages;
     a.counters = static_cast<unsigned long long *>(workspace);
     a.partials = reinterpret_cast<float *>(static_cast<unsigned char *>(workspace) + plan.counters_bytes);
-    a.B = B; a.H = H; a.N = N; a.Cmax = Cmax; a.S = plan.S; a.words = (N + 63) / 64; a.rows_pad = plan.rows_pad;
+    a.B = B; a.H = H; a.N = N; a.Cmax = Cmax; a.S = plan.S; a.words = (N + 63) / 64;
     a.scale_log2e = scale * 1.44269504088896340736f;
     a.n_rg = plan.n_rg;
     a.position_ids = nullptr; a.cos_tab = nullptr; a.sin_tab = nullptr; a.max_pos = 0; a.k_rot = nullptr;
@@ -157,7 +157,7 @@ extern "C" int rd_tree_attn_rope(const void *q, const void *k_cache, const void 
     a.ctx_len = ctx_len; a.n_packed = n_packed; a.mask_bits = tree_mask_bits; a.out = out;
     a.counters = static_cast<unsigned long long *>(workspace);
     a.partials = reinterpret_cast<float *>(static_cast<unsigned char *>(workspace) + plan.counters_bytes);
-    a.B = B; a.H = H; a.N = N; a.Cmax = Cmax; a.S = plan.S; a.words = (N + 63) / 64; a.rows_pad = plan.rows_pad;
+    a.B = B; a.H = H; a.N = N; a.Cmax = Cmax; a.S = plan.S; a.words = (N + 63) / 64;
     a.scale_log2e = scale * 1.44269504088896340736f;
     a.n_rg = plan.n_rg;
     a.block_table = nullptr; a.page_size = 0; a.max_pages = 0; a.n_pages = 0;

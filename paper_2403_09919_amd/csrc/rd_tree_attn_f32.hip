@@ -1,187 +1,367 @@
-// rd_tree_attn, fp32 path: the same split-key scheme as the bf16 kernel with plain fp32
-// FMA arithmetic (no matrix cores), for fp32 Q/K/V where results must hold to ~1e-6.
+// rd_tree_attn, fp32: for fp32 Q/K/V, where results must hold to ~1e-6, on the fp32 matrix instruction
+// (v_mfma_f32_16x16x4_f32: fp32 products and sums, twice the rate of the vector units).
 //
-// A workgroup handles 16 packed rows of one (sequence, head) over one key range; wave w
-// owns rows 4w..4w+3 completely (scores, softmax state, output), so waves only meet at
-// the barriers that recycle the K/V tiles in LDS.  Per 64-key tile: lane = key for the
-// scores (K rows padded by one float so the 64 lanes hit 64 banks), lane = output column
-// for the value product (probabilities are broadcast reads).
+// The keys of a head are a sequence of 16-key tiles, the context's first, then the packed keys'; wave w of a workgroup
+// takes tiles w, w + 8, ... and keeps a softmax state of its own.  Nothing but Q passes through LDS in the loop:
+//   * S^T = K Q^T: the A operand is K as loaded, lane (r16, g) = key r16, floats 16c + 4g .. +3 (the order of the
+//     contraction is free as long as Q's is the same);
+//   * O^T = V^T P^T: a lane's four scores are keys 4g+i of row r16; step i of the product takes exactly those, so the
+//     probabilities are the B operand as they are, and the A operand is V as loaded, lane (r16, g) = floats
+//     64jj + 4 r16 .. +3 of key 4g+i (d-tile e of jj holds d = 64jj + 4m + e).
+// The next tile's K and V are in flight meanwhile; the eight states meet in LDS once, at the end.
+// Short contexts are bound by latency, long ones by the block's chain of loads and products (3 us per 128 keys and
+// workgroup at D = 128), wide beams by the matrix unit.  One row tile per workgroup: two share a tile's loads but
+// lengthen every chain (7.6 against 5.5 us at the first shape below, 117 against 136 us at the last but one), and K/V of a
+// head's row groups come from L2.  Against vector arithmetic on LDS tiles with the packed keys as a workgroup of their
+// own, us per launch: H=4, C=128, D=64, 9 packed rows 14.4 -> 5.5; B=3, H=26, C=250 56.7 -> 13.6; H=10, C=3000 43 -> 16.5;
+// H=5, C=1000, 52 rows 64.7 -> 13.4; B=4, H=40, C=2000, 33 rows 453 -> 117; B=8, H=32, C=1500 487 -> 101.
 #include "rd_attn_common.h"
+#include <type_traits>
 
 namespace rd {
 
-constexpr int kF32TileKeys = 64;
-constexpr int kF32Rows = 16;
+typedef __attribute__((ext_vector_type(4))) float f32x4;
 
-template <int D>
-__global__ __launch_bounds__(kAttnThreads) void rd_tree_attn_f32_kernel(AttnArgs a, int row_groups)
+constexpr int kF32Waves = 8;
+
+__device__ __forceinline__ float quad_max_f32(float x)
 {
-    constexpr int kKStride = D + 1;
-    constexpr int kCols = D / 64;                        // output columns per lane
+    auto a = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+    x = fmaxf(__uint_as_float(a[0]), __uint_as_float(a[1]));
+    auto b = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+    return fmaxf(__uint_as_float(b[0]), __uint_as_float(b[1]));
+}
+__device__ __forceinline__ float quad_sum_f32(float x)
+{
+    auto a = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+    x = __uint_as_float(a[0]) + __uint_as_float(a[1]);
+    auto b = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+    return __uint_as_float(b[0]) + __uint_as_float(b[1]);
+}
+
+// NQ = row tiles (16 packed rows) per workgroup (one, as launched); more rows are row groups.
+template <int D, int NQ>
+__global__ __launch_bounds__(kF32Waves * 64, 2) void rd_tree_attn_f32_kernel(AttnArgs a)
+{
+    constexpr int NW = kF32Waves;
+    constexpr int KC = D / 16;                                  // 16-byte pieces of a row per lane group
+    constexpr int JJ = D / 64;                                  // 64-column pieces of the output
+    constexpr int kRows = NQ * 16;
+    constexpr int kUnits = NQ * JJ * 4;                         // output fragments: (row tile, jj, i), 64 lanes x 4 floats
+    constexpr int kUPW = (kUnits + NW - 1) / NW;                // ... finished by wave f mod NW
+    constexpr int kPF = kRows * 2 + kUnits * 256;               // floats per partial: (m,l) per row, then the fragments
+    constexpr int kMLStride = NW * 2 + 4;                       // floats per row of the waves' (m, l) table
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-    float *sQ = reinterpret_cast<float *>(smem);         // [16][D]
-    float *sK = sQ + kF32Rows * D;                       // [64][D+1]
-    float *sV = sK + kF32TileKeys * kKStride;            // [64][D]
-    float *sS = sV + kF32TileKeys * D;                   // [16][64]
+    f32x4 *sQ = reinterpret_cast<f32x4 *>(smem);                // [NQ][KC][64 lanes]
+    f32x4 *sO = sQ + NQ * KC * 64;                              // [NW][kUnits][64 lanes]
+    float *sML = reinterpret_cast<float *>(sO + NW * kUnits * 64);   // [kRows][NW] (m, l)
 
     const int tid = threadIdx.x;
     const int lane = tid & 63;
-    const int wave = tid >> 6;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int r16 = lane & 15, g = lane >> 4;
 
-    const int n_part = a.S + 1;
-    const int rg = blockIdx.x % row_groups;
-    const int split = (blockIdx.x / row_groups) % n_part;
-    const int bh = blockIdx.x / (row_groups * n_part);
-    const int b = bh / a.H;
+    // which (sequence, head) -- all workgroups of one on one XCD -- and which of its a.S workgroups
+    const int k = (int)(blockIdx.x >> 3);
+    const int hl = a.S == 1 ? k : k / a.S;
+    const int r_wg = k - hl * a.S;
+    const int bh = hl * 8 + (int)(blockIdx.x & 7);
+    if (bh >= a.B * a.H) return;
+    const int b = a.B == 1 ? 0 : bh / a.H;
     const int C = clampi(a.ctx_len[b], 0, a.Cmax);
-    const int P = clampi(a.n_packed[b], 0, a.N);
-    const bool is_tree = (split == a.S);
-    const int row0 = rg * kF32Rows;
-
-    int k_begin, k_end;
-    const float *Kb, *Vb;
-    if (is_tree) {
-        k_begin = 0;
-        k_end = P;
-        Kb = static_cast<const float *>(a.k_new) + (size_t)bh * a.N * D;
-        Vb = static_cast<const float *>(a.v_new) + (size_t)bh * a.N * D;
-    } else {
-        ctx_range(C, a.S, split, kBlockKeys, &k_begin, &k_end);
-        Kb = static_cast<const float *>(a.k_cache) + (size_t)bh * a.Cmax * D;
-        Vb = static_cast<const float *>(a.v_cache) + (size_t)bh * a.Cmax * D;
+    const int P_all = clampi(a.n_packed[b], 0, a.N);
+    // row groups with packed rows share the head's workgroups; output rows of the others are zero
+    const int n_act = a.n_rg == 1 ? 1 : max((P_all + kRows - 1) / kRows, 1);
+    const int ranges = n_act == 1 ? a.S : a.S / n_act;
+    const int split = n_act == 1 ? r_wg : r_wg / n_act;
+    const int rg = r_wg - split * n_act;
+    if (a.n_rg > 1) {
+        float *z = static_cast<float *>(a.out) + (size_t)bh * a.N * D;
+        for (int i = n_act * kRows * D + (r_wg * NW * 64 + tid) * 4; i < a.N * D; i += a.S * NW * 64 * 4)
+            *reinterpret_cast<float4 *>(z + i) = make_float4(0.f, 0.f, 0.f, 0.f);
     }
-    if (row0 >= P) k_end = k_begin;                      // nothing to score: empty partial
+    if (split >= ranges) return;
+    const int row0 = rg * kRows;
+    const int P = clampi(P_all - row0, 0, kRows);
+    const int Ng = min(kRows, a.N - row0);
+    const int tree_end = min(P_all, row0 + kRows);              // (the mask is lower triangular)
 
-    {   // Q rows of this group (rows >= P zeroed)
-        const float *Qb = static_cast<const float *>(a.q) + (size_t)bh * a.N * D;
-        for (int i = tid; i < kF32Rows * D; i += kAttnThreads) {
-            const int row = row0 + i / D;
-            sQ[i] = (row < P) ? Qb[(size_t)row * D + (i % D)] : 0.f;
+    const int nA = (C + 15) >> 4;
+    const int nT = P > 0 ? nA + ((tree_end + 15) >> 4) : 0;
+    const int nblk = (nT + NW - 1) / NW;
+    const int per = ranges == 1 ? max(nblk, 1) : max((nblk + ranges - 1) / ranges, 1);
+    const int n_part = ranges == 1 ? 1 : max((nblk + per - 1) / per, 1);
+    if (split >= n_part) return;
+    const int tile_begin = split * per * NW;
+    const int tile_end = min(nT, tile_begin + per * NW);
+
+    const float *Qb = static_cast<const float *>(a.q) + ((size_t)bh * a.N + row0) * D;
+    const uintptr_t Kc = reinterpret_cast<uintptr_t>(a.k_cache) + (size_t)bh * a.Cmax * D * 4;
+    const uintptr_t Vc = reinterpret_cast<uintptr_t>(a.v_cache) + (size_t)bh * a.Cmax * D * 4;
+    const uintptr_t Kn = reinterpret_cast<uintptr_t>(a.k_new) + (size_t)bh * a.N * D * 4 - Kc;   // from the cache's rows to the packed ones
+    const uintptr_t Vn = reinterpret_cast<uintptr_t>(a.v_new) + (size_t)bh * a.N * D * 4 - Vc;
+    typedef const __attribute__((address_space(1))) f32x4 gvec;
+
+    constexpr int kQFrags = NQ * KC, kQPer = (kQFrags + NW - 1) / NW;
+    f32x4 qreg[kQPer];
+#pragma unroll
+    for (int i = 0; i < kQPer; ++i) {
+        const int f = min(wave + NW * i, kQFrags - 1);
+        qreg[i] = *reinterpret_cast<const f32x4 *>(Qb + (size_t)min(f / KC * 16 + r16, Ng - 1) * D + (f % KC) * 16 + g * 4);
+    }
+
+    // K, V and visibility words of a tile.  A wave whose turn falls past the end takes the last tile again (masked), a
+    // workgroup without tiles the first there is: no branch around the loads.  Rows past a tile's keys are its last key.
+    f32x4 kreg[KC], vreg[4][JJ];
+    uint64_t mword[NQ];
+    auto fetch = [&](int tile, auto which_k, auto which_v) __attribute__((always_inline)) {
+        const int tl = max(min(tile, tile_end - 1), 0);
+        const bool tree = tl >= nA;
+        const int first = (tl - (tree ? nA : 0)) * 16;
+        const int keys = max(min(16, (tree ? tree_end : C) - first), 1);
+        if (decltype(which_k)::value) {
+            const uintptr_t p = Kc + (tree ? Kn : 0) + (size_t)first * D * 4 + (uint32_t)min(r16, keys - 1) * (D * 4) + g * 16;
+#pragma unroll
+            for (int c = 0; c < KC; ++c) kreg[c] = *(gvec *)(p + c * 64);
+            const int word = tree ? min(first >> 6, a.words - 1) : 0;
+#pragma unroll
+            for (int qt = 0; qt < NQ; ++qt)
+                mword[qt] = a.mask_bits[((size_t)b * a.N + min(row0 + qt * 16 + r16, a.N - 1)) * a.words + word];
         }
-    }
-
-    float m_run[4], l_run[4], o[4][kCols];
+        if (decltype(which_v)::value) {
+            const uintptr_t p = Vc + (tree ? Vn : 0) + (size_t)first * D * 4 + r16 * 16;
 #pragma unroll
-    for (int r = 0; r < 4; ++r) {
-        m_run[r] = -INFINITY;
-        l_run[r] = 0.f;
+            for (int i = 0; i < 4; ++i)
 #pragma unroll
-        for (int c = 0; c < kCols; ++c) o[r][c] = 0.f;
-    }
+                for (int jj = 0; jj < JJ; ++jj) vreg[i][jj] = *(gvec *)(p + (uint32_t)min(4 * g + i, keys - 1) * (D * 4) + jj * 256);
+        }
+    };
+    using yes = std::true_type;
+    using no = std::false_type;
+    const int t_first = tile_begin + wave;
+    fetch(t_first, yes{}, yes{});
 
-    for (int t0 = k_begin; t0 < k_end; t0 += kF32TileKeys) {
-        __syncthreads();                                 // previous tile fully consumed (and Q stored)
-        for (int i = tid; i < kF32TileKeys * (D / 4); i += kAttnThreads) {
-            const int kr = i / (D / 4), c4 = (i % (D / 4)) * 4;
-            const int key = t0 + kr;
-            float4 kv = make_float4(0.f, 0.f, 0.f, 0.f), vv = kv;
-            if (key < k_end) {
-                kv = *reinterpret_cast<const float4 *>(Kb + (size_t)key * D + c4);
-                vv = *reinterpret_cast<const float4 *>(Vb + (size_t)key * D + c4);
+#pragma unroll
+    for (int i = 0; i < kQPer; ++i) {
+        const int f = wave + NW * i;
+        if (f < kQFrags) sQ[f * 64 + lane] = f / KC * 16 + r16 < P ? qreg[i] : f32x4{0.f, 0.f, 0.f, 0.f};
+    }
+    float m_run[NQ], l_run[NQ];
+    f32x4 oacc[NQ][JJ][4];
+#pragma unroll
+    for (int qt = 0; qt < NQ; ++qt) {
+        m_run[qt] = -INFINITY;
+        l_run[qt] = 0.f;
+#pragma unroll
+        for (int jj = 0; jj < JJ; ++jj)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) oacc[qt][jj][e] = f32x4{0.f, 0.f, 0.f, 0.f};
+    }
+    rd_lds_barrier();         // Q visible to all waves
+
+    auto tile_step = [&](int tile, auto more) __attribute__((always_inline)) {
+        const bool tree = tile >= nA;
+        const int first = (tile - (tree ? nA : 0)) * 16;
+        const int rem = (tree ? tree_end : C) - first;          // keys of the tile inside the range
+        f32x4 sacc[NQ];
+        uint32_t bits[NQ];
+#pragma unroll
+        for (int qt = 0; qt < NQ; ++qt) {
+            sacc[qt] = f32x4{0.f, 0.f, 0.f, 0.f};
+            const uint32_t vis = tree ? (uint32_t)(mword[qt] >> ((first & 63) + 4 * g)) & 0xfu : 0xfu;
+            const int left = rem - 4 * g;
+            const uint32_t tail = left >= 4 ? 0xfu : (left <= 0 ? 0u : (1u << left) - 1u);
+            bits[qt] = qt * 16 + r16 < P ? vis & tail : 0u;
+        }
+#pragma unroll
+        for (int c = 0; c < KC; ++c) {
+            f32x4 q[NQ];
+#pragma unroll
+            for (int qt = 0; qt < NQ; ++qt) q[qt] = sQ[(qt * KC + c) * 64 + lane];
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+#pragma unroll
+                for (int qt = 0; qt < NQ; ++qt) sacc[qt] = __builtin_amdgcn_mfma_f32_16x16x4f32(kreg[c][e], q[qt][e], sacc[qt], 0, 0, 0);
+        }
+        if (decltype(more)::value) fetch(tile + NW, yes{}, no{});
+        float p[NQ][4];
+#pragma unroll
+        for (int qt = 0; qt < NQ; ++qt) {
+            float s[4], mx = -INFINITY;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                s[i] = (bits[qt] >> i) & 1u ? sacc[qt][i] * a.scale_log2e : -INFINITY;
+                mx = fmaxf(mx, s[i]);
             }
-            float *kd = sK + kr * kKStride + c4;
-            kd[0] = kv.x; kd[1] = kv.y; kd[2] = kv.z; kd[3] = kv.w;
-            *reinterpret_cast<float4 *>(sV + kr * D + c4) = vv;
-        }
-        __syncthreads();
-
-        // scores of this wave's four rows against key t0 + lane
-        float s[4] = {0.f, 0.f, 0.f, 0.f};
-        const float *krow = sK + lane * kKStride;
-        const float *q0 = sQ + (wave * 4) * D;
-#pragma unroll 8
-        for (int d = 0; d < D; ++d) {
-            const float kv = krow[d];
-            s[0] = fmaf(q0[d], kv, s[0]);
-            s[1] = fmaf(q0[D + d], kv, s[1]);
-            s[2] = fmaf(q0[2 * D + d], kv, s[2]);
-            s[3] = fmaf(q0[3 * D + d], kv, s[3]);
-        }
-        const int key = t0 + lane;
-        float alpha[4];
+            const float m_new = fmaxf(m_run[qt], quad_max_f32(mx));
+            const float m_safe = m_new == -INFINITY ? 0.f : m_new;
+            const float alpha = __builtin_amdgcn_exp2f(m_run[qt] - m_safe);
+            m_run[qt] = m_new;
+            float sum = 0.f;
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            bool ok = key < k_end;
-            if (is_tree) {                               // packed keys t0 .. t0+63 are mask word t0/64 of the row
-                const int qrow = row0 + wave * 4 + r;
-                const uint64_t mw = qrow < P ? a.mask_bits[((size_t)b * a.N + qrow) * a.words + (t0 >> 6)] : 0ull;
-                ok = ok && ((mw >> lane) & 1ull);
+            for (int i = 0; i < 4; ++i) {
+                p[qt][i] = __builtin_amdgcn_exp2f(s[i] - m_safe);
+                sum += p[qt][i];
             }
-            const float sv = ok ? s[r] * a.scale_log2e : -INFINITY;
-            float tmax = sv;
+            l_run[qt] = l_run[qt] * alpha + sum;
+            if (__builtin_amdgcn_ballot_w64(alpha != 1.0f) != 0) {
 #pragma unroll
-            for (int off = 32; off > 0; off >>= 1) tmax = fmaxf(tmax, __shfl_xor(tmax, off, 64));
-            const float m_new = fmaxf(m_run[r], tmax);
-            const float m_safe = (m_new == -INFINITY) ? 0.f : m_new;
-            alpha[r] = __builtin_amdgcn_exp2f(m_run[r] - m_safe);
-            m_run[r] = m_new;
-            const float p = __builtin_amdgcn_exp2f(sv - m_safe);
-            float psum = p;
+                for (int jj = 0; jj < JJ; ++jj)
 #pragma unroll
-            for (int off = 32; off > 0; off >>= 1) psum += __shfl_xor(psum, off, 64);
-            l_run[r] = l_run[r] * alpha[r] + psum;
-            sS[(wave * 4 + r) * kF32TileKeys + lane] = p;
-        }
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-        __builtin_amdgcn_wave_barrier();                 // sS rows are private to this wave
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
-
-#pragma unroll
-        for (int r = 0; r < 4; ++r)
-#pragma unroll
-            for (int c = 0; c < kCols; ++c) o[r][c] *= alpha[r];
-        const float *ps = sS + (wave * 4) * kF32TileKeys;
-        for (int k = 0; k < kF32TileKeys; ++k) {
-#pragma unroll
-            for (int c = 0; c < kCols; ++c) {
-                const float vv = sV[k * D + c * 64 + lane];
-#pragma unroll
-                for (int r = 0; r < 4; ++r) o[r][c] = fmaf(ps[r * kF32TileKeys + k], vv, o[r][c]);
+                    for (int e = 0; e < 4; ++e) oacc[qt][jj][e] *= alpha;
             }
         }
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+            for (int jj = 0; jj < JJ; ++jj)
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+#pragma unroll
+                    for (int qt = 0; qt < NQ; ++qt)
+                        oacc[qt][jj][e] = __builtin_amdgcn_mfma_f32_16x16x4f32(vreg[i][jj][e], p[qt][i], oacc[qt][jj][e], 0, 0, 0);
+        if (decltype(more)::value) fetch(tile + NW, no{}, yes{});
+    };
+    if (t_first < tile_end) {
+        int tile = t_first;
+        for (; tile + NW < tile_end; tile += NW) tile_step(tile, yes{});
+        tile_step(tile, no{});
     }
 
-    const size_t pf = (size_t)a.rows_pad * (2 + D);
-    float *part = a.partials + ((size_t)bh * n_part + split) * pf;
+    // ---- the waves' states meet in LDS; fragment (qt, jj, i) holds, per lane, d = 64jj + 16g + 4i .. +3 of row r16
 #pragma unroll
-    for (int r = 0; r < 4; ++r) {
-        const int qrow = row0 + wave * 4 + r;
-        if (qrow < P) {
-            if (lane == 0) {
-                st_dev(part + qrow, m_run[r]);
-                st_dev(part + a.rows_pad + qrow, l_run[r]);
-            }
+    for (int qt = 0; qt < NQ; ++qt) {
+        const float l = quad_sum_f32(l_run[qt]);
+        if (g == 0) *reinterpret_cast<float2 *>(sML + (qt * 16 + r16) * kMLStride + wave * 2) = make_float2(m_run[qt], l);
 #pragma unroll
-            for (int c = 0; c < kCols; ++c) st_dev(part + 2 * a.rows_pad + (size_t)qrow * D + c * 64 + lane, o[r][c]);
+        for (int jj = 0; jj < JJ; ++jj)
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+                sO[(wave * kUnits + (qt * JJ + jj) * 4 + i) * 64 + lane] =
+                    f32x4{oacc[qt][jj][0][i], oacc[qt][jj][1][i], oacc[qt][jj][2][i], oacc[qt][jj][3][i]};
+    }
+    rd_lds_barrier();
+    const int n_waves = clampi(tile_end - tile_begin, 1, NW);   // waves that had a tile
+    float fm[kUPW], fl[kUPW];
+    f32x4 fo[kUPW];
+#pragma unroll
+    for (int i = 0; i < kUPW; ++i) {
+        const int f = min(wave + NW * i, kUnits - 1), row = f / (JJ * 4) * 16 + r16;
+        f32x4 ml[NW / 2];
+#pragma unroll
+        for (int w = 0; w < NW / 2; ++w) ml[w] = *reinterpret_cast<const f32x4 *>(sML + row * kMLStride + w * 4);
+        float m = -INFINITY;
+#pragma unroll
+        for (int w = 0; w < NW; ++w) m = fmaxf(m, ml[w / 2][2 * (w & 1)]);
+        const float ms = m == -INFINITY ? 0.f : m;
+        f32x4 o = {0.f, 0.f, 0.f, 0.f};
+        float l = 0.f;
+        auto add = [&](int w) __attribute__((always_inline)) {
+            const float s = __builtin_amdgcn_exp2f(ml[w / 2][2 * (w & 1)] - ms);
+            l += s * ml[w / 2][2 * (w & 1) + 1];
+            o += s * sO[(w * kUnits + f) * 64 + lane];
+        };
+#pragma unroll
+        for (int w = 0; w < NW / 2; ++w) add(w);
+        if (n_waves > NW / 2) {
+#pragma unroll
+            for (int w = NW / 2; w < NW; ++w) add(w);
+        }
+        fm[i] = m; fl[i] = l; fo[i] = o;
+    }
+
+    float *outp = static_cast<float *>(a.out) + ((size_t)bh * a.N + row0) * D;
+    auto put = [&](int i, f32x4 o, float l) __attribute__((always_inline)) {
+        const int f = wave + NW * i, row = f / (JJ * 4) * 16 + r16;
+        if (f < kUnits && row < Ng) {
+            const float inv = row < P ? 1.0f / l : 0.f;         // rows beyond the packed count are zero
+            f32x4 y = o * inv;
+            if (row >= P) y = f32x4{0.f, 0.f, 0.f, 0.f};
+            *reinterpret_cast<f32x4 *>(outp + (size_t)row * D + (f / 4 % JJ) * 64 + g * 16 + (f & 3) * 4) = y;
+        }
+    };
+    if (n_part == 1) {
+#pragma unroll
+        for (int i = 0; i < kUPW; ++i) put(i, fo[i], fl[i]);
+        return;
+    }
+    // ---- partial state -> workspace; the last workgroup of this head (and row group) merges
+    const size_t unit = (size_t)bh * a.n_rg + rg;
+    float *part = a.partials + ((size_t)bh * a.S + split * n_act + rg) * kPF;
+#pragma unroll
+    for (int i = 0; i < kUPW; ++i) {
+        const int f = wave + NW * i, row = f / (JJ * 4) * 16 + r16;
+        if (f < kUnits && row < P) {
+            if (f % (JJ * 4) == 0 && g == 0) st_dev2(part + 2 * row, fm[i], fl[i]);
+            st_dev4(part + 2 * kRows + f * 256 + lane * 4, fo[i][0], fo[i][1], fo[i][2], fo[i][3]);
         }
     }
-
-    if (arrive_is_last(a.counters + bh, (uint32_t)(n_part * row_groups)) != kNotLast) {
-        combine_partials<D, float>(a.partials + (size_t)bh * n_part * pf, n_part, pf, a.rows_pad, P, a.N,
-                                   static_cast<float *>(a.out) + (size_t)bh * a.N * D);
-        if (tid == 0) a.counters[bh] = 0;
+    const int last = arrive_is_last(a.counters + unit, (uint32_t)n_part);
+    if (last == kNotLast) return;
+    const bool cached = last == kLastClean;
+    constexpr int kChunk = 8;                                   // partials whose loads are in flight together
+    const float *hp = a.partials + ((size_t)bh * a.S + rg) * kPF;
+#pragma unroll
+    for (int i = 0; i < kUPW; ++i) {
+        const int f = wave + NW * i, row = f / (JJ * 4) * 16 + r16;
+        float M = -INFINITY, den = 0.f;
+        f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll 1
+        for (int s0 = 0; s0 < n_part; s0 += kChunk) {
+            float2 ml[kChunk];
+            f32x4 fr[kChunk];
+#pragma unroll
+            for (int c = 0; c < kChunk; ++c) {
+                ml[c] = make_float2(-INFINITY, 0.f);            // absent: weight 2^-inf = 0
+                fr[c] = f32x4{0.f, 0.f, 0.f, 0.f};
+                if (s0 + c < n_part && f < kUnits && row < P) {
+                    const float *ps = hp + (size_t)(s0 + c) * n_act * kPF, *pf = ps + 2 * kRows + f * 256 + lane * 4;
+                    if (cached) {
+                        ml[c] = *reinterpret_cast<const float2 *>(ps + 2 * row);
+                        fr[c] = *reinterpret_cast<const f32x4 *>(pf);
+                    } else {
+                        ml[c] = ld_dev2(ps + 2 * row);
+                        const float2 lo = ld_dev2(pf), hi = ld_dev2(pf + 2);
+                        fr[c] = f32x4{lo.x, lo.y, hi.x, hi.y};
+                    }
+                }
+            }
+            float Mn = M;
+#pragma unroll
+            for (int c = 0; c < kChunk; ++c) Mn = fmaxf(Mn, ml[c].x);
+            const float Ms = Mn == -INFINITY ? 0.f : Mn, resc = __builtin_amdgcn_exp2f(M - Ms);
+            den *= resc;
+            acc *= resc;
+#pragma unroll
+            for (int c = 0; c < kChunk; ++c) {
+                const float w = __builtin_amdgcn_exp2f(ml[c].x - Ms);
+                den += w * ml[c].y;
+                acc += w * fr[c];
+            }
+            M = Mn;
+        }
+        put(i, acc, den);
     }
+    if (tid == 0) a.counters[unit] = 0;       // leave the workspace ready for the next call
 }
 
-template <int D>
+template <int D, int NQ>
 static int launch_f32(const AttnArgs &a, hipStream_t stream)
 {
-    const size_t smem = sizeof(float) * ((size_t)kF32Rows * D + (size_t)kF32TileKeys * (D + 1) +
-                                         (size_t)kF32TileKeys * D + (size_t)kF32Rows * kF32TileKeys);
+    constexpr size_t smem = (size_t)NQ * (D / 16) * 1024 + (size_t)kF32Waves * NQ * (D / 16) * 1024 + (size_t)NQ * 16 * (kF32Waves * 2 + 4) * sizeof(float);
+    static_assert(smem <= 160 * 1024, "LDS of a compute unit");
     static std::atomic<unsigned long long> configured{0};
-    const int st = ensure_dynamic_lds(reinterpret_cast<const void *>(&rd_tree_attn_f32_kernel<D>), smem, configured);
+    const int st = ensure_dynamic_lds(reinterpret_cast<const void *>(&rd_tree_attn_f32_kernel<D, NQ>), smem, configured);
     if (st != RD_OK) return st;
-    const int row_groups = a.rows_pad / kF32Rows;
-    const size_t wgs = (size_t)a.B * a.H * (a.S + 1) * row_groups;
+    const size_t wgs = ((size_t)a.B * a.H + 7) / 8 * 8 * a.S;
     if (wgs > 0x7fffffffull) return RD_ERR_UNSUPPORTED;
-    const unsigned grid = (unsigned)wgs;
-    hipLaunchKernelGGL((rd_tree_attn_f32_kernel<D>), dim3(grid), dim3(kAttnThreads), smem, stream, a, row_groups);
+    hipLaunchKernelGGL((rd_tree_attn_f32_kernel<D, NQ>), dim3((unsigned)wgs), dim3(kF32Waves * 64), smem, stream, a);
     return rd_check_launch();
 }
 
 int tree_attn_f32(const AttnArgs &a, int D, hipStream_t stream)
 {
-    return D == 128 ? launch_f32<128>(a, stream) : launch_f32<64>(a, stream);
+    return D == 128 ? launch_f32<128, 1>(a, stream) : launch_f32<64, 1>(a, stream);
 }
 
 }  // namespace rd
