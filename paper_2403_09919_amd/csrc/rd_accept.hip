@@ -115,12 +115,9 @@ __global__ __launch_bounds__(kAccThreads) void rd_accept_kernel(
     const int v0 = chunk * chunk_len;
     const int v1 = min(V, v0 + chunk_len);
     float4 x0[U];
-    if (SPEC && (V & 3) == 0) {
+    if (SPEC && V >= 4) {
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const int v = v0 + (u * kAccThreads + tid) * 4;
-            x0[u] = *reinterpret_cast<const float4 *>(row + (v < v1 ? v : v0));
-        }
+        for (int u = 0; u < U; ++u) x0[u] = rd::row4(row, v0 + (u * kAccThreads + tid) * 4, V);
     }
     int P = n_packed[b];
     P = P < 1 ? 1 : (P > N ? N : P);
@@ -144,26 +141,23 @@ __global__ __launch_bounds__(kAccThreads) void rd_accept_kernel(
     // ---- phase 1: this chunk's (max, first index) -> the row's key ---------------------------------
     float bv = -INFINITY;
     int bi = 0x7fffffff;
-    if ((V & 3) == 0) {
-        // U loads per thread in flight together; a load past the end of the chunk is redirected to
-        // the chunk's first vector and ignored, so that no load depends on a branch.
+    if (V >= 4) {
+        // U loads per thread in flight together; entries past the end of the row are -inf with indices past every
+        // real one's, and a chunk is whole but for the row's last
         for (int base = v0; base < v1; base += kAccThreads * 4 * U) {
             float4 x[U];
 #pragma unroll
             for (int u = 0; u < U; ++u) {
-                const int v = base + (u * kAccThreads + tid) * 4;
                 if (SPEC && base == v0) x[u] = x0[u];
-                else x[u] = *reinterpret_cast<const float4 *>(row + (v < v1 ? v : v0));
+                else x[u] = rd::row4(row, base + (u * kAccThreads + tid) * 4, V);
             }
 #pragma unroll
             for (int u = 0; u < U; ++u) {                              // ascending v per thread
                 const int v = base + (u * kAccThreads + tid) * 4;
-                if (v < v1) {
-                    if (better(x[u].x, v, bv, bi)) { bv = x[u].x; bi = v; }
-                    if (better(x[u].y, v + 1, bv, bi)) { bv = x[u].y; bi = v + 1; }
-                    if (better(x[u].z, v + 2, bv, bi)) { bv = x[u].z; bi = v + 2; }
-                    if (better(x[u].w, v + 3, bv, bi)) { bv = x[u].w; bi = v + 3; }
-                }
+                if (better(x[u].x, v, bv, bi)) { bv = x[u].x; bi = v; }
+                if (better(x[u].y, v + 1, bv, bi)) { bv = x[u].y; bi = v + 1; }
+                if (better(x[u].z, v + 2, bv, bi)) { bv = x[u].z; bi = v + 2; }
+                if (better(x[u].w, v + 3, bv, bi)) { bv = x[u].w; bi = v + 3; }
             }
         }
     } else {
@@ -172,11 +166,11 @@ __global__ __launch_bounds__(kAccThreads) void rd_accept_kernel(
             if (better(x, v, bv, bi)) { bv = x; bi = v; }
         }
     }
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) {
-        const float ov = __shfl_xor(bv, off, 64);
-        const int oi = __shfl_xor(bi, off, 64);
-        if (better(ov, oi, bv, bi)) { bv = ov; bi = oi; }
+    {   // the wave's largest value, then the smallest index that holds it
+        const float m = rd::wave_reduce_max(bv);
+        const uint32_t i = bv == m ? (uint32_t)bi : 0x7fffffffu;
+        bi = (int)rd::wave_reduce_min_u(i);
+        bv = m;
     }
     RD_TR(1);
     if (lane == 0) { s_val[wave] = bv; s_idx[wave] = bi; }

@@ -3,10 +3,10 @@
 //
 // Launch 1 (the HBM stream): grid (chunks, N, B); a workgroup reduces one chunk of 4096 entries of a
 // valid row of the LLM's logits (scaled by 1/temperature) and of the draft model's logits to
-// (maximum, sum of exp(x - maximum)) each, with all of its 16-byte loads in flight together, and
-// stores the two pairs in the workspace.  Rows of slots at the last position carry no draft
-// distribution and their draft half is skipped.  No atomics, no counters: the partials are
-// combined in a fixed order by launch 2, so results do not depend on timing.
+// (maximum, sum of exp(x - maximum)) each and stores the two pairs in the workspace.  Every wave finds by itself which
+// draft row belongs to the slot, all 16-byte loads of both rows are in flight together, and the waves
+// meet once.  Rows of slots at the last position carry no draft distribution and their draft half is skipped.  No
+// atomics, no counters: the partials are combined in a fixed order by launch 2, so results do not depend on timing.
 // Launch 2 (grid: chunks of 4096 vocabulary entries x sequences, 256 threads).  Every workgroup of a
 // sequence repeats the small part: log-sum-exps of the rows from the partials; one thread per
 // candidate token gathers the two logits of its token under its parent slot and decides
@@ -19,6 +19,9 @@
 // chunk's weights and takes, by a block-wide prefix scan, the first token of positive weight whose
 // cumulative weight exceeds the target.  After a fully accepted candidate the weights are p itself,
 // whose chunk totals follow from launch 1's partials: workgroup 0 goes straight to the last step.
+// Both launches are chains of memory round trips (0.6-1 us each), so what bounds them is the number of loads that wait
+// for another: the partials of all rows and chunks, the tokens and the gathered logits are fetched side by side, and
+// the totals travel as write-through stores (a device-scope fence writes back the XCD's L2).
 #include "rd_internal.h"
 #include <math.h>
 
@@ -35,18 +38,15 @@ constexpr int kSelWaves = kSelThreads / 64;
 constexpr int kMaxSelChunks = 256;           // V <= 1 Mi entries
 static_assert(kSelChunk == kLseChunk, "launch 2 takes the chunk totals of p from launch 1's partials");
 
-// Entries v .. v+3 of a row, -inf past the end (weight 0, neutral for the maximum).  No branch: a
-// load inside a branch makes the compiler wait for every load in flight at the join, which turns a
-// batch of loads into a chain of round trips.  Addresses past the end are pulled back into the row
-// and the values replaced afterwards.  VEC: V is a multiple of 4 (16-byte loads), else four scalar loads.
+// Entries v .. v+3 of a row, -inf past the end (weight 0, neutral for the maximum).  VEC: rows of four entries and
+// more, 16-byte loads; else scalar loads.
 template <bool VEC>
 __device__ __forceinline__ float4 load4(const float *row, int v, int V)
 {
-    float4 r;
     if constexpr (VEC) {
-        r = *reinterpret_cast<const float4 *>(row + min(v, V - 4));
-        if (v >= V) r = make_float4(-INFINITY, -INFINITY, -INFINITY, -INFINITY);
+        return rd::row4(row, v, V);
     } else {
+        float4 r;
         r.x = row[min(v, V - 1)];
         r.y = row[min(v + 1, V - 1)];
         r.z = row[min(v + 2, V - 1)];
@@ -55,34 +55,29 @@ __device__ __forceinline__ float4 load4(const float *row, int v, int V)
         if (v + 1 >= V) r.y = -INFINITY;
         if (v + 2 >= V) r.z = -INFINITY;
         if (v + 3 >= V) r.w = -INFINITY;
+        return r;
     }
-    return r;
 }
 
-// (maximum, sum exp(x*scale - maximum)) of up to 16 values per thread over the workgroup
-__device__ __forceinline__ float2 chunk_max_sum(const float4 (&x)[4], float scale, float *s_red)
+// (maximum, sum exp(x*scale - maximum)) of 16 values per lane over the wave
+__device__ __forceinline__ float2 wave_max_sum(const float4 (&x)[4], float scale)
 {
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     float m = -INFINITY;
 #pragma unroll
     for (int u = 0; u < 4; ++u) m = fmaxf(fmaxf(fmaxf(x[u].x, x[u].y), fmaxf(x[u].z, x[u].w)) * scale, m);
-    for (int off = 32; off > 0; off >>= 1) m = fmaxf(m, __shfl_xor(m, off, 64));
-    if (lane == 0) s_red[wave] = m;
-    __syncthreads();
-    m = fmaxf(fmaxf(s_red[0], s_red[1]), fmaxf(s_red[2], s_red[3]));
-    __syncthreads();
+    m = rd::wave_reduce_max(m);
     float s = 0.f;
-    if (m > -INFINITY) {
+    const float ms = m > -INFINITY ? m : 0.f;
 #pragma unroll
-        for (int u = 0; u < 4; ++u)
-            s += __expf(x[u].x * scale - m) + __expf(x[u].y * scale - m) + __expf(x[u].z * scale - m) + __expf(x[u].w * scale - m);
-    }
-    for (int off = 32; off > 0; off >>= 1) s += __shfl_xor(s, off, 64);
-    if (lane == 0) s_red[wave] = s;
-    __syncthreads();
-    s = (s_red[0] + s_red[1]) + (s_red[2] + s_red[3]);
-    __syncthreads();
-    return make_float2(m, s);
+    for (int u = 0; u < 4; ++u)
+        s += __expf(x[u].x * scale - ms) + __expf(x[u].y * scale - ms) + __expf(x[u].z * scale - ms) + __expf(x[u].w * scale - ms);
+    return make_float2(m, rd::wave_reduce_sum(s));
+}
+// the same over waves
+__device__ __forceinline__ float2 merge_max_sum(float2 a, float2 b)
+{
+    const float m = fmaxf(a.x, b.x), ms = m > -INFINITY ? m : 0.f;
+    return make_float2(m, a.y * __expf(a.x - ms) + b.y * __expf(b.x - ms));
 }
 
 // The draft model's logits of the distribution after candidate w's token j (which sits in packed
@@ -102,36 +97,64 @@ __global__ __launch_bounds__(kLseThreads) void rd_lse_chunk_kernel(
     int rows_per_step, const int32_t *__restrict__ unpack_index,
     const int32_t *__restrict__ n_packed, int W, int L, int V, int chunks, float inv_t, float4 *__restrict__ part)
 {
-    __shared__ float s_red[kLseThreads / 64];
-    __shared__ int s_owner;
-    const int tid = threadIdx.x;
+    constexpr int kWaves = kLseThreads / 64;
+    __shared__ float4 s_red[kWaves];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int chunk = blockIdx.x, p = blockIdx.y, b = blockIdx.z;
     const int N = W * L;
+    // which (candidate, position) this slot holds: the first entry of unpack_index that names it.  Every wave looks
+    // through all entries while they are few; else each thread takes some and the waves meet.
+    constexpr int kWaveScan = 2, kTok = (RD_MAX_N + kLseThreads - 1) / kLseThreads;
+    __shared__ int s_owner[kWaves];
+    const bool by_wave = N <= 64 * kWaveScan;               // uniform
+    const int first = by_wave ? lane : tid, stride = by_wave ? 64 : kLseThreads;
+    int slot[kWaveScan];
+    static_assert(kTok <= kWaveScan, "entries per thread");
+#pragma unroll
+    for (int i = 0; i < kWaveScan; ++i) slot[i] = unpack_index[(size_t)b * N + min(i * stride + first, N - 1)];
     int P = n_packed[b];
     P = P < 1 ? 1 : (P > N ? N : P);
     if (p >= P) return;
-    // which (candidate, position) this slot holds: the first entry of unpack_index that names it
-    if (tid == 0) s_owner = 0x7fffffff;
-    __syncthreads();
-    for (int e = tid; e < N; e += kLseThreads)
-        if (unpack_index[(size_t)b * N + e] == p) atomicMin(&s_owner, e);
     const size_t rowid = (size_t)b * N + p;
     const float *zp = logits + rowid * V;
     const int v0 = chunk * kLseChunk;
     float4 xp[4], xq[4];
 #pragma unroll
     for (int u = 0; u < 4; ++u) xp[u] = load4<VEC>(zp, v0 + (u * kLseThreads + tid) * 4, V);
-    const float2 a = chunk_max_sum(xp, inv_t, s_red);       // (its barriers also publish s_owner)
-    float2 c = make_float2(0.f, 1.f);
-    const int owner = s_owner;
+    int owner = 0x7fffffff;
+#pragma unroll
+    for (int i = kWaveScan - 1; i >= 0; --i) {
+        const unsigned long long hit = __ballot(slot[i] == p && i * stride + first < N);
+        if (hit) owner = i * stride + (by_wave ? 0 : wave * 64) + __ffsll((long long)hit) - 1;
+    }
+    if (!by_wave) {
+        if (lane == 0) s_owner[wave] = owner;
+        rd_lds_barrier();
+        owner = min(min(s_owner[0], s_owner[1]), min(s_owner[2], s_owner[3]));
+    }
+    owner = __builtin_amdgcn_readfirstlane(owner);
     const int ow = owner / L, oj = owner - ow * L;
-    if (owner != 0x7fffffff && oj < L - 1) {                // uniform: not at the last position, a draft row exists
+    const bool draft = owner != 0x7fffffff && oj < L - 1;   // uniform: not at the last position, a draft row exists
+    if (draft) {
         const float *zq = draft_row_ptr(draft_logits, step_row, rows_per_step, b, ow, oj, p, W, L, V);
 #pragma unroll
         for (int u = 0; u < 4; ++u) xq[u] = load4<VEC>(zq, v0 + (u * kLseThreads + tid) * 4, V);
-        c = chunk_max_sum(xq, 1.0f, s_red);
     }
-    if (tid == 0) part[rowid * chunks + chunk] = make_float4(a.x, a.y, c.x, c.y);
+    float2 a = wave_max_sum(xp, inv_t), c = make_float2(0.f, 1.f / kWaves);
+    if (draft) c = wave_max_sum(xq, 1.0f);
+    if (lane == 0) s_red[wave] = make_float4(a.x, a.y, c.x, c.y);
+    __syncthreads();
+    if (tid == 0) {
+        a = make_float2(s_red[0].x, s_red[0].y);
+        c = make_float2(s_red[0].z, s_red[0].w);
+#pragma unroll
+        for (int w = 1; w < kWaves; ++w) {
+            a = merge_max_sum(a, make_float2(s_red[w].x, s_red[w].y));
+            c = merge_max_sum(c, make_float2(s_red[w].z, s_red[w].w));
+        }
+        part[rowid * chunks + chunk] = make_float4(a.x, a.y, c.x, c.y);
+    }
 }
 
 // weight of entry v in the distribution the next token is drawn from
@@ -191,9 +214,6 @@ __device__ __forceinline__ float chunk_weights(const float *zp, const float *zq,
     return sum;
 }
 
-__device__ __forceinline__ void st_dev(float *p, float v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
-__device__ __forceinline__ float ld_dev(const float *p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
-
 template <bool VEC>
 __global__ __launch_bounds__(kSelThreads) void rd_accept_sample_kernel(
     const float *__restrict__ logits, const float *__restrict__ draft_logits, const int32_t *__restrict__ step_row,
@@ -211,7 +231,8 @@ __global__ __launch_bounds__(kSelThreads) void rd_accept_sample_kernel(
     __shared__ int s_best, s_pick, s_lastpos;
     __shared__ uint32_t s_last;
     __shared__ float s_wave[kSelWaves];
-    __shared__ float s_total[kMaxSelChunks];
+    __shared__ int s_ci, s_residual;
+    __shared__ float s_base, s_target;
 
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int chunk = blockIdx.x, b = blockIdx.y;
@@ -223,46 +244,82 @@ __global__ __launch_bounds__(kSelThreads) void rd_accept_sample_kernel(
     RD_TR(0);
 
     // ---- every workgroup of the sequence: log-sum-exps, rejection tests, best candidate -------------------
-    for (int r = tid; r < N; r += kSelThreads) {
-        float lp = 0.f, lq = 0.f;
-        if (r < P) {
-            const float4 *pr = part + ((size_t)b * N + r) * chunks;
-            float mp = -INFINITY, mq = -INFINITY;
-            for (int c = 0; c < chunks; ++c) { mp = fmaxf(mp, pr[c].x); mq = fmaxf(mq, pr[c].z); }
-            float sp = 0.f, sq = 0.f;
-            for (int c = 0; c < chunks; ++c) {              // in chunk order: the same bits in every workgroup
-                const float4 v = pr[c];
-                sp += v.y * __expf(v.x - mp);
-                sq += v.w * __expf(v.z - mq);
-            }
-            lp = mp + __logf(sp);
-            lq = mq + __logf(sq);
+    // candidate tokens: at most two per thread; slot of a token and of its parent, and (where it has one) the
+    // draft distribution it was drawn from, all fetched before anything waits
+    constexpr int kTok = (RD_MAX_N + kSelThreads - 1) / kSelThreads;
+    int tx[kTok], ts[kTok], tc[kTok], tr[kTok];
+#pragma unroll
+    for (int k = 0; k < kTok; ++k) {
+        const int e = min(k * kSelThreads + tid, N - 1), ep = max(e - 1, 0), j = e % L;
+        tx[k] = beams[(size_t)b * N + e];
+        tc[k] = unpack_index[(size_t)b * N + e];
+        ts[k] = unpack_index[(size_t)b * N + ep];
+        tr[k] = step_row && L > 1 ? step_row[((size_t)b * W + e / L) * (L - 1) + max(j - 1, 0)] : 0;
+    }
+    // Partials: a group of G lanes (a power of two) takes a row, one or more chunks per lane; up to four rows per lane
+    // group have their loads in flight together.  Rows of padding slots are read and ignored.
+    int G = 1;
+    while (G < chunks && G < 64) G <<= 1;
+    const int rows_per = kSelThreads / G, gl = tid & (G - 1), gr = tid / G;
+    for (int r0 = 0; r0 < P; r0 += 4 * rows_per) {
+        float4 v[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const int r = min(r0 + k * rows_per + gr, N - 1);
+            v[k] = part[((size_t)b * N + r) * chunks + min(gl, chunks - 1)];
         }
-        s_lse_p[r] = lp;
-        s_lse_q[r] = lq;
-        s_slot[r] = min(max(unpack_index[(size_t)b * N + r], 0), N - 1);
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            if (r0 + k * rows_per >= P) break;              // uniform
+            const int r = r0 + k * rows_per + gr;
+            float4 x = gl < chunks ? v[k] : make_float4(-INFINITY, 0.f, -INFINITY, 0.f);
+            for (int c = gl + G; c < chunks; c += G) {      // more than 64 chunks
+                const float4 y = part[((size_t)b * N + min(r, N - 1)) * chunks + c];
+                const float2 p2 = merge_max_sum(make_float2(x.x, x.y), make_float2(y.x, y.y));
+                const float2 q2 = merge_max_sum(make_float2(x.z, x.w), make_float2(y.z, y.w));
+                x = make_float4(p2.x, p2.y, q2.x, q2.y);
+            }
+            float mp = x.x, mq = x.z;
+            for (int off = 1; off < G; off <<= 1) { mp = fmaxf(mp, __shfl_xor(mp, off, 64)); mq = fmaxf(mq, __shfl_xor(mq, off, 64)); }
+            float sp = x.y * __expf(x.x - (mp > -INFINITY ? mp : 0.f)), sq = x.w * __expf(x.z - (mq > -INFINITY ? mq : 0.f));
+            for (int off = 1; off < G; off <<= 1) { sp += __shfl_xor(sp, off, 64); sq += __shfl_xor(sq, off, 64); }
+            if (gl == 0 && r < P) {
+                s_lse_p[r] = mp + __logf(sp);
+                s_lse_q[r] = mq + __logf(sq);
+            }
+        }
+    }
+    // the logits of the candidate tokens under their parents
+    float zp_t[kTok], zq_t[kTok], u_t[kTok];
+#pragma unroll
+    for (int k = 0; k < kTok; ++k) {
+        const int e = min(k * kSelThreads + tid, N - 1), j = max(e % L, 1);
+        const int x = min(max(tx[k], 0), V - 1);
+        tc[k] = min(max(tc[k], 0), N - 1);
+        ts[k] = min(max(ts[k], 0), N - 1);
+        const int s = e % L == 0 ? 0 : ts[k];
+        const size_t qrow = step_row ? (size_t)(j - 1) * rows_per_step + min(max(tr[k], 0), rows_per_step - 1) : (size_t)b * N + s;
+        zp_t[k] = L > 1 ? logits[((size_t)b * N + s) * V + x] : 0.f;
+        zq_t[k] = L > 1 ? draft_logits[qrow * V + x] : 0.f;
+        u_t[k] = u_accept[(size_t)b * N + tc[k]];
+        if (k * kSelThreads + tid < N) s_slot[e] = tc[k];
     }
     if (tid == 0) { s_best = -1; s_pick = 0x7fffffff; s_lastpos = -1; }
     __syncthreads();
     RD_TR(1);
 
     // one thread per candidate token: the rejection test of token (w, j), j >= 1
-    for (int e = tid; e < N; e += kSelThreads) {
-        const int j = e % L;
-        const int x = beams[(size_t)b * N + e];
+#pragma unroll
+    for (int k = 0; k < kTok; ++k) {
+        const int e = k * kSelThreads + tid;
+        if (e >= N) continue;
+        const int x = tx[k];
         bool ok;
-        if (j == 0) {
+        if (e % L == 0) {
             ok = (root_token == nullptr) || (x == my_root);
         } else {
-            ok = false;
-            if (x >= 0 && x < V) {
-                const int s = s_slot[e - 1], c = s_slot[e];
-                const float *zq_row = draft_row_ptr(draft_logits, step_row, rows_per_step, b, e / L, j - 1, s, W, L, V);
-                const float lp = logits[((size_t)b * N + s) * V + x] * inv_t - s_lse_p[s];
-                const float lq = zq_row[x] - s_lse_q[s];
-                const float ratio = fminf(__expf(lp - lq), 1.0f);
-                ok = u_accept[(size_t)b * N + c] < ratio;
-            }
+            const float lp = zp_t[k] * inv_t - s_lse_p[ts[k]], lq = zq_t[k] - s_lse_q[ts[k]];
+            ok = x >= 0 && x < V && u_t[k] < fminf(__expf(lp - lq), 1.0f);
         }
         s_ok[e] = ok ? 1 : 0;
     }
@@ -302,46 +359,76 @@ __global__ __launch_bounds__(kSelThreads) void rd_accept_sample_kernel(
     if (residual) {
         // this workgroup's chunk of the residual: total -> workspace, then find out who is last
         float t = chunk_weights<VEC>(zp, zq, chunk, V, inv_t, lse_p, lse_q, true, w);
-        for (int off = 32; off > 0; off >>= 1) t += __shfl_xor(t, off, 64);
+        t = rd::wave_reduce_sum(t);
         if (lane == 0) s_wave[wave] = t;
         __syncthreads();
         if (tid == 0) {
-            st_dev(chunk_totals + (size_t)b * chunks + chunk, (s_wave[0] + s_wave[1]) + (s_wave[2] + s_wave[3]));
-            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");          // the total is visible before the arrival
+            rd::st_dev(chunk_totals + (size_t)b * chunks + chunk, (s_wave[0] + s_wave[1]) + (s_wave[2] + s_wave[3]));
+            rd::wait_dev_stores();                                      // the total is visible before the arrival
             const uint32_t prev = __hip_atomic_fetch_add(counters + b, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             s_last = (prev + 1u == (uint32_t)chunks) ? 1u : 0u;
         }
         __syncthreads();
         if (!s_last) return;
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
         if (tid == 0) counters[b] = 0;                      // ready for the next call
-        for (int i = tid; i < chunks; i += kSelThreads) s_total[i] = ld_dev(chunk_totals + (size_t)b * chunks + i);
-        __syncthreads();
-        float total = 0.f;
-        for (int i = 0; i < chunks; ++i) total += s_total[i];
-        if (!(total > 0.f)) residual = false;               // p == q everywhere: draw from p
-        __syncthreads();
     } else if (chunk != 0) {
         return;
     }
     RD_TR(4);
-    if (!residual)                                          // chunk totals of p from launch 1's partials
-        for (int i = tid; i < chunks; i += kSelThreads) s_total[i] = prow[i].y * __expf(prow[i].x - lse_p);
-    __syncthreads();
-    float total = 0.f;
-    for (int i = 0; i < chunks; ++i) total += s_total[i];
-    const float target = u_draw * total;
-    // the chunk in which the running total crosses the target; if rounding leaves none, the last chunk
-    // that holds any weight
-    int ci = -1, lastc = 0;
-    float base = 0.f, run = 0.f;
-    for (int i = 0; i < chunks; ++i) {
-        if (s_total[i] > 0.f) lastc = i;
-        const float next = run + s_total[i];
-        if (ci < 0 && target < next) { ci = i; base = run; }
-        run = next;
+    // Running totals of the chunks in chunk order, by the first wave: lane l holds chunks per*l .. per*l + per - 1.
+    // The chunk in which the running total crosses the target; if rounding leaves none, the last that holds any weight.
+    if (wave == 0) {
+        const int per = (chunks + 63) / 64;
+        float mine[kMaxSelChunks / 64], sum = 0.f;
+        bool any = false;
+        for (int attempt = 0; attempt < 2; ++attempt) {     // once more if p == q everywhere: draw from p
+            sum = 0.f;
+#pragma unroll
+            for (int k = 0; k < kMaxSelChunks / 64; ++k) {
+                const int i = min(lane * per + k, chunks - 1);
+                mine[k] = 0.f;
+                if (k < per) {
+                    // totals of p from launch 1's partials
+                    const float t = residual ? rd::ld_dev(chunk_totals + (size_t)b * chunks + i) : prow[i].y * __expf(prow[i].x - lse_p);
+                    if (lane * per + k < chunks) mine[k] = t;
+                }
+                sum += mine[k];
+            }
+            any = __ballot(sum > 0.f) != 0;
+            if (any || !residual) break;
+            residual = false;
+        }
+        float incl = sum;
+#pragma unroll
+        for (int off = 1; off < 64; off <<= 1) {
+            const float o = __shfl_up(incl, off, 64);
+            if (lane >= off) incl += o;
+        }
+        const float target = u_draw * __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(incl), 63));
+        float run = incl - sum, base = 0.f;
+        int ci = 0x7fffffff, lastc = -1;
+#pragma unroll
+        for (int k = 0; k < kMaxSelChunks / 64; ++k) {
+            if (mine[k] > 0.f) lastc = lane * per + k;
+            const float next = run + mine[k];
+            if (ci == 0x7fffffff && mine[k] > 0.f && target < next) { ci = lane * per + k; base = run; }
+            run = next;
+        }
+        const unsigned long long cross = __ballot(ci != 0x7fffffff), held = __ballot(lastc >= 0);
+        if (cross) {
+            const int w0 = __ffsll((long long)cross) - 1;
+            ci = __builtin_amdgcn_readlane(ci, w0);
+            base = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(base), w0));
+        } else {
+            ci = held ? __builtin_amdgcn_readlane(lastc, 63 - __clzll((long long)held)) : 0;
+            base = 0.f;
+        }
+        if (lane == 0) { s_ci = ci; s_base = base; s_target = target; s_residual = residual ? 1 : 0; }
     }
-    if (ci < 0) { ci = lastc; base = 0.f; }
+    __syncthreads();
+    const int ci = s_ci;
+    const float base = s_base, target = s_target;
+    residual = s_residual != 0;
     // cumulative weights inside the chunk, in token order.  The scan sums in another order than the
     // chunk totals did, so its last value may fall short of the target by rounding: then the chunk's
     // last token of positive weight is the one.
@@ -420,7 +507,7 @@ extern "C" int rd_accept_sample(const float *logits, const float *draft_logits, 
     float4 *part = reinterpret_cast<float4 *>(ws + plan.part_off);
     const float inv_t = 1.0f / temperature;
     hipStream_t s = (hipStream_t)stream;
-    const bool vec = (V & 3) == 0;                          // rows stay 16-byte aligned
+    const bool vec = V >= 4;
     hipLaunchKernelGGL(vec ? rd_lse_chunk_kernel<true> : rd_lse_chunk_kernel<false>, dim3(plan.chunks, N, B),
                        dim3(kLseThreads), 0, s, logits, draft_logits, draft_step_row, draft_rows_per_step, unpack_index, n_packed, W, L, V,
                        plan.chunks, inv_t, part);

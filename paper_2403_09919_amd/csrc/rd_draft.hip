@@ -88,22 +88,36 @@ __device__ __forceinline__ void linear_epilogue(const LinArgs<T> &a, f32x4 v, in
     const int m = m_tile + r16;
     if (m >= a.M) return;
     const size_t prow = (size_t)(a.m0 + m) * a.mstride;         // physical row of the activation buffers
+    const int n0 = n_tile + 4 * g;
+    if (EPI == EPI_HEAD) {
+        float *y = a.y_f32 + prow * a.ldy + n0;
+        if (a.bias == nullptr && n0 + 4 <= a.N) {               // (the logit rows start at any multiple of 4 bytes)
+            *reinterpret_cast<rd::f4_any *>(y) = rd::f4_any{v[0], v[1], v[2], v[3]};
+            return;
+        }
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+            if (n0 + i < a.N) y[i] = v[i] + (a.bias ? a.bias[n0 + i] : 0.f);
+        return;
+    }
+    if (n0 >= a.N) return;                                      // (N is a multiple of 64 here)
+    typedef __attribute__((ext_vector_type(4))) T vec4;
+    const size_t o = prow * a.ldy + n0;
+    rd::f4_any bias = {0.f, 0.f, 0.f, 0.f};
+    if (a.bias) bias = *reinterpret_cast<const rd::f4_any *>(a.bias + n0);
+    const f32x4 res = EPI == EPI_MLP ? *reinterpret_cast<const f32x4 *>(a.res + o) : f32x4{0.f, 0.f, 0.f, 0.f};
+    f32x4 y;
+    vec4 yb;
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-        const int n = n_tile + 4 * g + i;
-        if (n >= a.N) continue;
-        float y = v[i] + (a.bias ? a.bias[n] : 0.f);
-        const size_t o = prow * a.ldy + n;
-        if (EPI == EPI_HEAD) {
-            a.y_f32[o] = y;
-        } else {
-            y = silu(y);
-            if (EPI == EPI_MLP) y += a.res[o];
-            a.y_f32[o] = y;
-            a.y_bf[o] = (T)y;
-            if (EPI == EPI_RNN) a.s_bf[prow * a.N + n] = (T)y;
-        }
+        float t = silu(v[i] + bias[i]);
+        if (EPI == EPI_MLP) t += res[i];
+        y[i] = t;
+        yb[i] = (T)t;
     }
+    *reinterpret_cast<f32x4 *>(a.y_f32 + o) = y;
+    *reinterpret_cast<vec4 *>(a.y_bf + o) = yb;
+    if (EPI == EPI_RNN) *reinterpret_cast<vec4 *>(a.s_bf + prow * a.N + n0) = yb;
 }
 
 // The last workgroup of a column group adds the KS partial tiles of each output tile in split order
@@ -527,11 +541,11 @@ __global__ __launch_bounds__(kChunkThreads) void rd_topw_chunk_kernel(const floa
     const int t0 = c * kChunk + tid * kChunkPer;            // this lane's first token
     float x[kChunkPer];
     int k[kChunkPer];
-    if ((V & 3) == 0 && t0 + kChunkPer <= V) {
+    if (t0 + kChunkPer <= V) {
 #pragma unroll
         for (int j = 0; j < kChunkPer; j += 4) {
-            const float4 q = *reinterpret_cast<const float4 *>(z + t0 + j);
-            x[j] = q.x; x[j + 1] = q.y; x[j + 2] = q.z; x[j + 3] = q.w;
+            const rd::f4_any q = *reinterpret_cast<const rd::f4_any *>(z + t0 + j);
+            x[j] = q[0]; x[j + 1] = q[1]; x[j + 2] = q[2]; x[j + 3] = q[3];
         }
     } else {
 #pragma unroll

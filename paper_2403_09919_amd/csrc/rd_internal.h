@@ -106,6 +106,51 @@ __device__ __forceinline__ void st_dev4(float *p, float a, float b, float c, flo
 // L2, which is what the exchange avoids.
 __device__ __forceinline__ void wait_dev_stores() { asm volatile("s_waitcnt vmcnt(0)" : : : "memory"); }
 
+// ---- rows of any length in 16-byte loads --------------------------------------------------------------
+// Rows of V floats start at multiples of 4 bytes only, unless V is a multiple of 4; global memory instructions of any
+// width need no more.  (Scalar loads for such rows cost a vocabulary-wide pass two to three times its time.)
+typedef float f4_any __attribute__((ext_vector_type(4), aligned(4)));
+// Entries v .. v+3 of a row of n >= 4, -inf past the end.  No branch: a load inside a branch makes the compiler wait
+// for every load in flight at the join.  Addresses past the end are pulled back and the values moved.
+__device__ __forceinline__ float4 row4(const float *row, int v, int n)
+{
+    const int a = min(v, n - 4), d = v - a;
+    const f4_any q = *reinterpret_cast<const f4_any *>(row + a);
+    float4 r = make_float4(q[0], q[1], q[2], q[3]);
+    if (d & 1) r = make_float4(r.y, r.z, r.w, -INFINITY);
+    if (d & 2) r = make_float4(r.z, r.w, -INFINITY, -INFINITY);
+    if (d > 3) r = make_float4(-INFINITY, -INFINITY, -INFINITY, -INFINITY);
+    return r;
+}
+
+// ---- reductions over the 64 lanes, the same value in every lane --------------------------------------
+// Data-parallel primitives inside rows of 16 and the gfx950 lane swaps across them: about ten instructions, where
+// __shfl_xor is six round trips through LDS.
+template <int kCtrl> __device__ __forceinline__ float dpp(float x)
+{
+    return __uint_as_float((uint32_t)__builtin_amdgcn_update_dpp((int)__float_as_uint(x), (int)__float_as_uint(x), kCtrl, 0xf, 0xf, false));
+}
+template <typename Op> __device__ __forceinline__ float wave_reduce(float x, Op op)
+{
+    x = op(x, dpp<0xB1>(x));            // quad_perm [1,0,3,2]: lane ^ 1
+    x = op(x, dpp<0x4E>(x));            // quad_perm [2,3,0,1]: lane ^ 2
+    x = op(x, dpp<0x141>(x));           // row_half_mirror: the other quad of the 8
+    x = op(x, dpp<0x140>(x));           // row_mirror: the other half of the 16
+    auto a = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+    x = op(__uint_as_float(a[0]), __uint_as_float(a[1]));
+    auto b = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+    return op(__uint_as_float(b[0]), __uint_as_float(b[1]));
+}
+__device__ __forceinline__ float wave_reduce_max(float x) { return wave_reduce(x, [](float a, float b) { return fmaxf(a, b); }); }
+// (non-negative integers below 2^31: their order is that of their bits)
+__device__ __forceinline__ uint32_t wave_reduce_min_u(uint32_t x)
+{
+    return __float_as_uint(wave_reduce(__uint_as_float(x), [](float a, float b) {
+        return __uint_as_float(min(__float_as_uint(a), __float_as_uint(b)));
+    }));
+}
+__device__ __forceinline__ float wave_reduce_sum(float x) { return wave_reduce(x, [](float a, float b) { return a + b; }); }
+
 }  // namespace rd
 
 // Optional phase timestamps for tuning builds (-DRD_TRACE): thread 0 of every workgroup stores
