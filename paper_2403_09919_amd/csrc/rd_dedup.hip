@@ -1,6 +1,6 @@
 // rd_dedup: dynamic tree attention construction (Sec. 3.3, App. A.1) for gfx950.
 //
-// One workgroup per sequence, everything in LDS, data-parallel phases separated by barriers
+// One workgroup per sequence (more where the dense mask is asked for), everything in LDS, data-parallel phases separated by barriers
 // (the whole input is a few hundred bytes; what costs time is dependent latency, so no phase
 // is a serial walk over positions):
 //   A  stage the W x L candidates; owner[i][j] = i.
@@ -21,10 +21,12 @@ RD_TRACE_DEFINE(rd_debug_set_trace_dedup)
 
 namespace {
 
-constexpr int kDedupThreads = 384;
+constexpr int kDedupThreads = 384;                 // the fewest: one thread per token
+constexpr int kWideThreads = 1024;                 // more than 16 candidates: their pairs are what takes time (9.0 us at 70 with 384)
+constexpr int kMaskRows = 32;                      // rows of the dense mask per workgroup
 constexpr int kMaskWords = (RD_MAX_N + 63) / 64;
 
-__global__ __launch_bounds__(kDedupThreads) void rd_dedup_kernel(
+__global__ __launch_bounds__(kWideThreads) void rd_dedup_kernel(
     const int32_t *__restrict__ beams, const int32_t *__restrict__ ctx_len, int W, int L,
     int32_t *__restrict__ prefix_tree, int32_t *__restrict__ packed_tokens,
     int32_t *__restrict__ n_packed, int32_t *__restrict__ unpack_index,
@@ -38,8 +40,11 @@ __global__ __launch_bounds__(kDedupThreads) void rd_dedup_kernel(
     __shared__ uint64_t s_bits[RD_MAX_N][kMaskWords];   // mask row of each packed slot
     __shared__ int s_P;
 
-    const int b = blockIdx.x;
-    const int tid = threadIdx.x;
+    // The dense mask, N bytes per row, is too much for one compute unit (28 us at N = 350): further workgroups of the
+    // sequence repeat the phases and write kMaskRows rows of it each.
+    const int b = blockIdx.x, slice = blockIdx.y;
+    const bool main_wg = slice == 0;
+    const int tid = threadIdx.x, threads = blockDim.x;
     const int N = W * L;
     const int words = (N + 63) >> 6;
     const size_t seq = (size_t)b * N;
@@ -66,7 +71,7 @@ __global__ __launch_bounds__(kDedupThreads) void rd_dedup_kernel(
     // ---- B: common prefixes of all pairs ----------------------------------------------------------------
     // Both rows are read eight tokens at a time (independent LDS reads), the match length follows
     // in registers, and the atomics that lower the owners are issued without waiting on each other.
-    for (int pr = tid; pr < W * W; pr += kDedupThreads) {
+    for (int pr = tid; pr < W * W; pr += threads) {
         const int pi = pr / W, pk = pr - pi * W;
         if (pk < pi) {
             const int32_t *ri = s_beam + pi * L, *rk = s_beam + pk * L;
@@ -104,7 +109,10 @@ __global__ __launch_bounds__(kDedupThreads) void rd_dedup_kernel(
         int base = 0;
         for (int k = 0; k < tid; ++k) base += L - s_first[k];
         if (tid < W) s_base[tid] = base;
-        else { s_P = base; n_packed[b] = base; }
+        else {
+            s_P = base;
+            if (main_wg) n_packed[b] = base;
+        }
     }
     rd_lds_barrier();
     RD_TR(3);
@@ -113,17 +121,21 @@ __global__ __launch_bounds__(kDedupThreads) void rd_dedup_kernel(
     if (tok) {
         const int slot = s_base[owner] + j - s_first[owner];   // (owner, j) is a kept token: j >= first_kept[owner]
         s_slot[e] = slot;
-        unpack_index[seq + e] = slot;
-        if (prefix_tree) prefix_tree[seq + e] = owner;
+        if (main_wg) {
+            unpack_index[seq + e] = slot;
+            if (prefix_tree) prefix_tree[seq + e] = owner;
+        }
     }
     rd_lds_barrier();
 
     // ---- E: one thread per kept token ---------------------------------------------------------------------------
     if (tok && owner == i) {
         const int slot = s_slot[e];
-        packed_tokens[seq + slot] = s_beam[e];
-        parent[seq + slot] = j ? s_slot[e - 1] : -1;
-        position_ids[seq + slot] = ctx + j;
+        if (main_wg) {
+            packed_tokens[seq + slot] = s_beam[e];
+            parent[seq + slot] = j ? s_slot[e - 1] : -1;
+            position_ids[seq + slot] = ctx + j;
+        }
         uint64_t path[kMaskWords];             // slots on the path from the root to (i, j)
 #pragma unroll
         for (int w = 0; w < kMaskWords; ++w) path[w] = 0;
@@ -141,30 +153,31 @@ __global__ __launch_bounds__(kDedupThreads) void rd_dedup_kernel(
 
     // ---- F: paddings and masks ---------------------------------------------------------------------------------
     const int P = s_P;
-    for (int p = P + tid; p < N; p += kDedupThreads) {
+    for (int p = P + tid; p < N && main_wg; p += threads) {
         packed_tokens[seq + p] = -1;
         parent[seq + p] = -1;
         position_ids[seq + p] = -1;
     }
-    if (tree_mask_bits) {
+    if (main_wg && tree_mask_bits) {
         uint64_t *dst = tree_mask_bits + seq * words;
-        for (int i = tid; i < N * words; i += kDedupThreads) dst[i] = s_bits[i / words][i % words];
+        for (int i = tid; i < N * words; i += threads) dst[i] = s_bits[i / words][i % words];
     }
     if (tree_mask) {
         uint8_t *dst = tree_mask + seq * N;
+        const int p0 = slice * kMaskRows, rows = min(kMaskRows, N - p0);
         if ((N & 3) == 0) {                          // N*N and seq*N are multiples of 4: 32-bit stores
             uint32_t *dst4 = reinterpret_cast<uint32_t *>(dst);
             const int n4 = N >> 2;
-            for (int i = tid; i < N * n4; i += kDedupThreads) {
-                const int p = i / n4, q0 = (i % n4) << 2;
+            for (int i = tid; i < rows * n4; i += threads) {
+                const int p = p0 + i / n4, q0 = (i % n4) << 2;
                 const uint64_t w = s_bits[p][q0 >> 6] >> (q0 & 63);
-                dst4[i] = (uint32_t)(w & 1) | (uint32_t)((w >> 1) & 1) << 8 |
-                          (uint32_t)((w >> 2) & 1) << 16 | (uint32_t)((w >> 3) & 1) << 24;
+                dst4[p * n4 + (q0 >> 2)] = (uint32_t)(w & 1) | (uint32_t)((w >> 1) & 1) << 8 |
+                                           (uint32_t)((w >> 2) & 1) << 16 | (uint32_t)((w >> 3) & 1) << 24;
             }
         } else {
-            for (int i = tid; i < N * N; i += kDedupThreads) {
-                const int p = i / N, q = i % N;
-                dst[i] = (uint8_t)((s_bits[p][q >> 6] >> (q & 63)) & 1);
+            for (int i = tid; i < rows * N; i += threads) {
+                const int p = p0 + i / N, q = i % N;
+                dst[p * N + q] = (uint8_t)((s_bits[p][q >> 6] >> (q & 63)) & 1);
             }
         }
     }
@@ -183,7 +196,8 @@ extern "C" int rd_dedup(const int32_t *beams, const int32_t *ctx_len, int B, int
     if (!beams || !packed_tokens || !n_packed || !unpack_index || !parent || !position_ids)
         return RD_ERR_INVALID_ARG;
     if (!rd_aligned(tree_mask, 4) || !rd_aligned(tree_mask_bits, 8)) return RD_ERR_INVALID_ARG;
-    hipLaunchKernelGGL(rd_dedup_kernel, dim3(B), dim3(kDedupThreads), 0, (hipStream_t)stream,
+    const int slices = tree_mask ? (W * L + kMaskRows - 1) / kMaskRows : 1;
+    hipLaunchKernelGGL(rd_dedup_kernel, dim3(B, slices), dim3(W > 16 ? kWideThreads : kDedupThreads), 0, (hipStream_t)stream,
                        beams, ctx_len, W, L, prefix_tree, packed_tokens, n_packed, unpack_index,
                        parent, position_ids, tree_mask, tree_mask_bits);
     return rd_check_launch();
