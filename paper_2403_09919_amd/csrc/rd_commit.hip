@@ -1,8 +1,9 @@
 // rd_commit: the accepted tokens join the context (Sec. 3.4).  Pure data movement: for each
 // (sequence, head) the K and V rows of the accepted packed slots are appended to the cache
 // behind ctx_len; one more workgroup per sequence writes the new context length and picks
-// the hidden state of the last accepted token.  A few KB per sequence, so the launch is
-// latency-bound: every thread issues its 16-byte copy at once, nothing waits on anything else.
+// the hidden state of the last accepted token.  A few KB per sequence, so the launch is a chain of memory round
+// trips: the counts and the slots are fetched together, and the rows as soon as their slots are known, whether or
+// not they turn out to be among those that fit (only the stores depend on that).
 #include "rd_internal.h"
 
 namespace {
@@ -15,12 +16,13 @@ __device__ __forceinline__ int clamp_i(int x, int lo, int hi) { return x < lo ? 
 __global__ __launch_bounds__(kCommitThreads) void rd_commit_kernel(
     const uint4 *__restrict__ k_new, const uint4 *__restrict__ v_new,
     const int32_t *__restrict__ accepted_idx, const int32_t *__restrict__ best_len,
-    const int32_t *__restrict__ ctx_len, int H, int N, int Cmax, int L, int row_vecs /* 16-byte vectors per K/V row */,
+    const int32_t *__restrict__ ctx_len, int H, int N, int Cmax, int L, int row_shift /* log2 of the 16-byte vectors per K/V row */,
     uint4 *__restrict__ k_cache, uint4 *__restrict__ v_cache, int32_t *__restrict__ ctx_len_out,
     int32_t *__restrict__ n_committed, const uint4 *__restrict__ hidden, int hid_vecs, uint4 *__restrict__ hidden_last,
     const int32_t *__restrict__ block_table /* NULL: dense cache */, int page_size, int max_pages, int n_pages)
 {
     const int b = blockIdx.y, h = blockIdx.x, tid = threadIdx.x;
+    const int my_slot = accepted_idx[(size_t)b * L + min(tid >> row_shift, L - 1)];
     const int bl = clamp_i(best_len[b], 0, L);
     const int c = clamp_i(ctx_len[b], 0, Cmax);
     const int n = min(bl, Cmax - c);
@@ -38,21 +40,22 @@ __global__ __launch_bounds__(kCommitThreads) void rd_commit_kernel(
         return;
     }
     const size_t bh = (size_t)b * H + h;
-    const int total = n * row_vecs;                 // vectors per tensor for this head
-    for (int i = tid; i < total; i += kCommitThreads) {
-        const int t = i / row_vecs, v = i - t * row_vecs;
-        const int slot = clamp_i(accepted_idx[(size_t)b * L + t], 0, N - 1);
-        const size_t src = (bh * N + slot) * row_vecs + v;
+    for (int i = tid; i < L << row_shift; i += kCommitThreads) {
+        const int t = i >> row_shift, v = i & ((1 << row_shift) - 1);
+        const int slot = clamp_i(i == tid ? my_slot : accepted_idx[(size_t)b * L + t], 0, N - 1);
+        const size_t src = ((bh * N + slot) << row_shift) + v;
+        const uint4 kv = k_new[src], vv = v_new[src];
+        if (t >= n) break;
         size_t dst;
         if (block_table == nullptr) {
-            dst = (bh * Cmax + (size_t)(c + t)) * row_vecs + v;
+            dst = ((bh * Cmax + (size_t)(c + t)) << row_shift) + v;
         } else {                                    // position c+t lives in page block_table[b][(c+t)/page_size]
             const int pos = c + t;
             const int page = clamp_i(block_table[(size_t)b * max_pages + pos / page_size], 0, n_pages - 1);
-            dst = (((size_t)page * H + h) * page_size + (size_t)(pos % page_size)) * row_vecs + v;
+            dst = ((((size_t)page * H + h) * page_size + (size_t)(pos % page_size)) << row_shift) + v;
         }
-        k_cache[dst] = k_new[src];
-        v_cache[dst] = v_new[src];
+        k_cache[dst] = kv;
+        v_cache[dst] = vv;
     }
 }
 
@@ -79,10 +82,10 @@ extern "C" int rd_commit(const void *k_new, const void *v_new, const int32_t *ac
         if (!rd_aligned(hidden, 16) || !rd_aligned(hidden_last, 16)) return RD_ERR_INVALID_ARG;
         hid_vecs = (int)(Dh * es / 16);
     }
-    const int row_vecs = (int)(D * es / 16);
+    const int row_shift = __builtin_ctz((unsigned)(D * es / 16));         // (a power of two: D is 64 or 128)
     hipLaunchKernelGGL(rd_commit_kernel, dim3(H + 1, B), dim3(kCommitThreads), 0, (hipStream_t)stream,
                        static_cast<const uint4 *>(k_new), static_cast<const uint4 *>(v_new), accepted_idx, best_len,
-                       ctx_len, H, N, Cmax, L, row_vecs, static_cast<uint4 *>(k_cache), static_cast<uint4 *>(v_cache),
+                       ctx_len, H, N, Cmax, L, row_shift, static_cast<uint4 *>(k_cache), static_cast<uint4 *>(v_cache),
                        ctx_len_out, n_committed, static_cast<const uint4 *>(hidden), hid_vecs,
                        static_cast<uint4 *>(hidden_last), nullptr, 0, 0, 0);
     return rd_check_launch();
@@ -114,10 +117,10 @@ extern "C" int rd_commit_paged(const void *k_new, const void *v_new, const int32
         if (!rd_aligned(hidden, 16) || !rd_aligned(hidden_last, 16)) return RD_ERR_INVALID_ARG;
         hid_vecs = (int)(Dh * es / 16);
     }
-    const int row_vecs = (int)(D * es / 16);
+    const int row_shift = __builtin_ctz((unsigned)(D * es / 16));         // (a power of two: D is 64 or 128)
     hipLaunchKernelGGL(rd_commit_kernel, dim3(H + 1, B), dim3(kCommitThreads), 0, (hipStream_t)stream,
                        static_cast<const uint4 *>(k_new), static_cast<const uint4 *>(v_new), accepted_idx, best_len,
-                       ctx_len, H, N, page_size * max_pages, L, row_vecs, static_cast<uint4 *>(k_pages),
+                       ctx_len, H, N, page_size * max_pages, L, row_shift, static_cast<uint4 *>(k_pages),
                        static_cast<uint4 *>(v_pages), ctx_len_out, n_committed, static_cast<const uint4 *>(hidden),
                        hid_vecs, static_cast<uint4 *>(hidden_last), block_table, page_size, max_pages, n_pages);
     return rd_check_launch();
