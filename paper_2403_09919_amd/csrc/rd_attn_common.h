@@ -29,9 +29,9 @@ struct AttnPlan {
 //   * a workgroup is 1.0 (eight waves) or 1.2 (four) plus 2.0 + 0.5 r or 1.15 + 0.3 r per block, r = row tiles with
 //     packed rows; at five row tiles K comes in operand order, 0.3 more per block of eight waves;
 //   * one eight-wave workgroup fills a compute unit, two of four waves do; more start as those retire;
-//   * the workgroups that run at one time share 5.0 (eight waves) or 5.25 TB/s, a compute unit gets 28 GB/s at most,
+//   * the workgroups that run at one time share 5.0 (eight waves) or 5.25 TB/s, a compute unit gets 32 GB/s at most,
 //     and one with two workgroups takes twice as long as one with one (the rest of the chip then idles, which leaves
-//     the others more: half of that is counted); latency and bandwidth overlap in part (root of the sum of squares);
+//     the others more: half of that is counted); latency and bandwidth overlap but for where they are close (fourth root of the sum of fourth powers);
 //   * more than one range per head adds a merge: 1.5, and the partial results written and read back, the reading by
 //     one compute unit at 50 GB/s.
 // Beams of more than 80 packed rows are cut into row groups, as equal as whole tiles allow; every group walks the
@@ -67,8 +67,9 @@ static inline AttnPlan attn_plan_make(int B, int H, int N, int D, int Cmax)
             auto round = [&](long long n) {
                 const long long per_cu = (n + 255) / 256;
                 const double sharing = ((n < 256 ? n : 256) + (double)n / per_cu) / 2;
-                const double t_bw = per_cu * bytes / (rate / sharing < 28e3 ? rate / sharing : 28e3);
-                return sqrt(t_lat * t_lat + t_bw * t_bw);
+                const double t_bw = per_cu * bytes / (rate / sharing < 32e3 ? rate / sharing : 32e3);
+                const double l2 = t_lat * t_lat, b2 = t_bw * t_bw;
+                return sqrt(sqrt(l2 * l2 + b2 * b2));
             };
             double T = full * round(slots) + (rest ? round(rest) : 0.0);
             if (n_part > 1) T += 1.5 + n_part * part / 50e3 + 2.0 * (double)BH * n_act * n_part * part / 4e6;
