@@ -1220,8 +1220,8 @@ int launch_linear_mt(const LinArgs<T> &a, hipStream_t stream)
     if constexpr (MT >= 4) {                                    // (at 113 rows and more even half a chip of these beats narrower ones)
         if (a.N >= (MT == 8 ? 128 : 256) * 64) return launch_linear_nt<T, MT, 4, EPI>(a, stream);
     }
-    if constexpr (MT >= 2) {
-        if (a.N >= 256 * 32) return launch_linear_nt<T, MT, 2, EPI>(a, stream);
+    if constexpr (MT >= 2) {                                    // (140 rows, N = 6528: 1609 us per call with one, 1407 with two, 1532 with four)
+        if (a.N >= (MT == 8 ? 192 : 256) * 32) return launch_linear_nt<T, MT, 2, EPI>(a, stream);
     }
     return launch_linear_nt<T, MT, 1, EPI>(a, stream);
 }
