@@ -22,6 +22,26 @@ struct AttnPlan {
     size_t total_bytes;
 };
 
+// Row groups of a head in the matrix-core kernel with `waves` waves per workgroup, and the 16-row tiles of each.
+struct AttnGroups { int rg_tiles, n_rg; };
+static inline AttnGroups attn_groups(int N, int waves)
+{
+    constexpr int kMaxTilesPerGroup = 5, kWideTilesPerGroup = 4;    // as instantiated
+    const int nq_all = (N + 15) / 16, n_rg = (nq_all + kMaxTilesPerGroup - 1) / kMaxTilesPerGroup;
+    const int nq = N > 32 * waves ? kWideTilesPerGroup : (nq_all + n_rg - 1) / n_rg;
+    return {nq, (nq_all + nq - 1) / nq};
+}
+
+// Bytes of the completion counters, in front of the partial results.  One workspace may serve calls planned for
+// different contexts (ctx_bound of rd_tree_attn_bounded): a counter must never lie where another of these plans keeps
+// partial results.  The waves, and with them the row groups, follow from the context, so there is room for the most
+// groups that any plan of the shape has.
+static inline size_t attn_counters_bytes(long long BH, int N)
+{
+    const int n8 = attn_groups(N, 8).n_rg, n4 = attn_groups(N, 4).n_rg;
+    return ((size_t)BH * (n8 > n4 ? n8 : n4) * sizeof(unsigned long long) + 255) / 256 * 256;
+}
+
 // Plan of the matrix-core kernel (rd_tree_attn_mfma.h), for contexts of up to Cmax keys: waves per workgroup, rows
 // per workgroup and workgroups per head, from an estimate of the launch time.  Lengths are upper bounds and the
 // packed rows are not known at all here (distinct prefixes are taken to be 0.6 of the candidates' tokens); the kernel
@@ -38,9 +58,8 @@ struct AttnPlan {
 // head's keys, and workgroups of groups that turn out empty go to the others.
 static inline AttnPlan attn_plan_make(int B, int H, int N, int D, int Cmax)
 {
-    constexpr int kMaxTilesPerGroup = 5, kWideTilesPerGroup = 4;    // as instantiated
     const long long BH = (long long)B * H;
-    const int nq_all = (N + 15) / 16;
+    const size_t counters_bytes = attn_counters_bytes(BH, N);
     const double rows = 0.6 * N, scale = D == 128 ? 1.0 : 0.6;
     const int tiles = (Cmax + 31) / 32 + ((int)rows + 31) / 32;
     static const int waves_env = env_int("RD_ATTN_WAVES", 0), forced = env_int("RD_ATTN_SPLITS", 0);
@@ -48,9 +67,7 @@ static inline AttnPlan attn_plan_make(int B, int H, int N, int D, int Cmax)
     double best_T = 1e30;
     for (int waves = 8; waves >= 4; waves -= 4) {
         if (waves_env && waves != waves_env) continue;
-        int n_rg = (nq_all + kMaxTilesPerGroup - 1) / kMaxTilesPerGroup;
-        const int nq = N > 32 * waves ? kWideTilesPerGroup : (nq_all + n_rg - 1) / n_rg;
-        n_rg = (nq_all + nq - 1) / nq;
+        const int nq = attn_groups(N, waves).rg_tiles, n_rg = attn_groups(N, waves).n_rg;
         int n_act = (int)((rows + 16 * nq - 1) / (16 * nq));
         n_act = n_act < 1 ? 1 : n_act;
         double r = n_act > 1 ? nq : (rows + 15) / 16;
@@ -80,7 +97,7 @@ static inline AttnPlan attn_plan_make(int B, int H, int N, int D, int Cmax)
                 best.S = S;
                 best.rg_tiles = nq;
                 best.n_rg = n_rg;
-                best.counters_bytes = ((size_t)BH * n_rg * sizeof(unsigned long long) + 255) / 256 * 256;
+                best.counters_bytes = counters_bytes;
                 best.total_bytes = best.counters_bytes + (S > 1 ? ((size_t)BH * S * (size_t)(nq * 16 * (2 + D)) * sizeof(float) + 255) / 256 * 256 : 0);
             }
         }

@@ -1,0 +1,65 @@
+"""Launch plans of the attention kernels (csrc/rd_attn_common.h), on the CPU: a small program that prints them is
+compiled against the header, host pass only."""
+import os
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+PROGRAM = r"""
+#include "rd_attn_common.h"
+#include <stdio.h>
+#include <string.h>
+using namespace rd;
+
+// One line per plan that breaks a rule; the last line counts the plans looked at.
+int main()
+{
+    const int ctxs[] = {0, 1, 32, 100, 300, 700, 1000, 1400, 1500, 2048, 3000, 5000, 9000, 20000, 40000, 131072};
+    const int shapes[][2] = {{1, 1}, {1, 4}, {1, 5}, {1, 32}, {2, 40}, {4, 32}, {8, 32}, {3, 26}, {16, 52}, {24, 32}};
+    long n = 0;
+    for (int f32 = 0; f32 < 2; ++f32)
+        for (int D = 64; D <= 128; D += 64)
+            for (auto &s : shapes)
+                for (int N = 1; N <= RD_MAX_N; ++N) {
+                    size_t first = 0;
+                    for (int C : ctxs) {
+                        const AttnPlan p = attn_plan(s[0], s[1], N, D, C, f32 != 0);
+                        const long long BH = (long long)s[0] * s[1];
+                        const size_t part = (size_t)p.rg_tiles * 16 * (2 + D) * sizeof(float);
+                        auto bad = [&](const char *what) { printf("B=%d H=%d N=%d D=%d C=%d f32=%d: %s\n", s[0], s[1], N, D, C, f32, what); };
+                        if (C == ctxs[0]) first = p.counters_bytes;
+                        if (p.counters_bytes != first) bad("the counters' place depends on the context");
+                        if (p.counters_bytes < (size_t)BH * p.n_rg * sizeof(unsigned long long)) bad("counters overlap the partial results");
+                        if (p.S > 1 && p.total_bytes < p.counters_bytes + (size_t)BH * p.S * part) bad("no room for the partial results");
+                        if (p.rg_tiles * p.n_rg * 16 < N) bad("rows without a group");
+                        if (p.S < p.n_rg || (p.waves != 4 && p.waves != 8)) bad("workgroups");
+                        AttnPlan again = attn_plan(s[0], s[1], N, D, C, f32 != 0);
+                        if (memcmp(&p, &again, sizeof(p)) != 0) bad("a repeated call plans otherwise");
+                        ++n;
+                    }
+                }
+    printf("plans %ld\n", n);
+}
+"""
+
+
+@pytest.fixture(scope="module")
+def report(tmp_path_factory):
+    tmp = tmp_path_factory.mktemp("plan")
+    src, exe = str(tmp / "plan.hip"), str(tmp / "plan")
+    with open(src, "w") as f:
+        f.write(PROGRAM)
+    hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
+    subprocess.run([hipcc, "--offload-arch=gfx950", "--cuda-host-only", "-O1", "-std=c++17", "-I", os.path.join(ROOT, "include"),
+                    "-I", os.path.join(ROOT, "paper_2403_09919_amd", "csrc"), "-Wno-unused-function", src, "-o", exe],
+                   check=True, capture_output=True, text=True)
+    return subprocess.run([exe], check=True, capture_output=True, text=True, timeout=300).stdout.splitlines()
+
+
+def test_workspace_layout_is_the_same_for_every_context(report):
+    """One workspace may serve calls planned for different contexts (rd_tree_attn_bounded): the completion counters have
+    to lie at the same place in front of the partial results whatever the plan."""
+    assert report[-1].startswith("plans ") and int(report[-1].split()[1]) > 200000
+    assert report[:-1] == [], (len(report) - 1, report[:5])

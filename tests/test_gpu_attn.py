@@ -442,3 +442,26 @@ def test_plan_from_a_context_bound(rd, dtype):
                               workspace=ws, ctx_bound=bound)
         torch.cuda.synchronize()
         compare(host(got), ref, dtype, "bound %d" % bound)
+
+
+@pytest.mark.parametrize("W", [30, 40])
+def test_one_workspace_for_bounds_with_different_row_groups(rd, W):
+    """A beam of 150 or 200 tokens is cut into two or three, three or four row groups depending on the bound of the
+    contexts; calls planned for alternating bounds share one workspace, as a decoding loop whose contexts grow does."""
+    announce("attn bounds with different row groups, W=%d" % W)
+    B, H, D, L, Cmax, dtype = 2, 32, 128, 5, 700, "bf16"
+    t = make_case(B, H, D, W, L, (700, 410), dtype, seed=11, V=32000, share="high")
+    d = oracle.dedup(t["beams"], t["ctx_len"])
+    scale = float(1.0 / np.sqrt(D))
+    ref = oracle.tree_attn(t["q"], t["k_cache"], t["v_cache"], t["ctx_len"], t["k_new"], t["v_new"],
+                           d["n_packed"], d["tree_mask"], dtype, scale)
+    td = {k: dev(v) for k, v in t.items()}
+    npk, mask = dev(d["n_packed"]), dev(d["tree_mask_bits"])
+    bounds = (300, 700, 300, 100, 700, 200, 300, 700)
+    ws = rd.new_workspace(max(rd.rd_tree_attn_workspace(B, H, W * L, D, c, rd.RD_BF16) for c in bounds), "cuda")
+    for i, bound in enumerate(bounds):
+        out = torch.full_like(td["q"], float("nan"))
+        rd.rd_tree_attn(td["q"], td["k_cache"], td["v_cache"], td["ctx_len"], td["k_new"], td["v_new"], npk, mask, scale,
+                        out=out, workspace=ws, ctx_bound=bound)
+        torch.cuda.synchronize()
+        compare(host(out), ref, dtype, "call %d, bound %d" % (i, bound))
