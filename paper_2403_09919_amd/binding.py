@@ -143,7 +143,7 @@ def rd_tree_attn(q, k_cache, v_cache, ctx_len, k_new, v_new, n_packed, tree_mask
     if workspace is None:
         B, H, N, D = q.shape
         Cmax = k_cache.shape[2]
-        workspace = new_workspace(rd_tree_attn_workspace(B, H, N, D, Cmax if ctx_bound is None else min(ctx_bound, Cmax), _dt_code(q)), q.device)
+        workspace = new_workspace(rd_tree_attn_workspace(B, H, N, D, Cmax if ctx_bound is None else min(int(ctx_bound), Cmax), _dt_code(q)), q.device)
     _check(_call.tree_attn(q, k_cache, v_cache, ctx_len, k_new, v_new, n_packed, tree_mask_bits, scale, out, workspace, ctx_bound),
            "rd_tree_attn" if ctx_bound is None else "rd_tree_attn_bounded")
     return out

@@ -11,6 +11,7 @@
 #include <torch/csrc/autograd/python_variable.h>
 #include <c10/hip/HIPStream.h>
 #include <initializer_list>
+#include <limits.h>
 #include <string>
 #include "rd.h"
 
@@ -108,10 +109,25 @@ int integer(PyObject *o)
     if (v != (long)(int)v) { PyErr_SetString(PyExc_OverflowError, "value does not fit a C int"); throw PyError(); }
     return (int)v;
 }
+// What int(o) accepts, moved into a C int's range where it lies outside (a context bound above every capacity is one)
+int bound(PyObject *o)
+{
+    PyObject *n = PyNumber_Long(o);
+    if (!n) throw PyError();
+    int over = 0;
+    const long v = PyLong_AsLongAndOverflow(n, &over);
+    Py_DECREF(n);
+    if (over > 0 || v > INT_MAX) return INT_MAX;
+    return over < 0 || v < INT_MIN ? INT_MIN : (int)v;
+}
+// What float(o) accepts
 float real(PyObject *o)
 {
-    const double v = PyFloat_AsDouble(o);
-    if (v == -1.0 && PyErr_Occurred()) throw PyError();
+    if (PyFloat_CheckExact(o)) return (float)PyFloat_AS_DOUBLE(o);
+    PyObject *f = PyNumber_Float(o);
+    if (!f) throw PyError();
+    const double v = PyFloat_AS_DOUBLE(f);
+    Py_DECREF(f);
     return (float)v;
 }
 
@@ -203,7 +219,7 @@ struct Attn {
 int capacity(PyObject *k_cache)
 {
     const at::Tensor &t = tensor(k_cache, "k_cache");
-    if (t.dim() != 4) bad("k_cache must have 4 dimensions, got " + std::to_string(t.dim()));
+    if (t.dim() < 3) bad("k_cache must have 4 dimensions, got " + std::to_string(t.dim()));     // (the whole shape is checked where keys are held)
     return (int)t.size(2);
 }
 
@@ -217,8 +233,8 @@ PyObject *tree_attn(Args a)
     void *s = stream();
     if (a[11] == Py_None)
         return status([&] { return rd_tree_attn(t.q, kc, vc, t.ctx_len, t.k_new, t.v_new, t.n_packed, t.mask, t.B, t.H, t.N, t.D, Cmax, t.dt, scale, t.out, t.ws.p, t.ws.bytes, s); });
-    const int bound = integer(a[11]);
-    return status([&] { return rd_tree_attn_bounded(t.q, kc, vc, t.ctx_len, t.k_new, t.v_new, t.n_packed, t.mask, t.B, t.H, t.N, t.D, Cmax, bound, t.dt, scale, t.out, t.ws.p, t.ws.bytes, s); });
+    const int most = bound(a[11]);
+    return status([&] { return rd_tree_attn_bounded(t.q, kc, vc, t.ctx_len, t.k_new, t.v_new, t.n_packed, t.mask, t.B, t.H, t.N, t.D, Cmax, most, t.dt, scale, t.out, t.ws.p, t.ws.bytes, s); });
 }
 
 // q, k_cache, v_cache, ctx_len, k_new, v_new, n_packed, tree_mask_bits, position_ids, cos_tab, sin_tab, scale, out,

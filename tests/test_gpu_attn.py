@@ -465,3 +465,20 @@ def test_one_workspace_for_bounds_with_different_row_groups(rd, W):
                         out=out, workspace=ws, ctx_bound=bound)
         torch.cuda.synchronize()
         compare(host(out), ref, dtype, "call %d, bound %d" % (i, bound))
+
+
+@pytest.mark.parametrize("bound", [300.0, "300", np.int64(300), np.float32(300.5), 2 ** 40, torch.tensor(300)])
+def test_bound_and_scale_of_any_number_type(rd, bound):
+    """ctx_bound is whatever int() takes and scale whatever float() takes; a bound beyond a C int is above every capacity."""
+    announce("attn bound %r" % (bound,))
+    B, H, D, W, L = 1, 2, 64, 3, 4
+    t = make_case(B, H, D, W, L, [600], "bf16", seed=6)
+    d = oracle.dedup(t["beams"], t["ctx_len"])
+    ref = oracle.tree_attn(t["q"], t["k_cache"], t["v_cache"], t["ctx_len"], t["k_new"], t["v_new"], d["n_packed"], d["tree_mask"], "bf16", 0.125)
+    args = [dev(t[k]) for k in ("q", "k_cache", "v_cache", "ctx_len", "k_new", "v_new")] + [dev(d["n_packed"]), dev(d["tree_mask_bits"])]
+    for scale in (0.125, "0.125", np.float32(0.125)):
+        got = rd.rd_tree_attn(*args, scale, ctx_bound=bound)
+        torch.cuda.synchronize()
+        compare(host(got), ref, "bf16", "bound %r, scale %r" % (bound, scale))
+    with pytest.raises(rd.RdError):
+        rd.rd_tree_attn(*args, 0.125, ctx_bound=-2 ** 40)
