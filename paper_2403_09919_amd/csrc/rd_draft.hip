@@ -1220,8 +1220,17 @@ int launch_linear_mt(const LinArgs<T> &a, hipStream_t stream)
     if constexpr (MT >= 4) {                                    // (at 113 rows and more even half a chip of these beats narrower ones)
         if (a.N >= (MT == 8 ? 128 : 256) * 64) return launch_linear_nt<T, MT, 4, EPI>(a, stream);
     }
-    if constexpr (MT >= 2) {                                    // (140 rows, N = 6528: 1609 us per call with one, 1407 with two, 1532 with four)
-        if (a.N >= (MT == 8 ? 192 : 256) * 32) return launch_linear_nt<T, MT, 2, EPI>(a, stream);
+    if constexpr (MT >= 2) {
+        // At 65 rows and more every workgroup reads all activations from L2, twice as often with one tile as with two:
+        // two tiles from 192 workgroups on (N = 6144..8191; 128 rows, us per call, one -> two tiles: 6200 tokens at a hidden
+        // size of 1024 160 -> 133 and at 4096 378 -> 270; MLP layers of 6272 and 8064 471 -> 414, 590 -> 514; hidden size
+        // 6272 527 -> 408, 8064 740 -> 593).  Not the RNN at hidden sizes that are odd multiples of 64, where only four
+        // waves share K and half as many workgroups leave a compute unit too few of them (80 rows: 6720 500 -> 540, 8128
+        // 637 -> 747; 128 rows: 7488 696 -> 727, 8128 770 -> 838), except above 96 rows below 208 workgroups (128 rows:
+        // 6208 544 -> 516, 6592 582 -> 570; but 80 rows 454 -> 469, 480 -> 506).
+        int least = 256;
+        if (MT == 8 && (EPI != EPI_RNN || a.K1 / 32 % 4 == 0 || (a.M > 96 && a.N < 208 * 32))) least = 192;
+        if (a.N >= least * 32) return launch_linear_nt<T, MT, 2, EPI>(a, stream);
     }
     return launch_linear_nt<T, MT, 1, EPI>(a, stream);
 }

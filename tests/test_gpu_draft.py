@@ -402,3 +402,35 @@ def test_split_layers_repeat_and_graph_replay(rd):
         torch.cuda.synchronize()
         graph.replay()
         same(("replay", rep))
+
+
+@pytest.mark.parametrize("Dm,V,B,W", [(6208, 130, 12, 8), (6208, 130, 14, 7), (6592, 130, 16, 8), (6720, 130, 16, 8), (6528, 130, 9, 8),
+                                      (64, 6143, 10, 8), (64, 6145, 10, 8), (1088, 8190, 16, 8)])
+def test_layers_of_192_to_256_workgroups(rd, Dm, V, B, W):
+    """65 rows and more through unsplit layers of 6144 to 8191 columns: one or two column tiles per workgroup by rows,
+    columns and waves (RNN at the lines of its rule, output layer at the edge).  The logits behind the second token of every
+    candidate against 64 bits.  Bound: the state may round to the neighbouring bf16 value where the 32-bit sum differs
+    (2^-8 of each term), and a 32-bit sum of 2 Dm terms."""
+    announce(f"draft layers of half width Dm={Dm} V={V} B={B} W={W}")
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(Dm + V)
+
+    def r(*shape, std):
+        return (torch.randn(shape, generator=gen, device="cuda") * std).to(torch.bfloat16)
+
+    p = dict(emb=r(V, Dm, std=1.0), rnn_u=r(Dm, Dm, std=Dm ** -0.5), rnn_w=r(Dm, Dm, std=Dm ** -0.5),
+             rnn_b=torch.randn((Dm,), generator=gen, device="cuda") * 0.1, mlp_w=r(0, 2 * Dm, 2 * Dm, std=1.0),
+             mlp_b=torch.zeros((0, 2 * Dm), device="cuda"), head_w=r(V, 2 * Dm, std=Dm ** -0.5))
+    h, last = r(B, Dm, std=1.0), torch.randint(0, V, (B,), generator=gen, device="cuda", dtype=torch.int32)
+    got = rd.rd_draft(p, h, last, W, 3, steps=True)
+    torch.cuda.synchronize()
+    emb, u, w, head = (p[k].double() for k in ("emb", "rnn_u", "rnn_w", "head_w"))
+    tok = got["beams"][:, :, 1].long().reshape(-1)
+    z = torch.matmul(emb[last.long()], u.t()).repeat_interleave(W, 0) + torch.matmul(emb[tok], w.t()) + p["rnn_b"].double()
+    x = torch.cat([torch.nn.functional.silu(z), h.double().repeat_interleave(W, 0)], 1)
+    ref = torch.matmul(x.to(torch.bfloat16).double(), head.t())
+    bound = (2.0 ** -8 + 2 * Dm * 2.0 ** -24) * torch.matmul(x.abs(), head.abs().t())
+    rows = got["step_row"][:, :, 1].long().reshape(-1)
+    err = (got["step_logits"][1][rows].double() - ref).abs()
+    assert torch.isfinite(err).all() and (err <= bound).all(), (err / bound).max()
+    assert err.square().mean() <= 1e-4 * ref.square().mean()       # neighbours are rare: far below the bound on the whole
