@@ -42,6 +42,15 @@ static inline size_t attn_counters_bytes(long long BH, int N)
     return ((size_t)BH * (n8 > n4 ? n8 : n4) * sizeof(unsigned long long) + 255) / 256 * 256;
 }
 
+// The next number of workgroups per head that a plan's search has to look at: those that leave the longest range at `per`
+// of the nblk blocks take no less time than the fewest of them (`every` of the searches below looks at all: they agree).
+static inline int attn_next_split(int S, int nblk, int per, int n_act)
+{
+    if (per <= 1) return 1 << 30;
+    const int next = (nblk + per - 2) / (per - 1) * n_act;
+    return next > S ? next : S + 1;
+}
+
 // Plan of the matrix-core kernel (rd_tree_attn_mfma.h), for contexts of up to Cmax keys: waves per workgroup, rows
 // per workgroup and workgroups per head, from an estimate of the launch time.  Lengths are upper bounds and the
 // packed rows are not known at all here (distinct prefixes are taken to be 0.6 of the candidates' tokens); the kernel
@@ -56,7 +65,7 @@ static inline size_t attn_counters_bytes(long long BH, int N)
 //     one compute unit at 50 GB/s.
 // Beams of more than 80 packed rows are cut into row groups, as equal as whole tiles allow; every group walks the
 // head's keys, and workgroups of groups that turn out empty go to the others.
-static inline AttnPlan attn_plan_make(int B, int H, int N, int D, int Cmax)
+static inline AttnPlan attn_plan_make(int B, int H, int N, int D, int Cmax, bool every = false)
 {
     const long long BH = (long long)B * H;
     const size_t counters_bytes = attn_counters_bytes(BH, N);
@@ -77,8 +86,9 @@ static inline AttnPlan attn_plan_make(int B, int H, int N, int D, int Cmax)
         const double t_wg = waves == 8 ? 1.0 : 1.2, rate = waves == 8 ? 5.0e6 : 5.25e6;
         const long long slots = waves == 8 ? 256 : 512;
         const double part = r * 16 * (2 + D) * sizeof(float);
-        for (int S = n_rg; S <= 64 * n_rg && S <= nblk * n_rg; ++S) {
+        for (int S = n_rg, next; S <= 64 * n_rg && S <= nblk * n_rg; S = next) {
             const int ranges = S / n_act, per = (nblk + ranges - 1) / ranges, n_part = (nblk + per - 1) / per;
+            next = forced > 0 || every ? S + 1 : attn_next_split(S, nblk, per, n_act);
             const double t_lat = t_wg + per * t_blk, bytes = (double)(per * waves < tiles ? per * waves : tiles) * 32 * D * 4 / n_act;
             const long long wgs = (BH + 7) / 8 * 8 * S, full = wgs / slots, rest = wgs % slots;
             auto round = [&](long long n) {
@@ -108,7 +118,7 @@ static inline AttnPlan attn_plan_make(int B, int H, int N, int D, int Cmax)
 // Plan of the fp32 kernel (rd_tree_attn_f32.hip; row groups of one tile): workgroups per head, estimated as above.  A
 // workgroup is eight waves of 16-key tiles; a block of 128 keys takes 3.0 us (D = 128) or half of that, a compute
 // unit reads 40 GB/s, the chip 5 TB/s.
-static inline AttnPlan attn_plan_make_f32(int B, int H, int N, int D, int Cmax)
+static inline AttnPlan attn_plan_make_f32(int B, int H, int N, int D, int Cmax, bool every = false)
 {
     AttnPlan best = {};
     const long long BH = (long long)B * H;
@@ -117,8 +127,9 @@ static inline AttnPlan attn_plan_make_f32(int B, int H, int N, int D, int Cmax)
     const int tiles = (Cmax + 15) / 16 + ((int)rows + 15) / 16, nblk = tiles > 8 ? (tiles + 7) / 8 : 1;
     const int n_rg = (N + 15) / 16, n_act = rows > 16 ? (int)((rows + 15) / 16) : 1;
     double best_T = 1e30;
-    for (int S = n_rg; S <= 64 * n_rg && S <= nblk * n_rg; ++S) {
+    for (int S = n_rg, next; S <= 64 * n_rg && S <= nblk * n_rg; S = next) {
         const int ranges = S / n_act, per = (nblk + ranges - 1) / ranges, n_part = (nblk + per - 1) / per;
+        next = forced > 0 || every ? S + 1 : attn_next_split(S, nblk, per, n_act);
         const double t_lat = 1.5 + per * t_blk, bytes = (double)(per * 8 < tiles ? per * 8 : tiles) * 16 * D * 8;
         const long long wgs = (BH + 7) / 8 * 8 * S, full = wgs / 256, rest = wgs % 256;
         auto round = [&](long long n) {
@@ -141,16 +152,24 @@ static inline AttnPlan attn_plan_make_f32(int B, int H, int N, int D, int Cmax)
     return best;
 }
 
-// The search takes up to some microseconds; a program calls with the same few shapes, so each thread keeps its last plan.
+// A search takes 0.4 us, up to 2 at few heads and long contexts (4 with every number of workgroups looked at); a program
+// calls with few shapes at a time (the models it serves, their batches, a context bound that grows), so each thread keeps
+// its last eight plans, the oldest of which makes room.
 static inline AttnPlan attn_plan(int B, int H, int N, int D, int Cmax, bool f32 = false)
 {
-    static thread_local int key[6] = {0, 0, 0, 0, -1, 0};
-    static thread_local AttnPlan plan;
-    if (key[0] != B || key[1] != H || key[2] != N || key[3] != D || key[4] != Cmax || key[5] != (int)f32) {
-        plan = f32 ? attn_plan_make_f32(B, H, N, D, Cmax) : attn_plan_make(B, H, N, D, Cmax);
-        key[0] = B; key[1] = H; key[2] = N; key[3] = D; key[4] = Cmax; key[5] = (int)f32;
-    }
-    return plan;
+    constexpr int kKept = 8;
+    struct Entry {
+        int B, H, N, D, Cmax, f32;      // B = 0: empty
+        AttnPlan plan;
+    };
+    static thread_local Entry kept[kKept] = {};
+    static thread_local int oldest = 0;
+    for (const Entry &e : kept)
+        if (e.B == B && e.H == H && e.N == N && e.D == D && e.Cmax == Cmax && e.f32 == (int)f32) return e.plan;
+    Entry &e = kept[oldest];
+    oldest = (oldest + 1) % kKept;
+    e = {B, H, N, D, Cmax, (int)f32, f32 ? attn_plan_make_f32(B, H, N, D, Cmax) : attn_plan_make(B, H, N, D, Cmax)};
+    return e.plan;
 }
 
 struct AttnArgs {

@@ -35,8 +35,14 @@ int main()
                         if (p.S > 1 && p.total_bytes < p.counters_bytes + (size_t)BH * p.S * part) bad("no room for the partial results");
                         if (p.rg_tiles * p.n_rg * 16 < N) bad("rows without a group");
                         if (p.S < p.n_rg || (p.waves != 4 && p.waves != 8)) bad("workgroups");
-                        AttnPlan again = attn_plan(s[0], s[1], N, D, C, f32 != 0);
-                        if (memcmp(&p, &again, sizeof(p)) != 0) bad("a repeated call plans otherwise");
+                        // kept plans: the one just made, and one that may have been pushed out since
+                        for (int other : {C, ctxs[0], 300}) {
+                            const AttnPlan kept = attn_plan(s[0], s[1], N, D, other, f32 != 0);
+                            const AttnPlan made = f32 ? attn_plan_make_f32(s[0], s[1], N, D, other) : attn_plan_make(s[0], s[1], N, D, other);
+                            if (memcmp(&kept, &made, sizeof(kept)) != 0) bad("a kept plan is not the one of these arguments");
+                        }
+                        const AttnPlan all = N % 7 ? p : f32 ? attn_plan_make_f32(s[0], s[1], N, D, C, true) : attn_plan_make(s[0], s[1], N, D, C, true);
+                        if (memcmp(&p, &all, sizeof(p)) != 0) bad("the search leaves out a better plan");
                         ++n;
                     }
                 }
