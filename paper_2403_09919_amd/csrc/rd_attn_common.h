@@ -13,6 +13,8 @@
 
 namespace rd {
 
+typedef __attribute__((ext_vector_type(4))) float f32x4;
+
 struct AttnPlan {
     int waves;         // waves per workgroup (4 or 8); a block is a tile of keys per wave
     int S;             // workgroups per (sequence, head)
@@ -42,13 +44,37 @@ static inline size_t attn_counters_bytes(long long BH, int N)
     return ((size_t)BH * (n8 > n4 ? n8 : n4) * sizeof(unsigned long long) + 255) / 256 * 256;
 }
 
-// The next number of workgroups per head that a plan's search has to look at: those that leave the longest range at `per`
-// of the nblk blocks take no less time than the fewest of them (`every` of the searches below looks at all: they agree).
-static inline int attn_next_split(int S, int nblk, int per, int n_act)
+// Looks for the workgroups per head S with the shortest estimate of the launch, from n_rg (one per row group) up: S / n_act
+// ranges of at most `per` of a head's nblk blocks, n_part of them with keys.  Those that leave the longest range at `per`
+// blocks take no less time than the fewest of them, so only these are looked at (`every`: all; they agree).  est(S, per,
+// n_part) gives microseconds; returns the best, and its S in *best_S, if it is below best_T, else best_T.
+template <typename Est>
+static inline double attn_search(int n_rg, int n_act, int nblk, bool every, double best_T, int *best_S, Est est)
 {
-    if (per <= 1) return 1 << 30;
-    const int next = (nblk + per - 2) / (per - 1) * n_act;
-    return next > S ? next : S + 1;
+    static const int forced_env = env_int("RD_ATTN_SPLITS", 0);
+    const int most = (nblk < 64 ? nblk : 64) * n_rg;
+    const int forced = forced_env > 0 && forced_env < n_rg ? n_rg : (forced_env < most ? forced_env : most);
+    for (int S = n_rg, next; S <= most; S = next) {
+        const int ranges = S / n_act, per = (nblk + ranges - 1) / ranges, n_part = (nblk + per - 1) / per;
+        next = S + 1;
+        if (forced <= 0 && !every) {
+            if (per <= 1) next = most + 1;
+            else if ((nblk + per - 2) / (per - 1) * n_act > S) next = (nblk + per - 2) / (per - 1) * n_act;
+        }
+        const double T = est(S, per, n_part);
+        if (forced > 0 ? S == forced : T < best_T * (1 - 1e-9)) {
+            best_T = T;
+            *best_S = S;
+        }
+    }
+    return best_T;
+}
+
+// Microseconds that merging n_part partial results of `part` bytes each takes: written and read back, the reading by one
+// compute unit at 50 GB/s.
+static inline double attn_merge_us(long long units, int n_part, double part)
+{
+    return n_part > 1 ? 1.5 + n_part * part / 50e3 + 2.0 * (double)units * n_part * part / 4e6 : 0.0;
 }
 
 // Plan of the matrix-core kernel (rd_tree_attn_mfma.h), for contexts of up to Cmax keys: waves per workgroup, rows
@@ -61,8 +87,7 @@ static inline int attn_next_split(int S, int nblk, int per, int n_act)
 //   * the workgroups that run at one time share 5.0 (eight waves) or 5.25 TB/s, a compute unit gets 32 GB/s at most,
 //     and one with two workgroups takes twice as long as one with one (the rest of the chip then idles, which leaves
 //     the others more: half of that is counted); latency and bandwidth overlap but for where they are close (fourth root of the sum of fourth powers);
-//   * more than one range per head adds a merge: 1.5, and the partial results written and read back, the reading by
-//     one compute unit at 50 GB/s.
+//   * more than one range per head adds a merge (attn_merge_us).
 // Beams of more than 80 packed rows are cut into row groups, as equal as whole tiles allow; every group walks the
 // head's keys, and workgroups of groups that turn out empty go to the others.
 static inline AttnPlan attn_plan_make(int B, int H, int N, int D, int Cmax, bool every = false)
@@ -71,7 +96,7 @@ static inline AttnPlan attn_plan_make(int B, int H, int N, int D, int Cmax, bool
     const size_t counters_bytes = attn_counters_bytes(BH, N);
     const double rows = 0.6 * N, scale = D == 128 ? 1.0 : 0.6;
     const int tiles = (Cmax + 31) / 32 + ((int)rows + 31) / 32;
-    static const int waves_env = env_int("RD_ATTN_WAVES", 0), forced = env_int("RD_ATTN_SPLITS", 0);
+    static const int waves_env = env_int("RD_ATTN_WAVES", 0);
     AttnPlan best = {};
     double best_T = 1e30;
     for (int waves = 8; waves >= 4; waves -= 4) {
@@ -86,11 +111,10 @@ static inline AttnPlan attn_plan_make(int B, int H, int N, int D, int Cmax, bool
         const double t_wg = waves == 8 ? 1.0 : 1.2, rate = waves == 8 ? 5.0e6 : 5.25e6;
         const long long slots = waves == 8 ? 256 : 512;
         const double part = r * 16 * (2 + D) * sizeof(float);
-        for (int S = n_rg, next; S <= 64 * n_rg && S <= nblk * n_rg; S = next) {
-            const int ranges = S / n_act, per = (nblk + ranges - 1) / ranges, n_part = (nblk + per - 1) / per;
-            next = forced > 0 || every ? S + 1 : attn_next_split(S, nblk, per, n_act);
+        int S = 0;
+        const double T = attn_search(n_rg, n_act, nblk, every, best_T, &S, [&](int wgs_per_head, int per, int n_part) {
             const double t_lat = t_wg + per * t_blk, bytes = (double)(per * waves < tiles ? per * waves : tiles) * 32 * D * 4 / n_act;
-            const long long wgs = (BH + 7) / 8 * 8 * S, full = wgs / slots, rest = wgs % slots;
+            const long long wgs = (BH + 7) / 8 * 8 * wgs_per_head, full = wgs / slots, rest = wgs % slots;
             auto round = [&](long long n) {
                 const long long per_cu = (n + 255) / 256;
                 const double sharing = ((n < 256 ? n : 256) + (double)n / per_cu) / 2;
@@ -98,18 +122,16 @@ static inline AttnPlan attn_plan_make(int B, int H, int N, int D, int Cmax, bool
                 const double l2 = t_lat * t_lat, b2 = t_bw * t_bw;
                 return sqrt(sqrt(l2 * l2 + b2 * b2));
             };
-            double T = full * round(slots) + (rest ? round(rest) : 0.0);
-            if (n_part > 1) T += 1.5 + n_part * part / 50e3 + 2.0 * (double)BH * n_act * n_part * part / 4e6;
-            const bool take = forced > 0 ? S == (forced < n_rg ? n_rg : (forced < nblk * n_rg ? forced : nblk * n_rg)) : T < best_T * (1 - 1e-9);
-            if (take) {
-                best_T = T;
-                best.waves = waves;
-                best.S = S;
-                best.rg_tiles = nq;
-                best.n_rg = n_rg;
-                best.counters_bytes = counters_bytes;
-                best.total_bytes = best.counters_bytes + (S > 1 ? ((size_t)BH * S * (size_t)(nq * 16 * (2 + D)) * sizeof(float) + 255) / 256 * 256 : 0);
-            }
+            return full * round(slots) + (rest ? round(rest) : 0.0) + attn_merge_us(BH * n_act, n_part, part);
+        });
+        if (S > 0) {
+            best_T = T;
+            best.waves = waves;
+            best.S = S;
+            best.rg_tiles = nq;
+            best.n_rg = n_rg;
+            best.counters_bytes = counters_bytes;
+            best.total_bytes = counters_bytes + (S > 1 ? ((size_t)BH * S * (size_t)(nq * 16 * (2 + D)) * sizeof(float) + 255) / 256 * 256 : 0);
         }
     }
     return best;
@@ -122,33 +144,23 @@ static inline AttnPlan attn_plan_make_f32(int B, int H, int N, int D, int Cmax, 
 {
     AttnPlan best = {};
     const long long BH = (long long)B * H;
-    static const int forced = env_int("RD_ATTN_SPLITS", 0);
     const double rows = 0.6 * N, t_blk = D == 128 ? 3.0 : 1.5, part = 16.0 * (2 + D) * sizeof(float);
     const int tiles = (Cmax + 15) / 16 + ((int)rows + 15) / 16, nblk = tiles > 8 ? (tiles + 7) / 8 : 1;
     const int n_rg = (N + 15) / 16, n_act = rows > 16 ? (int)((rows + 15) / 16) : 1;
-    double best_T = 1e30;
-    for (int S = n_rg, next; S <= 64 * n_rg && S <= nblk * n_rg; S = next) {
-        const int ranges = S / n_act, per = (nblk + ranges - 1) / ranges, n_part = (nblk + per - 1) / per;
-        next = forced > 0 || every ? S + 1 : attn_next_split(S, nblk, per, n_act);
+    best.waves = 8;
+    best.rg_tiles = 1;
+    best.n_rg = n_rg;
+    attn_search(n_rg, n_act, nblk, every, 1e30, &best.S, [&](int wgs_per_head, int per, int n_part) {
         const double t_lat = 1.5 + per * t_blk, bytes = (double)(per * 8 < tiles ? per * 8 : tiles) * 16 * D * 8;
-        const long long wgs = (BH + 7) / 8 * 8 * S, full = wgs / 256, rest = wgs % 256;
+        const long long wgs = (BH + 7) / 8 * 8 * wgs_per_head, full = wgs / 256, rest = wgs % 256;
         auto round = [&](long long n) {
             const double t_bw = bytes / (5e6 / n < 40e3 ? 5e6 / n : 40e3);
             return sqrt(t_lat * t_lat + t_bw * t_bw);
         };
-        double T = full * round(256) + (rest ? round(rest) : 0.0);
-        if (n_part > 1) T += 1.5 + n_part * part / 50e3 + 2.0 * (double)BH * n_act * n_part * part / 4e6;
-        const bool take = forced > 0 ? S == (forced < n_rg ? n_rg : (forced < nblk * n_rg ? forced : nblk * n_rg)) : T < best_T * (1 - 1e-9);
-        if (take) {
-            best_T = T;
-            best.waves = 8;
-            best.S = S;
-            best.rg_tiles = 1;
-            best.n_rg = n_rg;
-            best.counters_bytes = ((size_t)BH * n_rg * sizeof(unsigned long long) + 255) / 256 * 256;
-            best.total_bytes = best.counters_bytes + ((size_t)BH * (S > 2 ? S : 2) * (size_t)(16 * (2 + D)) * sizeof(float) + 255) / 256 * 256;
-        }
-    }
+        return full * round(256) + (rest ? round(rest) : 0.0) + attn_merge_us(BH * n_act, n_part, part);
+    });
+    best.counters_bytes = ((size_t)BH * n_rg * sizeof(unsigned long long) + 255) / 256 * 256;
+    best.total_bytes = best.counters_bytes + ((size_t)BH * (best.S > 2 ? best.S : 2) * (size_t)(16 * (2 + D)) * sizeof(float) + 255) / 256 * 256;
     return best;
 }
 
@@ -211,6 +223,23 @@ __device__ __forceinline__ void store_out4(_Float16 *dst, float a, float b, floa
 
 // XCD this workgroup runs on (hardware register XCC_ID).
 __device__ __forceinline__ uint32_t xcc_id() { return __builtin_amdgcn_s_getreg((31 << 11) | 20) & 0xfu; }
+
+// max / sum over the four lanes l, l^16, l^32, l^48 (the four key groups of a score tile's column) with the gfx950
+// lane-swap instructions: each gives a lane the pair {x[l], x[l^k]}.
+__device__ __forceinline__ float quad_max(float x)
+{
+    auto a = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+    x = fmaxf(__uint_as_float(a[0]), __uint_as_float(a[1]));
+    auto b = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+    return fmaxf(__uint_as_float(b[0]), __uint_as_float(b[1]));
+}
+__device__ __forceinline__ float quad_sum(float x)
+{
+    auto a = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+    x = __uint_as_float(a[0]) + __uint_as_float(a[1]);
+    auto b = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+    return __uint_as_float(b[0]) + __uint_as_float(b[1]);
+}
 
 enum { kNotLast = 0, kLastClean = 1, kLastMixed = 2 };
 

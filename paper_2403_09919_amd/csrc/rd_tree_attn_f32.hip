@@ -20,40 +20,23 @@
 
 namespace rd {
 
-typedef __attribute__((ext_vector_type(4))) float f32x4;
-
 constexpr int kF32Waves = 8;
 
-__device__ __forceinline__ float quad_max_f32(float x)
-{
-    auto a = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
-    x = fmaxf(__uint_as_float(a[0]), __uint_as_float(a[1]));
-    auto b = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
-    return fmaxf(__uint_as_float(b[0]), __uint_as_float(b[1]));
-}
-__device__ __forceinline__ float quad_sum_f32(float x)
-{
-    auto a = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
-    x = __uint_as_float(a[0]) + __uint_as_float(a[1]);
-    auto b = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
-    return __uint_as_float(b[0]) + __uint_as_float(b[1]);
-}
-
-// NQ = row tiles (16 packed rows) per workgroup (one, as launched); more rows are row groups.
-template <int D, int NQ>
+// A workgroup takes one row tile (16 packed rows); more rows are row groups.
+template <int D>
 __global__ __launch_bounds__(kF32Waves * 64, 2) void rd_tree_attn_f32_kernel(AttnArgs a)
 {
     constexpr int NW = kF32Waves;
     constexpr int KC = D / 16;                                  // 16-byte pieces of a row per lane group
     constexpr int JJ = D / 64;                                  // 64-column pieces of the output
-    constexpr int kRows = NQ * 16;
-    constexpr int kUnits = NQ * JJ * 4;                         // output fragments: (row tile, jj, i), 64 lanes x 4 floats
-    constexpr int kUPW = (kUnits + NW - 1) / NW;                // ... finished by wave f mod NW
+    constexpr int kRows = 16;
+    constexpr int kUnits = JJ * 4;                              // output fragments: (jj, i), 64 lanes x 4 floats
+    static_assert(kUnits <= NW && KC <= NW, "a wave finishes one output fragment and brings in one of Q");
     constexpr int kPF = kRows * 2 + kUnits * 256;               // floats per partial: (m,l) per row, then the fragments
     constexpr int kMLStride = NW * 2 + 4;                       // floats per row of the waves' (m, l) table
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-    f32x4 *sQ = reinterpret_cast<f32x4 *>(smem);                // [NQ][KC][64 lanes]
-    f32x4 *sO = sQ + NQ * KC * 64;                              // [NW][kUnits][64 lanes]
+    f32x4 *sQ = reinterpret_cast<f32x4 *>(smem);                // [KC][64 lanes]
+    f32x4 *sO = sQ + KC * 64;                                   // [NW][kUnits][64 lanes]
     float *sML = reinterpret_cast<float *>(sO + NW * kUnits * 64);   // [kRows][NW] (m, l)
 
     const int tid = threadIdx.x;
@@ -102,18 +85,13 @@ __global__ __launch_bounds__(kF32Waves * 64, 2) void rd_tree_attn_f32_kernel(Att
     const uintptr_t Vn = reinterpret_cast<uintptr_t>(a.v_new) + (size_t)bh * a.N * D * 4 - Vc;
     typedef const __attribute__((address_space(1))) f32x4 gvec;
 
-    constexpr int kQFrags = NQ * KC, kQPer = (kQFrags + NW - 1) / NW;
-    f32x4 qreg[kQPer];
-#pragma unroll
-    for (int i = 0; i < kQPer; ++i) {
-        const int f = min(wave + NW * i, kQFrags - 1);
-        qreg[i] = *reinterpret_cast<const f32x4 *>(Qb + (size_t)min(f / KC * 16 + r16, Ng - 1) * D + (f % KC) * 16 + g * 4);
-    }
+    const int q_frag = min(wave, KC - 1);
+    const f32x4 qreg = *reinterpret_cast<const f32x4 *>(Qb + (size_t)min(r16, Ng - 1) * D + q_frag * 16 + g * 4);
 
     // K, V and visibility words of a tile.  A wave whose turn falls past the end takes the last tile again (masked), a
     // workgroup without tiles the first there is: no branch around the loads.  Rows past a tile's keys are its last key.
     f32x4 kreg[KC], vreg[4][JJ];
-    uint64_t mword[NQ];
+    uint64_t mword;
     auto fetch = [&](int tile, auto which_k, auto which_v) __attribute__((always_inline)) {
         const int tl = max(min(tile, tile_end - 1), 0);
         const bool tree = tl >= nA;
@@ -124,9 +102,7 @@ __global__ __launch_bounds__(kF32Waves * 64, 2) void rd_tree_attn_f32_kernel(Att
 #pragma unroll
             for (int c = 0; c < KC; ++c) kreg[c] = *(gvec *)(p + c * 64);
             const int word = tree ? min(first >> 6, a.words - 1) : 0;
-#pragma unroll
-            for (int qt = 0; qt < NQ; ++qt)
-                mword[qt] = a.mask_bits[((size_t)b * a.N + min(row0 + qt * 16 + r16, a.N - 1)) * a.words + word];
+            mword = a.mask_bits[((size_t)b * a.N + min(row0 + r16, a.N - 1)) * a.words + word];
         }
         if (decltype(which_v)::value) {
             const uintptr_t p = Vc + (tree ? Vn : 0) + (size_t)first * D * 4 + r16 * 16;
@@ -141,85 +117,60 @@ __global__ __launch_bounds__(kF32Waves * 64, 2) void rd_tree_attn_f32_kernel(Att
     const int t_first = tile_begin + wave;
     fetch(t_first, yes{}, yes{});
 
+    if (wave < KC) sQ[wave * 64 + lane] = r16 < P ? qreg : f32x4{0.f, 0.f, 0.f, 0.f};
+    float m_run = -INFINITY, l_run = 0.f;
+    f32x4 oacc[JJ][4];
 #pragma unroll
-    for (int i = 0; i < kQPer; ++i) {
-        const int f = wave + NW * i;
-        if (f < kQFrags) sQ[f * 64 + lane] = f / KC * 16 + r16 < P ? qreg[i] : f32x4{0.f, 0.f, 0.f, 0.f};
-    }
-    float m_run[NQ], l_run[NQ];
-    f32x4 oacc[NQ][JJ][4];
+    for (int jj = 0; jj < JJ; ++jj)
 #pragma unroll
-    for (int qt = 0; qt < NQ; ++qt) {
-        m_run[qt] = -INFINITY;
-        l_run[qt] = 0.f;
-#pragma unroll
-        for (int jj = 0; jj < JJ; ++jj)
-#pragma unroll
-            for (int e = 0; e < 4; ++e) oacc[qt][jj][e] = f32x4{0.f, 0.f, 0.f, 0.f};
-    }
+        for (int e = 0; e < 4; ++e) oacc[jj][e] = f32x4{0.f, 0.f, 0.f, 0.f};
     rd_lds_barrier();         // Q visible to all waves
 
     auto tile_step = [&](int tile, auto more) __attribute__((always_inline)) {
         const bool tree = tile >= nA;
         const int first = (tile - (tree ? nA : 0)) * 16;
         const int rem = (tree ? tree_end : C) - first;          // keys of the tile inside the range
-        f32x4 sacc[NQ];
-        uint32_t bits[NQ];
-#pragma unroll
-        for (int qt = 0; qt < NQ; ++qt) {
-            sacc[qt] = f32x4{0.f, 0.f, 0.f, 0.f};
-            const uint32_t vis = tree ? (uint32_t)(mword[qt] >> ((first & 63) + 4 * g)) & 0xfu : 0xfu;
-            const int left = rem - 4 * g;
-            const uint32_t tail = left >= 4 ? 0xfu : (left <= 0 ? 0u : (1u << left) - 1u);
-            bits[qt] = qt * 16 + r16 < P ? vis & tail : 0u;
-        }
+        const uint32_t vis = tree ? (uint32_t)(mword >> ((first & 63) + 4 * g)) & 0xfu : 0xfu;
+        const int left = rem - 4 * g;
+        const uint32_t tail = left >= 4 ? 0xfu : (left <= 0 ? 0u : (1u << left) - 1u);
+        const uint32_t bits = r16 < P ? vis & tail : 0u;
+        f32x4 sacc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int c = 0; c < KC; ++c) {
-            f32x4 q[NQ];
+            const f32x4 q = sQ[c * 64 + lane];
 #pragma unroll
-            for (int qt = 0; qt < NQ; ++qt) q[qt] = sQ[(qt * KC + c) * 64 + lane];
-#pragma unroll
-            for (int e = 0; e < 4; ++e)
-#pragma unroll
-                for (int qt = 0; qt < NQ; ++qt) sacc[qt] = __builtin_amdgcn_mfma_f32_16x16x4f32(kreg[c][e], q[qt][e], sacc[qt], 0, 0, 0);
+            for (int e = 0; e < 4; ++e) sacc = __builtin_amdgcn_mfma_f32_16x16x4f32(kreg[c][e], q[e], sacc, 0, 0, 0);
         }
         if (decltype(more)::value) fetch(tile + NW, yes{}, no{});
-        float p[NQ][4];
+        float s[4], p[4], mx = -INFINITY;
 #pragma unroll
-        for (int qt = 0; qt < NQ; ++qt) {
-            float s[4], mx = -INFINITY;
+        for (int i = 0; i < 4; ++i) {
+            s[i] = (bits >> i) & 1u ? sacc[i] * a.scale_log2e : -INFINITY;
+            mx = fmaxf(mx, s[i]);
+        }
+        const float m_new = fmaxf(m_run, quad_max(mx));
+        const float m_safe = m_new == -INFINITY ? 0.f : m_new;
+        const float alpha = __builtin_amdgcn_exp2f(m_run - m_safe);
+        m_run = m_new;
+        float sum = 0.f;
 #pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                s[i] = (bits[qt] >> i) & 1u ? sacc[qt][i] * a.scale_log2e : -INFINITY;
-                mx = fmaxf(mx, s[i]);
-            }
-            const float m_new = fmaxf(m_run[qt], quad_max_f32(mx));
-            const float m_safe = m_new == -INFINITY ? 0.f : m_new;
-            const float alpha = __builtin_amdgcn_exp2f(m_run[qt] - m_safe);
-            m_run[qt] = m_new;
-            float sum = 0.f;
+        for (int i = 0; i < 4; ++i) {
+            p[i] = __builtin_amdgcn_exp2f(s[i] - m_safe);
+            sum += p[i];
+        }
+        l_run = l_run * alpha + sum;
+        if (__builtin_amdgcn_ballot_w64(alpha != 1.0f) != 0) {
 #pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                p[qt][i] = __builtin_amdgcn_exp2f(s[i] - m_safe);
-                sum += p[qt][i];
-            }
-            l_run[qt] = l_run[qt] * alpha + sum;
-            if (__builtin_amdgcn_ballot_w64(alpha != 1.0f) != 0) {
+            for (int jj = 0; jj < JJ; ++jj)
 #pragma unroll
-                for (int jj = 0; jj < JJ; ++jj)
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) oacc[qt][jj][e] *= alpha;
-            }
+                for (int e = 0; e < 4; ++e) oacc[jj][e] *= alpha;
         }
 #pragma unroll
         for (int i = 0; i < 4; ++i)
 #pragma unroll
             for (int jj = 0; jj < JJ; ++jj)
 #pragma unroll
-                for (int e = 0; e < 4; ++e)
-#pragma unroll
-                    for (int qt = 0; qt < NQ; ++qt)
-                        oacc[qt][jj][e] = __builtin_amdgcn_mfma_f32_16x16x4f32(vreg[i][jj][e], p[qt][i], oacc[qt][jj][e], 0, 0, 0);
+                for (int e = 0; e < 4; ++e) oacc[jj][e] = __builtin_amdgcn_mfma_f32_16x16x4f32(vreg[i][jj][e], p[i], oacc[jj][e], 0, 0, 0);
         if (decltype(more)::value) fetch(tile + NW, no{}, yes{});
     };
     if (t_first < tile_end) {
@@ -228,140 +179,120 @@ __global__ __launch_bounds__(kF32Waves * 64, 2) void rd_tree_attn_f32_kernel(Att
         tile_step(tile, no{});
     }
 
-    // ---- the waves' states meet in LDS; fragment (qt, jj, i) holds, per lane, d = 64jj + 16g + 4i .. +3 of row r16
+    // ---- the waves' states meet in LDS; fragment (jj, i) holds, per lane, d = 64jj + 16g + 4i .. +3 of row r16
+    const float l_sum = quad_sum(l_run);
+    if (g == 0) *reinterpret_cast<float2 *>(sML + r16 * kMLStride + wave * 2) = make_float2(m_run, l_sum);
 #pragma unroll
-    for (int qt = 0; qt < NQ; ++qt) {
-        const float l = quad_sum_f32(l_run[qt]);
-        if (g == 0) *reinterpret_cast<float2 *>(sML + (qt * 16 + r16) * kMLStride + wave * 2) = make_float2(m_run[qt], l);
+    for (int jj = 0; jj < JJ; ++jj)
 #pragma unroll
-        for (int jj = 0; jj < JJ; ++jj)
-#pragma unroll
-            for (int i = 0; i < 4; ++i)
-                sO[(wave * kUnits + (qt * JJ + jj) * 4 + i) * 64 + lane] =
-                    f32x4{oacc[qt][jj][0][i], oacc[qt][jj][1][i], oacc[qt][jj][2][i], oacc[qt][jj][3][i]};
-    }
+        for (int i = 0; i < 4; ++i)
+            sO[(wave * kUnits + jj * 4 + i) * 64 + lane] = f32x4{oacc[jj][0][i], oacc[jj][1][i], oacc[jj][2][i], oacc[jj][3][i]};
     rd_lds_barrier();
     const int n_waves = clampi(tile_end - tile_begin, 1, NW);   // waves that had a tile
-    float fm[kUPW], fl[kUPW];
-    f32x4 fo[kUPW];
+    const int f = min(wave, kUnits - 1);                        // this wave's fragment of the output
+    f32x4 ml[NW / 2];
 #pragma unroll
-    for (int i = 0; i < kUPW; ++i) {
-        const int f = min(wave + NW * i, kUnits - 1), row = f / (JJ * 4) * 16 + r16;
-        f32x4 ml[NW / 2];
+    for (int w = 0; w < NW / 2; ++w) ml[w] = *reinterpret_cast<const f32x4 *>(sML + r16 * kMLStride + w * 4);
+    float fm = -INFINITY, fl = 0.f;
 #pragma unroll
-        for (int w = 0; w < NW / 2; ++w) ml[w] = *reinterpret_cast<const f32x4 *>(sML + row * kMLStride + w * 4);
-        float m = -INFINITY;
+    for (int w = 0; w < NW; ++w) fm = fmaxf(fm, ml[w / 2][2 * (w & 1)]);
+    const float ms = fm == -INFINITY ? 0.f : fm;
+    f32x4 fo = {0.f, 0.f, 0.f, 0.f};
+    auto add = [&](int w) __attribute__((always_inline)) {
+        const float s = __builtin_amdgcn_exp2f(ml[w / 2][2 * (w & 1)] - ms);
+        fl += s * ml[w / 2][2 * (w & 1) + 1];
+        fo += s * sO[(w * kUnits + f) * 64 + lane];
+    };
 #pragma unroll
-        for (int w = 0; w < NW; ++w) m = fmaxf(m, ml[w / 2][2 * (w & 1)]);
-        const float ms = m == -INFINITY ? 0.f : m;
-        f32x4 o = {0.f, 0.f, 0.f, 0.f};
-        float l = 0.f;
-        auto add = [&](int w) __attribute__((always_inline)) {
-            const float s = __builtin_amdgcn_exp2f(ml[w / 2][2 * (w & 1)] - ms);
-            l += s * ml[w / 2][2 * (w & 1) + 1];
-            o += s * sO[(w * kUnits + f) * 64 + lane];
-        };
+    for (int w = 0; w < NW / 2; ++w) add(w);
+    if (n_waves > NW / 2) {
 #pragma unroll
-        for (int w = 0; w < NW / 2; ++w) add(w);
-        if (n_waves > NW / 2) {
-#pragma unroll
-            for (int w = NW / 2; w < NW; ++w) add(w);
-        }
-        fm[i] = m; fl[i] = l; fo[i] = o;
+        for (int w = NW / 2; w < NW; ++w) add(w);
     }
 
     float *outp = static_cast<float *>(a.out) + ((size_t)bh * a.N + row0) * D;
-    auto put = [&](int i, f32x4 o, float l) __attribute__((always_inline)) {
-        const int f = wave + NW * i, row = f / (JJ * 4) * 16 + r16;
-        if (f < kUnits && row < Ng) {
-            const float inv = row < P ? 1.0f / l : 0.f;         // rows beyond the packed count are zero
+    auto put = [&](f32x4 o, float l) __attribute__((always_inline)) {
+        if (wave < kUnits && r16 < Ng) {
+            const float inv = r16 < P ? 1.0f / l : 0.f;         // rows beyond the packed count are zero
             f32x4 y = o * inv;
-            if (row >= P) y = f32x4{0.f, 0.f, 0.f, 0.f};
-            *reinterpret_cast<f32x4 *>(outp + (size_t)row * D + (f / 4 % JJ) * 64 + g * 16 + (f & 3) * 4) = y;
+            if (r16 >= P) y = f32x4{0.f, 0.f, 0.f, 0.f};
+            *reinterpret_cast<f32x4 *>(outp + (size_t)r16 * D + (f / 4) * 64 + g * 16 + (f & 3) * 4) = y;
         }
     };
     if (n_part == 1) {
-#pragma unroll
-        for (int i = 0; i < kUPW; ++i) put(i, fo[i], fl[i]);
+        put(fo, fl);
         return;
     }
     // ---- partial state -> workspace; the last workgroup of this head (and row group) merges
     const size_t unit = (size_t)bh * a.n_rg + rg;
     float *part = a.partials + ((size_t)bh * a.S + split * n_act + rg) * kPF;
-#pragma unroll
-    for (int i = 0; i < kUPW; ++i) {
-        const int f = wave + NW * i, row = f / (JJ * 4) * 16 + r16;
-        if (f < kUnits && row < P) {
-            if (f % (JJ * 4) == 0 && g == 0) st_dev2(part + 2 * row, fm[i], fl[i]);
-            st_dev4(part + 2 * kRows + f * 256 + lane * 4, fo[i][0], fo[i][1], fo[i][2], fo[i][3]);
-        }
+    const bool real = wave < kUnits && r16 < P;
+    if (real) {
+        if (f == 0 && g == 0) st_dev2(part + 2 * r16, fm, fl);
+        st_dev4(part + 2 * kRows + f * 256 + lane * 4, fo[0], fo[1], fo[2], fo[3]);
     }
     const int last = arrive_is_last(a.counters + unit, (uint32_t)n_part);
     if (last == kNotLast) return;
     const bool cached = last == kLastClean;
     constexpr int kChunk = 8;                                   // partials whose loads are in flight together
     const float *hp = a.partials + ((size_t)bh * a.S + rg) * kPF;
-#pragma unroll
-    for (int i = 0; i < kUPW; ++i) {
-        const int f = wave + NW * i, row = f / (JJ * 4) * 16 + r16;
-        float M = -INFINITY, den = 0.f;
-        f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+    float M = -INFINITY, den = 0.f;
+    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll 1
-        for (int s0 = 0; s0 < n_part; s0 += kChunk) {
-            float2 ml[kChunk];
-            f32x4 fr[kChunk];
+    for (int s0 = 0; s0 < n_part; s0 += kChunk) {
+        float2 pml[kChunk];
+        f32x4 pfr[kChunk];
 #pragma unroll
-            for (int c = 0; c < kChunk; ++c) {
-                ml[c] = make_float2(-INFINITY, 0.f);            // absent: weight 2^-inf = 0
-                fr[c] = f32x4{0.f, 0.f, 0.f, 0.f};
-                if (s0 + c < n_part && f < kUnits && row < P) {
-                    const float *ps = hp + (size_t)(s0 + c) * n_act * kPF, *pf = ps + 2 * kRows + f * 256 + lane * 4;
-                    if (cached) {
-                        ml[c] = *reinterpret_cast<const float2 *>(ps + 2 * row);
-                        fr[c] = *reinterpret_cast<const f32x4 *>(pf);
-                    } else {
-                        ml[c] = ld_dev2(ps + 2 * row);
-                        const float2 lo = ld_dev2(pf), hi = ld_dev2(pf + 2);
-                        fr[c] = f32x4{lo.x, lo.y, hi.x, hi.y};
-                    }
+        for (int c = 0; c < kChunk; ++c) {
+            pml[c] = make_float2(-INFINITY, 0.f);               // absent: weight 2^-inf = 0
+            pfr[c] = f32x4{0.f, 0.f, 0.f, 0.f};
+            if (s0 + c < n_part && real) {
+                const float *ps = hp + (size_t)(s0 + c) * n_act * kPF, *pf = ps + 2 * kRows + f * 256 + lane * 4;
+                if (cached) {
+                    pml[c] = *reinterpret_cast<const float2 *>(ps + 2 * r16);
+                    pfr[c] = *reinterpret_cast<const f32x4 *>(pf);
+                } else {
+                    pml[c] = ld_dev2(ps + 2 * r16);
+                    const float2 lo = ld_dev2(pf), hi = ld_dev2(pf + 2);
+                    pfr[c] = f32x4{lo.x, lo.y, hi.x, hi.y};
                 }
             }
-            float Mn = M;
-#pragma unroll
-            for (int c = 0; c < kChunk; ++c) Mn = fmaxf(Mn, ml[c].x);
-            const float Ms = Mn == -INFINITY ? 0.f : Mn, resc = __builtin_amdgcn_exp2f(M - Ms);
-            den *= resc;
-            acc *= resc;
-#pragma unroll
-            for (int c = 0; c < kChunk; ++c) {
-                const float w = __builtin_amdgcn_exp2f(ml[c].x - Ms);
-                den += w * ml[c].y;
-                acc += w * fr[c];
-            }
-            M = Mn;
         }
-        put(i, acc, den);
+        float Mn = M;
+#pragma unroll
+        for (int c = 0; c < kChunk; ++c) Mn = fmaxf(Mn, pml[c].x);
+        const float Ms = Mn == -INFINITY ? 0.f : Mn, resc = __builtin_amdgcn_exp2f(M - Ms);
+        den *= resc;
+        acc *= resc;
+#pragma unroll
+        for (int c = 0; c < kChunk; ++c) {
+            const float w = __builtin_amdgcn_exp2f(pml[c].x - Ms);
+            den += w * pml[c].y;
+            acc += w * pfr[c];
+        }
+        M = Mn;
     }
+    put(acc, den);
     if (tid == 0) a.counters[unit] = 0;       // leave the workspace ready for the next call
 }
 
-template <int D, int NQ>
+template <int D>
 static int launch_f32(const AttnArgs &a, hipStream_t stream)
 {
-    constexpr size_t smem = (size_t)NQ * (D / 16) * 1024 + (size_t)kF32Waves * NQ * (D / 16) * 1024 + (size_t)NQ * 16 * (kF32Waves * 2 + 4) * sizeof(float);
+    constexpr size_t smem = (size_t)(D / 16) * 1024 + (size_t)kF32Waves * (D / 16) * 1024 + (size_t)16 * (kF32Waves * 2 + 4) * sizeof(float);
     static_assert(smem <= 160 * 1024, "LDS of a compute unit");
     static std::atomic<unsigned long long> configured{0};
-    const int st = ensure_dynamic_lds(reinterpret_cast<const void *>(&rd_tree_attn_f32_kernel<D, NQ>), smem, configured);
+    const int st = ensure_dynamic_lds(reinterpret_cast<const void *>(&rd_tree_attn_f32_kernel<D>), smem, configured);
     if (st != RD_OK) return st;
     const size_t wgs = ((size_t)a.B * a.H + 7) / 8 * 8 * a.S;
     if (wgs > 0x7fffffffull) return RD_ERR_UNSUPPORTED;
-    hipLaunchKernelGGL((rd_tree_attn_f32_kernel<D, NQ>), dim3((unsigned)wgs), dim3(kF32Waves * 64), smem, stream, a);
+    hipLaunchKernelGGL((rd_tree_attn_f32_kernel<D>), dim3((unsigned)wgs), dim3(kF32Waves * 64), smem, stream, a);
     return rd_check_launch();
 }
 
 int tree_attn_f32(const AttnArgs &a, int D, hipStream_t stream)
 {
-    return D == 128 ? launch_f32<128, 1>(a, stream) : launch_f32<64, 1>(a, stream);
+    return D == 128 ? launch_f32<128>(a, stream) : launch_f32<64>(a, stream);
 }
 
 }  // namespace rd

@@ -30,19 +30,17 @@ extern __device__ unsigned long long *rd_trace_buf;     // defined by the includ
 
 namespace rd {
 
-typedef __attribute__((ext_vector_type(4))) float f32x4;
-typedef f32x4 f32x4_t;
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
 typedef __attribute__((ext_vector_type(8))) _Float16 f16x8;
 // 16-bit element types of the MFMA kernels: eight-element operand vector and the matrix instruction
 template <typename T> struct Elem;
 template <> struct Elem<__bf16> {
     typedef bf16x8 vec8;
-    static __device__ __forceinline__ f32x4_t mfma(vec8 a, vec8 b, f32x4_t c) { return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0); }
+    static __device__ __forceinline__ f32x4 mfma(vec8 a, vec8 b, f32x4 c) { return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0); }
 };
 template <> struct Elem<_Float16> {
     typedef f16x8 vec8;
-    static __device__ __forceinline__ f32x4_t mfma(vec8 a, vec8 b, f32x4_t c) { return __builtin_amdgcn_mfma_f32_16x16x32_f16(a, b, c, 0, 0, 0); }
+    static __device__ __forceinline__ f32x4 mfma(vec8 a, vec8 b, f32x4 c) { return __builtin_amdgcn_mfma_f32_16x16x32_f16(a, b, c, 0, 0, 0); }
 };
 typedef __attribute__((ext_vector_type(4))) short s16x4;
 typedef __attribute__((ext_vector_type(8))) short s16x8;
@@ -85,23 +83,6 @@ __device__ __forceinline__ void wave_lds_sync()
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
-}
-
-// max / sum over the four lanes l, l^16, l^32, l^48 (the four 8-key groups of a score tile
-// column) with the gfx950 lane-swap instructions: each gives a lane the pair {x[l], x[l^k]}.
-__device__ __forceinline__ float quad_max(float x)
-{
-    auto a = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
-    x = fmaxf(__uint_as_float(a[0]), __uint_as_float(a[1]));
-    auto b = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
-    return fmaxf(__uint_as_float(b[0]), __uint_as_float(b[1]));
-}
-__device__ __forceinline__ float quad_sum(float x)
-{
-    auto a = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
-    x = __uint_as_float(a[0]) + __uint_as_float(a[1]);
-    auto b = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
-    return __uint_as_float(b[0]) + __uint_as_float(b[1]);
 }
 
 // Rotary embedding of eight elements ("rotate half": element i pairs with element i + D/2), in the
@@ -703,6 +684,7 @@ __global__ __launch_bounds__(NW * 64, 2) void rd_tree_attn_mfma_kernel(AttnArgs 
     RD_TR(5);
     if (last == kNotLast) return;
     const bool cached = (last == kLastClean);
+    // (the fp32 kernel merges alike, but as a function of both this moves registers about and costs 1 % at five row tiles)
     constexpr int kChunk = 6;                                   // partials whose loads are in flight together
     constexpr int kPair = QWA < 2 || JW > 1 ? 1 : 2;                       // row tiles merged together
     const float *hp = a.partials + ((size_t)bh * a.S + rg) * kPF;
