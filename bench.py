@@ -25,8 +25,10 @@ from __future__ import annotations
 
 import argparse
 import dataclasses
+import hashlib
 import json
 import os
+import re
 import sys
 import time
 
@@ -38,6 +40,7 @@ if ROOT not in sys.path:
 
 HBM_PEAK_GBS = 8000.0
 TRAFFIC_TABLE = os.path.join(ROOT, "profiles", "rd_tree_attn_hbm_traffic.md")
+ATTENTION_SOURCES = tuple(os.path.join(ROOT, "paper_2403_09919_amd", "csrc", f) for f in ("rd_tree_attn_mfma.h", "rd_attn_common.h"))
 LAYERS_BY_HEADS = {32: 32, 40: 40, 52: 60}      # decoder layers of the 7B / 13B / 33B models the shapes come from
 FLUSH_BYTES = 1 << 30                           # larger than the 256 MB infinity cache plus every L2
 
@@ -64,19 +67,32 @@ def parse():
     return ap.parse_args()
 
 
-def read_traffic_table():
+def attention_digest(paths=ATTENTION_SOURCES):
+    """Digest of the attention kernel's code and launch plan, without comments and layout."""
+    h = hashlib.sha256()
+    for p in paths:
+        with open(p) as f:
+            h.update("".join(re.sub(r"//[^\n]*", "", f.read()).split()).encode())
+    return h.hexdigest()[:16]
+
+
+def read_traffic_table(path=TRAFFIC_TABLE, digest=None):
     """HBM bytes per rd_tree_attn launch by configuration, from the committed counter summary
-    (rows `| config | FETCH_SIZE | WRITE_SIZE | fetch scale | write scale | bytes |`)."""
-    out = {}
+    (rows `| config | FETCH_SIZE | WRITE_SIZE | fetch scale | write scale | bytes |`).  Empty (the JSON line then says
+    null) unless the summary was measured on this very kernel and plan, which its `sources:` line names."""
+    digest = digest or attention_digest()
+    out, current = {}, False
     try:
-        with open(TRAFFIC_TABLE) as f:
+        with open(path) as f:
             for line in f:
+                if line.startswith("sources:"):
+                    current = line.split()[1] == digest
                 cells = [c.strip() for c in line.strip().strip("|").split("|")]
                 if len(cells) >= 6 and cells[0].isdigit():
                     out[int(cells[0])] = int(float(cells[5]))
     except OSError:
         pass
-    return out
+    return out if current else {}
 
 
 class Workload:

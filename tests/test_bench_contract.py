@@ -27,3 +27,20 @@ def test_product_code_does_not_import_the_oracle():
     top_level = [l for l in bench.splitlines() if re.match(r"(import|from)\s+oracle\b", l)]
     assert top_level == []                              # only inside cpu_baseline()
     assert re.search(r"def cpu_baseline\(.*?\n(.*\n)*?\s+import oracle", bench)
+
+
+def test_traffic_is_reported_only_for_the_kernel_it_was_measured_on(tmp_path):
+    """The counter summary names the sources it was measured on; with other sources its figures are not reported."""
+    import bench
+    src = tmp_path / "kernel.h"
+    src.write_text("int a = 1; // one\n")
+    measured = bench.attention_digest([src])
+    table = tmp_path / "table.md"
+    table.write_text("sources: %s\n| 2 | 1.0 | 2.0 | 1 | 1 | 4096 |\n" % measured)
+    assert bench.read_traffic_table(table, measured) == {2: 4096}
+    src.write_text("int a =\n  1; // another comment\n")
+    assert bench.read_traffic_table(table, bench.attention_digest([src])) == {2: 4096}
+    src.write_text("int a = 2; // one\n")
+    assert bench.read_traffic_table(table, bench.attention_digest([src])) == {}
+    table.write_text("| 2 | 1.0 | 2.0 | 1 | 1 | 4096 |\n")
+    assert bench.read_traffic_table(table, measured) == {}
