@@ -19,7 +19,7 @@ Beside the headline figures the JSON line carries a `configs` block with the att
 HBM peak, the plain streaming-read floor of the same bytes, the step time and the CPU oracle's rate
 for each of the five synthetic configurations.
 
-Prints one JSON line (see README for the fields).
+Prints one JSON line.
 """
 from __future__ import annotations
 

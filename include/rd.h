@@ -399,7 +399,7 @@ int rd_commit_paged(const void *k_new, const void *v_new, const int32_t *accepte
  * initial contents required, not shared by concurrent calls.
  * Limits: Dm a multiple of 64; W <= 128, W <= V; B*W <= 512; V <= 262144; L <= 384.
  * The call enqueues at most 4 + n_mlp launches per drafted position (5 + n_mlp after the first; one
- * fewer for W <= 8 and V <= 32768) while B*W <= 128; every further 128 rows add one launch per linear layer.
+ * fewer for W <= 8 and V <= 32768) while B*W <= 128; every further 128 rows add at most one launch per linear layer.
  */
 typedef struct {
     const void *emb, *rnn_u, *rnn_w;

@@ -1,7 +1,7 @@
 // rd_dedup: dynamic tree attention construction (Sec. 3.3, App. A.1) for gfx950.
 //
-// One workgroup per sequence (more where the dense mask is asked for), everything in LDS, data-parallel phases separated by barriers
-// (the whole input is a few hundred bytes; what costs time is dependent latency, so no phase
+// One workgroup per sequence (more where the dense mask is asked for), everything in LDS, data-parallel phases
+// separated by barriers (the whole input is a few hundred bytes; what costs time is dependent latency, so no phase
 // is a serial walk over positions):
 //   A  stage the W x L candidates; owner[i][j] = i.
 //   B  one thread per ordered pair (i, k < i): walk their common prefix and lower owner[i][j]
@@ -22,8 +22,13 @@ RD_TRACE_DEFINE(rd_debug_set_trace_dedup)
 namespace {
 
 constexpr int kDedupThreads = 384;                 // the fewest: one thread per token
-constexpr int kWideThreads = 1024;                 // more than 16 candidates: their pairs are what takes time (9.0 us at 70 with 384)
-constexpr int kMaskRows = 32;                      // rows of the dense mask per workgroup
+// More than 16 candidates: their pairs are what takes time (us, 384 / 1024 threads: 16 candidates 3.82 / 3.86, 20 4.34 / 3.90,
+// 30 5.20 / 4.38, 70 12.8 / 8.8).
+constexpr int kWideThreads = 1024;
+// Rows of the dense mask per workgroup (us, all rows in one / 32 / 16: N = 40 3.95 / 3.82 / 3.83; N = 80, 16 sequences 4.94 /
+// 4.56 / 4.42; N = 150 8.6 / 5.4 / 5.0; N = 350 31.8 / 10.9 / 9.9).  Every workgroup repeats the construction, so fewer rows cost
+// where there are more workgroups than compute units: 24 sequences of N = 350 take 34.3 / 19.3 / 23.3 (14.2 with 48 rows).
+constexpr int kMaskRows = 32;
 constexpr int kMaskWords = (RD_MAX_N + 63) / 64;
 
 __global__ __launch_bounds__(kWideThreads) void rd_dedup_kernel(
@@ -40,8 +45,8 @@ __global__ __launch_bounds__(kWideThreads) void rd_dedup_kernel(
     __shared__ uint64_t s_bits[RD_MAX_N][kMaskWords];   // mask row of each packed slot
     __shared__ int s_P;
 
-    // The dense mask, N bytes per row, is too much for one compute unit (28 us at N = 350): further workgroups of the
-    // sequence repeat the phases and write kMaskRows rows of it each.
+    // The dense mask, N bytes per row, is too much for one compute unit: further workgroups of the sequence repeat the
+    // phases and write kMaskRows rows of it each.
     const int b = blockIdx.x, slice = blockIdx.y;
     const bool main_wg = slice == 0;
     const int tid = threadIdx.x, threads = blockDim.x;

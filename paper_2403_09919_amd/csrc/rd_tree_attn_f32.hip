@@ -44,7 +44,8 @@ __global__ __launch_bounds__(kF32Waves * 64, 2) void rd_tree_attn_f32_kernel(Att
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int r16 = lane & 15, g = lane >> 4;
 
-    // which (sequence, head) -- all workgroups of one on one XCD -- and which of its a.S workgroups
+    // which (sequence, head) -- all workgroups of one on one XCD (10 heads, C=3000: 18.7 us, spread over all 19.4; 5 heads,
+    // C=6000: 19.9 and 20.7) -- and which of its a.S workgroups
     const int k = (int)(blockIdx.x >> 3);
     const int hl = a.S == 1 ? k : k / a.S;
     const int r_wg = k - hl * a.S;

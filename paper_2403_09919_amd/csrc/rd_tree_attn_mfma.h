@@ -11,15 +11,17 @@
 //     column per lane) comes from the row-major V tiles by transpose reads.
 // The next block's K and V are in flight meanwhile.
 //
-// What bounds it.  Long contexts in large batches: HBM (38.6 us for 201 MB of K and V at B=8, H=32, C=1536, 5.2 TB/s).
+// What bounds it.  Long contexts in large batches: HBM (43.5 us for 201 MB of K and V at B=8, H=32, C=1536, 4.6 TB/s).
 // Everything else: latency -- loads in operand order (see stage_k), and per block the LDS traffic, the vector
 // arithmetic of the softmax and the matrix products, which two waves per SIMD in step overlap badly.  Hence: one
 // barrier where the data is ready and one where it is free, no exchange of maxima in between (kSlack); tiles of the
 // context and of the tree in one sequence, so that a short context and its tree are one block and one workgroup;
 // no more workgroups per head than the lengths at hand need (n_part).  Against the kernel it replaced, whose waves
 // met at three barriers per block and whose packed keys were a workgroup of their own at short contexts, us per
-// launch: H=8, C=87, 20 packed rows 9.4 -> 5.3; B=11, H=40, C=180 31.2 -> 13.1; B=20, H=26, C=300, D=64 29.3 -> 19.3;
-// B=6, H=40, C=700, 96 packed rows 56.6 -> 36.8; B=8, H=32, C=1536 41.9 -> 39.2; B=16, H=52, C=2048 190 -> 190.
+// launch, K and V from memory: H=8, C=87, 20 packed rows 9.3 -> 5.4; B=11, H=40, C=180 36.0 -> 16.1; B=20, H=26, C=300,
+// D=64 21.4 -> 16.7; H=32, C=1024 12.7 -> 12.1; H=32, C=1777, 147 rows 33.9 -> 30.0; B=8, H=32, C=1536 45.8 -> 43.5;
+// B=4, H=40, C=4096, 27 to 38 rows of 80 76.4 -> 74.4; nothing at B=6, H=40, C=700, 83 to 130 rows (53.9 -> 53.4) and
+// B=16, H=52, C=2048 (182.6 -> 183.3).
 #pragma once
 #include "rd_attn_common.h"
 #include <type_traits>
@@ -161,7 +163,10 @@ __global__ __launch_bounds__(NW * 64, 2) void rd_tree_attn_mfma_kernel(AttnArgs 
 
     // ---- which (sequence, head), which of its a.S workgroups.  Workgroups are dealt round-robin to the 8 XCDs; all of
     // a head's go to one of them, whose L2 then serves Q, K/V shared by row groups and the partial results (merging
-    // partials past the L2 takes about twice as long).  Head numbers past the end fill up the last eight.
+    // partials past the L2 takes about twice as long).  Head numbers past the end fill up the last eight.  So too with
+    // fewer than eight heads, which leaves XCDs idle: spread over all of them, 30 of 31 shapes are slower (us, on one
+    // XCD / spread: 1 head, C=32000 32.0 / 33.5; 4 heads, C=8000 18.7 / 20.1; 5 heads, C=16000 24.4 / 26.2; 12 heads, C=4000
+    // 17.1 / 17.4; 26 heads, C=6000 27.0 / 28.1), the one being 10 heads, C=6000 and 350 tokens (38.7 / 33.1).
     const int k = (int)(blockIdx.x >> 3);
     const int hl = a.S == 1 ? k : k / a.S;
     const int r_wg = k - hl * a.S;

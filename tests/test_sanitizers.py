@@ -1,5 +1,5 @@
-"""Host code under AddressSanitizer and UndefinedBehaviorSanitizer (CPU only; GPU code cannot be
-sanitized on the test machines):
+"""Host code under AddressSanitizer and UndefinedBehaviorSanitizer (CPU only; GPU code is not run
+under a sanitizer):
   * the oracle (oracle/rd_oracle.c, gcc -fsanitize=address,undefined) runs its own pins;
   * the library's host code -- argument checks, launch plans, workspace sizing -- (host pass only,
     clang -fsanitize=address,undefined) runs the C ABI's argument-error cases, none of which launches.
