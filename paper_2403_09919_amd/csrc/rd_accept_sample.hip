@@ -39,23 +39,15 @@ constexpr int kMaxSelChunks = 256;           // V <= 1 Mi entries
 static_assert(kSelChunk == kLseChunk, "launch 2 takes the chunk totals of p from launch 1's partials");
 
 // Entries v .. v+3 of a row, -inf past the end (weight 0, neutral for the maximum).  VEC: rows of four entries and
-// more, 16-byte loads; else scalar loads.
-template <bool VEC>
+// more, 16-byte loads, in their places if ORDERED; else scalar loads.
+template <bool VEC, bool ORDERED>
 __device__ __forceinline__ float4 load4(const float *row, int v, int V)
 {
     if constexpr (VEC) {
-        return rd::row4(row, v, V);
+        return ORDERED ? rd::row4(row, v, V) : rd::row4_set(row, v, V);
     } else {
-        float4 r;
-        r.x = row[min(v, V - 1)];
-        r.y = row[min(v + 1, V - 1)];
-        r.z = row[min(v + 2, V - 1)];
-        r.w = row[min(v + 3, V - 1)];
-        if (v >= V) r.x = -INFINITY;
-        if (v + 1 >= V) r.y = -INFINITY;
-        if (v + 2 >= V) r.z = -INFINITY;
-        if (v + 3 >= V) r.w = -INFINITY;
-        return r;
+        const float x = row[min(v, V - 1)], y = row[min(v + 1, V - 1)], z = row[min(v + 2, V - 1)], w = row[min(v + 3, V - 1)];
+        return make_float4(v < V ? x : -INFINITY, v + 1 < V ? y : -INFINITY, v + 2 < V ? z : -INFINITY, v + 3 < V ? w : -INFINITY);
     }
 }
 
@@ -121,7 +113,7 @@ __global__ __launch_bounds__(kLseThreads) void rd_lse_chunk_kernel(
     const int v0 = chunk * kLseChunk;
     float4 xp[4], xq[4];
 #pragma unroll
-    for (int u = 0; u < 4; ++u) xp[u] = load4<VEC>(zp, v0 + (u * kLseThreads + tid) * 4, V);
+    for (int u = 0; u < 4; ++u) xp[u] = load4<VEC, false>(zp, v0 + (u * kLseThreads + tid) * 4, V);
     int owner = 0x7fffffff;
 #pragma unroll
     for (int i = kWaveScan - 1; i >= 0; --i) {
@@ -139,7 +131,7 @@ __global__ __launch_bounds__(kLseThreads) void rd_lse_chunk_kernel(
     if (draft) {
         const float *zq = draft_row_ptr(draft_logits, step_row, rows_per_step, b, ow, oj, p, W, L, V);
 #pragma unroll
-        for (int u = 0; u < 4; ++u) xq[u] = load4<VEC>(zq, v0 + (u * kLseThreads + tid) * 4, V);
+        for (int u = 0; u < 4; ++u) xq[u] = load4<VEC, false>(zq, v0 + (u * kLseThreads + tid) * 4, V);
     }
     float2 a = wave_max_sum(xp, inv_t), c = make_float2(0.f, 1.f / kWaves);
     if (draft) c = wave_max_sum(xq, 1.0f);
@@ -199,9 +191,9 @@ __device__ __forceinline__ float chunk_weights(const float *zp, const float *zq,
     const float *zr = residual ? zq : zp;                   // no draft row to read when drawing from p (value unused)
     float4 a[kSelPer / 4], q[kSelPer / 4];
 #pragma unroll
-    for (int i = 0; i < kSelPer / 4; ++i) a[i] = load4<VEC>(zp, v0 + 4 * i, V);
+    for (int i = 0; i < kSelPer / 4; ++i) a[i] = load4<VEC, true>(zp, v0 + 4 * i, V);
 #pragma unroll
-    for (int i = 0; i < kSelPer / 4; ++i) q[i] = load4<VEC>(zr, v0 + 4 * i, V);
+    for (int i = 0; i < kSelPer / 4; ++i) q[i] = load4<VEC, true>(zr, v0 + 4 * i, V);
     float sum = 0.f;
 #pragma unroll
     for (int i = 0; i < kSelPer / 4; ++i) {

@@ -110,17 +110,31 @@ __device__ __forceinline__ void wait_dev_stores() { asm volatile("s_waitcnt vmcn
 // Rows of V floats start at multiples of 4 bytes only, unless V is a multiple of 4; global memory instructions of any
 // width need no more.  (Scalar loads for such rows cost a vocabulary-wide pass two to three times its time.)
 typedef float f4_any __attribute__((ext_vector_type(4), aligned(4)));
-// Entries v .. v+3 of a row of n >= 4, -inf past the end.  No branch: a load inside a branch makes the compiler wait
-// for every load in flight at the join.  Addresses past the end are pulled back and the values moved.
+// Past a row's end addresses are pulled back.  No branches: an `if` on what was loaded becomes one here, which waits for
+// every load in flight, load after load, in the workgroup that holds the row's end.
+// Four entries from v on or, at the end of the row (n >= 4), its last four; *at: the first one's index.
+__device__ __forceinline__ float4 row4_at(const float *row, int v, int n, int *at)
+{
+    const int a = *at = min(v, n - 4);
+    const f4_any q = *reinterpret_cast<const f4_any *>(row + a);
+    return make_float4(q[0], q[1], q[2], q[3]);
+}
+// The entries v .. v+3 that exist, -inf in place of the others; in any order.
+__device__ __forceinline__ float4 row4_set(const float *row, int v, int n)
+{
+    int a;
+    const float4 q = row4_at(row, v, n, &a);
+    return make_float4(a < v ? -INFINITY : q.x, a + 1 < v ? -INFINITY : q.y, a + 2 < v ? -INFINITY : q.z, a + 3 < v ? -INFINITY : q.w);
+}
+// Entries v .. v+3, -inf past the end.
 __device__ __forceinline__ float4 row4(const float *row, int v, int n)
 {
-    const int a = min(v, n - 4), d = v - a;
-    const f4_any q = *reinterpret_cast<const f4_any *>(row + a);
-    float4 r = make_float4(q[0], q[1], q[2], q[3]);
-    if (d & 1) r = make_float4(r.y, r.z, r.w, -INFINITY);
-    if (d & 2) r = make_float4(r.z, r.w, -INFINITY, -INFINITY);
-    if (d > 3) r = make_float4(-INFINITY, -INFINITY, -INFINITY, -INFINITY);
-    return r;
+    int a;
+    const float4 q = row4_at(row, v, n, &a);
+    const int d = v - a;
+    const bool one = d & 1, two = d & 2, all = d > 3;
+    const float x = one ? q.y : q.x, y = one ? q.z : q.y, z = one ? q.w : q.z, w = one ? -INFINITY : q.w;
+    return make_float4(all ? -INFINITY : (two ? z : x), all ? -INFINITY : (two ? w : y), all || two ? -INFINITY : z, all || two ? -INFINITY : w);
 }
 
 // ---- reductions over the 64 lanes, the same value in every lane --------------------------------------
