@@ -144,16 +144,37 @@ template <int kCtrl> __device__ __forceinline__ float dpp(float x)
 {
     return __uint_as_float((uint32_t)__builtin_amdgcn_update_dpp((int)__float_as_uint(x), (int)__float_as_uint(x), kCtrl, 0xf, 0xf, false));
 }
+// K values at once, over aligned groups of `lanes` lanes, a power of two that is the same in the whole wave.
+template <int K, typename Op> __device__ __forceinline__ void group_reduce(float (&x)[K], int lanes, Op op)
+{
+    auto each = [&](auto other) __attribute__((always_inline)) {
+#pragma unroll
+        for (int k = 0; k < K; ++k) x[k] = op(x[k], other(x[k]));
+    };
+    if (lanes > 1) each([](float a) __attribute__((always_inline)) { return dpp<0xB1>(a); });      // quad_perm [1,0,3,2]: lane ^ 1
+    if (lanes > 2) each([](float a) __attribute__((always_inline)) { return dpp<0x4E>(a); });      // quad_perm [2,3,0,1]: lane ^ 2
+    if (lanes > 4) each([](float a) __attribute__((always_inline)) { return dpp<0x141>(a); });     // row_half_mirror: the other quad of the 8
+    if (lanes > 8) each([](float a) __attribute__((always_inline)) { return dpp<0x140>(a); });     // row_mirror: the other half of the 16
+    if (lanes > 16) {
+#pragma unroll
+        for (int k = 0; k < K; ++k) {
+            auto a = __builtin_amdgcn_permlane16_swap(__float_as_uint(x[k]), __float_as_uint(x[k]), false, false);
+            x[k] = op(__uint_as_float(a[0]), __uint_as_float(a[1]));
+        }
+    }
+    if (lanes > 32) {
+#pragma unroll
+        for (int k = 0; k < K; ++k) {
+            auto a = __builtin_amdgcn_permlane32_swap(__float_as_uint(x[k]), __float_as_uint(x[k]), false, false);
+            x[k] = op(__uint_as_float(a[0]), __uint_as_float(a[1]));
+        }
+    }
+}
 template <typename Op> __device__ __forceinline__ float wave_reduce(float x, Op op)
 {
-    x = op(x, dpp<0xB1>(x));            // quad_perm [1,0,3,2]: lane ^ 1
-    x = op(x, dpp<0x4E>(x));            // quad_perm [2,3,0,1]: lane ^ 2
-    x = op(x, dpp<0x141>(x));           // row_half_mirror: the other quad of the 8
-    x = op(x, dpp<0x140>(x));           // row_mirror: the other half of the 16
-    auto a = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
-    x = op(__uint_as_float(a[0]), __uint_as_float(a[1]));
-    auto b = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
-    return op(__uint_as_float(b[0]), __uint_as_float(b[1]));
+    float v[1] = {x};
+    group_reduce(v, 64, op);
+    return v[0];
 }
 __device__ __forceinline__ float wave_reduce_max(float x) { return wave_reduce(x, [](float a, float b) { return fmaxf(a, b); }); }
 // (non-negative integers below 2^31: their order is that of their bits)
