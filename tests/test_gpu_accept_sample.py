@@ -259,6 +259,15 @@ def test_accept_sample_degenerate_shapes(rd, B, W, L, V):
     check(rd, c, 1.0, what="degenerate")
 
 
+@pytest.mark.parametrize("B,W,L,V", [(2, 4, 3, 8192), (1, 8, 5, 20483), (1, 6, 4, 36866), (1, 5, 4, 69633), (1, 3, 3, 150001),
+                                     (1, 2, 3, 270001), (1, 48, 3, 17000), (1, 70, 5, 20001), (2, 24, 2, 4099)])
+def test_accept_sample_chunk_and_row_counts(rd, B, W, L, V):
+    """Vocabularies of 2, 6, 10, 18, 37 and 66 chunks of 4096 (a row's partials lie in groups of 2 to 64 lanes, or several
+    per lane) and more rows than one pass over the partials takes; row ends of 1 to 3 entries past a multiple of four."""
+    announce(f"accept_sample chunks B={B} W={W} L={L} V={V}")
+    check(rd, make_case(B, W, L, V, seed=7 * W + V, share="uniform"), 0.9, what="chunks")
+
+
 def test_masked_vocabulary_entries(rd):
     """-inf logits (a masked vocabulary) carry no probability: never drawn, and a candidate token the LLM
     masks is rejected whatever the uniform number."""
