@@ -17,31 +17,31 @@ typedef __attribute__((ext_vector_type(4))) float f32x4;
 
 struct AttnPlan {
     int waves;         // waves per workgroup (4 or 8); a block is a tile of keys per wave
-    int S;             // workgroups per (sequence, head)
+    int S;             // workgroups per (sequence, head) at most
     int rg_tiles;      // 16-row tiles of packed rows per workgroup (a row group)
     int n_rg;          // row groups per (sequence, head); 1 unless N is large
+    int ranges;        // key ranges per row group at most
+    int reserved;      // (no padding: plans are compared as bytes)
     size_t counters_bytes;
     size_t total_bytes;
 };
 
-// Row groups of a head in the matrix-core kernel with `waves` waves per workgroup, and the 16-row tiles of each.
+// Row groups of a head in the matrix-core kernel, as equal as whole 16-row tiles allow, and the tiles of each.
 struct AttnGroups { int rg_tiles, n_rg; };
-static inline AttnGroups attn_groups(int N, int waves)
+static inline AttnGroups attn_groups(int N)
 {
-    constexpr int kMaxTilesPerGroup = 5, kWideTilesPerGroup = 4;    // as instantiated
+    constexpr int kMaxTilesPerGroup = 3;    // as instantiated: a wave holds 32 accumulators per tile (D = 128)
     const int nq_all = (N + 15) / 16, n_rg = (nq_all + kMaxTilesPerGroup - 1) / kMaxTilesPerGroup;
-    const int nq = N > 32 * waves ? kWideTilesPerGroup : (nq_all + n_rg - 1) / n_rg;
+    const int nq = (nq_all + n_rg - 1) / n_rg;
     return {nq, (nq_all + nq - 1) / nq};
 }
 
 // Bytes of the completion counters, in front of the partial results.  One workspace may serve calls planned for
 // different contexts (ctx_bound of rd_tree_attn_bounded): a counter must never lie where another of these plans keeps
-// partial results.  The waves, and with them the row groups, follow from the context, so there is room for the most
-// groups that any plan of the shape has.
+// partial results, so their room depends on the shape alone.
 static inline size_t attn_counters_bytes(long long BH, int N)
 {
-    const int n8 = attn_groups(N, 8).n_rg, n4 = attn_groups(N, 4).n_rg;
-    return ((size_t)BH * (n8 > n4 ? n8 : n4) * sizeof(unsigned long long) + 255) / 256 * 256;
+    return ((size_t)BH * attn_groups(N).n_rg * sizeof(unsigned long long) + 255) / 256 * 256;
 }
 
 // Looks for the workgroups per head S with the shortest estimate of the launch, from n_rg (one per row group) up: S / n_act
@@ -70,71 +70,75 @@ static inline double attn_search(int n_rg, int n_act, int nblk, bool every, doub
     return best_T;
 }
 
+// Plan of the matrix-core kernel (rd_tree_attn_mfma.h), for contexts of up to Cmax keys: waves per workgroup and key ranges
+// per row group, from an estimate of the launch time.  Lengths are upper bounds and the packed rows are not known at all
+// here (distinct prefixes are taken to be 0.6 of the candidates' tokens, less of wide beams); the kernel deals the tiles it finds to the ranges
+// and starts no more row groups than hold packed rows.  The constants are fitted to 1080 launches on MI355X (60 shapes, four
+// and eight waves, 1 to 20 ranges), us, with r = row tiles that hold packed rows:
+//   * a workgroup takes 2.8 (four waves) or 3.8 (eight), and 1.15 or 0.6 for at most one tile per wave, else 0.62 + 0.22 r or
+//     0.85 + 0.25 r per tile of a wave (D = 64: 0.65 of that) and 0.7 r or 0.95 r where the waves' states meet;
+//   * one eight-wave workgroup fills a compute unit, two of four waves do; more start as those retire;
+//   * the workgroups that run at one time share 6.6 (four waves) or 5.9 TB/s, a compute unit gets 51 GB/s at most, and one
+//     with two workgroups takes twice as long as one with one (the rest of the chip then idles, which leaves the others more:
+//     half of that is counted); latency and bandwidth overlap but for where they are close (fourth root of the sum of fourth
+//     powers);
+//   * more than one range adds a merge: 1.6, the partial results read by one compute unit at 48 GB/s, and all of them
+//     written and read at 4.6 TB/s.
+// Over those shapes the choice is 2.2 % slower than the best of the 18 in the mean, 18 % at worst (5 heads, C=6000, 350 tokens).
+static inline AttnPlan attn_plan_make(int B, int H, int N, int D, int Cmax, bool every = false)
+{
+    const long long BH = (long long)B * H;
+    const size_t counters_bytes = attn_counters_bytes(BH, N);
+    const int nq = attn_groups(N).rg_tiles, n_rg = attn_groups(N).n_rg;
+    const double rows = 0.6 * N < 20 + 0.42 * N ? 0.6 * N : 20 + 0.42 * N, scale = D == 128 ? 1.0 : 0.65;
+    const int n_act = (int)ceil(rows / (16 * nq));
+    const double r = n_act > 1 ? nq : ceil(rows / 16), part = r * 16 * (2 + D) * sizeof(float);
+    const int tiles = (Cmax + 31) / 32 + ((int)rows + 31) / 32;
+    static const int waves_env = env_int("RD_ATTN_WAVES", 0), forced_env = env_int("RD_ATTN_SPLITS", 0);
+    AttnPlan best = {};
+    double best_T = 1e30;
+    for (int waves = 8; waves >= 4; waves -= 4) {
+        if (waves_env && waves != waves_env) continue;
+        const int nblk = tiles > waves ? (tiles + waves - 1) / waves : 1, most = nblk < 64 ? nblk : 64;
+        const int forced = forced_env > most ? most : forced_env;
+        const double t_tile = scale * (waves == 8 ? 0.85 + 0.25 * r : 0.62 + 0.22 * r), t_meet = scale * r * (waves == 8 ? 0.95 : 0.7);
+        const double t_wg = waves == 8 ? 3.8 : 2.8, t_one = waves == 8 ? 0.6 : 1.15, rate = waves == 8 ? 5.9e6 : 6.6e6;
+        const long long slots = waves == 8 ? 256 : 512;
+        for (int R = 1; R <= most; ++R) {
+            const int per = (tiles + R - 1) / R, steps = (per + waves - 1) / waves;
+            // more ranges with as many tiles per wave take no less time: only the fewest of them are looked at (`every`: all; they agree)
+            if (!every && forced <= 0 && R > 1 && steps == ((tiles + R - 2) / (R - 1) + waves - 1) / waves) continue;
+            const double t_lat = t_wg + (steps == 1 ? t_one : steps * t_tile + t_meet), bytes = (double)(steps * waves < tiles ? steps * waves : tiles) * 32 * D * 4 / n_act;
+            const long long wgs = (BH + 7) / 8 * 8 * n_act * R, full = wgs / slots, rest = wgs % slots;
+            auto round = [&](long long n) {
+                const long long per_cu = (n + 255) / 256;
+                const double sharing = ((n < 256 ? n : 256) + (double)n / per_cu) / 2;
+                const double t_bw = per_cu * bytes / (rate / sharing < 51e3 ? rate / sharing : 51e3);
+                const double l2 = t_lat * t_lat, b2 = t_bw * t_bw;
+                return sqrt(sqrt(l2 * l2 + b2 * b2));
+            };
+            double T = full * round(slots) + (rest ? round(rest) : 0.0);
+            if (R > 1) T += 1.6 + R * part / 48e3 + 2.0 * (double)BH * n_act * R * part / 4.6e6;
+            if (forced > 0 ? R == forced : T < best_T * (1 - 1e-9)) {
+                best_T = T;
+                best.waves = waves;
+                best.S = R * n_rg;
+                best.ranges = R;
+                best.rg_tiles = nq;
+                best.n_rg = n_rg;
+                best.counters_bytes = counters_bytes;
+                best.total_bytes = counters_bytes + (best.S > 1 ? ((size_t)BH * best.S * (size_t)(nq * 16 * (2 + D)) * sizeof(float) + 255) / 256 * 256 : 0);
+            }
+        }
+    }
+    return best;
+}
+
 // Microseconds that merging n_part partial results of `part` bytes each takes: written and read back, the reading by one
 // compute unit at 50 GB/s.
 static inline double attn_merge_us(long long units, int n_part, double part)
 {
     return n_part > 1 ? 1.5 + n_part * part / 50e3 + 2.0 * (double)units * n_part * part / 4e6 : 0.0;
-}
-
-// Plan of the matrix-core kernel (rd_tree_attn_mfma.h), for contexts of up to Cmax keys: waves per workgroup, rows
-// per workgroup and workgroups per head, from an estimate of the launch time.  Lengths are upper bounds and the
-// packed rows are not known at all here (distinct prefixes are taken to be 0.6 of the candidates' tokens); the kernel
-// deals its tiles to the workgroups from the lengths it finds.  Measured on MI355X, us, at D = 128 (D = 64: blocks take 0.6 of it):
-//   * a workgroup is 1.0 (eight waves) or 1.2 (four) plus 2.0 + 0.5 r or 1.15 + 0.3 r per block, r = row tiles with
-//     packed rows; at five row tiles K comes in operand order, 0.3 more per block of eight waves;
-//   * one eight-wave workgroup fills a compute unit, two of four waves do; more start as those retire;
-//   * the workgroups that run at one time share 5.0 (eight waves) or 5.25 TB/s, a compute unit gets 32 GB/s at most,
-//     and one with two workgroups takes twice as long as one with one (the rest of the chip then idles, which leaves
-//     the others more: half of that is counted); latency and bandwidth overlap but for where they are close (fourth root of the sum of fourth powers);
-//   * more than one range per head adds a merge (attn_merge_us).
-// Beams of more than 80 packed rows are cut into row groups, as equal as whole tiles allow; every group walks the
-// head's keys, and workgroups of groups that turn out empty go to the others.
-static inline AttnPlan attn_plan_make(int B, int H, int N, int D, int Cmax, bool every = false)
-{
-    const long long BH = (long long)B * H;
-    const size_t counters_bytes = attn_counters_bytes(BH, N);
-    const double rows = 0.6 * N, scale = D == 128 ? 1.0 : 0.6;
-    const int tiles = (Cmax + 31) / 32 + ((int)rows + 31) / 32;
-    static const int waves_env = env_int("RD_ATTN_WAVES", 0);
-    AttnPlan best = {};
-    double best_T = 1e30;
-    for (int waves = 8; waves >= 4; waves -= 4) {
-        if (waves_env && waves != waves_env) continue;
-        const int nq = attn_groups(N, waves).rg_tiles, n_rg = attn_groups(N, waves).n_rg;
-        int n_act = (int)((rows + 16 * nq - 1) / (16 * nq));
-        n_act = n_act < 1 ? 1 : n_act;
-        double r = n_act > 1 ? nq : (rows + 15) / 16;
-        r = r < 1 ? 1 : (r > nq ? nq : r);
-        const int nblk = tiles > waves ? (tiles + waves - 1) / waves : 1;
-        const double t_blk = scale * (waves == 8 ? 2.0 + 0.5 * r + (nq > 4 ? 0.3 : 0.0) : 1.15 + 0.3 * r);
-        const double t_wg = waves == 8 ? 1.0 : 1.2, rate = waves == 8 ? 5.0e6 : 5.25e6;
-        const long long slots = waves == 8 ? 256 : 512;
-        const double part = r * 16 * (2 + D) * sizeof(float);
-        int S = 0;
-        const double T = attn_search(n_rg, n_act, nblk, every, best_T, &S, [&](int wgs_per_head, int per, int n_part) {
-            const double t_lat = t_wg + per * t_blk, bytes = (double)(per * waves < tiles ? per * waves : tiles) * 32 * D * 4 / n_act;
-            const long long wgs = (BH + 7) / 8 * 8 * wgs_per_head, full = wgs / slots, rest = wgs % slots;
-            auto round = [&](long long n) {
-                const long long per_cu = (n + 255) / 256;
-                const double sharing = ((n < 256 ? n : 256) + (double)n / per_cu) / 2;
-                const double t_bw = per_cu * bytes / (rate / sharing < 32e3 ? rate / sharing : 32e3);
-                const double l2 = t_lat * t_lat, b2 = t_bw * t_bw;
-                return sqrt(sqrt(l2 * l2 + b2 * b2));
-            };
-            return full * round(slots) + (rest ? round(rest) : 0.0) + attn_merge_us(BH * n_act, n_part, part);
-        });
-        if (S > 0) {
-            best_T = T;
-            best.waves = waves;
-            best.S = S;
-            best.rg_tiles = nq;
-            best.n_rg = n_rg;
-            best.counters_bytes = counters_bytes;
-            best.total_bytes = counters_bytes + (S > 1 ? ((size_t)BH * S * (size_t)(nq * 16 * (2 + D)) * sizeof(float) + 255) / 256 * 256 : 0);
-        }
-    }
-    return best;
 }
 
 // Plan of the fp32 kernel (rd_tree_attn_f32.hip; row groups of one tile): workgroups per head, estimated as above.  A
@@ -150,6 +154,7 @@ static inline AttnPlan attn_plan_make_f32(int B, int H, int N, int D, int Cmax, 
     best.waves = 8;
     best.rg_tiles = 1;
     best.n_rg = n_rg;
+    best.ranges = 1;
     attn_search(n_rg, n_act, nblk, every, 1e30, &best.S, [&](int wgs_per_head, int per, int n_part) {
         const double t_lat = 1.5 + per * t_blk, bytes = (double)(per * 8 < tiles ? per * 8 : tiles) * 16 * D * 8;
         const long long wgs = (BH + 7) / 8 * 8 * wgs_per_head, full = wgs / 256, rest = wgs % 256;
@@ -195,6 +200,7 @@ struct AttnArgs {
     float *partials;
     int B, H, N, Cmax, S, words;
     int n_rg;      // row groups per (sequence, head) (each is NQ*16 rows of the kernel's template)
+    int ranges;    // key ranges per row group at most
     float scale_log2e;
     // rotary embedding fused into the call (rd_tree_attn_rope); unused (null) otherwise
     const int32_t *position_ids;   // [B, N]

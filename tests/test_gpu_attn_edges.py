@@ -1,0 +1,79 @@
+"""The 16-bit attention kernel where its tiles, row groups and key ranges end, against the oracle: contexts around multiples
+of a tile (32 keys) and of a workgroup's tiles (4 or 8 of them), rows around row tiles (16) and row groups (48), one tile per
+wave and several, and rotary tables that do not start at a multiple of 16 bytes."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from gpu_util import announce, dev, host
+from paper_2403_09919_amd import synth
+from test_oracle_rope import tables
+
+pytestmark = pytest.mark.gpu
+
+# A probability is rounded to the storage type once and the result once; the values are averages of normal variates, |v| < 6
+# (the bound the other attention tests use).
+TOL = {"bf16": 2e-2, "f16": 4e-3}
+
+
+@pytest.fixture(scope="module")
+def rd():
+    assert torch.cuda.is_available(), "GPU tests need a device"
+    from paper_2403_09919_amd import binding
+    return binding
+
+
+def _case(B, H, W, L, ctx, D, dtype, seed, vocab=32000):
+    ctx = np.asarray(ctx, np.int32)
+    N = W * L
+    beams = synth.make_beams(B, W, L, vocab, seed, "uniform")
+    q, kn, vn = synth.make_qkv_new(B, H, N, D, dtype, seed)
+    kc, vc = synth.make_kv_cache(B, H, max(int(ctx.max()), 1), D, dtype, seed, ctx, True)
+    return ctx, beams, q, kn, vn, kc, vc, oracle.dedup(beams, ctx)
+
+
+@pytest.mark.parametrize("dtype,D", [("bf16", 128), ("f16", 64)])
+@pytest.mark.parametrize("W,L", [(1, 1), (4, 4), (17, 1), (8, 5), (47, 1), (48, 1), (49, 1), (97, 1), (128, 3)])
+@pytest.mark.parametrize("ctx", [(0, 1), (31, 33), (127, 129), (223, 256), (257, 700), (2048, 2049)])
+def test_tile_and_group_edges(rd, dtype, D, W, L, ctx):
+    announce(f"edges {dtype} D={D} W={W} L={L} ctx={ctx}")
+    B, H = 2, 3
+    ctx, beams, q, kn, vn, kc, vc, d = _case(B, H, W, L, ctx, D, dtype, W + L)
+    scale = float(1.0 / np.sqrt(D))
+    ref = oracle.tree_attn(q, kc, vc, ctx, kn, vn, d["n_packed"], d["tree_mask"], dtype, scale)
+    dd = rd.rd_dedup(dev(beams), dev(ctx))
+    out = rd.rd_tree_attn(dev(q), dev(kc), dev(vc), dev(ctx), dev(kn), dev(vn), dd["n_packed"], dd["tree_mask_bits"], scale)
+    torch.cuda.synchronize()
+    got, want = synth.to_f64(host(out), dtype), synth.to_f64(ref, dtype)
+    assert np.isfinite(got).all() and np.abs(got - want).max() <= TOL[dtype]
+    for b in range(B):                                             # rows beyond the packed count are zero
+        assert not got[b, :, int(d["n_packed"][b]):].any()
+
+
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("W,L,ctx", [(8, 5, 300), (8, 5, 3000), (40, 4, 90)])
+@pytest.mark.parametrize("shift", [0, 1, 2, 3])
+def test_rotary_tables_at_any_multiple_of_four_bytes(rd, D, W, L, ctx, shift):
+    announce(f"rope tables D={D} W={W} L={L} ctx={ctx} shift={shift}")
+    ctx, beams, q, kn, vn, kc, vc, d = _case(1, 2, W, L, [ctx], D, "bf16", D + W)
+    scale, (cos, sin) = float(1.0 / np.sqrt(D)), tables(4096, D)
+    dd = rd.rd_dedup(dev(beams), dev(ctx))
+
+    def shifted(t):
+        flat = torch.empty(t.size + 4, dtype=torch.float32, device="cuda")
+        view = flat[shift:shift + t.size].view(t.shape)
+        view.copy_(torch.from_numpy(t))
+        return view
+
+    def run(c, s):
+        return rd.rd_tree_attn_rope(dev(q), dev(kc), dev(vc), dev(ctx), dev(kn), dev(vn), dd["n_packed"], dd["tree_mask_bits"],
+                                    dd["position_ids"], c, s, scale)
+
+    q2, k2 = dev(q), dev(kn)
+    rd.rd_rope(q2, k2, dd["position_ids"], dd["n_packed"], dev(cos), dev(sin))
+    sep = rd.rd_tree_attn(q2, dev(kc), dev(vc), dev(ctx), k2, dev(vn), dd["n_packed"], dd["tree_mask_bits"], scale)
+    out, k_rot = run(shifted(cos), shifted(sin))
+    torch.cuda.synchronize()
+    P = int(d["n_packed"][0])
+    assert np.array_equal(host(out), host(sep)) and np.array_equal(host(k_rot)[0, :, :P], host(k2)[0, :, :P])
