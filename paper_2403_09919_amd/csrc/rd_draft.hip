@@ -7,9 +7,9 @@
 //     go from memory straight into the A operand of v_mfma_f32_16x16x32_bf16 (lane = one output
 //     column x 8 consecutive k), the activations (a few hundred KB, L2 resident) into the B
 //     operand, and the partial sums meet in LDS.  Bias, SiLU, skip connection and the bf16
-//     copy that the next layer reads are fused into the epilogue.  At more than 32 rows the
-//     layers with few columns use 128- or 64-column workgroups and split K over 2 to 8
-//     workgroups per column group as well; the last of them to finish adds the partial tiles;
+//     copy that the next layer reads are fused into the epilogue.  At more than 32 rows a kernel
+//     of 256-column workgroups with K split over them, fed through LDS, takes over (rd_gemm_kernel), and
+//     a second one adds the partial tiles;
 //   * three selection launches, all merges of sorted lists: per chunk of 4096 logits and row, the
 //     pieces of the log-sum-exp and the W best tokens; per row, its log-sum-exp and the W best
 //     tokens of its chunks as cumulative scores; per sequence, the best W of the (candidate, token)
@@ -48,9 +48,7 @@ constexpr int kNarrowBeam = 64;        // up to here the selection kernels keep 
 constexpr int kSelThreads = 256;       // row pass and beam step: four waves bring the lists into LDS, the first one merges
 constexpr int kMaxVocab = 262144;      // 64 chunks of 4096 logits: one lane per chunk in the row pass
 constexpr int kSplitMaxWgs = 256;      // workgroups of a launch whose K is split over workgroups
-constexpr int kRowParts = (kMaxRows + kRowsPerLaunch - 1) / kRowsPerLaunch;
-constexpr int kSplitMaxGroups = 128;   // ... and its column groups (one arrival counter each)
-constexpr int kSplitTiles = 64;        // ... and the 16x16 output tiles a workgroup holds
+constexpr int kGemmCols = 16;          // its column tiles per workgroup
 
 enum { EPI_HEAD = 0, EPI_RNN = 1, EPI_MLP = 2 };
 
@@ -65,7 +63,6 @@ struct LinArgs {
     const float *bias;                 // [N] or NULL
     int M, N;
     int m0;                            // first logical row of this launch (a launch covers rows m0 .. m0+M-1)
-    int parts;                         // rd_head_rows_kernel: workgroups of 128 rows per column group (0: one)
     int mstride;                       // logical row m of X (without a map), Y and res is physical row m*mstride
     // epilogue
     float *y_f32;                      // HEAD: logits [M][ldy];  RNN/MLP: activations fp32 [M][ldy]
@@ -73,10 +70,9 @@ struct LinArgs {
     T *s_bf;                           // RNN: next state [M][N]
     const float *res;                  // MLP: skip input fp32 [M][ldy]
     int ldy;
-    // K split over workgroups (kernels instantiated with KSP): workgroup = (column group, split)
+    // rd_gemm_kernel: K split over workgroups
     int ksplit;                        // splits per column group
     float *kpart;                      // partial tiles [group][split][tile][64 lanes] x 4 floats
-    uint32_t *kcount;                  // arrivals per column group, zero between launches
 };
 
 __device__ __forceinline__ float silu(float x) { return x / (1.0f + __expf(-x)); }
@@ -122,49 +118,12 @@ __device__ __forceinline__ void linear_epilogue(const LinArgs<T> &a, f32x4 v, in
     if (EPI == EPI_RNN) *reinterpret_cast<vec4 *>(a.s_bf + prow * a.N + n0) = yb;
 }
 
-// The last workgroup of a column group adds the KS partial tiles of each output tile in split order
-// and finishes them.  A wave's loads are issued together (in batches of at most 32 partial tiles) before
-// the sums.
-template <typename T, int MT, int NT, int NWV, int EPI, int KS>
-__device__ __forceinline__ void linear_finish_split(const LinArgs<T> &a, int group, int n0, int wave, int lane)
-{
-    constexpr int kTiles = MT * NT, kMine = kTiles / NWV;       // tiles per wave
-    constexpr int kBatch = kMine * KS > 32 ? 32 / KS : kMine;   // tiles whose loads are in flight together (<= 128 registers)
-    static_assert(kTiles % NWV == 0 && kMine % kBatch == 0, "every wave finishes the same number of tiles, in whole batches");
-    const int r16 = lane & 15, g = lane >> 4;
-#pragma unroll
-    for (int i0 = 0; i0 < kMine; i0 += kBatch) {
-        float2 lo[kBatch][KS], hi[kBatch][KS];
-#pragma unroll
-        for (int i = 0; i < kBatch; ++i)
-#pragma unroll
-            for (int sp = 0; sp < KS; ++sp) {
-                const float *src = a.kpart + ((((size_t)group * KS + sp) * kTiles + wave + (i0 + i) * NWV) * 64 + lane) * 4;
-                lo[i][sp] = rd::ld_dev2(src);
-                hi[i][sp] = rd::ld_dev2(src + 2);
-            }
-#pragma unroll
-        for (int i = 0; i < kBatch; ++i) {
-            const int id = wave + (i0 + i) * NWV;
-            f32x4 v = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-            for (int sp = 0; sp < KS; ++sp) v += f32x4{lo[i][sp].x, lo[i][sp].y, hi[i][sp].x, hi[i][sp].y};
-            linear_epilogue<T, EPI>(a, v, (id / NT) * 16, n0 + (id % NT) * 16, r16, g);
-        }
-    }
-}
-
 // A workgroup owns NT*16 output columns for all M = MT*16 rows; its NWV waves split K.  The host
 // picks NT so that the activations, which every workgroup re-reads through the caches, do not
 // outweigh the weights it streams (their ratio is MT : NT) while the launch still covers the chip,
 // and NWV so that the launch has enough waves in flight to keep the HBM stream busy; every wave's
 // share of K is a whole number of 32-wide steps inside one of the two products.
-//
-// KSP: K is also split over a.ksplit workgroups per column group, for layers with so few columns that
-// NT-wide workgroups alone would leave most of the chip idle.  Every workgroup stores its partial
-// tiles (write-through) and signals; the last to arrive for its column group adds the partials in
-// split order (so the sum does not depend on who was last) and runs the epilogue.
-template <typename T, int MT, int NT, int NWV, int EPI, bool TILED, bool KSP = false>
+template <typename T, int MT, int NT, int NWV, int EPI, bool TILED>
 __global__ __launch_bounds__(NWV * 64) void rd_linear_kernel(LinArgs<T> a)
 {
     typedef typename Elem16<T>::vec8 vec8;
@@ -175,15 +134,11 @@ __global__ __launch_bounds__(NWV * 64) void rd_linear_kernel(LinArgs<T> a)
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int r16 = lane & 15, g = lane >> 4;
-    const int groups = KSP ? (int)gridDim.x / a.ksplit : (int)gridDim.x;
-    const int group = KSP ? (int)blockIdx.x % groups : (int)blockIdx.x;
-    const int split = KSP ? (int)blockIdx.x / groups : 0;
-    const int n0 = group * (16 * NT);
+    const int n0 = (int)blockIdx.x * (16 * NT);
 
     // this wave's share of the k-steps (32 wide); the host guarantees it lies within one product
     const int ks1 = a.K1 >> 5, ks = ks1 + (a.K2 >> 5);
-    const int parts = KSP ? a.ksplit * NWV : NWV, part = split * NWV + wave;
-    const int kb = (int)((long long)ks * part / parts), ke = (int)((long long)ks * (part + 1) / parts);
+    const int kb = (int)((long long)ks * wave / NWV), ke = (int)((long long)ks * (wave + 1) / NWV);
     const bool second = kb >= ks1;
     const T *wbase = second ? a.w2 : a.w1;
     const int K = second ? a.K2 : a.K1;
@@ -262,28 +217,8 @@ __global__ __launch_bounds__(NWV * 64) void rd_linear_kernel(LinArgs<T> a)
 #pragma unroll
             for (int w = 1; w < NWV; ++w) v += s_part[w][j][lane];
             const int id = p * kGroup + j;
-            if constexpr (KSP)
-                rd::st_dev4(a.kpart + ((((size_t)group * a.ksplit + split) * kTiles + id) * 64 + lane) * 4, v[0], v[1], v[2], v[3]);
-            else
-                linear_epilogue<T, EPI>(a, v, (id / NT) * 16, n0 + (id % NT) * 16, r16, g);
+            linear_epilogue<T, EPI>(a, v, (id / NT) * 16, n0 + (id % NT) * 16, r16, g);
         }
-    }
-    if constexpr (KSP) {
-        __shared__ uint32_t s_last;
-        rd::wait_dev_stores();
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");      // this workgroup's partial tiles are acknowledged
-        __syncthreads();
-        if (tid == 0) {
-            const uint32_t prev = __hip_atomic_fetch_add(a.kcount + group, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            s_last = (prev + 1u == (uint32_t)a.ksplit) ? 1u : 0u;
-            if (s_last) a.kcount[group] = 0;                        // ready for the next launch
-        }
-        __syncthreads();
-        if (!s_last) return;
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
-        if (a.ksplit == 8) linear_finish_split<T, MT, NT, NWV, EPI, 8>(a, group, n0, wave, lane);
-        else if (a.ksplit == 4) linear_finish_split<T, MT, NT, NWV, EPI, 4>(a, group, n0, wave, lane);
-        else linear_finish_split<T, MT, NT, NWV, EPI, 2>(a, group, n0, wave, lane);
     }
 }
 
@@ -300,9 +235,7 @@ __global__ __launch_bounds__(NWV * 64) void rd_linear_kernel(LinArgs<T> a)
 constexpr int kRowsKC = 256;                       // k per chunk
 constexpr int kRowsStride = kRowsKC * 2 + 16;      // bytes per staged activation row
 
-// KSP (layers with few columns): K is also split over a.ksplit workgroups per column group, exchanged as in
-// rd_linear_kernel (partial tiles stored write-through, last arriver sums in split order).
-template <typename T, int MT, bool TILED, int EPI = EPI_HEAD, bool KSP = false>
+template <typename T, int MT, bool TILED>
 __global__ __launch_bounds__(512) void rd_head_rows_kernel(LinArgs<T> a)
 {
     typedef typename Elem16<T>::vec8 vec8;
@@ -315,30 +248,9 @@ __global__ __launch_bounds__(512) void rd_head_rows_kernel(LinArgs<T> a)
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int cp = wave & 3, kh = wave >> 2;                           // column pair, half of every chunk's k-steps
     const int r16 = lane & 15, g = lane >> 4;
-    // More than 128 rows: a.parts workgroups, of 128 rows each, per (column group, split).  They are neighbours on one
-    // XCD (workgroups are dealt to the 8 XCDs in turn), so that one of them reads the weights from memory and the others
-    // from L2.
-    const int groups = (a.N + 127) / 128;
-    int unit = (int)blockIdx.x;
-    if (a.parts > 1) {
-        const int y = (int)blockIdx.x >> 3;
-        unit = y / a.parts * 8 + ((int)blockIdx.x & 7);
-        if (unit >= groups * (KSP ? a.ksplit : 1)) return;
-        const int part = y % a.parts;
-        a.m0 += part * kRowsPerLaunch;
-        a.M = min(a.M - part * kRowsPerLaunch, kRowsPerLaunch);
-        if (KSP) {
-            a.kcount += part * groups;
-            a.kpart += (size_t)part * groups * a.ksplit * (MT * 8) * 256;
-        }
-    }
-    const int group = KSP ? unit % groups : unit;
-    const int split = KSP ? unit / groups : 0;
+    const int group = (int)blockIdx.x;
     const int n_tile = (group * 8 + cp * 2) * 16;                      // this wave's 32 columns: tiles n_tile, n_tile + 16
-    // this workgroup's chunks of K: [c_first, c_first + nchunks)
-    const int all_chunks = a.K1 / kRowsKC;
-    const int c_first = KSP ? all_chunks * split / a.ksplit : 0;
-    const int nchunks = KSP ? all_chunks * (split + 1) / a.ksplit - c_first : all_chunks;
+    const int nchunks = a.K1 / kRowsKC;
 
     const T *wp[2];                                                    // this lane's first weight vector of either tile
     constexpr int wstep = TILED ? 512 : 32;
@@ -346,9 +258,9 @@ __global__ __launch_bounds__(512) void rd_head_rows_kernel(LinArgs<T> a)
     for (int t = 0; t < 2; ++t) {
         if (TILED) {
             const int ntile = min(n_tile / 16 + t, (a.N + 15) / 16 - 1);   // tiles past N read the last one; never stored
-            wp[t] = a.w1 + (size_t)ntile * (a.K1 >> 5) * 512 + lane * 8 + (c_first * kSteps + kh * kMine) * wstep;
+            wp[t] = a.w1 + (size_t)ntile * (a.K1 >> 5) * 512 + lane * 8 + kh * kMine * wstep;
         } else {
-            wp[t] = a.w1 + (size_t)min(n_tile + t * 16 + r16, a.N - 1) * a.K1 + 8 * g + (c_first * kSteps + kh * kMine) * wstep;
+            wp[t] = a.w1 + (size_t)min(n_tile + t * 16 + r16, a.N - 1) * a.K1 + 8 * g + kh * kMine * wstep;
         }
     }
     const T *xsrc[kPieces];
@@ -357,7 +269,7 @@ __global__ __launch_bounds__(512) void rd_head_rows_kernel(LinArgs<T> a)
     for (int i = 0; i < kPieces; ++i) {
         const int p = tid + 512 * i, row = p >> 5, ch = p & 31;
         const size_t prow = (size_t)(a.m0 + min(row, a.M - 1)) * a.mstride;
-        xsrc[i] = a.x1 + prow * a.ldx1 + ch * 8 + c_first * kRowsKC;
+        xsrc[i] = a.x1 + prow * a.ldx1 + ch * 8;
         xdst[i] = row * kRowsStride + ch * 16;
     }
     f32x4 acc[MT][2];
@@ -421,43 +333,217 @@ __global__ __launch_bounds__(512) void rd_head_rows_kernel(LinArgs<T> a)
         }
     }
     rd_lds_barrier();
-    if constexpr (!KSP) {
-        if (kh == 1) return;
+    if (kh == 1) return;
 #pragma unroll
-        for (int mt = 0; mt < MT; ++mt) {
-            linear_epilogue<T, EPI>(a, acc[mt][0] + s_acc[(mt * 2 + 0) * 64], mt * 16, n_tile, r16, g);
-            linear_epilogue<T, EPI>(a, acc[mt][1] + s_acc[(mt * 2 + 1) * 64], mt * 16, n_tile + 16, r16, g);
+    for (int mt = 0; mt < MT; ++mt) {
+        linear_epilogue<T, EPI_HEAD>(a, acc[mt][0] + s_acc[(mt * 2 + 0) * 64], mt * 16, n_tile, r16, g);
+        linear_epilogue<T, EPI_HEAD>(a, acc[mt][1] + s_acc[(mt * 2 + 1) * 64], mt * 16, n_tile + 16, r16, g);
+    }
+}
+
+// Layers of 33 rows and more.  A workgroup of eight waves owns RT row tiles x CT column tiles of the output and a share of K;
+// wave (wr, wc) of WR x WC owns a block of RT/WR x CT/WC tiles.  Per k-step of 32 the operands of all its tiles, (RT + CT) KB,
+// are copied from memory straight into buffers in LDS, three k-steps ahead for the activations (from L2), as many as LDS holds
+// for the weights (5 at RT = 16, 8 at RT = 4), with one LDS-only barrier a step; operands are read into registers two row tiles
+// ahead, across that barrier.  K is split over a.ksplit workgroups; each leaves its tiles in the workspace and
+// rd_linear_finish_kernel adds them up in split order.  Workgroups of one split read the same activations: an XCD gets
+// consecutive column groups of one split.
+//
+// What bounds it.  64 and 128 rows: the weights' stream, 5.2 TB/s (the MLP layer at a hidden size of 5120 40 us, and 6 of
+// adding up).  256 rows: LDS, whose reads and copies take as long as the matrix instructions (blocks of 8 x 8 tiles would
+// need less, but their accumulators spill), and the matrix rate itself: the output layer at a hidden size of 6656 208 us, 128
+// without the copies, 1.05 PFLOP/s (a library product of 8192^3 reaches 1.22).  Against the kernels it replaced, one that
+// staged the activations of 128 rows through registers and one that split K over the waves, us per layer: 256 rows, hidden
+// size 6656, RNN 137 -> 52 + 14, MLP 173 -> 107 + 18, output layer 297 -> 208 + 17; 64 rows, 5120, RNN 37 -> 24 + 6, MLP 56 ->
+// 43 + 6.  A call: 256 rows 2832 -> 2124, 64 rows 1085 -> 1056, 80 rows, hidden size 1024 and 50000 tokens 592 -> 465; shapes that the
+// old kernels' rules fitted badly gain most (80 rows, hidden size 4160, 12000 tokens 1377 -> 677).
+constexpr int kGemmX = 4;              // buffers for the activations' k-steps
+template <int RT, int CT> constexpr int gemm_w_buffers() { return (160 - kGemmX * RT) / CT; }      // ... and for the weights'
+template <int RT, int CT> constexpr size_t gemm_lds() { return (size_t)(kGemmX * RT + gemm_w_buffers<RT, CT>() * CT) * 1024; }
+
+template <typename T, int RT, int CT, int WR, int WC, int EPI, bool TILED>
+__global__ __launch_bounds__(WR * WC * 64, 1) void rd_gemm_kernel(LinArgs<T> a)
+{
+    typedef typename Elem16<T>::vec8 vec8;
+    constexpr int NX = kGemmX, NW = gemm_w_buffers<RT, CT>();
+    constexpr int PX = (RT + 3) / 4, PW = CT / 4;                       // 1 KB pieces a wave copies per k-step: four waves X, four W
+    constexpr int MT = RT / WR, NT = CT / WC;                           // a wave's tiles
+    static_assert(WR * WC == 8 && CT % 4 == 0 && MT % 2 == 0 && NT % (MT / 2) == 0, "whole pieces, and halves of a step");
+    extern __shared__ __align__(16) unsigned char s_buf[];
+    typedef __attribute__((address_space(3))) unsigned char lds_byte;
+    const uint32_t lds0 = (uint32_t)(uintptr_t)(lds_byte *)s_buf;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int r16 = lane & 15, g = lane >> 4;
+    const int groups = (a.N + 16 * CT - 1) / (16 * CT);
+    const int unit = (int)(blockIdx.x & 7) * ((int)gridDim.x >> 3) + (int)(blockIdx.x >> 3);
+    if (unit >= groups * a.ksplit) return;
+    const int split = unit / groups, group = unit - split * groups;
+    const int n0 = group * (16 * CT);
+
+    // this workgroup's k-steps: [kb, ke) of those of the first product and, behind them, of the second
+    const int ks1 = a.K1 >> 5, ks = ks1 + (a.K2 >> 5);
+    const int kb = (int)((long long)ks * split / a.ksplit), steps = (int)((long long)ks * (split + 1) / a.ksplit) - kb;
+
+    // A wave's pieces: the first four waves copy row tiles wave, wave + 4, .. of the activations (past the last: that one
+    // again, to the same place), the others column tiles of the weights.  (Loads return in order: a wave that copied both would
+    // wait for its newest weights whenever it waits for activations.)  Rows are copied four lanes to a row (64 bytes of it);
+    // the 16-byte pieces of a row are swizzled so that the 16 rows of an operand read lie in distinct banks.
+    const bool is_x = wave < 4;
+    const int wq = wave & 3, prow = lane >> 2, pch = (lane & 3) ^ (prow >> 2);
+    uintptr_t row_at1[PX], row_at2[PX];         // activations: a lane's row in either product
+    uint32_t woff[PW];
+    int wtile[PW];
+    if (is_x) {
+        int row1[PX], row2[PX];
+#pragma unroll
+        for (int i = 0; i < PX; ++i) row1[i] = row2[i] = a.m0 + min(min(wq + 4 * i, RT - 1) * 16 + prow, a.M - 1);
+        if (a.map1 != nullptr) {                // (the RNN: both products have one)
+            int m1[PX], m2[PX];
+#pragma unroll
+            for (int i = 0; i < PX; ++i) { m1[i] = a.map1[row1[i]]; m2[i] = a.map2[row2[i]]; }
+#pragma unroll
+            for (int i = 0; i < PX; ++i) { row1[i] = m1[i]; row2[i] = m2[i]; }
+        } else {
+#pragma unroll
+            for (int i = 0; i < PX; ++i) row1[i] *= a.mstride;
+        }
+#pragma unroll
+        for (int i = 0; i < PX; ++i) {
+            row_at1[i] = reinterpret_cast<uintptr_t>(a.x1) + ((size_t)row1[i] * a.ldx1 + pch * 8) * 2;
+            row_at2[i] = reinterpret_cast<uintptr_t>(a.x2) + ((size_t)row2[i] * a.ldx2 + pch * 8) * 2;
         }
     } else {
-        // this workgroup's tiles, numbered as an MT x 8 grid (row tile, column tile), -> workspace
-        constexpr int kTiles = MT * 8;
-        if (kh == 0) {
 #pragma unroll
-            for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-                for (int t = 0; t < 2; ++t) {
-                    const f32x4 v = acc[mt][t] + s_acc[(mt * 2 + t) * 64];
-                    const int id = mt * 8 + cp * 2 + t;
-                    rd::st_dev4(a.kpart + ((((size_t)group * a.ksplit + split) * kTiles + id) * 64 + lane) * 4, v[0], v[1], v[2], v[3]);
-                }
+        for (int i = 0; i < PW; ++i) {
+            wtile[i] = min(n0 / 16 + wq + 4 * i, (a.N + 15) / 16 - 1);  // past N: the last one again; never stored
+            woff[i] = TILED ? lane * 16 : (uint32_t)min((wq + 4 * i) * 16 + prow, a.N - 1 - n0);      // row-major: of the row in the group
         }
-        __shared__ uint32_t s_last;
-        rd::wait_dev_stores();
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");      // this workgroup's partial tiles are acknowledged
-        __syncthreads();
-        if (tid == 0) {
-            const uint32_t prev = __hip_atomic_fetch_add(a.kcount + group, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            s_last = (prev + 1u == (uint32_t)a.ksplit) ? 1u : 0u;
-            if (s_last) a.kcount[group] = 0;                        // ready for the next launch
-        }
-        __syncthreads();
-        if (!s_last) return;
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
-        const int n0 = group * 128;
-        if (a.ksplit == 8) linear_finish_split<T, MT, 8, 8, EPI, 8>(a, group, n0, wave, lane);
-        else if (a.ksplit == 4) linear_finish_split<T, MT, 8, 8, EPI, 4>(a, group, n0, wave, lane);
-        else linear_finish_split<T, MT, 8, 8, EPI, 2>(a, group, n0, wave, lane);
     }
+    const uintptr_t w1 = reinterpret_cast<uintptr_t>(a.w1), w2 = reinterpret_cast<uintptr_t>(a.w2);
+    auto copy_x = [&](int s) __attribute__((always_inline)) {
+        const int k = kb + s;
+        const bool second = k >= ks1;
+        const size_t at = (size_t)(second ? k - ks1 : k) * 64;
+#pragma unroll
+        for (int i = 0; i < PX; ++i) rd::dma16((second ? row_at2[i] : row_at1[i]) + at, lds0 + ((uint32_t)(s % NX) * RT + min(wq + 4 * i, RT - 1)) * 1024);
+    };
+    auto copy_w = [&](int s) __attribute__((always_inline)) {
+        const int k = kb + s;
+        const bool second = k >= ks1;
+        const int k1 = second ? k - ks1 : k, K = second ? a.K2 : a.K1;
+        const uintptr_t wb = second ? w2 : w1;
+        const uint32_t dst = lds0 + (NX * RT + (uint32_t)(s % NW) * CT + wq) * 1024;
+#pragma unroll
+        for (int i = 0; i < PW; ++i) {
+            if (TILED) rd::dma16(wb + ((size_t)wtile[i] * (K >> 5) + k1) * 1024, woff[i], dst + 4 * i * 1024);
+            else rd::dma16(wb + ((size_t)n0 * K + (size_t)k1 * 32) * 2, woff[i] * (uint32_t)K * 2 + pch * 16, dst + 4 * i * 1024);
+        }
+    };
+
+    const int wr = wave / WC, wc = wave % WC;
+    const int rd_rows = r16 * 64 + (g ^ (r16 >> 2)) * 16;               // operand order from copied rows
+    const int rd_w = NX * RT * 1024 + wc * NT * 1024 + (TILED ? lane * 16 : rd_rows), rd_x = wr * MT * 1024 + rd_rows;
+    auto read_w = [&](int s, int nt) __attribute__((always_inline)) { return *reinterpret_cast<const vec8 *>(s_buf + (s % NW) * (CT * 1024) + rd_w + nt * 1024); };
+    auto read_x = [&](int s, int mt) __attribute__((always_inline)) { return *reinterpret_cast<const vec8 *>(s_buf + (s % NX) * (RT * 1024) + rd_x + mt * 1024); };
+    f32x4 acc[MT][NT];
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt) acc[mt][nt] = f32x4{0.f, 0.f, 0.f, 0.f};
+
+    if (is_x) {
+        for (int s = 0; s < min(steps, NX - 1); ++s) copy_x(s);
+    } else {
+        for (int s = 0; s < min(steps, NW - 1); ++s) copy_w(s);
+    }
+    // k-step s, behind which at most NX - 3 (NW - 3) more are asked for, is in LDS when all waves have waited for their pieces of it
+    auto arrive = [&](int s) __attribute__((always_inline)) {
+        if (is_x) {
+            if (s + NX - 3 < steps) rd::wait_vm<(NX - 3) * PX>();
+            else rd::wait_vm<0>();
+        } else {
+            if (s + NW - 3 < steps) rd::wait_vm<(NW - 3) * PW>();
+            else rd::wait_vm<0>();
+        }
+        rd_lds_barrier();
+    };
+    // One k-step, a row tile at a time.  A row tile's operand is read two row tiles ahead, the next step's weights in the
+    // second half (after the last step: what lies there, ignored).
+    vec8 x[MT];
+    auto step = [&](int s, const vec8 (&w)[NT], vec8 (&wn)[NT]) __attribute__((always_inline)) {
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt) {
+            constexpr int kHalf = MT / 2;
+            if (mt == kHalf - 1 && s + 1 < steps) {
+                arrive(s + 1);                // (all waves have read the step before this one to its end: its buffer is free)
+                if (is_x) {
+                    if (s + NX - 1 < steps) copy_x(s + NX - 1);
+                } else {
+                    if (s + NW - 1 < steps) copy_w(s + NW - 1);
+                }
+            }
+            const vec8 xm = x[mt];
+            x[(mt + 2) % MT] = mt + 2 < MT ? read_x(s, mt + 2) : read_x(s + 1, mt + 2 - MT);
+            if (mt >= kHalf) {
+#pragma unroll
+                for (int i = 0; i < NT / kHalf; ++i) wn[(mt - kHalf) * (NT / kHalf) + i] = read_w(s + 1, (mt - kHalf) * (NT / kHalf) + i);
+            }
+#pragma unroll
+            for (int nt = 0; nt < NT; ++nt) acc[mt][nt] = Elem16<T>::mfma(w[nt], xm, acc[mt][nt]);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    };
+    if (steps > 0) {
+        vec8 w0[NT], w1r[NT];
+        arrive(0);
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt) w0[nt] = read_w(0, nt);
+        x[0] = read_x(0, 0);
+        x[1] = read_x(0, 1);
+        int s = 0;
+        for (; s + 2 <= steps; s += 2) {
+            step(s, w0, w1r);
+            step(s + 1, w1r, w0);
+        }
+        if (s < steps) step(s, w0, w1r);
+    }
+    if (a.ksplit == 1) {
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+            for (int nt = 0; nt < NT; ++nt)
+                linear_epilogue<T, EPI>(a, acc[mt][nt], (wr * MT + mt) * 16, n0 + (wc * NT + nt) * 16, r16, g);
+        return;
+    }
+    // tiles numbered as an RT x CT grid
+    float *out = a.kpart + ((size_t)group * a.ksplit + split) * (RT * CT) * 256 + lane * 4;
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt)
+            if ((wr * MT + mt) * 16 < a.M) *reinterpret_cast<f32x4 *>(out + ((wr * MT + mt) * CT + wc * NT + nt) * 256) = acc[mt][nt];
+}
+
+// Adds the partial tiles of rd_gemm_kernel in split order and finishes the layer, a wave per tile.
+template <typename T, int RT, int CT, int EPI>
+__global__ __launch_bounds__(256) void rd_linear_finish_kernel(LinArgs<T> a)
+{
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int nts = (a.N + 15) / 16, id = blockIdx.x * 4 + wave;
+    const int mt = id / nts, n_tile = id - mt * nts;
+    if (mt * 16 >= a.M) return;
+    const float *src = a.kpart + (((size_t)(n_tile / CT) * a.ksplit * RT + mt) * CT + n_tile % CT) * 256 + lane * 4;
+    f32x4 v = {0.f, 0.f, 0.f, 0.f};
+    for (int s0 = 0; s0 < a.ksplit; s0 += 8) {
+        f32x4 p[8];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) p[i] = *reinterpret_cast<const f32x4 *>(src + (size_t)min(s0 + i, a.ksplit - 1) * (RT * CT) * 256);
+#pragma unroll
+        for (int i = 0; i < 8; ++i)
+            if (s0 + i < a.ksplit) v += p[i];
+    }
+    linear_epilogue<T, EPI>(a, v, mt * 16, n_tile * 16, lane & 15, lane >> 4);
 }
 
 // rows m = b*W + w: X0 = [e(last token), h] (fp32 and bf16), state = e(last token), path = [last token]
@@ -465,11 +551,9 @@ template <typename T>
 __global__ void rd_draft_init_kernel(const T *__restrict__ emb, const T *__restrict__ h,
                                      const int32_t *__restrict__ last_token, int W, int L, int Dm, int V,
                                      float *__restrict__ x_f32, T *__restrict__ x_bf, T *__restrict__ s_bf,
-                                     int32_t *__restrict__ paths, float *__restrict__ cum, uint32_t *__restrict__ kcount)
+                                     int32_t *__restrict__ paths, float *__restrict__ cum)
 {
     const int m = blockIdx.x, b = m / W;
-    if (m == 0 && kcount)                                      // arrival counters of the split linear layers
-        for (int i = threadIdx.x; i < kSplitMaxGroups * kRowParts; i += blockDim.x) kcount[i] = 0;
     int tok = last_token[b];
     tok = tok < 0 ? 0 : (tok > V - 1 ? V - 1 : tok);
     for (int i = threadIdx.x * 8; i < Dm; i += blockDim.x * 8) {          // Dm is a multiple of 64
@@ -1039,8 +1123,11 @@ __global__ void rd_pack_weights_kernel(const uint16_t *__restrict__ src, int N, 
     *reinterpret_cast<uint4 *>(dst + (tile * 64 + lane) * 8) = v;
 }
 
+// Row tiles of rd_gemm_kernel's workgroups for a launch of `rows` rows (33 and more).
+int gemm_row_tiles(int rows) { return rows > 128 ? 16 : rows > 64 ? 8 : 4; }
+
 struct Plan {
-    size_t x_f32[3], x_bf[3], s_bf[2], logits, part_max, part_sum, part_cv, part_ci, row_score, row_tok, paths[2], cum[2], parent, tok, kcount, kpart, total;
+    size_t x_f32[3], x_bf[3], s_bf[2], logits, part_max, part_sum, part_cv, part_ci, row_score, row_tok, paths[2], cum[2], parent, tok, kpart, total;
 };
 
 Plan draft_plan(int B, int W, int L, int Dm, int V)
@@ -1063,8 +1150,7 @@ Plan draft_plan(int B, int W, int L, int Dm, int V)
     for (int i = 0; i < 2; ++i) { p.paths[i] = take(M * L * 4); p.cum[i] = take(M * 4); }
     p.parent = take(M * 4 * (size_t)(L > 1 ? L - 1 : 1));       // parent rows of every drafted position
     p.tok = take(M * 4);
-    p.kcount = take(kSplitMaxGroups * kRowParts * sizeof(uint32_t));
-    p.kpart = take(M > 32 ? (M + kRowsPerLaunch - 1) / kRowsPerLaunch * (size_t)kSplitMaxWgs * kSplitTiles * 1024 : 0);   // 33 rows and more: layers may split K over workgroups
+    p.kpart = take(M > 32 ? (size_t)kSplitMaxWgs * gemm_row_tiles((int)M) * kGemmCols * 1024 : 0);      // a launch's partial tiles
     p.total = off;
     return p;
 }
@@ -1110,72 +1196,27 @@ int launch_linear_nt(const LinArgs<T> &a, hipStream_t stream)
     return rd_check_launch();
 }
 
-// MLP layers at 33 rows and more: rd_head_rows_kernel with K split over as many workgroups per column group as bring 128
-// rows to about one workgroup per compute unit.  False if the shape does not fit.
-template <typename T, int MT>
-bool launch_mlp_rows(const LinArgs<T> &a, hipStream_t stream, int *status)
+// K split over as many workgroups per column group as bring the launch to about one per compute unit, with eight k-steps each
+// at least.
+template <typename T, int RT, int WR, int WC, int EPI>
+int launch_gemm(LinArgs<T> a, hipStream_t stream)
 {
-    static const int ks_env = rd::env_int("RD_DRAFT_KSPLIT", 0);
-    if (a.kpart == nullptr || ks_env == 1) return false;
-    static const int rows_on = rd::env_int("RD_DRAFT_MLP_ROWS", 1);
-    const int g128 = (a.N + 127) / 128, chunks = a.K1 / kRowsKC;
-    int sp = 0;
-    for (int c = 8; c >= 2 && sp == 0; c >>= 1)
-        if ((ks_env == 0 || ks_env == c) && g128 * c <= kSplitMaxWgs && chunks >= c) sp = c;
-    if (rows_on && a.K2 == 0 && a.map1 == nullptr && a.K1 % kRowsKC == 0 && g128 <= kSplitMaxGroups && sp) {
-        constexpr size_t smem = 2 * (size_t)MT * 16 * kRowsStride;
-        static std::atomic<unsigned long long> conf_t{0}, conf_r{0};
-        const void *fn = a.tiled ? reinterpret_cast<const void *>(&rd_head_rows_kernel<T, MT, true, EPI_MLP, true>)
-                                 : reinterpret_cast<const void *>(&rd_head_rows_kernel<T, MT, false, EPI_MLP, true>);
-        if (rd::ensure_dynamic_lds(fn, smem, a.tiled ? conf_t : conf_r) != RD_OK) { *status = RD_ERR_HIP; return true; }
-        LinArgs<T> b = a;
-        b.ksplit = sp;
-        const dim3 grid(a.parts > 1 ? (g128 * sp + 7) / 8 * 8 * a.parts : g128 * sp);
-        if (a.tiled) hipLaunchKernelGGL((rd_head_rows_kernel<T, MT, true, EPI_MLP, true>), grid, dim3(512), smem, stream, b);
-        else hipLaunchKernelGGL((rd_head_rows_kernel<T, MT, false, EPI_MLP, true>), grid, dim3(512), smem, stream, b);
-        *status = rd_check_launch();
-        return true;
-    }
-    return false;
-}
-
-// Layers with few columns at 17 rows and more: the widest workgroups the registers allow, and K
-// split over as many workgroups per column group as bring the launch to about one workgroup per
-// compute unit.  False if the shape does not fit (the caller then takes the unsplit kernels).
-template <typename T, int MT, int EPI>
-bool launch_linear_split(const LinArgs<T> &a, hipStream_t stream, int *status)
-{
-    if constexpr (MT >= 4 && EPI != EPI_HEAD) {
-        constexpr int NT = MT == 8 ? 4 : 8;
-        static_assert(MT * NT <= kSplitTiles, "partial tiles per workgroup");
-        constexpr int NWV = 8;                                  // 512 threads: <= 256 registers per lane, no accumulation registers
-        static const int ks_env = rd::env_int("RD_DRAFT_KSPLIT", 0);       // 1: never split; 2, 4, 8: only that split
-        constexpr int max_wgs = kSplitMaxWgs;                   // one workgroup of 8 waves per compute unit at this register count
-        if (a.kpart == nullptr || ks_env == 1) return false;
-        if constexpr (EPI == EPI_MLP) {
-            if (launch_mlp_rows<T, MT>(a, stream, status)) return true;
-        }
-        const int groups = (a.N + 16 * NT - 1) / (16 * NT);
-        if (groups > kSplitMaxGroups) return false;
-        const int ks1 = a.K1 / 32, ks = ks1 + a.K2 / 32;
-        auto ok = [&](int split) {                              // whole k-steps per wave, inside one product
-            if (groups * split > max_wgs || ks % (split * NWV) != 0) return false;
-            return a.K2 == 0 || ks1 % (ks / (split * NWV)) == 0;
-        };
-        int split = 0;
-        for (int c = 8; c >= 2 && split == 0; c >>= 1)
-            if ((ks_env == 0 || ks_env == c) && ok(c)) split = c;
-        if (split == 0) return false;
-        LinArgs<T> b = a;
-        b.ksplit = split;
-        const dim3 grid(groups * split);
-        if (a.tiled) hipLaunchKernelGGL((rd_linear_kernel<T, MT, NT, NWV, EPI, true, true>), grid, dim3(NWV * 64), 0, stream, b);
-        else hipLaunchKernelGGL((rd_linear_kernel<T, MT, NT, NWV, EPI, false, true>), grid, dim3(NWV * 64), 0, stream, b);
-        *status = rd_check_launch();
-        return true;
-    } else {
-        return false;
-    }
+    constexpr int CT = kGemmCols;
+    const int groups = (a.N + 16 * CT - 1) / (16 * CT), ks = (a.K1 + a.K2) / 32;
+    a.ksplit = groups < kSplitMaxWgs ? kSplitMaxWgs / groups : 1;
+    if (a.ksplit > ks / 8) a.ksplit = ks >= 8 ? ks / 8 : 1;
+    constexpr size_t smem = gemm_lds<RT, CT>();
+    static std::atomic<unsigned long long> conf_t{0}, conf_r{0};
+    const void *fn = a.tiled ? reinterpret_cast<const void *>(&rd_gemm_kernel<T, RT, CT, WR, WC, EPI, true>)
+                             : reinterpret_cast<const void *>(&rd_gemm_kernel<T, RT, CT, WR, WC, EPI, false>);
+    if (rd::ensure_dynamic_lds(fn, smem, a.tiled ? conf_t : conf_r) != RD_OK) return RD_ERR_HIP;
+    const dim3 grid((groups * a.ksplit + 7) / 8 * 8);
+    if (a.tiled) hipLaunchKernelGGL((rd_gemm_kernel<T, RT, CT, WR, WC, EPI, true>), grid, dim3(WR * WC * 64), smem, stream, a);
+    else hipLaunchKernelGGL((rd_gemm_kernel<T, RT, CT, WR, WC, EPI, false>), grid, dim3(WR * WC * 64), smem, stream, a);
+    if (a.ksplit == 1) return rd_check_launch();
+    const int tiles = (a.M + 15) / 16 * ((a.N + 15) / 16);
+    hipLaunchKernelGGL((rd_linear_finish_kernel<T, RT, CT, EPI>), dim3((tiles + 3) / 4), dim3(256), 0, stream, a);
+    return rd_check_launch();
 }
 
 // The output layer at 9 rows and more per launch, wide enough to cover half the chip with 128-column
@@ -1194,8 +1235,7 @@ bool launch_head_rows(const LinArgs<T> &a, hipStream_t stream, int *status)
         const void *fn = a.tiled ? reinterpret_cast<const void *>(&rd_head_rows_kernel<T, MT, true>)
                                  : reinterpret_cast<const void *>(&rd_head_rows_kernel<T, MT, false>);
         if (rd::ensure_dynamic_lds(fn, smem, a.tiled ? conf_t : conf_r) != RD_OK) { *status = RD_ERR_HIP; return true; }
-        const int g128 = (a.N + 127) / 128;
-        const dim3 grid(a.parts > 1 ? (g128 + 7) / 8 * 8 * a.parts : g128);
+        const dim3 grid((a.N + 127) / 128);
         if (a.tiled) hipLaunchKernelGGL((rd_head_rows_kernel<T, MT, true>), grid, dim3(512), smem, stream, a);
         else hipLaunchKernelGGL((rd_head_rows_kernel<T, MT, false>), grid, dim3(512), smem, stream, a);
         *status = rd_check_launch();
@@ -1205,67 +1245,52 @@ bool launch_head_rows(const LinArgs<T> &a, hipStream_t stream, int *status)
     }
 }
 
-// column tiles per workgroup: the most that still leave about one workgroup per compute unit (the
-// activation re-reads are MT : NT of the weight bytes, and measured they cost as much as the
+// Up to 32 rows without the column-split kernel: column tiles per workgroup, the most that still leave about one workgroup per
+// compute unit (the activation re-reads are MT : NT of the weight bytes, and measured they cost as much as the
 // weights' own stream; halving the workgroups below the number of compute units costs more)
 template <typename T, int MT, int EPI>
 int launch_linear_mt(const LinArgs<T> &a, hipStream_t stream)
 {
-    int status = RD_OK;
-    if (launch_linear_split<T, MT, EPI>(a, stream, &status)) return status;
-    if (launch_head_rows<T, MT, EPI>(a, stream, &status)) return status;
-    if constexpr (MT == 2 || MT == 4) {
+    if constexpr (MT == 2) {
         if (a.N >= 240 * 128) return launch_linear_nt<T, MT, 8, EPI>(a, stream);
-    }
-    if constexpr (MT >= 4) {                                    // (at 113 rows and more even half a chip of these beats narrower ones)
-        if (a.N >= (MT == 8 ? 128 : 256) * 64) return launch_linear_nt<T, MT, 4, EPI>(a, stream);
-    }
-    if constexpr (MT >= 2) {
-        // At 65 rows and more every workgroup reads all activations from L2, twice as often with one tile as with two:
-        // two tiles from 192 workgroups on (N = 6144..8191; 128 rows, us per call, one -> two tiles: 6200 tokens at a hidden
-        // size of 1024 160 -> 133 and at 4096 378 -> 270; MLP layers of 6272 and 8064 471 -> 414, 590 -> 514; hidden size
-        // 6272 527 -> 408, 8064 740 -> 593).  Not the RNN at hidden sizes that are odd multiples of 64, where only four
-        // waves share K and half as many workgroups leave a compute unit too few of them (80 rows: 6720 500 -> 540, 8128
-        // 637 -> 747; 128 rows: 7488 696 -> 727, 8128 770 -> 838), except above 96 rows below 208 workgroups (128 rows:
-        // 6208 544 -> 516, 6592 582 -> 570; but 80 rows 454 -> 469, 480 -> 506).
-        int least = 256;
-        if (MT == 8 && (EPI != EPI_RNN || a.K1 / 32 % 4 == 0 || (a.M > 96 && a.N < 208 * 32))) least = 192;
-        if (a.N >= least * 32) return launch_linear_nt<T, MT, 2, EPI>(a, stream);
+        if (a.N >= 256 * 32) return launch_linear_nt<T, MT, 2, EPI>(a, stream);
     }
     return launch_linear_nt<T, MT, 1, EPI>(a, stream);
 }
 
-// More than 128 rows: the output and MLP layers take them in one launch if the column-split kernel runs them (its
-// workgroups of 128 rows share the weights through L2; sums keep their order, so a row's result does not depend on the
-// number of rows) and the last 128 rows are not so few that another kernel would run them; else one launch per 128 rows,
-// each of which streams the weights again.  256 rows, Dm = 6656, 32000 tokens: 3201 -> 2790 us per call.  (Activations two
-// chunks ahead in registers instead of one: 4 % slower.)
+// Which kernel runs a layer.  rd_gemm_kernel, 256 rows at a time, from 33 rows on -- with fewer its partial sums cost more
+// than it saves (us per call at a hidden size of 4096 and 32000 tokens, all layers by it / as here: 16 rows 764 / 740, 32 rows
+// 822 / 803) -- but for the output layer up to 128 rows, which rd_head_rows_kernel runs without splitting K (64 rows 877 /
+// 861, 128 rows 1044 / 1012).
 template <typename T, int EPI>
 int launch_linear(const LinArgs<T> &all, hipStream_t stream)
 {
-    if constexpr (EPI != EPI_RNN) {
-        const int rest = (all.M - 1) % kRowsPerLaunch + 1;
-        if (all.M > kRowsPerLaunch && rest > (EPI == EPI_HEAD ? 8 : 32)) {
-            LinArgs<T> a = all;
-            a.parts = (all.M + kRowsPerLaunch - 1) / kRowsPerLaunch;
-            int status = RD_OK;
-            if constexpr (EPI == EPI_MLP) {
-                if (launch_mlp_rows<T, 8>(a, stream, &status)) return status;
-            } else {
-                if (launch_head_rows<T, 8, EPI>(a, stream, &status)) return status;
-            }
-        }
-    }
-    for (int m0 = 0; m0 < all.M; m0 += kRowsPerLaunch) {
+    for (int m0 = 0, rows; m0 < all.M; m0 += rows) {
+        rows = all.M - m0 < 256 ? all.M - m0 : 256;
         LinArgs<T> a = all;
         a.m0 = m0;
-        a.M = all.M - m0 < kRowsPerLaunch ? all.M - m0 : kRowsPerLaunch;
-        const int mt = (a.M + 15) / 16;
-        int st;
-        if (mt <= 1) st = launch_linear_mt<T, 1, EPI>(a, stream);
-        else if (mt <= 2) st = launch_linear_mt<T, 2, EPI>(a, stream);
-        else if (mt <= 4) st = launch_linear_mt<T, 4, EPI>(a, stream);
-        else st = launch_linear_mt<T, 8, EPI>(a, stream);
+        a.M = rows;
+        const int mt = (rows + 15) / 16;
+        int st = RD_OK;
+        bool done = false;
+        if constexpr (EPI == EPI_HEAD) {
+            if (mt <= 1) done = launch_head_rows<T, 1, EPI>(a, stream, &st);
+            else if (mt <= 2) done = launch_head_rows<T, 2, EPI>(a, stream, &st);
+            else if (mt <= 4) done = launch_head_rows<T, 4, EPI>(a, stream, &st);
+            else if (mt <= 8) done = launch_head_rows<T, 8, EPI>(a, stream, &st);
+        }
+        if (!done) {
+            if (all.M > 32) {                                   // (the workspace holds its partial sums only then)
+                const int rt = gemm_row_tiles(rows);
+                if (rt == 16) st = launch_gemm<T, 16, 2, 4, EPI>(a, stream);
+                else if (rt == 8) st = launch_gemm<T, 8, 2, 4, EPI>(a, stream);
+                else st = launch_gemm<T, 4, 1, 8, EPI>(a, stream);
+            } else if (mt <= 1) {
+                st = launch_linear_mt<T, 1, EPI>(a, stream);
+            } else {
+                st = launch_linear_mt<T, 2, EPI>(a, stream);
+            }
+        }
         if (st != RD_OK) return st;
     }
     return RD_OK;
@@ -1296,16 +1321,15 @@ int draft_run(const rd_draft_params *p, const void *h, const int32_t *last_token
     int32_t *paths[2] = {reinterpret_cast<int32_t *>(ws + plan.paths[0]), reinterpret_cast<int32_t *>(ws + plan.paths[1])};
     float *cum[2] = {reinterpret_cast<float *>(ws + plan.cum[0]), reinterpret_cast<float *>(ws + plan.cum[1])};
     int32_t *parent = reinterpret_cast<int32_t *>(ws + plan.parent), *tok = reinterpret_cast<int32_t *>(ws + plan.tok);
-    uint32_t *kcount = reinterpret_cast<uint32_t *>(ws + plan.kcount);
-    float *kpart = M > 32 ? reinterpret_cast<float *>(ws + plan.kpart) : nullptr;
+    float *kpart = reinterpret_cast<float *>(ws + plan.kpart);
     const E *emb = static_cast<const E *>(p->emb);
 
     hipLaunchKernelGGL(rd_draft_init_kernel<E>, dim3(M), dim3(256), 0, s, emb, static_cast<const E *>(h), last_token,
-                       W, L, Dm, V, x_f32[0], x_bf[0], s_bf[0], paths[0], cum[0], kcount);
+                       W, L, Dm, V, x_f32[0], x_bf[0], s_bf[0], paths[0], cum[0]);
     if (rd_check_launch() != RD_OK) return RD_ERR_HIP;
     if (T == 0) {                                   // nothing to draft: the candidates are the LLM's token alone
         hipLaunchKernelGGL(rd_draft_init_kernel<E>, dim3(M), dim3(256), 0, s, emb, static_cast<const E *>(h), last_token,
-                           W, L, Dm, V, x_f32[0], x_bf[0], s_bf[0], beams, beam_logp, kcount);
+                           W, L, Dm, V, x_f32[0], x_bf[0], s_bf[0], beams, beam_logp);
         return rd_check_launch();
     }
     // the h half of X0 must survive the MLP ping-pong: layers write X1 and X2 only
@@ -1317,7 +1341,7 @@ int draft_run(const rd_draft_params *p, const void *h, const int32_t *last_token
             a.w1 = static_cast<const E *>(p->rnn_u); a.x1 = s_bf[si]; a.map1 = parent + (size_t)(t - 2) * M; a.ldx1 = Dm; a.K1 = Dm;
             a.w2 = static_cast<const E *>(p->rnn_w); a.x2 = emb; a.map2 = tok; a.ldx2 = Dm; a.K2 = Dm;
             a.bias = p->rnn_b; a.M = M; a.N = Dm; a.mstride = 1; a.tiled = p->tiled;
-            a.y_f32 = x_f32[0]; a.y_bf = x_bf[0]; a.s_bf = s_bf[si ^ 1]; a.ldy = G; a.kpart = kpart; a.kcount = kcount;
+            a.y_f32 = x_f32[0]; a.y_bf = x_bf[0]; a.s_bf = s_bf[si ^ 1]; a.ldy = G; a.kpart = kpart;
             if (launch_linear<E, EPI_RNN>(a, s) != RD_OK) return RD_ERR_HIP;
             si ^= 1;
         }
@@ -1329,7 +1353,7 @@ int draft_run(const rd_draft_params *p, const void *h, const int32_t *last_token
             LinArgs<E> a = {};
             a.w1 = static_cast<const E *>(p->mlp_w) + (size_t)k * G * G; a.x1 = x_bf[in]; a.ldx1 = G; a.K1 = G;
             a.bias = p->mlp_b + (size_t)k * G; a.M = rows; a.N = G; a.mstride = mstride; a.tiled = p->tiled;
-            a.y_f32 = x_f32[out]; a.y_bf = x_bf[out]; a.res = x_f32[in]; a.ldy = G; a.kpart = kpart; a.kcount = kcount;
+            a.y_f32 = x_f32[out]; a.y_bf = x_bf[out]; a.res = x_f32[in]; a.ldy = G; a.kpart = kpart;
             if (launch_linear<E, EPI_MLP>(a, s) != RD_OK) return RD_ERR_HIP;
             in = out;
         }
@@ -1337,7 +1361,7 @@ int draft_run(const rd_draft_params *p, const void *h, const int32_t *last_token
             LinArgs<E> a = {};
             a.w1 = static_cast<const E *>(p->head_w); a.x1 = x_bf[in]; a.ldx1 = G; a.K1 = G;
             if (step_logits) logits = step_logits + (size_t)(t - 1) * M * V;   // every position keeps its matrix
-            a.M = rows; a.N = V; a.mstride = mstride; a.tiled = p->tiled; a.y_f32 = logits; a.ldy = V;
+            a.M = rows; a.N = V; a.mstride = mstride; a.tiled = p->tiled; a.y_f32 = logits; a.ldy = V; a.kpart = kpart;
             if (launch_linear<E, EPI_HEAD>(a, s) != RD_OK) return RD_ERR_HIP;
         }
         // from 16 candidates on (and while four lists per chunk fit the row pass's 64 lanes) the chunk pass

@@ -106,6 +106,38 @@ __device__ __forceinline__ void st_dev4(float *p, float a, float b, float c, flo
 // L2, which is what the exchange avoids.
 __device__ __forceinline__ void wait_dev_stores() { asm volatile("s_waitcnt vmcnt(0)" : : : "memory"); }
 
+// ---- memory straight into LDS -------------------------------------------------------------------------
+// Copies 1 KB of memory into LDS, 16 bytes per lane, without passing through registers: lane l's bytes come from
+// base + off and land at lds + 16 l.  Complete when the wave's count of vector memory operations says so (wait_vm);
+// loads return in the order they were issued.  The compiler knows nothing of these loads: whoever reads the bytes waits,
+// and no wave ends or lets its LDS go with one under way.  (m0 holds the destination; nothing else here uses it.)
+__device__ __forceinline__ uintptr_t uniform(uintptr_t x)         // (in scalar registers, whatever it was computed in)
+{
+    return (uintptr_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)x) | (uintptr_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(x >> 32)) << 32;
+}
+__device__ __forceinline__ void dma16(uintptr_t base, uint32_t off, uint32_t lds)
+{
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" : : "s"(__builtin_amdgcn_readfirstlane((int)lds)), "v"(off), "s"(uniform(base)) : "memory");
+}
+// The same from an address per lane.
+__device__ __forceinline__ void dma16(uintptr_t lane_address, uint32_t lds)
+{
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" : : "s"(__builtin_amdgcn_readfirstlane((int)lds)), "v"(lane_address) : "memory");
+}
+__device__ __forceinline__ void dma4(uintptr_t lane_address, uint32_t lds)
+{
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, off" : : "s"(__builtin_amdgcn_readfirstlane((int)lds)), "v"(lane_address) : "memory");
+}
+// 4 bytes per lane, from base + off.
+__device__ __forceinline__ void dma4(uintptr_t base, uint32_t off, uint32_t lds)
+{
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, %2" : : "s"(__builtin_amdgcn_readfirstlane((int)lds)), "v"(off), "s"(uniform(base)) : "memory");
+}
+// Returns when at most N of the wave's vector memory operations are outstanding.
+template <int N> __device__ __forceinline__ void wait_vm() { asm volatile("s_waitcnt vmcnt(%0)" : : "n"(N) : "memory"); }
+// Returns when the wave's LDS reads are in registers.
+__device__ __forceinline__ void wait_lds() { asm volatile("s_waitcnt lgkmcnt(0)" : : : "memory"); }
+
 // ---- rows of any length in 16-byte loads --------------------------------------------------------------
 // Rows of V floats start at multiples of 4 bytes only, unless V is a multiple of 4; global memory instructions of any
 // width need no more.  (Scalar loads for such rows cost a vocabulary-wide pass two to three times its time.)

@@ -106,46 +106,15 @@ __device__ __forceinline__ uint4 rope8(uint4 x, uint4 partner, const float (&cs)
     return __builtin_bit_cast(uint4, y);
 }
 
-// Copies 1 KB of memory into LDS, 16 bytes per lane, without passing through registers: lane l's bytes come from
-// base + off and land at lds + 16 l.  Complete when the wave's count of vector memory operations says so (wait_vm);
-// loads return in the order they were issued.  The compiler knows nothing of these loads: whoever reads the bytes waits,
-// and no wave ends or lets its LDS go with one under way.  (m0 holds the destination; nothing else here uses it.)
-__device__ __forceinline__ uintptr_t uniform(uintptr_t x)         // (in scalar registers, whatever it was computed in)
-{
-    return (uintptr_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)x) | (uintptr_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(x >> 32)) << 32;
-}
-__device__ __forceinline__ void dma16(uintptr_t base, uint32_t off, uint32_t lds)
-{
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" : : "s"(__builtin_amdgcn_readfirstlane((int)lds)), "v"(off), "s"(uniform(base)) : "memory");
-}
-// The same from an address per lane.
-__device__ __forceinline__ void dma16(uintptr_t lane_address, uint32_t lds)
-{
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" : : "s"(__builtin_amdgcn_readfirstlane((int)lds)), "v"(lane_address) : "memory");
-}
-__device__ __forceinline__ void dma4(uintptr_t lane_address, uint32_t lds)
-{
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, off" : : "s"(__builtin_amdgcn_readfirstlane((int)lds)), "v"(lane_address) : "memory");
-}
-// 4 bytes per lane, from base + off.
-__device__ __forceinline__ void dma4(uintptr_t base, uint32_t off, uint32_t lds)
-{
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, %2" : : "s"(__builtin_amdgcn_readfirstlane((int)lds)), "v"(off), "s"(uniform(base)) : "memory");
-}
-// Returns when at most N of the wave's vector memory operations are outstanding.
-template <int N> __device__ __forceinline__ void wait_vm() { asm volatile("s_waitcnt vmcnt(%0)" : : "n"(N) : "memory"); }
-// Returns when the wave's LDS reads are in registers.
-__device__ __forceinline__ void wait_lds() { asm volatile("s_waitcnt lgkmcnt(0)" : : : "memory"); }
+// Floats between rows of the waves' statistics: eight waves' 16 rows in distinct banks.  (Four waves and three row tiles: with
+// more than four floats a row the second workgroup does not fit the compute unit's LDS.)
+constexpr int stat_stride(int waves) { return waves == 8 ? 12 : 4; }
 
 // NW = waves per workgroup (4 or 8); NQ = row tiles (16 packed rows).
 // PAGED: the context keys and values live in fixed-size pages found through a block table
 // (a.block_table, a.page_size, a.max_pages) instead of one dense [B,H,Cmax,D] tensor.
 // ROPE: q and k_new arrive unrotated; the kernel applies the rotary embedding at a.position_ids
 // to the query rows as it brings them into LDS and to the packed-key tiles as it walks them.
-// Floats between rows of the waves' statistics: eight waves' 16 rows in distinct banks.  (Four waves and three row tiles: with
-// more than four floats a row the second workgroup does not fit the compute unit's LDS.)
-constexpr int stat_stride(int waves) { return waves == 8 ? 12 : 4; }
-
 template <typename T, int D, int NQ, int NW, bool PAGED, bool ROPE>
 __global__ __launch_bounds__(NW * 64, 2) void rd_tree_attn_mfma_kernel(AttnArgs a)
 {
