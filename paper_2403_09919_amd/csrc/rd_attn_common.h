@@ -21,7 +21,7 @@ struct AttnPlan {
     int rg_tiles;      // 16-row tiles of packed rows per workgroup (a row group)
     int n_rg;          // row groups per (sequence, head); 1 unless N is large
     int ranges;        // key ranges per row group at most
-    int reserved;      // (no padding: plans are compared as bytes)
+    int sorted;        // long sequences first: more workgroups than the chip holds, of eight tiles per wave and more
     size_t counters_bytes;
     size_t total_bytes;
 };
@@ -73,18 +73,20 @@ static inline double attn_search(int n_rg, int n_act, int nblk, bool every, doub
 // Plan of the matrix-core kernel (rd_tree_attn_mfma.h), for contexts of up to Cmax keys: waves per workgroup and key ranges
 // per row group, from an estimate of the launch time.  Lengths are upper bounds and the packed rows are not known at all
 // here (distinct prefixes are taken to be 0.6 of the candidates' tokens, less of wide beams); the kernel deals the tiles it finds to the ranges
-// and starts no more row groups than hold packed rows.  The constants are fitted to 1080 launches on MI355X (60 shapes, four
+// and starts no more row groups than hold packed rows.  The constants are fitted to 1320 launches on MI355X (100 shapes, four
 // and eight waves, 1 to 20 ranges), us, with r = row tiles that hold packed rows:
 //   * a workgroup takes 2.8 (four waves) or 3.8 (eight), and 1.15 or 0.6 for at most one tile per wave, else 0.62 + 0.22 r or
 //     0.85 + 0.25 r per tile of a wave (D = 64: 0.65 of that) and 0.7 r or 0.95 r where the waves' states meet;
 //   * one eight-wave workgroup fills a compute unit, two of four waves do; more start as those retire;
-//   * the workgroups that run at one time share 6.6 (four waves) or 5.9 TB/s, a compute unit gets 51 GB/s at most, and one
-//     with two workgroups takes twice as long as one with one (the rest of the chip then idles, which leaves the others more:
-//     half of that is counted); latency and bandwidth overlap but for where they are close (fourth root of the sum of fourth
-//     powers);
+//   * the workgroups that run at one time share 6.6 (four waves) or 5.9 TB/s of HBM, of which row groups of a range take one
+//     share together, a compute unit gets 51 GB/s at most, and one with two workgroups takes twice as long as one with one (the
+//     rest of the chip then idles, which leaves the others more: half of that is counted); latency and bandwidth overlap but
+//     for where they are close (fourth root of the sum of fourth powers);
 //   * more than one range adds a merge: 1.6, the partial results read by one compute unit at 48 GB/s, and all of them
 //     written and read at 4.6 TB/s.
-// Over those shapes the choice is 2.2 % slower than the best of the 18 in the mean, 18 % at worst (5 heads, C=6000, 350 tokens).
+// Several row groups take four waves: their number is only guessed here, and where one more than that no longer fits the chip
+// eight waves take two rounds (H=32, C=1777, 350 tokens: 21.9 us with 4 groups of packed rows, 36.6 with 5; four waves 21.5
+// and 29.7).  Over 100 shapes the choice is 1.4 % slower than the best of the 18 in the mean, 17 % at worst.
 static inline AttnPlan attn_plan_make(int B, int H, int N, int D, int Cmax, bool every = false)
 {
     const long long BH = (long long)B * H;
@@ -98,7 +100,7 @@ static inline AttnPlan attn_plan_make(int B, int H, int N, int D, int Cmax, bool
     AttnPlan best = {};
     double best_T = 1e30;
     for (int waves = 8; waves >= 4; waves -= 4) {
-        if (waves_env && waves != waves_env) continue;
+        if (waves_env ? waves != waves_env : waves == 8 && n_rg > 1) continue;
         const int nblk = tiles > waves ? (tiles + waves - 1) / waves : 1, most = nblk < 64 ? nblk : 64;
         const int forced = forced_env > most ? most : forced_env;
         const double t_tile = scale * (waves == 8 ? 0.85 + 0.25 * r : 0.62 + 0.22 * r), t_meet = scale * r * (waves == 8 ? 0.95 : 0.7);
@@ -108,12 +110,13 @@ static inline AttnPlan attn_plan_make(int B, int H, int N, int D, int Cmax, bool
             const int per = (tiles + R - 1) / R, steps = (per + waves - 1) / waves;
             // more ranges with as many tiles per wave take no less time: only the fewest of them are looked at (`every`: all; they agree)
             if (!every && forced <= 0 && R > 1 && steps == ((tiles + R - 2) / (R - 1) + waves - 1) / waves) continue;
-            const double t_lat = t_wg + (steps == 1 ? t_one : steps * t_tile + t_meet), bytes = (double)(steps * waves < tiles ? steps * waves : tiles) * 32 * D * 4 / n_act;
+            const double t_lat = t_wg + (steps == 1 ? t_one : steps * t_tile + t_meet);
+            const double all = (double)(steps * waves < tiles ? steps * waves : tiles) * 32 * D * 4;      // of K and V, for a workgroup
             const long long wgs = (BH + 7) / 8 * 8 * n_act * R, full = wgs / slots, rest = wgs % slots;
             auto round = [&](long long n) {
                 const long long per_cu = (n + 255) / 256;
                 const double sharing = ((n < 256 ? n : 256) + (double)n / per_cu) / 2;
-                const double t_bw = per_cu * bytes / (rate / sharing < 51e3 ? rate / sharing : 51e3);
+                const double t_hbm = per_cu * all / n_act * sharing / rate, t_cu = per_cu * all / 51e3, t_bw = t_hbm > t_cu ? t_hbm : t_cu;
                 const double l2 = t_lat * t_lat, b2 = t_bw * t_bw;
                 return sqrt(sqrt(l2 * l2 + b2 * b2));
             };
@@ -124,6 +127,7 @@ static inline AttnPlan attn_plan_make(int B, int H, int N, int D, int Cmax, bool
                 best.waves = waves;
                 best.S = R * n_rg;
                 best.ranges = R;
+                best.sorted = B > 1 && wgs > slots && steps >= 8;
                 best.rg_tiles = nq;
                 best.n_rg = n_rg;
                 best.counters_bytes = counters_bytes;
@@ -201,6 +205,7 @@ struct AttnArgs {
     int B, H, N, Cmax, S, words;
     int n_rg;      // row groups per (sequence, head) (each is NQ*16 rows of the kernel's template)
     int ranges;    // key ranges per row group at most
+    int sorted;    // workgroups of long sequences first
     float scale_log2e;
     // rotary embedding fused into the call (rd_tree_attn_rope); unused (null) otherwise
     const int32_t *position_ids;   // [B, N]

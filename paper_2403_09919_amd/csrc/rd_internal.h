@@ -124,10 +124,6 @@ __device__ __forceinline__ void dma16(uintptr_t lane_address, uint32_t lds)
 {
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" : : "s"(__builtin_amdgcn_readfirstlane((int)lds)), "v"(lane_address) : "memory");
 }
-__device__ __forceinline__ void dma4(uintptr_t lane_address, uint32_t lds)
-{
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, off" : : "s"(__builtin_amdgcn_readfirstlane((int)lds)), "v"(lane_address) : "memory");
-}
 // 4 bytes per lane, from base + off.
 __device__ __forceinline__ void dma4(uintptr_t base, uint32_t off, uint32_t lds)
 {

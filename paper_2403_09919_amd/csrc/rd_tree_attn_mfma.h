@@ -150,7 +150,7 @@ __global__ __launch_bounds__(NW * 64, 2) void rd_tree_attn_mfma_kernel(AttnArgs 
     RD_TR(0);
     // All arguments are fetched here, together: as the compiler places the loads they are a chain of four, 0.3 us each.
     asm volatile("" : : "s"(a.q), "s"(a.k_cache), "s"(a.v_cache), "s"(a.k_new), "s"(a.v_new), "s"(a.ctx_len), "s"(a.n_packed), "s"(a.mask_bits),
-                 "s"(a.B), "s"(a.H), "s"(a.N), "s"(a.Cmax), "s"(a.S), "s"(a.words), "s"(a.n_rg), "s"(a.ranges));
+                 "s"(a.B), "s"(a.H), "s"(a.N), "s"(a.Cmax), "s"(a.S), "s"(a.words), "s"(a.n_rg), "s"(a.ranges), "s"(a.sorted));
     if constexpr (ROPE) asm volatile("" : : "s"(a.position_ids), "s"(a.cos_tab), "s"(a.sin_tab), "s"(a.max_pos));
     if constexpr (PAGED) asm volatile("" : : "s"(a.block_table), "s"(a.page_size), "s"(a.max_pages), "s"(a.n_pages));
 
@@ -164,24 +164,46 @@ __global__ __launch_bounds__(NW * 64, 2) void rd_tree_attn_mfma_kernel(AttnArgs 
     const int xcd = (int)(blockIdx.x & 7), n_rg = a.n_rg;
     const int ranges = a.ranges;
     int bh, b, r_wg, n_act = 1;                                 // n_act row groups times ranges: the head's workgroups
-    if (n_rg == 1) {
+    if (n_rg == 1 && !a.sorted) {
         const int k = (int)(blockIdx.x >> 3), hl = ranges == 1 ? k : k / ranges;
         r_wg = k - hl * ranges;
         bh = hl * 8 + xcd;
         if (bh >= a.B * a.H) return;
         b = a.B == 1 ? 0 : bh / a.H;
+    } else if (a.B == 1) {                    // only row groups that hold packed rows get workgroups
+        n_act = max((clampi(packed[0], 0, a.N) + kRows - 1) / kRows, 1);
+        const int k = (int)(blockIdx.x >> 3), n_wg = n_act * ranges, hl = k / n_wg;
+        r_wg = k - hl * n_wg;
+        bh = hl * 8 + xcd;
+        if (bh >= a.H) return;
+        b = 0;
     } else {
         // Only row groups that hold packed rows get workgroups, so their number is the sequence's own: a lane counts those of
         // one sequence's heads on this XCD, and a running sum finds the workgroup's place.  (Workgroups without work in between
         // leave compute units idle beside others that have two: 29 us for 22 at H=32, C=1777, 147 of 350 rows.)
         const int k = (int)(blockIdx.x >> 3);
         int before = 0, at = -1, b0 = 0;
-        int act, first, need, sum;
+        // Where there are more workgroups than fit the chip at once, those of long sequences come first (a.sorted).
+        int seq, act, first, need, sum;
         for (; b0 < a.B; b0 += 64) {
-            const int s = min(b0 + lane, a.B - 1);
-            act = max((clampi(a.n_packed[s], 0, a.N) + kRows - 1) / kRows, 1);
+            const int here = min(a.B - b0, 64);
+            seq = min(lane, here - 1);
+            int rows = a.n_packed[b0 + seq];
+            if (a.sorted) {
+                const int keys = lane < here ? a.ctx_len[b0 + seq] : -1;
+                int place = 0;
+                for (int j = 0; j < here; ++j) {
+                    const int other = __builtin_amdgcn_readlane(keys, j);
+                    place += other > keys || (other == keys && j < lane) ? 1 : 0;
+                }
+                place = lane < here ? place : lane;             // (a permutation of the lanes)
+                seq = __builtin_amdgcn_ds_permute(place * 4, seq);
+                rows = __builtin_amdgcn_ds_permute(place * 4, rows);
+            }
+            const int s = b0 + seq;
+            act = max((clampi(rows, 0, a.N) + kRows - 1) / kRows, 1);
             first = (s * a.H + 7 - xcd) >> 3;
-            need = b0 + lane < a.B ? ((((s + 1) * a.H + 7 - xcd) >> 3) - first) * act * ranges : 0;
+            need = lane < here ? ((((s + 1) * a.H + 7 - xcd) >> 3) - first) * act * ranges : 0;
             sum = need;
 #pragma unroll
             for (int o = 1; o < 64; o <<= 1) {
@@ -199,11 +221,12 @@ __global__ __launch_bounds__(NW * 64, 2) void rd_tree_attn_mfma_kernel(AttnArgs 
         n_act = __builtin_amdgcn_readlane(act, at);
         const int n_wg = n_act * ranges, own = k - (before + __builtin_amdgcn_readlane(sum, at) - __builtin_amdgcn_readlane(need, at)), hl = own / n_wg;
         r_wg = own - hl * n_wg;
-        b = b0 + at;
+        b = b0 + __builtin_amdgcn_readlane(seq, at);
         bh = (__builtin_amdgcn_readlane(first, at) + hl) * 8 + xcd;
-        // output rows of the groups without packed rows are zero
+    }
+    if (n_rg > 1) {                           // output rows of the groups without packed rows are zero
         T *z = static_cast<T *>(a.out) + (size_t)bh * a.N * D;
-        for (int i = n_act * kRows * D + (r_wg * NW * 64 + tid) * 8; i < a.N * D; i += n_wg * NW * 64 * 8)
+        for (int i = n_act * kRows * D + (r_wg * NW * 64 + tid) * 8; i < a.N * D; i += n_act * ranges * NW * 64 * 8)
             *reinterpret_cast<uint4 *>(z + i) = make_uint4(0, 0, 0, 0);
     }
     const int C_b = ctx_len[b], P_b = packed[b];
@@ -212,44 +235,29 @@ __global__ __launch_bounds__(NW * 64, 2) void rd_tree_attn_mfma_kernel(AttnArgs 
     const int Ng = min(kRows, a.N - row0);                      // rows of `out` this group owns
     const int lrow = lane / G::kChunks, lchunk = lane % G::kChunks;
 
-    // ---- Q -> LDS, rows in K's order.  With the rotation a wave turns every NW-th (row tile, k-step) of the staged rows:
-    // the cosines and sines of a lane's pairs (k-steps t and t + KS/2) pass through the wave's V tile, which is fetched
-    // behind them, so that no wait for them is a wait for K and V.
+    // ---- Q -> LDS, rows in K's order: copied, or (rotation) through registers, a wave every NW-th (row tile, k-steps t and
+    // t + KS/2, which hold a lane's pairs).
     const uintptr_t Qb = reinterpret_cast<uintptr_t>(a.q) + ((size_t)bh * a.N + row0) * RB;
     constexpr int kQPieces = kRows * RB / 1024;
     constexpr int kQFrags = NQ * KS / 2, kQPer = (kQFrags + NW - 1) / NW;
-    static_assert(!ROPE || kQPer * 4096 <= G::kTileBytes, "cosines and sines of a wave's part of Q fit its V tile");
-    const bool tab16 = ROPE && ((reinterpret_cast<uintptr_t>(a.cos_tab) | reinterpret_cast<uintptr_t>(a.sin_tab)) & 15) == 0;      // (the tables may lie at any multiple of 4 bytes)
+    const int op_rd = r16 * RB + kswz<D>(r16, g) * 16;          // operand order: row r16 of a tile, 16-byte piece 4t + g
     int qpos[kQPer], kpos[2] = {0, 0};                          // kpos: of the first packed-key tile
-    if constexpr (ROPE) {
-#pragma unroll
-        for (int i = 0; i < kQPer; ++i)
-            qpos[i] = a.position_ids[(size_t)b * a.N + row0 + min(min(wave + NW * i, kQFrags - 1) / (KS / 2) * 16 + r16, Ng - 1)];
-#pragma unroll
-        for (int mt = 0; mt < 2; ++mt) kpos[mt] = a.position_ids[(size_t)b * a.N + min(mt * 16 + r16, a.N - 1)];
-    }
-    for (int p = wave; p < kQPieces; p += NW) {
-        const int row = p * G::kRowsPerLoad + lrow;
-        dma16(Qb, (uint32_t)(min(row, Ng - 1) * RB + kswz<D>(row, lchunk) * 16), ldsQ + p * 1024);
-    }
+    uint4 qlo[kQPer], qhi[kQPer];
     if constexpr (ROPE) {
 #pragma unroll
         for (int i = 0; i < kQPer; ++i) {
-            const int f = min(wave + NW * i, kQFrags - 1);
-            const size_t ang = (size_t)clampi(qpos[i], 0, a.max_pos - 1) * (D / 2) + (4 * (f % (KS / 2)) + g) * 8;
-            const uintptr_t cb = reinterpret_cast<uintptr_t>(a.cos_tab + ang), sb = reinterpret_cast<uintptr_t>(a.sin_tab + ang);
-            if (tab16) {
+            const int f = min(wave + NW * i, kQFrags - 1), row = min(f / (KS / 2) * 16 + r16, Ng - 1);
+            qpos[i] = a.position_ids[(size_t)b * a.N + row0 + row];
+            const unsigned char *q = reinterpret_cast<const unsigned char *>(Qb) + row * RB + (4 * (f % (KS / 2)) + g) * 16;
+            qlo[i] = ldg16(q);
+            qhi[i] = ldg16(q + D);
+        }
 #pragma unroll
-                for (int e = 0; e < 2; ++e) {
-                    dma16(cb + e * 16, ldsV + (4 * i + e) * 1024);
-                    dma16(sb + e * 16, ldsV + (4 * i + 2 + e) * 1024);
-                }
-            } else {
-                for (int e = 0; e < 8; ++e) {
-                    dma4(cb + e * 4, ldsV + 4 * i * 1024 + e * 256);
-                    dma4(sb + e * 4, ldsV + (4 * i + 2) * 1024 + e * 256);
-                }
-            }
+        for (int mt = 0; mt < 2; ++mt) kpos[mt] = a.position_ids[(size_t)b * a.N + min(mt * 16 + r16, a.N - 1)];
+    } else {
+        for (int p = wave; p < kQPieces; p += NW) {
+            const int row = p * G::kRowsPerLoad + lrow;
+            dma16(Qb, (uint32_t)(min(row, Ng - 1) * RB + kswz<D>(row, lchunk) * 16), ldsQ + p * 1024);
         }
     }
 
@@ -316,57 +324,41 @@ __global__ __launch_bounds__(NW * 64, 2) void rd_tree_attn_mfma_kernel(AttnArgs 
     const uint32_t mask_row = (uint32_t)min(row0 + lane, a.N - 1) * (uint32_t)a.words * 8;
     auto copy_mask = [&](int tile) __attribute__((always_inline)) { dma4(mask_b + (size_t)clampi(tile - nA, 0, 2 * a.words - 1) * 4, mask_row, ldsMask); };
 
-    // ---- the first tile
+    // ---- the first tile.  A wave that turns rows of Q asks for its tile behind that (the wait for the angles would else be one
+    // for K and V), the other waves' tiles keep the memory busy meanwhile.
+    const int nqt = (P + 15) >> 4;
     int page = page_of(t_first);
     const bool some = t_first < tile_end;
-    const size_t off_first = tile_off(t_first, page);
-    if (some) {
-        copy_mask(t_first);
-        copy_k((t_first >= nA ? Kn : Kc) + off_first, tile_keys(t_first));
-        if constexpr (ROPE) {
-            wait_vm<kLoads + 1>();            // this wave's part of Q and its angles are there
-        } else {
-            copy_v((t_first >= nA ? Vn : Vc) + off_first, tile_keys(t_first));
-            wait_vm<2 * kLoads + 1>();        // this wave's part of Q is there
-        }
-    } else {
-        wait_vm<0>();
-    }
-    page = page_of(t_first + NW);
-    const int op_rd = r16 * RB + kswz<D>(r16, g) * 16;          // operand order: row r16 of a tile, 16-byte piece 4t + g
     if constexpr (ROPE) {
-        RD_TR(9);
-        lds_barrier();                        // Q visible to all waves
 #pragma unroll
         for (int i = 0; i < kQPer; ++i) {
-            const int f = wave + NW * i;
-            if (f < kQFrags) {
-                const float *ang = reinterpret_cast<const float *>(sV + wave * G::kTileBytes + 4 * i * 1024);
+            const int f = wave + NW * i, t = f % (KS / 2);
+            if (f < kQFrags && f / (KS / 2) < nqt) {
+                const size_t o = (size_t)clampi(qpos[i], 0, a.max_pos - 1) * (D / 2) + (4 * t + g) * 8;
                 float cs[8], sn[8];
 #pragma unroll
-                for (int e = 0; e < 8; ++e) {
-                    const int o = tab16 ? (e / 4) * 256 + lane * 4 + e % 4 : e * 64 + lane;
-                    cs[e] = ang[o];
-                    sn[e] = ang[512 + o];
-                }
-                const int t = f % (KS / 2);
+                for (int e = 0; e < 8; ++e) { cs[e] = a.cos_tab[o + e]; sn[e] = a.sin_tab[o + e]; }
                 unsigned char *q = sQ + f / (KS / 2) * 16 * RB;
-                uint4 *lo = reinterpret_cast<uint4 *>(q + (op_rd ^ (4 * t * 16))), *hi = reinterpret_cast<uint4 *>(q + (op_rd ^ (4 * (t + KS / 2) * 16)));
-                const uint4 x = *lo, y = *hi;
-                *lo = rope8<T>(x, y, cs, sn, true);
-                *hi = rope8<T>(y, x, cs, sn, false);
+                *reinterpret_cast<uint4 *>(q + (op_rd ^ (4 * t * 16))) = rope8<T>(qlo[i], qhi[i], cs, sn, true);
+                *reinterpret_cast<uint4 *>(q + (op_rd ^ (4 * (t + KS / 2) * 16))) = rope8<T>(qhi[i], qlo[i], cs, sn, false);
             }
         }
-        RD_TR(10);
-        lds_barrier();                        // rotated Q visible to all waves
-        RD_TR(1);
-        if (some) copy_v((t_first >= nA ? Vn : Vc) + off_first, tile_keys(t_first));
-    } else {
-        lds_barrier();                        // Q visible to all waves
-        RD_TR(1);
     }
+    if (some) {
+        const size_t off = tile_off(t_first, page);
+        copy_mask(t_first);
+        copy_k((t_first >= nA ? Kn : Kc) + off, tile_keys(t_first));
+        copy_v((t_first >= nA ? Vn : Vc) + off, tile_keys(t_first));
+    }
+    page = page_of(t_first + NW);
+    if constexpr (!ROPE) {
+        if (some) wait_vm<2 * kLoads + 1>();  // this wave's part of Q is there
+        else wait_vm<0>();
+    }
+    RD_TR(9);
+    lds_barrier();                            // Q visible to all waves
+    RD_TR(1);
 
-    const int nqt = (P + 15) >> 4;
     const float c_abs = fabsf(a.scale_log2e);
     const bool c_neg = a.scale_log2e < 0.f;
     auto op = [&](const unsigned char *tile, int mt, int t) __attribute__((always_inline)) {
