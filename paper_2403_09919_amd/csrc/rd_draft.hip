@@ -358,7 +358,7 @@ __global__ __launch_bounds__(512) void rd_head_rows_kernel(LinArgs<T> a)
 // 43 + 6.  A call: 256 rows 2832 -> 2124, 64 rows 1085 -> 1056, 80 rows, hidden size 1024 and 50000 tokens 592 -> 465; shapes that the
 // old kernels' rules fitted badly gain most (80 rows, hidden size 4160, 12000 tokens 1377 -> 677).
 constexpr int kGemmX = 4;              // buffers for the activations' k-steps
-template <int RT, int CT> constexpr int gemm_w_buffers() { return (160 - kGemmX * RT) / CT; }      // ... and for the weights'
+template <int RT, int CT> constexpr int gemm_w_buffers() { return (160 - kGemmX * RT) / CT < 12 ? (160 - kGemmX * RT) / CT : 12; }      // ... and for the weights'
 template <int RT, int CT> constexpr size_t gemm_lds() { return (size_t)(kGemmX * RT + gemm_w_buffers<RT, CT>() * CT) * 1024; }
 
 template <typename T, int RT, int CT, int WR, int WC, int EPI, bool TILED>
@@ -1198,12 +1198,11 @@ int launch_linear_nt(const LinArgs<T> &a, hipStream_t stream)
 
 // K split over as many workgroups per column group as bring the launch to about one per compute unit, with eight k-steps each
 // at least.
-template <typename T, int RT, int WR, int WC, int EPI>
+template <typename T, int RT, int CT, int WR, int WC, int EPI>
 int launch_gemm(LinArgs<T> a, hipStream_t stream)
 {
-    constexpr int CT = kGemmCols;
     const int groups = (a.N + 16 * CT - 1) / (16 * CT), ks = (a.K1 + a.K2) / 32;
-    a.ksplit = groups < kSplitMaxWgs ? kSplitMaxWgs / groups : 1;
+    a.ksplit = CT == kGemmCols && groups < kSplitMaxWgs ? kSplitMaxWgs / groups : 1;
     if (a.ksplit > ks / 8) a.ksplit = ks >= 8 ? ks / 8 : 1;
     constexpr size_t smem = gemm_lds<RT, CT>();
     static std::atomic<unsigned long long> conf_t{0}, conf_r{0};
@@ -1261,7 +1260,13 @@ int launch_linear_mt(const LinArgs<T> &a, hipStream_t stream)
 // Which kernel runs a layer.  rd_gemm_kernel, 256 rows at a time, from 33 rows on -- with fewer its partial sums cost more
 // than it saves (us per call at a hidden size of 4096 and 32000 tokens, all layers by it / as here: 16 rows 764 / 740, 32 rows
 // 822 / 803) -- but for the output layer up to 128 rows, which rd_head_rows_kernel runs without splitting K (64 rows 877 /
-// 861, 128 rows 1044 / 1012).
+// 861, 128 rows 1044 / 1012), and for layers of up to 8 Mi weights and 64 rows, which take less time than a second launch costs
+// (rd_linear_kernel; 40 rows, us per call by hidden size, the limit at none / 1 / 4 / 8 / 16 Mi: 512 112 / 98 / 89 / 89 / 89,
+// 1024 121 / 121 / 114 / 107 / 107; 64 rows, 1536 140 / 140 / 140 / 139 / 143).  65 to 128 column groups of few k-steps take
+// workgroups of half as many columns, which need no split (80 rows, hidden size 704, 20445 tokens 154 -> 151, 128 rows 168 -> 160;
+// with many k-steps they take longer: hidden size 8256 689 -> 812).
+constexpr size_t kSmallLayer = 8u << 20;
+
 template <typename T, int EPI>
 int launch_linear(const LinArgs<T> &all, hipStream_t stream)
 {
@@ -1279,12 +1284,17 @@ int launch_linear(const LinArgs<T> &all, hipStream_t stream)
             else if (mt <= 4) done = launch_head_rows<T, 4, EPI>(a, stream, &st);
             else if (mt <= 8) done = launch_head_rows<T, 8, EPI>(a, stream, &st);
         }
+        if (!done && mt > 2 && mt <= 4 && (size_t)a.N * (a.K1 + a.K2) <= kSmallLayer) {
+            st = launch_linear_nt<T, 4, 1, EPI>(a, stream);
+            done = true;
+        }
         if (!done) {
             if (all.M > 32) {                                   // (the workspace holds its partial sums only then)
-                const int rt = gemm_row_tiles(rows);
-                if (rt == 16) st = launch_gemm<T, 16, 2, 4, EPI>(a, stream);
-                else if (rt == 8) st = launch_gemm<T, 8, 2, 4, EPI>(a, stream);
-                else st = launch_gemm<T, 4, 1, 8, EPI>(a, stream);
+                const int rt = gemm_row_tiles(rows), groups = (a.N + 16 * kGemmCols - 1) / (16 * kGemmCols);
+                const bool narrow = groups > 64 && groups <= 128 && a.K1 + a.K2 <= 4096;
+                if (rt == 16) st = launch_gemm<T, 16, 16, 2, 4, EPI>(a, stream);
+                else if (rt == 8) st = narrow ? launch_gemm<T, 8, 8, 2, 4, EPI>(a, stream) : launch_gemm<T, 8, 16, 2, 4, EPI>(a, stream);
+                else st = narrow ? launch_gemm<T, 4, 8, 2, 4, EPI>(a, stream) : launch_gemm<T, 4, 16, 1, 8, EPI>(a, stream);
             } else if (mt <= 1) {
                 st = launch_linear_mt<T, 1, EPI>(a, stream);
             } else {

@@ -13,7 +13,9 @@ pytestmark = pytest.mark.gpu
 # The deviation of a plain fp32 evaluation from the oracle (draft_tolerance.fp32_deviation) is at most 8.1e-4 over these
 # shapes, so the tolerance of test_gpu_draft (1e-2, derived from that deviation over its own shapes) covers them.
 SHAPES = [(64, 130, 1, 11, 3, 3), (64, 257, 2, 8, 8, 3), (192, 1000, 2, 5, 13, 3), (64, 301, 1, 16, 8, 3), (128, 515, 2, 43, 3, 3),
-          (320, 777, 1, 32, 8, 4), (64, 300, 1, 257, 1, 3), (64, 400, 2, 6, 50, 3), (64, 333, 0, 128, 4, 3), (64, 70003, 1, 13, 10, 3)]
+          (320, 777, 1, 32, 8, 4), (64, 300, 1, 257, 1, 3), (64, 400, 2, 6, 50, 3), (64, 333, 0, 128, 4, 3), (64, 70003, 1, 13, 10, 3),
+          # 64 rows and fewer: layers too large for the unsplit kernel, K split, not split and in workgroups of 128 columns
+          (320, 14000, 0, 5, 8, 3), (64, 66000, 0, 6, 10, 3), (192, 24000, 0, 5, 8, 3), (192, 24000, 0, 10, 8, 3)]
 
 
 @pytest.mark.parametrize("tiled", [False, True])
