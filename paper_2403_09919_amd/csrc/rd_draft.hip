@@ -45,6 +45,9 @@ constexpr int kMaxRows = 512;          // B*W
 constexpr int kRowsPerLaunch = 128;    // rows of one linear-layer launch (8 MFMA row tiles)
 constexpr int kMaxBeam = 128;          // W
 constexpr int kNarrowBeam = 64;        // up to here the selection kernels keep their lists in static LDS, one candidate per lane
+// Up to here candidates are ranked by counting, us per call so and by merges (three sequences, hidden size 512, 32000 tokens):
+// 16 candidates 171 / 227, 24 230 / 286, 28 253 / 303; 32, for whom the lower bound of 32 groups is too low, 390 / 317.
+constexpr int kFewBeam = 28;
 constexpr int kSelThreads = 256;       // row pass and beam step: four waves bring the lists into LDS, the first one merges
 constexpr int kMaxVocab = 262144;      // 64 chunks of 4096 logits: one lane per chunk in the row pass
 constexpr int kSplitMaxWgs = 256;      // workgroups of a launch whose K is split over workgroups
@@ -623,7 +626,145 @@ __device__ __forceinline__ void order_pair(float &va, int &ka, float &vb, int &k
     va = tv; vb = uv; ka = tk; kb = uk;
 }
 
-// First pass over the logits: workgroup (chunk c, row m) reduces 4096 logits to their maximum, the
+// First pass for up to 28 candidates, the same results: workgroup (chunk c, row m).  No list is sorted: the W-th best of the
+// maxima of 32 groups of logits is a lower bound of the chunk's W-th best logit, few logits but the W best reach it (some 1.2 W
+// of them in random rows), and those are ranked by counting how many of them are better.  A group is eight lanes; a lane owns
+// four quads of tokens, or, in a chunk of up to 1024, four tokens one by one, so that no group is empty where there are more
+// than 256 tokens.  Bound by vector instructions (256 rows of 32000 logits, eight workgroups per compute unit: 12.0 us, with
+// every lane's tokens sorted as below 19.1; 8 rows 5.6 and 8.2).  Where more than 512 logits reach the bound -- equal ones --
+// or a row holds NaN or +inf, W rounds pick the best one left.
+__global__ __launch_bounds__(kChunkThreads) void rd_topw_few_kernel(const float *__restrict__ logits, int V, int W, int chunks, int mstride,
+                                                                    float *__restrict__ part_max, float *__restrict__ part_sum,
+                                                                    float *__restrict__ part_cv, int32_t *__restrict__ part_ci)
+{
+    constexpr int kWaves = kChunkThreads / 64, kGroups = 32, kCap = 2 * kChunkThreads;
+    static_assert(kGroups * 8 == kChunkThreads && kFewBeam <= kGroups, "a group is eight lanes");
+    __shared__ float s_g[kGroups], s_v[kWaves];
+    __shared__ __align__(16) uint2 s_c[kCap];               // (logit, token) of those that reach the bound
+    __shared__ float s_cv[kWaves][kFewBeam];
+    __shared__ int s_ci[kWaves][kFewBeam];
+    __shared__ int s_n;
+    const int c = blockIdx.x, m = blockIdx.y * mstride, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const float *z = logits + (size_t)m * V;
+    // this lane's token j is t0 + (j / 4) * far + (j % 4) * near, none from V on
+    const bool quads = V - c * kChunk > 4 * kChunkThreads;              // uniform
+    const int t0 = c * kChunk + tid * (quads ? 4 : 1), far = quads ? 4 * kChunkThreads : kMaxVocab, near = quads ? 1 : kChunkThreads;
+    auto token = [&](int j) __attribute__((always_inline)) { return t0 + (j >> 2) * far + (j & 3) * near; };
+    float x[kChunkPer];
+    if ((c + 1) * kChunk <= V) {
+#pragma unroll
+        for (int j = 0; j < kChunkPer; j += 4) {
+            const rd::f4_any q = *reinterpret_cast<const rd::f4_any *>(z + token(j));
+            x[j] = q[0]; x[j + 1] = q[1]; x[j + 2] = q[2]; x[j + 3] = q[3];
+        }
+    } else {
+#pragma unroll
+        for (int j = 0; j < kChunkPer; ++j) x[j] = z[min(token(j), V - 1)];
+#pragma unroll
+        for (int j = 0; j < kChunkPer; ++j) x[j] = token(j) < V ? x[j] : -INFINITY;
+    }
+    float mx = -INFINITY;
+#pragma unroll
+    for (int j = 0; j < kChunkPer; ++j) mx = fmaxf(mx, x[j]);
+    mx = group8_max(mx);
+    if ((lane & 7) == 0) s_g[tid >> 3] = mx;
+    s_c[tid] = s_c[tid + kChunkThreads] = make_uint2(__float_as_uint(-INFINITY), 0x7fffffffu);     // (past the last: lose every comparison)
+    if (tid == 0) s_n = 0;
+    __syncthreads();
+    const float g = s_g[lane & (kGroups - 1)];
+    mx = wave_max(g);
+    float sum = 0.f;
+#pragma unroll
+    for (int j = 0; j < kChunkPer; ++j) sum += token(j) < V ? __expf(x[j] - mx) : 0.f;
+    for (int off = 32; off > 0; off >>= 1) sum += __shfl_xor(sum, off, 64);
+    if (lane == 0) s_v[wave] = sum;
+    // the bound: the group maximum that W - 1 others precede (lanes 32 and up repeat the lower ones)
+    int before = 0;
+#pragma unroll
+    for (int i = 0; i < kGroups; ++i) {
+        const float o = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(g), i));
+        before += (o > g || (o == g && i < (lane & (kGroups - 1)))) ? 1 : 0;
+    }
+    const int at = first_lane(before == W - 1);             // (none only among NaN)
+    const float bound = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(g), at < 0 ? 0 : at));
+    int mine = 0;
+#pragma unroll
+    for (int j = 0; j < kChunkPer; ++j) mine += (token(j) < V && x[j] >= bound) ? 1 : 0;
+    if (mine > 0) {
+        int pos = atomicAdd(&s_n, mine);
+#pragma unroll
+        for (int j = 0; j < kChunkPer; ++j) {
+            if (token(j) < V && x[j] >= bound) {
+                if (pos < kCap) s_c[pos] = make_uint2(__float_as_uint(x[j]), (unsigned)token(j));
+                ++pos;
+            }
+        }
+    }
+    __syncthreads();
+    const size_t slot = (size_t)m * chunks + c;
+    const float total = s_v[0] + s_v[1] + s_v[2] + s_v[3];
+    const int n = s_n;
+    if (tid == 0) {
+        part_max[slot] = mx;
+        part_sum[slot] = total;
+    }
+    if (n <= kCap && total == total) {                      // uniform
+        for (int i = tid; i < n; i += kChunkThreads) {
+            const uint2 e = s_c[i];
+            const float ev = __uint_as_float(e.x);
+            int rank = 0;
+            for (int k = 0; k < n; k += 8) {
+#pragma unroll
+                for (int u = 0; u < 8; u += 2) {
+                    const uint4 o = *reinterpret_cast<const uint4 *>(&s_c[k + u]);
+                    rank += better(__uint_as_float(o.x), (int)o.y, ev, (int)e.y) ? 1 : 0;
+                    rank += better(__uint_as_float(o.z), (int)o.w, ev, (int)e.y) ? 1 : 0;
+                }
+            }
+            if (rank < W) {
+                part_cv[slot * W + rank] = ev;
+                part_ci[slot * W + rank] = (int)e.y;
+            }
+        }
+        if (tid >= n && tid < W) {                          // fewer than W tokens in the chunk
+            part_cv[slot * W + tid] = -INFINITY;
+            part_ci[slot * W + tid] = 0x7fffffff;
+        }
+        return;
+    }
+    unsigned left = 0;                                      // this lane's tokens not yet picked
+#pragma unroll
+    for (int j = 0; j < kChunkPer; ++j) left |= (token(j) < V ? 1u : 0u) << j;
+    for (int r = 0; r < W; ++r) {
+        float hv = -INFINITY;
+        int hj = kChunkPer, ht = 0x7fffffff;
+#pragma unroll
+        for (int j = kChunkPer - 1; j >= 0; --j)
+            if ((left >> j & 1u) && x[j] >= hv) { hv = x[j]; hj = j; ht = token(j); }
+        const float best = wave_max(hv);
+        const int tok = (int)rd::wave_reduce_min_u(hv == best ? (unsigned)ht : 0x7fffffffu);
+        if (lane == 0) { s_cv[wave][r] = best; s_ci[wave][r] = tok; }
+        if (hj < kChunkPer && ht == tok) left &= ~(1u << hj);
+    }
+    __syncthreads();
+    // the four waves' lists: an entry's place is the number of better ones; all entries differ in their token but the
+    // fillers, which come last
+    for (int i = tid; i < kWaves * W; i += kChunkThreads) {
+        const int w = i / W, r = i - w * W, tok = s_ci[w][r];
+        const float v = s_cv[w][r];
+        int place = 0;
+        for (int k = 0; k < kWaves * W; ++k) {
+            const int kw = k / W, kr = k - kw * W, ot = s_ci[kw][kr];
+            place += better(s_cv[kw][kr], ot, v, tok) || (ot == tok && k < i) ? 1 : 0;
+        }
+        if (place < W) {
+            part_cv[slot * W + place] = v;
+            part_ci[slot * W + place] = tok;
+        }
+    }
+}
+
+// First pass for more candidates: workgroup (chunk c, row m) reduces 4096 logits to their maximum, the
 // sum of exp(x - maximum) and their W best (value, then smaller token).  A lane owns 16 consecutive
 // tokens and sorts them in registers (odd-even merge sort network); the sorted lists go to LDS.  Each
 // wave merges its 64 lists into its W best, wave 0 then merges the four waves' lists.
@@ -966,9 +1107,22 @@ __global__ __launch_bounds__(kSelThreads) void rd_beam_step_kernel(
     }
 }
 
-// Row pass and beam step in one launch, for beams of at most 8 candidates over at most 8 chunks (one wave
-// holds a whole sequence: lane = candidate row * 8 + chunk): the rows' sorted lists never leave LDS.  Same
-// merges, same tie rules and the same arithmetic as the two kernels above; one workgroup per sequence.
+// Row pass and beam step in one launch, one workgroup per sequence, for up to 28 candidates whose chunks' lists have a thread
+// each (few_lists).  Nothing is merged entry by entry: a thread takes one of the first entries of a list (G lanes to a row), of
+// each list as many as make 4 W entries together, and counts how many of these heads score more.  The W first heads are a lower
+// bound of the W best entries, a list whose first entry `before` heads precede holds at most W - before of them, and what
+// reaches the bound, little more than W entries, is ranked by counting in the whole order: score, then smaller candidate, then
+// logit, then smaller token.  Bound by the latency of its chain: loads, the rows' log-sum-exps, five barriers, the stores.
+// 64 rows of 16 sequences over 32000 tokens: 9.3 us, as two launches of merges 7.8 + 6.5.
+constexpr int kFewLists = 256;
+__host__ __device__ inline int few_group(int chunks)                  // lanes of a row: a power of two
+{
+    int G = 1;
+    while (G < chunks) G <<= 1;
+    return G;
+}
+bool few_lists(int W, int chunks) { return W <= kFewBeam && W * few_group(chunks) <= kFewLists; }
+
 __global__ __launch_bounds__(kSelThreads) void rd_row_beam_kernel(
     const float *__restrict__ part_max, const float *__restrict__ part_sum, const float *__restrict__ part_cv,
     const int32_t *__restrict__ part_ci, int chunks, const float *__restrict__ cum_cur, int V, int W, int L, int t, int live,
@@ -976,118 +1130,134 @@ __global__ __launch_bounds__(kSelThreads) void rd_row_beam_kernel(
     int32_t *__restrict__ parent_row, int32_t *__restrict__ tok_row,
     int32_t *__restrict__ beams_out, float *__restrict__ logp_out /* both NULL except at the last position */)
 {
-    constexpr int kW = 8;                                             // candidates, chunks and list length at most
-    __shared__ float s_cv[kW * kW * kW];                              // [row][chunk][W]: the chunk pass's lists
-    __shared__ int s_ci[kW * kW * kW];
-    __shared__ float s_score[kW * kW];                                // [row][W]: the rows' lists, cumulative scores
-    __shared__ int s_ctok[kW * kW];
-    __shared__ int s_win[kW], s_tok[kW], s_ptr[kW];
-    __shared__ float s_winv[kW];
-    const int b = blockIdx.x, tid = threadIdx.x, lane = tid & 63, g = lane >> 3, c = lane & 7;
-    const bool row_ok = g < live;
-    const size_t row = (size_t)b * W + (row_ok ? g : 0);              // rows b*W .. b*W+live-1 (at the first position: b*W)
-    const int n_surv = chunks * W;
-    const bool lane_ok = row_ok && c < chunks;
-    const float pm = lane_ok ? part_max[row * chunks + c] : -INFINITY;
-    const float gm = group8_max(pm);
-    float ps = lane_ok ? part_sum[row * chunks + c] * __expf(pm - gm) : 0.f;
+    static_assert(kFewLists == kSelThreads, "a list per thread");
+    constexpr int kEntries = kFewBeam * kFewBeam;                     // at most W lists with W entries each
+    constexpr int kPaths = 2 * kSelThreads;
+    struct Entry { float score, logit; int row, tok; };
+    __shared__ __align__(16) float s_head[kFewLists];
+    __shared__ __align__(16) Entry s_full[kFewLists], s_e[kEntries];
+    __shared__ int s_path[kPaths];
+    struct List { int slot, take, row; float base, lse; };
+    __shared__ List s_list[kFewBeam];
+    __shared__ int s_heads, s_lists, s_n;
+    __shared__ unsigned s_bound;
+    __shared__ int s_win[kFewBeam], s_tok[kFewBeam];
+    __shared__ float s_winv[kFewBeam];
+    const int b = blockIdx.x, tid = threadIdx.x;
+    const int G = few_group(chunks), per = live * G, depth = tid / per, g = (tid - depth * per) / G, c = tid & (G - 1);
+    // as many heads of each list as make kHeads times W of them all, where there are threads for them (W always)
+    constexpr int kHeads = 4;
+    const int n_lists = live * chunks, n_depth = min(min((kHeads * W + n_lists - 1) / n_lists, W), kFewLists / per);
+    const bool mine = c < chunks && depth < n_depth;
+    const size_t row0 = (size_t)b * W;                                // rows row0 .. row0+live-1 (at the first position: row0)
+    const size_t slot = (row0 + g) * chunks + min(c, chunks - 1);
+    float pm[1] = {part_max[slot]}, ps[1] = {part_sum[slot]};
+    const float logit = part_cv[slot * W + min(depth, W - 1)];
+    const int tok = part_ci[slot * W + min(depth, W - 1)];
+    const float base = cum_cur[row0 + g];
+    const bool paths_in_lds = W * L <= kPaths;                        // uniform
+    int path[2];
+    for (int u = 0; u < 2; ++u) path[u] = paths_cur[row0 * L + min(tid + u * kSelThreads, W * L - 1)];
+    if (paths_in_lds) { s_path[tid] = path[0]; s_path[tid + kSelThreads] = path[1]; }
+    // log-sum-exp of the row: sum_c part_sum[c] * exp(part_max[c] - max)
+    auto larger = [](float x, float y) __attribute__((always_inline)) { return fmaxf(x, y); };
+    auto plus = [](float x, float y) __attribute__((always_inline)) { return x + y; };
+    const float own = c < chunks ? pm[0] : -INFINITY;
+    pm[0] = own;
+    rd::group_reduce(pm, G, larger);
+    ps[0] = c < chunks ? ps[0] * __expf(own - pm[0]) : 0.f;
+    rd::group_reduce(ps, G, plus);
+    const float lse = pm[0] + __logf(ps[0]);
+    if (tid == 0) { s_heads = 0; s_lists = 0; s_n = 0; s_bound = 0xffffffffu; }
+    Entry head = {-INFINITY, -INFINITY, 0x7fffffff, 0x7fffffff};      // none: after all others
+    const float score = base + (logit - lse);
+    const bool on = mine && tok != 0x7fffffff && score == score;      // a row of NaN offers nothing
+    if (on) head = {score, logit, g, tok};
+    s_head[tid] = head.score;
+    s_full[tid] = head;
+    __syncthreads();
+    const int n_heads = per * n_depth;                                // <= 256
+    int before = 0;                                                   // heads of larger score
+#pragma unroll 4
+    for (int k = 0; k < n_heads; k += 4) {                            // (heads past the last are -inf)
+        const float4 h = *reinterpret_cast<const float4 *>(&s_head[k]);
+        before += (h.x > head.score ? 1 : 0) + (h.y > head.score ? 1 : 0) + (h.z > head.score ? 1 : 0) + (h.w > head.score ? 1 : 0);
+    }
+    // scores as unsigned integers in the same order
+    auto ordered = [](float x) __attribute__((always_inline)) {
+        const unsigned u = __float_as_uint(x + 0.f);                  // (-0 as 0)
+        return u & 0x80000000u ? ~u : u | 0x80000000u;
+    };
+    if (on && before < W) {
+        atomicAdd(&s_heads, 1);
+        atomicMin(&s_bound, ordered(head.score));
+    }
+    __syncthreads();
+    auto precedes = [](const Entry &x, const Entry &y) __attribute__((always_inline)) {
+        const bool same = x.score == y.score, same_row = x.row == y.row;      // (no branches)
+        return (x.score > y.score) | (same & ((x.row < y.row) | (same_row & better(x.logit, x.tok, y.logit, y.tok))));
+    };
+    const unsigned bound = s_heads < W ? 0u : s_bound;                // fewer entries than candidates: every one counts
+    if (on && s_heads > W) {                                          // equal scores about the W-th head: by the whole order
+        before = 0;
+        for (int k = 0; k < n_heads; ++k) before += precedes(s_full[k], head) ? 1 : 0;
+    }
+    if (on && depth == 0 && before < W) s_list[atomicAdd(&s_lists, 1)] = {(int)slot, W - before, g, base, lse};
+    __syncthreads();
+    const int entries = s_lists * W;
+    for (int i0 = 0; i0 < entries; i0 += 4 * kSelThreads) {           // (four entries' loads in flight together)
+        List list[4];
+        float v[4];
+        int tk[4];
+        bool take[4];
 #pragma unroll
-    for (int off = 1; off < 8; off <<= 1) ps += __shfl_xor(ps, off, 64);
-    const float lse = gm + __logf(ps);
-    const float base = row_ok ? cum_cur[row] : 0.f;
-    {   // the sequence's survivors -> LDS (two loads per thread in flight, addresses past the end pulled back)
-        const int total = live * n_surv;                              // <= 512
-        float v[2];
-        int ti[2];
-#pragma unroll
-        for (int u = 0; u < 2; ++u) {
-            const int idx = min(u * kSelThreads + tid, total - 1);
-            const int gg = idx / n_surv, q = idx - gg * n_surv;
-            const size_t src = ((size_t)b * W + gg) * n_surv + q;
+        for (int u = 0; u < 4; ++u) {
+            const int i = i0 + u * kSelThreads + tid, l = min(i, entries - 1) / W, r = min(i, entries - 1) - l * W;
+            list[u] = s_list[l];
+            take[u] = i < entries && r < list[u].take;
+            const size_t src = (size_t)list[u].slot * W + r;
             v[u] = part_cv[src];
-            ti[u] = part_ci[src];
+            tk[u] = part_ci[src];
         }
 #pragma unroll
-        for (int u = 0; u < 2; ++u) {
-            const int idx = u * kSelThreads + tid;
-            if (idx < total) {
-                const int gg = idx / n_surv, q = idx - gg * n_surv;
-                s_cv[gg * kW * kW + q] = v[u];
-                s_ci[gg * kW * kW + q] = ti[u];
-            }
+        for (int u = 0; u < 4; ++u) {
+            const Entry e = {list[u].base + (v[u] - list[u].lse), v[u], list[u].row, tk[u]};
+            if (take[u] && e.tok != 0x7fffffff && ordered(e.score) >= bound) s_e[atomicAdd(&s_n, 1)] = e;
         }
     }
     __syncthreads();
-    if (tid < 64) {
-        // rows: merge of each row's chunk lists into its W best tokens, as cumulative scores
-        const float *lv = s_cv + g * kW * kW + c * W;
-        const int *li = s_ci + g * kW * kW + c * W;
-        int ptr = 0;
-        int ht = li[0], nt = li[W > 1 ? 1 : 0];
-        float hv = lv[0], nv = lv[W > 1 ? 1 : 0];
-        bool on = lane_ok && ht != 0x7fffffff;
-        for (int r = 0; r < W; ++r) {
-            const float best = group8_max(on ? hv : -INFINITY);
-            const unsigned long long offers = __ballot(on && hv == best);
-            const unsigned mine = (unsigned)(offers >> (g * 8)) & 0xffu;
-            const int win = mine ? __ffs((int)mine) - 1 : -1;
-            if (c == 0 && row_ok) s_score[g * W + r] = win >= 0 ? base + (best - lse) : -INFINITY;
-            if (c == win) {
-                s_ctok[g * W + r] = ht;
-                ++ptr;
-                hv = nv; ht = nt;
-                on = ptr < W && ht != 0x7fffffff;
-                const int nx = ptr + 1 < W ? ptr + 1 : W - 1;
-                nv = lv[nx]; nt = li[nx];
-            } else if (c == 0 && win < 0 && row_ok) {
-                s_ctok[g * W + r] = 0;
-            }
+    const int n = s_n;
+    for (int i = tid; i < n; i += kSelThreads) {
+        const Entry e = s_e[i];
+        int rank = 0;
+        for (int k = 0; k < n; k += 4) {                              // four reads in flight
+#pragma unroll
+            for (int u = 0; u < 4; ++u) rank += (k + u < n && precedes(s_e[min(k + u, n - 1)], e)) ? 1 : 0;
+        }
+        if (rank < W) {
+            s_win[rank] = e.row;
+            s_winv[rank] = e.score;
+            s_tok[rank] = min(max(e.tok, 0), V - 1);
         }
     }
-    __syncthreads();
-    if (tid < 64) {
-        // sequence: merge of the live rows' lists, lane w = row w
-        int ptr = 0;
-        bool on = lane < live;
-        const int la = (on ? lane : 0) * W;
-        float hv = s_score[la], nv = s_score[la + (W > 1 ? 1 : 0)];
-        for (int r = 0; r < W; ++r) {
-            const float best = wave_max(on ? hv : -INFINITY);
-            int win = first_lane(on && hv == best);
-            if (win < 0) win = first_lane(on);                        // NaN scores: keep indices in range
-            if (win < 0) win = 0;
-            if (lane == win) {
-                s_win[r] = lane;
-                s_winv[r] = best;
-                s_ptr[r] = ptr < W ? ptr : W - 1;
-                if (on) {
-                    ++ptr;
-                    on = ptr < W;
-                    hv = nv;
-                    nv = s_score[la + (ptr + 1 < W ? ptr + 1 : W - 1)];
-                }
-            }
-        }
-    }
-    __syncthreads();
-    for (int r = tid; r < W; r += kSelThreads) {
-        const int tk = s_ctok[s_win[r] * W + s_ptr[r]];
-        s_tok[r] = tk < 0 ? 0 : (tk > V - 1 ? V - 1 : tk);
+    for (int r = n + tid; r < W; r += kSelThreads) {                  // NaN scores: keep indices in range
+        s_win[r] = 0;
+        s_winv[r] = -INFINITY;
+        s_tok[r] = 0;
     }
     __syncthreads();
     for (int i = tid; i < W * L; i += kSelThreads) {
         const int r = i / L, j = i - r * L;
-        const int pw = s_win[r];
-        const size_t src = ((size_t)b * W + pw) * L;
-        const int v = j < t ? paths_cur[src + j] : (j == t ? s_tok[r] : paths_cur[src]);
-        paths_next[((size_t)b * W + r) * L + j] = v;
-        if (beams_out) beams_out[((size_t)b * W + r) * L + j] = v;
+        const int src = s_win[r] * L + (j < t ? j : 0);
+        const int v = j == t ? s_tok[r] : paths_in_lds ? s_path[src] : paths_cur[row0 * L + src];
+        paths_next[(row0 + r) * L + j] = v;
+        if (beams_out) beams_out[(row0 + r) * L + j] = v;
     }
     for (int w = tid; w < W; w += kSelThreads) {
-        cum_next[(size_t)b * W + w] = s_winv[w];
-        parent_row[(size_t)b * W + w] = b * W + s_win[w];
-        tok_row[(size_t)b * W + w] = s_tok[w];
-        if (logp_out) logp_out[(size_t)b * W + w] = s_winv[w];
+        cum_next[row0 + w] = s_winv[w];
+        parent_row[row0 + w] = (int)row0 + s_win[w];
+        tok_row[row0 + w] = s_tok[w];
+        if (logp_out) logp_out[row0 + w] = s_winv[w];
     }
 }
 
@@ -1374,17 +1544,21 @@ int draft_run(const rd_draft_params *p, const void *h, const int32_t *last_token
             a.M = rows; a.N = V; a.mstride = mstride; a.tiled = p->tiled; a.y_f32 = logits; a.ldy = V; a.kpart = kpart;
             if (launch_linear<E, EPI_HEAD>(a, s) != RD_OK) return RD_ERR_HIP;
         }
-        // from 16 candidates on (and while four lists per chunk fit the row pass's 64 lanes) the chunk pass
+        // with many candidates (and while four lists per chunk fit the row pass's 64 lanes) the chunk pass
         // leaves its four waves' lists unmerged
-        const int lpc = (W >= 16 && chunks * 4 <= 64) ? 4 : 1;
-        hipLaunchKernelGGL(rd_topw_chunk_kernel, dim3(chunks, rows), dim3(kChunkThreads), 0, s, logits, V, W, chunks, mstride, lpc,
-                           part_max, part_sum, part_cv, part_ci);
+        const bool few = W <= kFewBeam;
+        const int lpc = (!few && chunks * 4 <= 64) ? 4 : 1;
+        if (few)
+            hipLaunchKernelGGL(rd_topw_few_kernel, dim3(chunks, rows), dim3(kChunkThreads), 0, s, logits, V, W, chunks, mstride,
+                               part_max, part_sum, part_cv, part_ci);
+        else
+            hipLaunchKernelGGL(rd_topw_chunk_kernel, dim3(chunks, rows), dim3(kChunkThreads), 0, s, logits, V, W, chunks, mstride, lpc,
+                               part_max, part_sum, part_cv, part_ci);
         if (rd_check_launch() != RD_OK) return RD_ERR_HIP;
         const bool last = t == T;
         const bool wide = W > kNarrowBeam;
         const int live = t == 1 ? 1 : W;
-        static const int fuse_on = rd::env_int("RD_DRAFT_FUSE_ROW_BEAM", 1);   // 0: the two kernels (for comparisons)
-        if (fuse_on && W <= 8 && chunks <= 8 && lpc == 1) {
+        if (few_lists(W, chunks)) {
             hipLaunchKernelGGL(rd_row_beam_kernel, dim3(B), dim3(kSelThreads), 0, s, part_max, part_sum, part_cv, part_ci, chunks,
                                cum[cur], V, W, L, t, live, paths[cur], paths[nxt], cum[nxt], parent + (size_t)(t - 1) * M, tok,
                                last ? beams : nullptr, last ? beam_logp : nullptr);

@@ -1,0 +1,63 @@
+"""The drafter's selection at the edges of its rules: candidates up to the most that are ranked by counting, lists up to one per
+thread and past it, chunks with fewer tokens than candidates' groups, and vocabularies of equal logits."""
+import numpy as np
+import pytest
+
+import torch
+
+from draft_tolerance import inputs_small
+from gpu_util import announce, dev, host
+from paper_2403_09919_amd import synth
+from test_gpu_draft import check, dev_params, rd  # noqa: F401  (rd: the fixture)
+from test_oracle_draft import make_params
+
+pytestmark = pytest.mark.gpu
+
+# (Dm, V, K, B, W, L, tokens that share one row of the output layer).  Scores are compared with the tolerance of test_gpu_draft,
+# whose derivation covers these models (hidden size 64, the same scale).
+SHAPES = [(64, 300, 1, 2, 28, 3, 1), (64, 300, 1, 2, 29, 3, 1), (64, 5000, 1, 2, 28, 3, 1), (64, 4096, 1, 2, 1, 4, 1), (64, 4097, 1, 2, 5, 4, 1),
+          (64, 33000, 1, 1, 16, 3, 1), (64, 33000, 1, 1, 17, 3, 1), (64, 70000, 0, 1, 8, 3, 1), (64, 20000, 1, 1, 28, 3, 1),
+          (64, 9000, 1, 2, 17, 4, 3), (64, 9000, 1, 2, 10, 4, 64), (64, 9000, 1, 2, 9, 4, 700)]
+
+
+def inputs(Dm, V, K, B, W, L, same):
+    p, h, last = inputs_small(Dm, V, K, B, W, L)
+    p["head_w"][:] = p["head_w"][np.arange(V) // same * same]
+    return p, h, last
+
+
+@pytest.mark.parametrize("Dm,V,K,B,W,L,same", SHAPES)
+def test_selection_edges(rd, Dm, V, K, B, W, L, same):  # noqa: F811
+    announce(f"draft selection Dm={Dm} V={V} K={K} B={B} W={W} L={L} same={same}")
+    p, h, last = inputs(Dm, V, K, B, W, L, same)
+    check(rd, p, h, last, W, L, "selection")
+    if same > 1:                                            # equal logits: the smaller token first, so no gap below a chosen one
+        beams = host(rd.rd_draft(dev_params(p), dev(h), dev(last), W, 2)["beams"])
+        for b in range(B):
+            chosen = set(beams[b, :, 1].tolist())
+            for tok in chosen:
+                assert all(x in chosen for x in range(tok // same * same, tok)), (b, tok)
+
+
+@pytest.mark.parametrize("V,W", [(20000, 8), (20000, 28), (20000, 29), (40, 28), (140000, 4), (140000, 8)])
+def test_equal_logits_take_the_smallest_tokens(rd, V, W):  # noqa: F811
+    announce(f"draft selection, equal logits V={V} W={W}")
+    p = make_params(V, 64, 0, 5)
+    p["head_w"][:] = 0
+    h = synth.f32_to_bf16_bits(np.ones((1, 64), np.float32))
+    got = rd.rd_draft(dev_params(p), dev(h), dev(np.array([2], np.int32)), W, 4)
+    torch.cuda.synchronize()
+    assert host(got["beams"])[0].tolist() == [[2, 0, 0, w] for w in range(W)]
+    assert np.allclose(host(got["beam_logp"]), -3 * np.log(V), atol=1e-4)
+
+
+def test_nan_logits_keep_tokens_in_range(rd):  # noqa: F811
+    announce("draft selection, NaN logits")
+    V, W = 9000, 8
+    p = make_params(V, 64, 1, 7)
+    p["head_w"][5] = synth.f32_to_bf16_bits(np.full(128, np.nan, np.float32))
+    h = synth.f32_to_bf16_bits(np.ones((1, 64), np.float32))
+    got = rd.rd_draft(dev_params(p), dev(h), dev(np.array([2], np.int32)), W, 4)
+    torch.cuda.synchronize()
+    beams = host(got["beams"])
+    assert (beams >= 0).all() and (beams < V).all()
