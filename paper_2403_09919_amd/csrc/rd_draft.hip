@@ -344,7 +344,7 @@ __global__ __launch_bounds__(512) void rd_head_rows_kernel(LinArgs<T> a)
     }
 }
 
-// Layers of 33 rows and more.  A workgroup of eight waves owns RT row tiles x CT column tiles of the output and a share of K;
+// Layers of many rows.  A workgroup of eight waves owns RT row tiles x CT column tiles of the output and a share of K;
 // wave (wr, wc) of WR x WC owns a block of RT/WR x CT/WC tiles.  Per k-step of 32 the operands of all its tiles, (RT + CT) KB,
 // are copied from memory straight into buffers in LDS, three k-steps ahead for the activations (from L2), as many as LDS holds
 // for the weights (5 at RT = 16, 8 at RT = 4), with one LDS-only barrier a step; operands are read into registers two row tiles
@@ -1301,8 +1301,10 @@ __global__ void rd_pack_weights_kernel(const uint16_t *__restrict__ src, int N, 
     *reinterpret_cast<uint4 *>(dst + (tile * 64 + lane) * 8) = v;
 }
 
-// Row tiles of rd_gemm_kernel's workgroups for a launch of `rows` rows (33 and more).
+// Row tiles of rd_gemm_kernel's workgroups for a launch of `rows` rows.
 int gemm_row_tiles(int rows) { return rows > 128 ? 16 : rows > 64 ? 8 : 4; }
+
+constexpr int kGemmRows = 9;            // the workspace holds rd_gemm_kernel's partial sums from this many rows on
 
 struct Plan {
     size_t x_f32[3], x_bf[3], s_bf[2], logits, part_max, part_sum, part_cv, part_ci, row_score, row_tok, paths[2], cum[2], parent, tok, kpart, total;
@@ -1328,7 +1330,7 @@ Plan draft_plan(int B, int W, int L, int Dm, int V)
     for (int i = 0; i < 2; ++i) { p.paths[i] = take(M * L * 4); p.cum[i] = take(M * 4); }
     p.parent = take(M * 4 * (size_t)(L > 1 ? L - 1 : 1));       // parent rows of every drafted position
     p.tok = take(M * 4);
-    p.kpart = take(M > 32 ? (size_t)kSplitMaxWgs * gemm_row_tiles((int)M) * kGemmCols * 1024 : 0);      // a launch's partial tiles
+    p.kpart = take(M >= kGemmRows ? (size_t)kSplitMaxWgs * gemm_row_tiles((int)M) * kGemmCols * 1024 : 0);      // a launch's partial tiles
     p.total = off;
     return p;
 }
@@ -1435,15 +1437,28 @@ int launch_linear_mt(const LinArgs<T> &a, hipStream_t stream)
     return launch_linear_nt<T, MT, 1, EPI>(a, stream);
 }
 
-// Which kernel runs a layer.  rd_gemm_kernel, 256 rows at a time, from 33 rows on -- with fewer its partial sums cost more
-// than it saves (us per call at a hidden size of 4096 and 32000 tokens, all layers by it / as here: 16 rows 764 / 740, 32 rows
-// 822 / 803) -- but for the output layer up to 128 rows, which rd_head_rows_kernel runs without splitting K (64 rows 877 /
+// Which kernel runs a layer.  rd_gemm_kernel, 256 rows at a time, from 33 rows on (with fewer: few_rows_gemm), but for the output
+// layer up to 128 rows, which rd_head_rows_kernel runs without splitting K (us per call at a hidden size of 4096, 64 rows 877 /
 // 861, 128 rows 1044 / 1012), and for layers of up to 8 Mi weights and 64 rows, which take less time than a second launch costs
 // (rd_linear_kernel; 40 rows, us per call by hidden size, the limit at none / 1 / 4 / 8 / 16 Mi: 512 112 / 98 / 89 / 89 / 89,
 // 1024 121 / 121 / 114 / 107 / 107; 64 rows, 1536 140 / 140 / 140 / 139 / 143).  65 to 128 column groups of few k-steps take
 // workgroups of half as many columns, which need no split (80 rows, hidden size 704, 20445 tokens 154 -> 151, 128 rows 168 -> 160;
 // with many k-steps they take longer: hidden size 8256 689 -> 812).
 constexpr size_t kSmallLayer = 8u << 20;
+
+// 9 to 32 rows: rd_linear_kernel reads every activation once per 16 columns and fills the chip in whole rounds of workgroups
+// only at some sizes, rd_gemm_kernel pays a second launch.  us per call of four MLP layers at 8 / 12 / 16 / 24 / 32 rows, hidden
+// size 2048 by the former 50 / 51 / 52 / 63 / 69, by the latter 75 / 75 / 75 / 78 / 79; 3072 108 / 118 / 133 / 162 / 183 and
+// 113 / 112 / 112 / 116 / 117; 4096 135 / 146 / 162 / 171 / 184 and 162 / 161 / 161 / 167 / 168; 5120 210 / 231 / 258 / 320 / 355
+// and 204 / 203 / 205 / 210 / 213; 6656 336 / 376 / 421 / 411 / 458 and 302 / 301 / 304 / 312 / 318.
+// Where rd_linear_kernel's workgroups are whole rounds of 256 it stays up to 24 rows (whole calls at 4096, 16 and 24 rows: 735 and
+// 756 so, 743 and 760 by rd_gemm_kernel).
+bool few_rows_gemm(int rows, int N, int K)
+{
+    const size_t weights = (size_t)N * K;
+    if (rows <= 24 && N % (16 * 256) == 0) return false;
+    return (rows >= 16 && weights >= (size_t)32 << 20) || (rows >= kGemmRows && weights >= (size_t)96 << 20);
+}
 
 template <typename T, int EPI>
 int launch_linear(const LinArgs<T> &all, hipStream_t stream)
@@ -1467,7 +1482,7 @@ int launch_linear(const LinArgs<T> &all, hipStream_t stream)
             done = true;
         }
         if (!done) {
-            if (all.M > 32) {                                   // (the workspace holds its partial sums only then)
+            if (all.M > 32 || (EPI != EPI_HEAD && few_rows_gemm(rows, a.N, a.K1 + a.K2))) {
                 const int rt = gemm_row_tiles(rows), groups = (a.N + 16 * kGemmCols - 1) / (16 * kGemmCols);
                 const bool narrow = groups > 64 && groups <= 128 && a.K1 + a.K2 <= 4096;
                 if (rt == 16) st = launch_gemm<T, 16, 16, 2, 4, EPI>(a, stream);

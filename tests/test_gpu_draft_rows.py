@@ -1,4 +1,4 @@
-"""The drafter's layers of 33 rows and more (rd_gemm_kernel) at the edges of its tiles, against the oracle: rows around 32, 64,
+"""The drafter's layers of many rows (rd_gemm_kernel) at the edges of its tiles, against the oracle: rows around 32, 64,
 128 and 256 (its row tiles, and the launches a call is cut into), columns that are no multiple of 16 or of the 256 of a
 workgroup, more column groups than workgroups of a launch (K not split), and the smallest K, both weight layouts."""
 import pytest
@@ -15,7 +15,9 @@ pytestmark = pytest.mark.gpu
 SHAPES = [(64, 130, 1, 11, 3, 3), (64, 257, 2, 8, 8, 3), (192, 1000, 2, 5, 13, 3), (64, 301, 1, 16, 8, 3), (128, 515, 2, 43, 3, 3),
           (320, 777, 1, 32, 8, 4), (64, 300, 1, 257, 1, 3), (64, 400, 2, 6, 50, 3), (64, 333, 0, 128, 4, 3), (64, 70003, 1, 13, 10, 3),
           # 64 rows and fewer: layers too large for the unsplit kernel, K split, not split and in workgroups of 128 columns
-          (320, 14000, 0, 5, 8, 3), (64, 66000, 0, 6, 10, 3), (192, 24000, 0, 5, 8, 3), (192, 24000, 0, 10, 8, 3)]
+          (320, 14000, 0, 5, 8, 3), (64, 66000, 0, 6, 10, 3), (192, 24000, 0, 5, 8, 3), (192, 24000, 0, 10, 8, 3),
+          # 9 to 32 rows of layers large enough for it, both products of the RNN too
+          (2944, 200, 1, 4, 4, 2), (2944, 100, 1, 17, 1, 2), (5056, 100, 1, 9, 1, 2), (4160, 100, 0, 8, 2, 3), (4096, 100, 0, 1, 32, 3)]
 
 
 @pytest.mark.parametrize("tiled", [False, True])
