@@ -358,7 +358,7 @@ __global__ __launch_bounds__(512) void rd_head_rows_kernel(LinArgs<T> a)
 // without the copies, 1.05 PFLOP/s (a library product of 8192^3 reaches 1.22).  Against the kernels it replaced, one that
 // staged the activations of 128 rows through registers and one that split K over the waves, us per layer: 256 rows, hidden
 // size 6656, RNN 137 -> 52 + 14, MLP 173 -> 107 + 18, output layer 297 -> 208 + 17; 64 rows, 5120, RNN 37 -> 24 + 6, MLP 56 ->
-// 43 + 6.  A call: 256 rows 2832 -> 2124, 64 rows 1085 -> 1056, 80 rows, hidden size 1024 and 50000 tokens 592 -> 465; shapes that the
+// 43 + 6.  A call: 256 rows 2832 -> 2124 (2072 with the selection below), 64 rows 1085 -> 1056 (1018), 80 rows, hidden size 1024 and 50000 tokens 592 -> 465; shapes that the
 // old kernels' rules fitted badly gain most (80 rows, hidden size 4160, 12000 tokens 1377 -> 677).
 constexpr int kGemmX = 4;              // buffers for the activations' k-steps
 template <int RT, int CT> constexpr int gemm_w_buffers() { return (160 - kGemmX * RT) / CT < 12 ? (160 - kGemmX * RT) / CT : 12; }      // ... and for the weights'

@@ -18,7 +18,7 @@
 // replaced, whose waves shared every block of tiles at two barriers and fetched K and V through registers, us per launch, K
 // and V from memory: H=32, C=1024 12.1 -> 10.8; B=4, H=32, C=1024 23.9 -> 19.6; H=32, C=1777, 61 rows 22.3 -> 16.7 and 147
 // rows 30.0 -> 22.0; B=10, H=52, C=63-92, 207 tokens 49.4 -> 33.2; B=4, H=40, C=4096 74.5 -> 68.8; B=16, H=52, C=2048 183.5 ->
-// 180.2; B=24, H=32, C=101-1500 79.2 -> 74.7; nothing at B=9, H=26, C=5384 (106.7 -> 106.3).
+// 180.2; B=24, H=32, C=101-1500 79.2 -> 68.1; nothing at B=9, H=26, C=5384 (106.7 -> 106.3).
 #pragma once
 #include "rd_attn_common.h"
 #include <type_traits>
