@@ -1210,9 +1210,13 @@ __global__ __launch_bounds__(kSelThreads) void rd_row_beam_kernel(
         before = 0;
         for (int k = 0; k < n_heads; ++k) before += precedes(s_full[k], head) ? 1 : 0;
     }
-    if (on && depth == 0 && before < W) s_list[atomicAdd(&s_lists, 1)] = {(int)slot, W - before, g, base, lse};
+    const bool whole = n_depth == W;                                  // uniform: every entry is a head (one candidate as a rule)
+    if (on && before < W) {
+        if (whole) s_e[atomicAdd(&s_n, 1)] = head;
+        else if (depth == 0) s_list[atomicAdd(&s_lists, 1)] = {(int)slot, W - before, g, base, lse};
+    }
     __syncthreads();
-    const int entries = s_lists * W;
+    const int entries = whole ? 0 : s_lists * W;
     for (int i0 = 0; i0 < entries; i0 += 4 * kSelThreads) {           // (four entries' loads in flight together)
         List list[4];
         float v[4];
@@ -1233,7 +1237,7 @@ __global__ __launch_bounds__(kSelThreads) void rd_row_beam_kernel(
             if (take[u] && e.tok != 0x7fffffff && ordered(e.score) >= bound) s_e[atomicAdd(&s_n, 1)] = e;
         }
     }
-    __syncthreads();
+    if (!whole) __syncthreads();
     const int n = s_n;
     for (int i = tid; i < n; i += kSelThreads) {
         const Entry e = s_e[i];
