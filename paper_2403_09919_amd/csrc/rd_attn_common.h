@@ -131,7 +131,7 @@ static inline AttnPlan attn_plan_make(int B, int H, int N, int D, int Cmax, bool
                 best.rg_tiles = nq;
                 best.n_rg = n_rg;
                 best.counters_bytes = counters_bytes;
-                best.total_bytes = counters_bytes + (best.S > 1 ? ((size_t)BH * best.S * (size_t)(nq * 16 * (2 + D)) * sizeof(float) + 255) / 256 * 256 : 0);
+                best.total_bytes = counters_bytes + (R > 1 ? ((size_t)BH * best.S * (size_t)(nq * 16 * (2 + D)) * sizeof(float) + 255) / 256 * 256 : 0);
             }
         }
     }

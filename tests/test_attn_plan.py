@@ -32,7 +32,9 @@ int main()
                         if (C == ctxs[0]) first = p.counters_bytes;
                         if (p.counters_bytes != first) bad("the counters' place depends on the context");
                         if (p.counters_bytes < (size_t)BH * p.n_rg * sizeof(unsigned long long)) bad("counters overlap the partial results");
-                        if (p.S > 1 && p.total_bytes < p.counters_bytes + (size_t)BH * p.S * part) bad("no room for the partial results");
+                        const bool partials = f32 ? p.S > 1 : p.ranges > 1;        // (one key range is written out directly)
+                        if (partials && p.total_bytes < p.counters_bytes + (size_t)BH * p.S * part) bad("no room for the partial results");
+                        if (!f32 && !partials && p.total_bytes != p.counters_bytes) bad("room for partial results that nothing writes");
                         if (p.rg_tiles * p.n_rg * 16 < N) bad("rows without a group");
                         if (p.S < p.n_rg || (p.waves != 4 && p.waves != 8)) bad("workgroups");
                         // kept plans: the one just made, and one that may have been pushed out since
