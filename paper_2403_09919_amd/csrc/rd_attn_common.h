@@ -20,7 +20,7 @@ struct AttnPlan {
     int S;             // workgroups per (sequence, head) at most
     int rg_tiles;      // 16-row tiles of packed rows per workgroup (a row group)
     int n_rg;          // row groups per (sequence, head); 1 unless N is large
-    int ranges;        // key ranges per row group at most
+    uint64_t ranges;   // key ranges per row group at most, by the number of row groups that hold packed rows (attn_ranges)
     int sorted;        // long sequences first: more workgroups than the chip holds, of eight tiles per wave and more
     size_t counters_bytes;
     size_t total_bytes;
@@ -35,6 +35,9 @@ static inline AttnGroups attn_groups(int N)
     const int nq = (nq_all + n_rg - 1) / n_rg;
     return {nq, (nq_all + nq - 1) / nq};
 }
+
+// Key ranges per row group where n_act groups (1 to 8) hold packed rows: a byte each, 1 to 64.
+__host__ __device__ inline int attn_ranges(uint64_t ranges, int n_act) { return (int)(ranges >> (8 * (n_act - 1))) & 0xff; }
 
 // Bytes of the completion counters, in front of the partial results.  One workspace may serve calls planned for
 // different contexts (ctx_bound of rd_tree_attn_bounded): a counter must never lie where another of these plans keeps
@@ -72,9 +75,10 @@ static inline double attn_search(int n_rg, int n_act, int nblk, bool every, doub
 
 // Plan of the matrix-core kernel (rd_tree_attn_mfma.h), for contexts of up to Cmax keys: waves per workgroup and key ranges
 // per row group, from an estimate of the launch time.  Lengths are upper bounds and the packed rows are not known at all
-// here (distinct prefixes are taken to be 0.6 of the candidates' tokens, less of wide beams); the kernel deals the tiles it finds to the ranges
-// and starts no more row groups than hold packed rows.  The constants are fitted to 1320 launches on MI355X (100 shapes, four
-// and eight waves, 1 to 20 ranges), us, with r = row tiles that hold packed rows:
+// here (distinct prefixes are taken to be 0.6 of the candidates' tokens, less of wide beams); the kernel starts no more row
+// groups than hold packed rows and deals the tiles it finds to the ranges that the plan has for so many groups.  The constants
+// are fitted to 1320 launches on MI355X (100 shapes, four and eight waves, 1 to 20 ranges), us, with r = row tiles that hold
+// packed rows:
 //   * a workgroup takes 2.8 (four waves) or 3.8 (eight), and 1.15 or 0.6 for at most one tile per wave, else 0.62 + 0.22 r or
 //     0.85 + 0.25 r per tile of a wave (D = 64: 0.65 of that) and 0.7 r or 0.95 r where the waves' states meet;
 //   * one eight-wave workgroup fills a compute unit, two of four waves do; more start as those retire;
@@ -92,24 +96,29 @@ static inline AttnPlan attn_plan_make(int B, int H, int N, int D, int Cmax, bool
     const long long BH = (long long)B * H;
     const size_t counters_bytes = attn_counters_bytes(BH, N);
     const int nq = attn_groups(N).rg_tiles, n_rg = attn_groups(N).n_rg;
-    const double rows = 0.6 * N < 20 + 0.42 * N ? 0.6 * N : 20 + 0.42 * N, scale = D == 128 ? 1.0 : 0.65;
-    const int n_act = (int)ceil(rows / (16 * nq));
-    const double r = n_act > 1 ? nq : ceil(rows / 16), part = r * 16 * (2 + D) * sizeof(float);
-    const int tiles = (Cmax + 31) / 32 + ((int)rows + 31) / 32;
+    const double guess = 0.6 * N < 20 + 0.42 * N ? 0.6 * N : 20 + 0.42 * N, scale = D == 128 ? 1.0 : 0.65;
+    const int n_guess = (int)ceil(guess / (16 * nq));
     static const int waves_env = env_int("RD_ATTN_WAVES", 0), forced_env = env_int("RD_ATTN_SPLITS", 0);
-    AttnPlan best = {};
-    double best_T = 1e30;
-    for (int waves = 8; waves >= 4; waves -= 4) {
-        if (waves_env ? waves != waves_env : waves == 8 && n_rg > 1) continue;
+    struct Choice {
+        double T;
+        int R, sorted;
+    };
+    // The best number of ranges where n_act row groups hold `rows` packed rows; `usual` instead (if there is one) unless the
+    // estimate is less than `margin` of that one's.
+    auto choose = [&](int waves, int n_act, double rows, int usual, double margin) {
+        const double r = n_act > 1 ? nq : ceil(rows / 16), part = r * 16 * (2 + D) * sizeof(float);
+        const int tiles = (Cmax + 31) / 32 + ((int)rows + 31) / 32;
         const int nblk = tiles > waves ? (tiles + waves - 1) / waves : 1, most = nblk < 64 ? nblk : 64;
         const int forced = forced_env > most ? most : forced_env;
         const double t_tile = scale * (waves == 8 ? 0.85 + 0.25 * r : 0.62 + 0.22 * r), t_meet = scale * r * (waves == 8 ? 0.95 : 0.7);
         const double t_wg = waves == 8 ? 3.8 : 2.8, t_one = waves == 8 ? 0.6 : 1.15, rate = waves == 8 ? 5.9e6 : 6.6e6;
         const long long slots = waves == 8 ? 256 : 512;
+        Choice best = {1e30, 1, 0};
+        double T_usual = 1e30;
         for (int R = 1; R <= most; ++R) {
             const int per = (tiles + R - 1) / R, steps = (per + waves - 1) / waves;
             // more ranges with as many tiles per wave take no less time: only the fewest of them are looked at (`every`: all; they agree)
-            if (!every && forced <= 0 && R > 1 && steps == ((tiles + R - 2) / (R - 1) + waves - 1) / waves) continue;
+            if (!every && forced <= 0 && R > 1 && R != usual && steps == ((tiles + R - 2) / (R - 1) + waves - 1) / waves) continue;
             const double t_lat = t_wg + (steps == 1 ? t_one : steps * t_tile + t_meet);
             const double all = (double)(steps * waves < tiles ? steps * waves : tiles) * 32 * D * 4;      // of K and V, for a workgroup
             const long long wgs = (BH + 7) / 8 * 8 * n_act * R, full = wgs / slots, rest = wgs % slots;
@@ -122,20 +131,40 @@ static inline AttnPlan attn_plan_make(int B, int H, int N, int D, int Cmax, bool
             };
             double T = full * round(slots) + (rest ? round(rest) : 0.0);
             if (R > 1) T += 1.6 + R * part / 48e3 + 2.0 * (double)BH * n_act * R * part / 4.6e6;
-            if (forced > 0 ? R == forced : T < best_T * (1 - 1e-9)) {
-                best_T = T;
-                best.waves = waves;
-                best.S = R * n_rg;
-                best.ranges = R;
-                best.sorted = B > 1 && wgs > slots && steps >= 8;
-                best.rg_tiles = nq;
-                best.n_rg = n_rg;
-                best.counters_bytes = counters_bytes;
-                best.total_bytes = counters_bytes + (R > 1 ? ((size_t)BH * best.S * (size_t)(nq * 16 * (2 + D)) * sizeof(float) + 255) / 256 * 256 : 0);
-            }
+            if (forced > 0 ? R == forced : T < best.T * (1 - 1e-9)) best = {T, R, B > 1 && wgs > slots && steps >= 8};
+            if (R == usual) T_usual = T;
+        }
+        if (T_usual * margin <= best.T) best.R = usual;
+        return best;
+    };
+    AttnPlan plan = {};
+    Choice best = {1e30, 1, 0};
+    for (int waves = 8; waves >= 4; waves -= 4) {
+        if (waves_env ? waves != waves_env : waves == 8 && n_rg > 1) continue;
+        const Choice c = choose(waves, n_guess, guess, 0, 1.0);
+        if (c.T < best.T * (1 - 1e-9)) {
+            best = c;
+            plan.waves = waves;
         }
     }
-    return best;
+    // The kernel finds how many row groups hold packed rows and takes the ranges of that number: those of the guess unless the
+    // estimate promises 7 % (it is not exact to less: 30 x 5 tokens, H=32, C=2048, 120 packed rows 23.2 us with the guess's four,
+    // 24.0 with five, where it promises 4 %).  us with the guess's ranges for all -> these, H=32: 70 x 5 tokens, C=1777, 30
+    // packed rows 18.6 -> 15.0, 96 20.8 -> 17.4, 200 29.9 -> 25.8; C=4096, 200 47.6 -> 39.2; B=2, 50 x 5, C=3000, 40 41.1 -> 29.7;
+    // B=4, H=40, 16 x 5, C=4096, 60 94.6 -> 84.7.
+    int most = 1;
+    for (int n = 1; n <= n_rg; ++n) {
+        const int R = n == n_guess ? best.R : choose(plan.waves, n, (n - 0.5) * 16 * nq, best.R, 0.93).R;
+        plan.ranges |= (uint64_t)R << (8 * (n - 1));
+        plan.S = R * n > plan.S ? R * n : plan.S;
+        most = R > most ? R : most;
+    }
+    plan.sorted = best.sorted;
+    plan.rg_tiles = nq;
+    plan.n_rg = n_rg;
+    plan.counters_bytes = counters_bytes;
+    plan.total_bytes = counters_bytes + (most > 1 ? ((size_t)BH * plan.S * (size_t)(nq * 16 * (2 + D)) * sizeof(float) + 255) / 256 * 256 : 0);
+    return plan;
 }
 
 // Microseconds that merging n_part partial results of `part` bytes each takes: written and read back, the reading by one
@@ -158,7 +187,7 @@ static inline AttnPlan attn_plan_make_f32(int B, int H, int N, int D, int Cmax, 
     best.waves = 8;
     best.rg_tiles = 1;
     best.n_rg = n_rg;
-    best.ranges = 1;
+    best.ranges = 1;       // (not used: workgroups are dealt by S)
     attn_search(n_rg, n_act, nblk, every, 1e30, &best.S, [&](int wgs_per_head, int per, int n_part) {
         const double t_lat = 1.5 + per * t_blk, bytes = (double)(per * 8 < tiles ? per * 8 : tiles) * 16 * D * 8;
         const long long wgs = (BH + 7) / 8 * 8 * wgs_per_head, full = wgs / 256, rest = wgs % 256;
@@ -204,7 +233,7 @@ struct AttnArgs {
     float *partials;
     int B, H, N, Cmax, S, words;
     int n_rg;      // row groups per (sequence, head) (each is NQ*16 rows of the kernel's template)
-    int ranges;    // key ranges per row group at most
+    uint64_t ranges;   // key ranges per row group at most, by the number of groups with packed rows (attn_ranges)
     int sorted;    // workgroups of long sequences first
     float scale_log2e;
     // rotary embedding fused into the call (rd_tree_attn_rope); unused (null) otherwise

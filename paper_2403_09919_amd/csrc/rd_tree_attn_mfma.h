@@ -162,8 +162,7 @@ __global__ __launch_bounds__(NW * 64, 2) void rd_tree_attn_mfma_kernel(AttnArgs 
     typedef const __attribute__((address_space(4))) int32_t cint32;
     cint32 *ctx_len = (cint32 *)(uintptr_t)a.ctx_len, *packed = (cint32 *)(uintptr_t)a.n_packed;
     const int xcd = (int)(blockIdx.x & 7), n_rg = a.n_rg;
-    const int ranges = a.ranges;
-    int bh, b, r_wg, n_act = 1;                                 // n_act row groups times ranges: the head's workgroups
+    int bh, b, r_wg, n_act = 1, ranges = attn_ranges(a.ranges, 1);      // n_act row groups times ranges: the head's workgroups
     if (n_rg == 1 && !a.sorted) {
         const int k = (int)(blockIdx.x >> 3), hl = ranges == 1 ? k : k / ranges;
         r_wg = k - hl * ranges;
@@ -172,6 +171,7 @@ __global__ __launch_bounds__(NW * 64, 2) void rd_tree_attn_mfma_kernel(AttnArgs 
         b = a.B == 1 ? 0 : bh / a.H;
     } else if (a.B == 1) {                    // only row groups that hold packed rows get workgroups
         n_act = max((clampi(packed[0], 0, a.N) + kRows - 1) / kRows, 1);
+        ranges = attn_ranges(a.ranges, n_act);
         const int k = (int)(blockIdx.x >> 3), n_wg = n_act * ranges, hl = k / n_wg;
         r_wg = k - hl * n_wg;
         bh = hl * 8 + xcd;
@@ -203,7 +203,7 @@ __global__ __launch_bounds__(NW * 64, 2) void rd_tree_attn_mfma_kernel(AttnArgs 
             const int s = b0 + seq;
             act = max((clampi(rows, 0, a.N) + kRows - 1) / kRows, 1);
             first = (s * a.H + 7 - xcd) >> 3;
-            need = lane < here ? ((((s + 1) * a.H + 7 - xcd) >> 3) - first) * act * ranges : 0;
+            need = lane < here ? ((((s + 1) * a.H + 7 - xcd) >> 3) - first) * act * attn_ranges(a.ranges, act) : 0;
             sum = need;
 #pragma unroll
             for (int o = 1; o < 64; o <<= 1) {
@@ -219,6 +219,7 @@ __global__ __launch_bounds__(NW * 64, 2) void rd_tree_attn_mfma_kernel(AttnArgs 
         }
         if (at < 0) return;
         n_act = __builtin_amdgcn_readlane(act, at);
+        ranges = attn_ranges(a.ranges, n_act);
         const int n_wg = n_act * ranges, own = k - (before + __builtin_amdgcn_readlane(sum, at) - __builtin_amdgcn_readlane(need, at)), hl = own / n_wg;
         r_wg = own - hl * n_wg;
         b = b0 + __builtin_amdgcn_readlane(seq, at);

@@ -32,7 +32,13 @@ int main()
                         if (C == ctxs[0]) first = p.counters_bytes;
                         if (p.counters_bytes != first) bad("the counters' place depends on the context");
                         if (p.counters_bytes < (size_t)BH * p.n_rg * sizeof(unsigned long long)) bad("counters overlap the partial results");
-                        const bool partials = f32 ? p.S > 1 : p.ranges > 1;        // (one key range is written out directly)
+                        int most = 1;              // key ranges; one is written out directly
+                        for (int g = 1; !f32 && g <= p.n_rg; ++g) {
+                            const int R = attn_ranges(p.ranges, g);
+                            most = R > most ? R : most;
+                            if (R < 1 || R * g > p.S) bad("key ranges without workgroups");
+                        }
+                        const bool partials = f32 ? p.S > 1 : most > 1;
                         if (partials && p.total_bytes < p.counters_bytes + (size_t)BH * p.S * part) bad("no room for the partial results");
                         if (!f32 && !partials && p.total_bytes != p.counters_bytes) bad("room for partial results that nothing writes");
                         if (p.rg_tiles * p.n_rg * 16 < N) bad("rows without a group");
@@ -48,6 +54,15 @@ int main()
                         ++n;
                     }
                 }
+    // Beams whose candidates share most of their prefixes: the rows of one or two groups out of many still get
+    // workgroups for about half of the chip's 256 compute units and more, as their keys allow (33 tiles of them and more here).
+    const int shared[][4] = {{1, 32, 350, 1777}, {1, 32, 350, 4096}, {1, 32, 150, 2048}, {2, 32, 250, 3000}, {4, 40, 80, 4096}, {1, 4, 384, 6000}};
+    for (auto &s : shared)
+        for (int g = 1; g <= 2; ++g) {
+            const AttnPlan p = attn_plan_make(s[0], s[1], s[2], 128, s[3]);
+            const int wgs = s[0] * s[1] * g * attn_ranges(p.ranges, g), least = s[0] * s[1] * 10 < 120 ? s[0] * s[1] * 10 : 120;
+            if (wgs < least) printf("B=%d H=%d N=%d C=%d: %d workgroups for %d groups of packed rows\n", s[0], s[1], s[2], s[3], wgs, g);
+        }
     printf("plans %ld\n", n);
 }
 """

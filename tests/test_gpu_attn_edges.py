@@ -77,3 +77,28 @@ def test_rotary_tables_at_any_multiple_of_four_bytes(rd, D, W, L, ctx, shift):
     torch.cuda.synchronize()
     P = int(d["n_packed"][0])
     assert np.array_equal(host(out), host(sep)) and np.array_equal(host(k_rot)[0, :, :P], host(k2)[0, :, :P])
+
+
+@pytest.mark.parametrize("dtype,D", [("bf16", 128), ("f16", 64)])
+@pytest.mark.parametrize("H,W,L,ctx,vocabs", [(4, 70, 5, [1777], [1]), (4, 70, 5, [1777], [2]), (4, 70, 5, [4096], [3]), (3, 16, 5, [4096, 700, 3000], [2, 32000, 5]),
+                                              (5, 30, 5, [2048, 2048], [2, 32000]), (2, 128, 3, [0, 3000, 31, 1500], [1, 4, 8, 32000])])
+def test_few_packed_rows_in_a_wide_beam(rd, dtype, D, H, W, L, ctx, vocabs):
+    """Candidates that share most of their prefixes (small vocabularies) beside ones that do not: the key ranges of a head go
+    by how many of its row groups hold packed rows, and the sequences of a batch differ in that."""
+    announce(f"few packed rows {dtype} D={D} H={H} W={W} L={L} ctx={ctx} vocabs={vocabs}")
+    B = len(ctx)
+    ctx, _, q, kn, vn, kc, vc, _ = _case(B, H, W, L, ctx, D, dtype, W + H)
+    beams = np.concatenate([synth.make_beams(1, W, L, v, 7 + i, "uniform") for i, v in enumerate(vocabs)])
+    d = oracle.dedup(beams, ctx)
+    scale = float(1.0 / np.sqrt(D))
+    ref = oracle.tree_attn(q, kc, vc, ctx, kn, vn, d["n_packed"], d["tree_mask"], dtype, scale)
+    ws = rd.new_workspace(rd.rd_tree_attn_workspace(B, H, W * L, D, kc.shape[2], rd.RD_BF16 if dtype == "bf16" else rd.RD_F16), "cuda")
+    for _ in range(2):                                             # the second call finds the counters as the first left them
+        out = torch.full_like(dev(q), float("nan"))
+        rd.rd_tree_attn(dev(q), dev(kc), dev(vc), dev(ctx), dev(kn), dev(vn), dev(d["n_packed"]), dev(d["tree_mask_bits"]), scale,
+                        out=out, workspace=ws)
+        torch.cuda.synchronize()
+        got, want = synth.to_f64(host(out), dtype), synth.to_f64(ref, dtype)
+        assert np.isfinite(got).all() and np.abs(got - want).max() <= TOL[dtype]
+        for b in range(B):
+            assert not got[b, :, int(d["n_packed"][b]):].any()
