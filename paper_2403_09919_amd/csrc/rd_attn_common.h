@@ -15,13 +15,17 @@ namespace rd {
 
 typedef __attribute__((ext_vector_type(4))) float f32x4;
 
+constexpr int kOneStep = 64;     // sequences that the lanes of a wave hold one by one
+
 struct AttnPlan {
     int waves;         // waves per workgroup (4 or 8); a block is a tile of keys per wave
-    int S;             // workgroups per (sequence, head) at most
+    int S;             // workgroups per (sequence, head) at most; 1 with several row groups: one takes them all in turn
     int rg_tiles;      // 16-row tiles of packed rows per workgroup (a row group)
     int n_rg;          // row groups per (sequence, head); 1 unless N is large
     uint64_t ranges;   // key ranges per row group at most, by the number of row groups that hold packed rows (attn_ranges)
-    int sorted;        // long sequences first: more workgroups than the chip holds, of eight tiles per wave and more
+    int sorted;        // long sequences first: more workgroups than the chip holds, of eight tiles per wave and more, and
+                       // at most kOneStep sequences (us, ranked in steps of 64 / not at all: 8 x 5 tokens, H=4, 100 to 1500 keys,
+                       // B=512 205 / 180; H=32, 100 to 1000 keys 1231 / 926)
     size_t counters_bytes;
     size_t total_bytes;
 };
@@ -131,7 +135,7 @@ static inline AttnPlan attn_plan_make(int B, int H, int N, int D, int Cmax, bool
             };
             double T = full * round(slots) + (rest ? round(rest) : 0.0);
             if (R > 1) T += 1.6 + R * part / 48e3 + 2.0 * (double)BH * n_act * R * part / 4.6e6;
-            if (forced > 0 ? R == forced : T < best.T * (1 - 1e-9)) best = {T, R, B > 1 && wgs > slots && steps >= 8};
+            if (forced > 0 ? R == forced : T < best.T * (1 - 1e-9)) best = {T, R, B > 1 && B <= kOneStep && wgs > slots && steps >= 8};
             if (R == usual) T_usual = T;
         }
         if (T_usual * margin <= best.T) best.R = usual;
@@ -160,6 +164,14 @@ static inline AttnPlan attn_plan_make(int B, int H, int N, int D, int Cmax, bool
         most = R > most ? R : most;
     }
     plan.sorted = best.sorted;
+    // Hundreds of sequences: finding a workgroup's place in the batch (0.5 us per 256 sequences and workgroup, also of those
+    // that then have nothing to do) costs more than reading K and V once per row group where contexts are short beside the batch.
+    // us, by places / one workgroup per head, which takes the row groups in turn (one group of packed rows; two): 16 x 5 tokens,
+    // H=4, up to 300 keys, B=1024 130 / 110 and 169 / 158, B=2048 307 / 211 and 379 / 310; H=8, B=600, up to 1000 keys 366 / 356
+    // and 404 / 456.
+    // (A launch holds fewer than 2^32 threads.)
+    const bool many = B > 256 && BH >= 2048 && (long long)n_rg * Cmax <= B, too_many = BH * n_rg >= 1ll << 24;
+    if (n_rg > 1 && most == 1 && ((many && !plan.sorted) || too_many)) plan.S = 1;
     plan.rg_tiles = nq;
     plan.n_rg = n_rg;
     plan.counters_bytes = counters_bytes;

@@ -115,7 +115,8 @@ constexpr int stat_stride(int waves) { return waves == 8 ? 12 : 4; }
 // (a.block_table, a.page_size, a.max_pages) instead of one dense [B,H,Cmax,D] tensor.
 // ROPE: q and k_new arrive unrotated; the kernel applies the rotary embedding at a.position_ids
 // to the query rows as it brings them into LDS and to the packed-key tiles as it walks them.
-template <typename T, int D, int NQ, int NW, bool PAGED, bool ROPE>
+// ALL: a workgroup takes all row groups of a head, one after the other (one key range each).
+template <typename T, int D, int NQ, int NW, bool PAGED, bool ROPE, bool ALL>
 __global__ __launch_bounds__(NW * 64, 2) void rd_tree_attn_mfma_kernel(AttnArgs a)
 {
     using G = Geo<D>;
@@ -141,8 +142,6 @@ __global__ __launch_bounds__(NW * 64, 2) void rd_tree_attn_mfma_kernel(AttnArgs 
     const int tid = threadIdx.x;
     const int lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int r16 = lane & 15;
-    const int g = lane >> 4;
     typedef __attribute__((address_space(3))) unsigned char lds_byte;
     const uint32_t lds0 = (uint32_t)(uintptr_t)(lds_byte *)smem;
     const uint32_t ldsK = lds0 + wave * G::kTileBytes, ldsV = ldsK + NW * G::kTileBytes;
@@ -163,14 +162,31 @@ __global__ __launch_bounds__(NW * 64, 2) void rd_tree_attn_mfma_kernel(AttnArgs 
     cint32 *ctx_len = (cint32 *)(uintptr_t)a.ctx_len, *packed = (cint32 *)(uintptr_t)a.n_packed;
     const int xcd = (int)(blockIdx.x & 7), n_rg = a.n_rg;
     int bh, b, r_wg, n_act = 1, ranges = attn_ranges(a.ranges, 1);      // n_act row groups times ranges: the head's workgroups
-    if (n_rg == 1 && !a.sorted) {
+    auto groups_of = [&](int rows) __attribute__((always_inline)) { return max((clampi(rows, 0, a.N) + kRows - 1) / kRows, 1); };
+    auto heads_before = [&](int s) __attribute__((always_inline)) { return (s * a.H + 7 - xcd) >> 3; };         // this XCD's, of sequences before s
+    auto wgs_of = [&](int s, int act) __attribute__((always_inline)) { return (heads_before(s + 1) - heads_before(s)) * act * attn_ranges(a.ranges, act); };
+    auto running = [&](int x) __attribute__((always_inline)) {             // sum over the lanes up to this one
+#pragma unroll
+        for (int o = 1; o < 64; o <<= 1) {
+            const int up = __shfl_up(x, o, 64);                 // (by all lanes)
+            x += lane >= o ? up : 0;
+        }
+        return x;
+    };
+    if constexpr (ALL) {                      // one workgroup per head, which takes the row groups one after the other
+        bh = (int)(blockIdx.x >> 3) * 8 + xcd;
+        if (bh >= a.B * a.H) return;
+        b = bh / a.H;
+        r_wg = 0;
+        n_act = groups_of(packed[b]);
+    } else if (n_rg == 1 && !a.sorted) {
         const int k = (int)(blockIdx.x >> 3), hl = ranges == 1 ? k : k / ranges;
         r_wg = k - hl * ranges;
         bh = hl * 8 + xcd;
         if (bh >= a.B * a.H) return;
         b = a.B == 1 ? 0 : bh / a.H;
     } else if (a.B == 1) {                    // only row groups that hold packed rows get workgroups
-        n_act = max((clampi(packed[0], 0, a.N) + kRows - 1) / kRows, 1);
+        n_act = groups_of(packed[0]);
         ranges = attn_ranges(a.ranges, n_act);
         const int k = (int)(blockIdx.x >> 3), n_wg = n_act * ranges, hl = k / n_wg;
         r_wg = k - hl * n_wg;
@@ -179,59 +195,83 @@ __global__ __launch_bounds__(NW * 64, 2) void rd_tree_attn_mfma_kernel(AttnArgs 
         b = 0;
     } else {
         // Only row groups that hold packed rows get workgroups, so their number is the sequence's own: a lane counts those of
-        // one sequence's heads on this XCD, and a running sum finds the workgroup's place.  (Workgroups without work in between
+        // one sequence's heads on this XCD, of four in large batches (a step of 64 costs 0.4 us: 512 sequences, H=32, 20 to 300
+        // keys, 80 tokens 680 us by steps of 64, 614 by 256), and a running sum finds the workgroup's place.  (Workgroups without work in between
         // leave compute units idle beside others that have two: 29 us for 22 at H=32, C=1777, 147 of 350 rows.)
-        const int k = (int)(blockIdx.x >> 3);
-        int before = 0, at = -1, b0 = 0;
-        // Where there are more workgroups than fit the chip at once, those of long sequences come first (a.sorted).
-        int seq, act, first, need, sum;
-        for (; b0 < a.B; b0 += 64) {
-            const int here = min(a.B - b0, 64);
-            seq = min(lane, here - 1);
-            int rows = a.n_packed[b0 + seq];
-            if (a.sorted) {
-                const int keys = lane < here ? a.ctx_len[b0 + seq] : -1;
+        int own = (int)(blockIdx.x >> 3);     // in the end: the workgroup's number among its sequence's
+        if (a.B <= kOneStep) {                // a sequence to a lane
+            int seq = min(lane, a.B - 1), rows = a.n_packed[seq];
+            if (a.sorted) {                   // where there are more workgroups than fit the chip at once, those of long sequences first
+                const int keys = lane < a.B ? a.ctx_len[seq] : -1;
                 int place = 0;
-                for (int j = 0; j < here; ++j) {
+                for (int j = 0; j < a.B; ++j) {
                     const int other = __builtin_amdgcn_readlane(keys, j);
                     place += other > keys || (other == keys && j < lane) ? 1 : 0;
                 }
-                place = lane < here ? place : lane;             // (a permutation of the lanes)
+                place = lane < a.B ? place : lane;              // (a permutation of the lanes)
                 seq = __builtin_amdgcn_ds_permute(place * 4, seq);
                 rows = __builtin_amdgcn_ds_permute(place * 4, rows);
             }
-            const int s = b0 + seq;
-            act = max((clampi(rows, 0, a.N) + kRows - 1) / kRows, 1);
-            first = (s * a.H + 7 - xcd) >> 3;
-            need = lane < here ? ((((s + 1) * a.H + 7 - xcd) >> 3) - first) * act * attn_ranges(a.ranges, act) : 0;
-            sum = need;
+            const int act = groups_of(rows), need = lane < a.B ? wgs_of(seq, act) : 0, sum = running(need);
+            const uint64_t past = __builtin_amdgcn_ballot_w64(sum > own);
+            if (past == 0) return;
+            const int at = __builtin_ctzll(past);
+            own -= __builtin_amdgcn_readlane(sum, at) - __builtin_amdgcn_readlane(need, at);
+            n_act = __builtin_amdgcn_readlane(act, at);
+            b = __builtin_amdgcn_readlane(seq, at);
+        } else {
+            int s0 = 0, need[4], act[4], at;
+            for (;; s0 += 256) {              // four sequences to a lane
+                int rows[4], all = 0;
 #pragma unroll
-            for (int o = 1; o < 64; o <<= 1) {
-                const int up = __shfl_up(sum, o, 64);           // (by all lanes)
-                sum += lane >= o ? up : 0;
+                for (int u = 0; u < 4; ++u) rows[u] = a.n_packed[min(s0 + lane * 4 + u, a.B - 1)];
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    const int s = s0 + lane * 4 + u;
+                    act[u] = groups_of(rows[u]);
+                    need[u] = s < a.B ? wgs_of(s, act[u]) : 0;
+                    all += need[u];
+                }
+                const int sum = running(all);
+                const uint64_t past = __builtin_amdgcn_ballot_w64(sum > own);
+                if (past != 0) {
+                    at = __builtin_ctzll(past);
+                    own -= __builtin_amdgcn_readlane(sum, at) - __builtin_amdgcn_readlane(all, at);
+                    break;
+                }
+                own -= __builtin_amdgcn_readlane(sum, 63);
+                if (s0 + 256 >= a.B) return;
             }
-            const uint64_t past = __builtin_amdgcn_ballot_w64(before + sum > k);
-            if (past != 0) {
-                at = __builtin_ctzll(past);
-                break;
+            b = s0 + at * 4;
+            n_act = __builtin_amdgcn_readlane(act[0], at);
+#pragma unroll
+            for (int u = 0; u < 3; ++u) {     // past the lane's first sequences
+                const int n = __builtin_amdgcn_readlane(need[u], at);
+                if (b == s0 + at * 4 + u && own >= n) {
+                    own -= n;
+                    ++b;
+                    n_act = __builtin_amdgcn_readlane(act[u + 1], at);
+                }
             }
-            before += __builtin_amdgcn_readlane(sum, 63);
         }
-        if (at < 0) return;
-        n_act = __builtin_amdgcn_readlane(act, at);
         ranges = attn_ranges(a.ranges, n_act);
-        const int n_wg = n_act * ranges, own = k - (before + __builtin_amdgcn_readlane(sum, at) - __builtin_amdgcn_readlane(need, at)), hl = own / n_wg;
+        const int n_wg = n_act * ranges, hl = own / n_wg;
         r_wg = own - hl * n_wg;
-        b = b0 + __builtin_amdgcn_readlane(seq, at);
-        bh = (__builtin_amdgcn_readlane(first, at) + hl) * 8 + xcd;
+        bh = (heads_before(b) + hl) * 8 + xcd;
     }
     if (n_rg > 1) {                           // output rows of the groups without packed rows are zero
         T *z = static_cast<T *>(a.out) + (size_t)bh * a.N * D;
-        for (int i = n_act * kRows * D + (r_wg * NW * 64 + tid) * 8; i < a.N * D; i += n_act * ranges * NW * 64 * 8)
+        const int n_wg = ALL ? 1 : n_act * ranges;
+        for (int i = n_act * kRows * D + (r_wg * NW * 64 + tid) * 8; i < a.N * D; i += n_wg * NW * 64 * 8)
             *reinterpret_cast<uint4 *>(z + i) = make_uint4(0, 0, 0, 0);
     }
     const int C_b = ctx_len[b], P_b = packed[b];
-    const int split = n_act == 1 ? r_wg : r_wg / n_act, rg = r_wg - split * n_act;
+    const int split = ALL || n_act == 1 ? r_wg : r_wg / n_act;
+    int rg = ALL ? 0 : r_wg - split * n_act;
+    for (;;) {                                // (ALL: row groups)
+    int lane_ = tid & 63, bh_ = bh;
+    if constexpr (ALL) asm volatile("" : "+v"(lane_), "+s"(bh_));      // (addresses made anew for every group: kept over the loop they spill)
+    const int lane = lane_, bh = bh_, r16 = lane & 15, g = lane >> 4;
     const int row0 = rg * kRows;
     const int Ng = min(kRows, a.N - row0);                      // rows of `out` this group owns
     const int lrow = lane / G::kChunks, lchunk = lane % G::kChunks;
@@ -821,6 +861,9 @@ __global__ __launch_bounds__(NW * 64, 2) void rd_tree_attn_mfma_kernel(AttnArgs 
     constexpr int kHalf = (NQ + 1) / 2;
     if (NQ > 1 && nqt <= kHalf) walk(std::integral_constant<int, kHalf>{});
     else walk(std::integral_constant<int, NQ>{});
+    if (!ALL || ++rg >= n_act) return;
+    lds_barrier();                            // all waves have read what the next group's copies overwrite
+    }
 }
 
 template <int D, int NQ, int NW>
@@ -829,23 +872,30 @@ static constexpr size_t mfma_smem_bytes()
     return (size_t)2 * NW * Geo<D>::kTileBytes + (size_t)NQ * 16 * Geo<D>::kRowBytes + NW * 256 + (size_t)2 * NQ * 16 * stat_stride(NW) * sizeof(float);
 }
 
-template <typename T, int D, int NQ, int NW, bool PAGED, bool ROPE>
+template <typename T, int D, int NQ, int NW, bool PAGED, bool ROPE, bool ALL = false>
 static int launch_mfma(const AttnArgs &a, hipStream_t stream)
 {
     constexpr size_t smem = mfma_smem_bytes<D, NQ, NW>();
     static_assert((smem + 256) * (8 / NW) <= 160 * 1024, "LDS of a compute unit: one workgroup of eight waves, two of four");
     static std::atomic<unsigned long long> configured{0};
-    const int st = ensure_dynamic_lds(reinterpret_cast<const void *>(&rd_tree_attn_mfma_kernel<T, D, NQ, NW, PAGED, ROPE>), smem, configured);
+    const int st = ensure_dynamic_lds(reinterpret_cast<const void *>(&rd_tree_attn_mfma_kernel<T, D, NQ, NW, PAGED, ROPE, ALL>), smem, configured);
     if (st != RD_OK) return st;
     const size_t wgs = ((size_t)a.B * a.H + 7) / 8 * 8 * a.S;
     if (wgs > 0x7fffffffull) return RD_ERR_UNSUPPORTED;
-    hipLaunchKernelGGL((rd_tree_attn_mfma_kernel<T, D, NQ, NW, PAGED, ROPE>), dim3((unsigned)wgs), dim3(NW * 64), smem, stream, a);
+    hipLaunchKernelGGL((rd_tree_attn_mfma_kernel<T, D, NQ, NW, PAGED, ROPE, ALL>), dim3((unsigned)wgs), dim3(NW * 64), smem, stream, a);
     return rd_check_launch();
 }
 
 template <typename T, int D, int NW, bool PAGED, bool ROPE>
 static int dispatch_nq(const AttnArgs &a, int rg_tiles, hipStream_t stream)
 {
+    if constexpr (NW == 4) {
+        if (a.n_rg > 1 && a.S == 1) {
+            if (rg_tiles == 2) return launch_mfma<T, D, 2, NW, PAGED, ROPE, true>(a, stream);
+            if (rg_tiles == 3) return launch_mfma<T, D, 3, NW, PAGED, ROPE, true>(a, stream);
+            return RD_ERR_UNSUPPORTED;
+        }
+    }
     switch (rg_tiles) {
     case 1: return launch_mfma<T, D, 1, NW, PAGED, ROPE>(a, stream);
     case 2: return launch_mfma<T, D, 2, NW, PAGED, ROPE>(a, stream);

@@ -5,19 +5,28 @@ import subprocess
 
 import pytest
 
+import attn_dealing
+
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
 PROGRAM = r"""
 #include "rd_attn_common.h"
 #include <stdio.h>
+#include <stdlib.h>
 #include <string.h>
 using namespace rd;
 
-// One line per plan that breaks a rule; the last line counts the plans looked at.
-int main()
+// With arguments (B H N D C) the way the launch deals its workgroups.  Else one line per plan that breaks a rule; the last line
+// counts the plans looked at.
+int main(int argc, char **argv)
 {
+    if (argc > 5) {
+        const AttnPlan p = attn_plan_make(atoi(argv[1]), atoi(argv[2]), atoi(argv[3]), atoi(argv[4]), atoi(argv[5]));
+        puts(p.n_rg > 1 && p.S == 1 ? "in turn" : p.sorted ? "ranked" : p.n_rg > 1 ? "places" : "heads");
+        return 0;
+    }
     const int ctxs[] = {0, 1, 32, 100, 300, 700, 1000, 1400, 1500, 2048, 3000, 5000, 9000, 20000, 40000, 131072};
-    const int shapes[][2] = {{1, 1}, {1, 4}, {1, 5}, {1, 32}, {2, 40}, {4, 32}, {8, 32}, {3, 26}, {16, 52}, {24, 32}};
+    const int shapes[][2] = {{1, 1}, {1, 4}, {1, 5}, {1, 32}, {2, 40}, {4, 32}, {8, 32}, {3, 26}, {16, 52}, {24, 32}, {70, 3}, {300, 8}, {2048, 4}};
     long n = 0;
     for (int f32 = 0; f32 < 2; ++f32)
         for (int D = 64; D <= 128; D += 64)
@@ -36,13 +45,13 @@ int main()
                         for (int g = 1; !f32 && g <= p.n_rg; ++g) {
                             const int R = attn_ranges(p.ranges, g);
                             most = R > most ? R : most;
-                            if (R < 1 || R * g > p.S) bad("key ranges without workgroups");
+                            if (R < 1 || (p.S > 1 ? R * g > p.S : R > 1)) bad("key ranges without workgroups");
                         }
                         const bool partials = f32 ? p.S > 1 : most > 1;
                         if (partials && p.total_bytes < p.counters_bytes + (size_t)BH * p.S * part) bad("no room for the partial results");
                         if (!f32 && !partials && p.total_bytes != p.counters_bytes) bad("room for partial results that nothing writes");
                         if (p.rg_tiles * p.n_rg * 16 < N) bad("rows without a group");
-                        if (p.S < p.n_rg || (p.waves != 4 && p.waves != 8)) bad("workgroups");
+                        if ((p.S < p.n_rg && (f32 || p.S != 1)) || p.ranges == 0 || (p.waves != 4 && p.waves != 8)) bad("workgroups");
                         // kept plans: the one just made, and one that may have been pushed out since
                         for (int other : {C, ctxs[0], 300}) {
                             const AttnPlan kept = attn_plan(s[0], s[1], N, D, other, f32 != 0);
@@ -69,7 +78,7 @@ int main()
 
 
 @pytest.fixture(scope="module")
-def report(tmp_path_factory):
+def program(tmp_path_factory):
     tmp = tmp_path_factory.mktemp("plan")
     src, exe = str(tmp / "plan.hip"), str(tmp / "plan")
     with open(src, "w") as f:
@@ -78,7 +87,12 @@ def report(tmp_path_factory):
     subprocess.run([hipcc, "--offload-arch=gfx950", "--cuda-host-only", "-O1", "-std=c++17", "-I", os.path.join(ROOT, "include"),
                     "-I", os.path.join(ROOT, "paper_2403_09919_amd", "csrc"), "-Wno-unused-function", src, "-o", exe],
                    check=True, capture_output=True, text=True)
-    return subprocess.run([exe], check=True, capture_output=True, text=True, timeout=300).stdout.splitlines()
+    return exe
+
+
+@pytest.fixture(scope="module")
+def report(program):
+    return subprocess.run([program], check=True, capture_output=True, text=True, timeout=300).stdout.splitlines()
 
 
 def test_workspace_layout_is_the_same_for_every_context(report):
@@ -86,3 +100,10 @@ def test_workspace_layout_is_the_same_for_every_context(report):
     to lie at the same place in front of the partial results whatever the plan."""
     assert report[-1].startswith("plans ") and int(report[-1].split()[1]) > 200000
     assert report[:-1] == [], (len(report) - 1, report[:5])
+
+
+@pytest.mark.parametrize("way,B,H,W,L,D,C", attn_dealing.SHAPES)
+def test_shapes_are_dealt_as_named(program, way, B, H, W, L, D, C):
+    for ctx in (C, (C + 31) // 32 * 32):                               # dense, and in pages of 32 keys
+        out = subprocess.run([program] + [str(x) for x in (B, H, W * L, D, ctx)], check=True, capture_output=True, text=True).stdout
+        assert out.strip() == way
