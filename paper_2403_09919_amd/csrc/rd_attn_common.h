@@ -94,7 +94,9 @@ static inline double attn_search(int n_rg, int n_act, int nblk, bool every, doub
 //     written and read at 4.6 TB/s.
 // Several row groups take four waves: their number is only guessed here, and where one more than that no longer fits the chip
 // eight waves take two rounds (H=32, C=1777, 350 tokens: 21.9 us with 4 groups of packed rows, 36.6 with 5; four waves 21.5
-// and 29.7).  Over 100 shapes the choice is 1.4 % slower than the best of the 18 in the mean, 17 % at worst.
+// and 29.7).  Eight where all of them fit the chip and a head has a tile for each wave at most, but more than four of them
+// (B=3, H=8, C=154, 88 tokens: 9.2 us by four waves, 7.4 by eight; B=2, H=4, C=70, 84 tokens 8.8 and 6.5; but D=64, B=1, H=8,
+// C=66, 72 tokens 4.65 and 4.8).  Over 100 shapes the choice is 1.4 % slower than the best of the 18 in the mean, 17 % at worst.
 static inline AttnPlan attn_plan_make(int B, int H, int N, int D, int Cmax, bool every = false)
 {
     const long long BH = (long long)B * H;
@@ -141,10 +143,12 @@ static inline AttnPlan attn_plan_make(int B, int H, int N, int D, int Cmax, bool
         if (T_usual * margin <= best.T) best.R = usual;
         return best;
     };
+    const int ctx_tiles = (Cmax + 31) / 32;
+    const bool eight = n_rg == 1 || ((BH + 7) / 8 * 8 * n_rg <= 256 && ctx_tiles >= (D == 128 ? 3 : 4) && ctx_tiles + (N + 31) / 32 <= 8);
     AttnPlan plan = {};
     Choice best = {1e30, 1, 0};
     for (int waves = 8; waves >= 4; waves -= 4) {
-        if (waves_env ? waves != waves_env : waves == 8 && n_rg > 1) continue;
+        if (waves_env ? waves != waves_env : waves == 8 && !eight) continue;
         const Choice c = choose(waves, n_guess, guess, 0, 1.0);
         if (c.T < best.T * (1 - 1e-9)) {
             best = c;
