@@ -1252,10 +1252,26 @@ __global__ __launch_bounds__(kSelThreads) void rd_row_beam_kernel(
             s_tok[rank] = min(max(e.tok, 0), V - 1);
         }
     }
-    for (int r = n + tid; r < W; r += kSelThreads) {                  // NaN scores: keep indices in range
+    for (int r = n + tid; r < W; r += kSelThreads) {                  // (keep indices in range)
         s_win[r] = 0;
         s_winv[r] = -INFINITY;
         s_tok[r] = 0;
+    }
+    if (n == 0) {
+        // No row has a score (a logit of +inf, or a whole chunk of -inf, makes its log-sum-exp NaN): the best logits of the
+        // first one, as the two kernels above have it.
+        __syncthreads();
+        const size_t first = row0 * chunks * W;
+        for (int i = tid; i < chunks * W; i += kSelThreads) {
+            const float v1 = part_cv[first + i];
+            const int t1 = part_ci[first + i];
+            int rank = 0;
+            for (int k = 0; k < chunks * W; ++k) {
+                const int t2 = part_ci[first + k];
+                rank += better(part_cv[first + k], t2, v1, t1) || (t2 == t1 && k < i) ? 1 : 0;
+            }
+            if (rank < W && t1 != 0x7fffffff) s_tok[rank] = min(max(t1, 0), V - 1);
+        }
     }
     __syncthreads();
     for (int i = tid; i < W * L; i += kSelThreads) {

@@ -61,3 +61,38 @@ def test_nan_logits_keep_tokens_in_range(rd):  # noqa: F811
     torch.cuda.synchronize()
     beams = host(got["beams"])
     assert (beams >= 0).all() and (beams < V).all()
+
+
+@pytest.mark.parametrize("what", ["one logit +inf", "a chunk of -inf"])
+@pytest.mark.parametrize("B,W,V", [(2, 1, 5000), (2, 4, 5000), (3, 12, 9000), (1, 28, 9000), (2, 3, 66000), (2, 20, 70000), (2, 40, 5000)])
+def test_rows_without_a_score(rd, what, B, W, V):
+    """A logit of +inf, or a whole chunk of 4096 logits at -inf, leaves a row without a finite log-sum-exp and all candidates
+    without a score: the first candidate's largest logits are taken, whichever kernels run the selection."""
+    announce(f"draft selection {what} B={B} W={W} V={V}")
+    Dm, L = 128, 4
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(W + V)
+
+    def randn(*shape, std=1.0, dtype=torch.bfloat16):
+        return torch.randn(shape, generator=gen, device="cuda", dtype=dtype).mul_(std)
+
+    params = dict(emb=randn(V, Dm, std=0.8), rnn_u=randn(Dm, Dm, std=Dm ** -0.5), rnn_w=randn(Dm, Dm, std=Dm ** -0.5),
+                  rnn_b=randn(Dm, std=0.01, dtype=torch.float32), mlp_w=randn(1, 2 * Dm, 2 * Dm, std=(2 * Dm) ** -0.5),
+                  mlp_b=randn(1, 2 * Dm, std=0.01, dtype=torch.float32), head_w=randn(V, 2 * Dm, std=2 * (2 * Dm) ** -0.5))
+    params["mlp_w"][0, Dm], params["mlp_b"][0, Dm] = 0, 50.0        # one input of the output layer is positive in every row
+    if what == "one logit +inf":
+        params["head_w"][77, Dm] = float("inf")
+    else:
+        params["head_w"][4096:8192, Dm] = float("-inf")
+    last = torch.randint(0, V, (B,), generator=gen, device="cuda", dtype=torch.int32)
+    r = rd.rd_draft(params, randn(B, Dm), last, W, L, steps=True)
+    torch.cuda.synchronize()
+    logits, beams = r["step_logits"].cpu(), r["beams"].cpu()
+    assert (r["beam_logp"] == float("-inf")).all()
+    for b in range(B):
+        path = [int(last[b])]
+        for t in range(L - 1):
+            order = torch.argsort(logits[t, b * W], descending=True, stable=True)[:W].tolist()
+            want = [path + [tok] for tok in order]
+            path.append(order[0])
+        assert beams[b].tolist() == want
