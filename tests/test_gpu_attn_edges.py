@@ -102,3 +102,29 @@ def test_few_packed_rows_in_a_wide_beam(rd, dtype, D, H, W, L, ctx, vocabs):
         assert np.isfinite(got).all() and np.abs(got - want).max() <= TOL[dtype]
         for b in range(B):
             assert not got[b, :, int(d["n_packed"][b]):].any()
+
+
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("W,L,C", [(3, 4, 60), (8, 5, 100), (8, 5, 190)])
+def test_fp16_tiles_far_below_the_largest_score(rd, D, W, L, C):
+    """One key draws nearly all of a row's weight and its value is zero (an attention sink), so the output is made of
+    probabilities 2^-18.4 below it.  A tile's are taken against the tile's own maximum: relative to one reference for all tiles
+    they would be subnormal in fp16, off by 2^-25 / 2^-18.4 = 1 %."""
+    announce(f"sink D={D} W={W} L={L} C={C}")
+    B, H, N = 1, 3, W * L
+    ctx, beams, q, kn, vn, kc, vc, d = _case(B, H, W, L, [C], D, "f16", C)
+    q[:], kn[:], kc[:] = 0, 0, 0
+    q[..., 0], kc[:, :, 0, 0] = 1, 18.4 * np.log(2.0)               # the score of key 0; all others have none
+    vc[:, :, :32] = 0
+    vc[:, :, 32:C], vn[:] = np.abs(vc[:, :, 32:C]) + np.float16(0.5), np.abs(vn) + np.float16(0.5)
+    npk, bits = dev(d["n_packed"]), dev(d["tree_mask_bits"])
+    got = host(rd.rd_tree_attn(dev(q), dev(kc), dev(vc), dev(ctx), dev(kn), dev(vn), npk, bits, 1.0))
+    ref = oracle.tree_attn(q, kc, vc, ctx, kn, vn, d["n_packed"], d["tree_mask"], "f16", 1.0)
+    P = int(d["n_packed"][0])
+    sink = float(np.exp(np.float64(kc[0, 0, 0, 0])))
+    mask = d["tree_mask"][0].astype(np.float64)[:P, :P]
+    num = vc[0, :, 32:C].astype(np.float64).sum(1)[:, None] + np.einsum("pq,hqd->hpd", mask, vn[0, :, :P].astype(np.float64))
+    want = num / (sink + (C - 1) + mask.sum(1))[None, :, None]
+    # one rounding of the probabilities and one of the result to 11 bits, and the result lies among fp16's subnormals in part
+    assert np.abs(ref[0, :, :P].astype(np.float64) - want).max() <= 2 ** -11 * want.max() + 2 ** -25
+    assert (np.abs(got[0, :, :P].astype(np.float64) - want) <= 2 ** -10 * want + 2 ** -25).all()
