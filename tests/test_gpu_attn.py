@@ -43,6 +43,13 @@ def compare(got, ref, dtype, what=""):
     return err
 
 
+def n_row_groups(N):
+    """Row groups (each of at most three 16-row tiles) of a head in the 16-bit kernel: an arrival word of 8 bytes each."""
+    tiles = -(-N // 16)
+    per = -(-tiles // -(-tiles // 3))
+    return -(-tiles // per)
+
+
 def make_case(B, H, D, W, L, ctx, dtype, seed, V=6, share="uniform", poison=True):
     ctx = np.asarray(ctx, np.int32)
     Cmax = int(max(ctx.max(), 0))
@@ -81,9 +88,9 @@ def test_config2_vicuna7b_full(rd):
 
 @pytest.mark.parametrize("idx", [3, 4, 5])
 def test_full_size_configs_whole_tensor(rd, idx):
-    """Full-size tensors in the launch configuration the benchmark uses (configs 3 and 4: eight-wave
-    workgroups with three and five row tiles, one key range per head; config 5: four-wave workgroups
-    with five row tiles), every head and every row against the oracle."""
+    """Full-size tensors in the launches the benchmark uses (four-wave workgroups with three row tiles; config 3: one key range
+    per head; config 4: two row groups, three ranges where both hold packed rows; config 5: two row groups, longest
+    sequences first), every head and every row against the oracle."""
     cfg = synth.CONFIGS[idx]
     announce("attn config %d (bf16, full size, whole tensor)" % idx)
     t = synth.make_attn_inputs(cfg)
@@ -92,8 +99,8 @@ def test_full_size_configs_whole_tensor(rd, idx):
 
 
 def test_four_wave_three_tiles_whole_tensor(rd):
-    """More heads than compute units and more than 64 MB of K/V: four-wave workgroups with three row
-    tiles, one fused key range per head, ragged contexts; every head and row against the oracle."""
+    """More heads than compute units and more than 64 MB of K/V: four-wave workgroups with three row tiles, one key range per head, ragged contexts; every
+    head and row against the oracle."""
     announce("attn bf16, 320 heads, 4-wave workgroups, whole tensor")
     B, H, D, W, L = 10, 32, 128, 8, 5
     ctx = [704, 641, 577, 700, 513, 690, 1, 333, 704, 129]
@@ -103,7 +110,7 @@ def test_four_wave_three_tiles_whole_tensor(rd):
 
 
 def test_fp16_large_cache_whole_tensor(rd):
-    """IEEE-half K/V of more than 64 MB, the size from which four-wave workgroups are used."""
+    """IEEE-half K/V of more than 64 MB: four-wave workgroups, three key ranges."""
     announce("attn fp16, 67 MB of K/V, whole tensor")
     B, H, D, W, L, C = 2, 32, 128, 8, 5, 2048
     assert 2 * B * H * C * D * 2 >= 64e6
@@ -241,13 +248,13 @@ def test_workspace_reuse_and_determinism(rd):
     compare(a, ref, "bf16")
 
 
-@pytest.mark.parametrize("shape", ["config2", "three-ranges"])
+@pytest.mark.parametrize("shape", ["config2", "row-groups"])
 def test_workspace_reused_by_different_inputs_back_to_back(rd, shape):
     """Eight DIFFERENT inputs of one shape go through ONE workspace back to back, with no
     synchronisation in between, each into its own output; every output is compared with the oracle.
     A merge that read a partial result or an arrival word left by the previous call would show here.
-    Shapes: the Vicuna-7B-shaped layer (four context ranges plus the packed keys per head) and a long
-    context whose heads have three fused ranges."""
+    Shapes: the Vicuna-7B-shaped layer (five ranges of the context's and the packed keys per head) and a long
+    context whose heads have two row groups of seven ranges."""
     if shape == "config2":
         B, H, D, W, L, ctxs = 1, 32, 128, 8, 5, [[1024]] * 8
     else:
@@ -278,7 +285,8 @@ def test_workspace_reused_by_different_inputs_back_to_back(rd, shape):
         ref = oracle.tree_attn(t["q"], t["k_cache"], t["v_cache"], t["ctx_len"], t["k_new"], t["v_new"],
                                d["n_packed"], d["tree_mask"], "bf16", scale)
         compare(host(o), ref, "bf16", "reuse %s #%d" % (shape, i))
-    assert int(ws[: 8 * B * H].to(torch.int64).sum()) == 0   # arrival words (one per sequence and head) are left clear
+    words = 8 * B * H * n_row_groups(N)
+    assert ws.numel() > 2 * words and int(ws[:words].to(torch.int64).sum()) == 0       # arrival words are left clear
 
 
 def test_whole_path_chained_on_device(rd):
@@ -445,26 +453,32 @@ def test_plan_from_a_context_bound(rd, dtype):
 
 
 @pytest.mark.parametrize("W", [30, 40])
-def test_one_workspace_for_bounds_with_different_row_groups(rd, W):
-    """A beam of 150 or 200 tokens is cut into two or three, three or four row groups depending on the bound of the
-    contexts; calls planned for alternating bounds share one workspace, as a decoding loop whose contexts grow does."""
-    announce("attn bounds with different row groups, W=%d" % W)
-    B, H, D, L, Cmax, dtype = 2, 32, 128, 5, 700, "bf16"
-    t = make_case(B, H, D, W, L, (700, 410), dtype, seed=11, V=32000, share="high")
+def test_one_workspace_for_bounds_with_different_ranges(rd, W):
+    """Beams of 150 or 200 tokens (four or five row groups) whose keys are split into more or fewer ranges, by the bound of the
+    contexts: calls planned for alternating bounds share one workspace, as a decoding loop whose contexts grow does, and the
+    arrival words of one plan must not lie where another has partial results."""
+    announce("attn bounds with different ranges, W=%d" % W)
+    B, H, D, L, Cmax, dtype = 2, 4, 128, 5, 4000, "bf16"
+    N = W * L
+    words = 8 * B * H * n_row_groups(N)
+    bounds = (300, 4000, 300, 1000, 100, 4000, 1000, 300, 4000)
+    need = {c: rd.rd_tree_attn_workspace(B, H, N, D, c, rd.RD_BF16) for c in bounds}
+    assert len(set(need.values())) >= 3 and min(need.values()) > 2 * words      # several plans, all with partial results
+    t = make_case(B, H, D, W, L, (Cmax, 410), dtype, seed=11, V=32000, share="high")
     d = oracle.dedup(t["beams"], t["ctx_len"])
     scale = float(1.0 / np.sqrt(D))
     ref = oracle.tree_attn(t["q"], t["k_cache"], t["v_cache"], t["ctx_len"], t["k_new"], t["v_new"],
                            d["n_packed"], d["tree_mask"], dtype, scale)
     td = {k: dev(v) for k, v in t.items()}
     npk, mask = dev(d["n_packed"]), dev(d["tree_mask_bits"])
-    bounds = (300, 700, 300, 100, 700, 200, 300, 700)
-    ws = rd.new_workspace(max(rd.rd_tree_attn_workspace(B, H, W * L, D, c, rd.RD_BF16) for c in bounds), "cuda")
+    ws = rd.new_workspace(max(need.values()), "cuda")
     for i, bound in enumerate(bounds):
         out = torch.full_like(td["q"], float("nan"))
         rd.rd_tree_attn(td["q"], td["k_cache"], td["v_cache"], td["ctx_len"], td["k_new"], td["v_new"], npk, mask, scale,
                         out=out, workspace=ws, ctx_bound=bound)
         torch.cuda.synchronize()
         compare(host(out), ref, dtype, "call %d, bound %d" % (i, bound))
+        assert int(ws[:words].to(torch.int64).sum()) == 0
 
 
 @pytest.mark.parametrize("bound", [300.0, "300", np.int64(300), np.float32(300.5), 2 ** 40, torch.tensor(300)])
