@@ -1471,12 +1471,15 @@ constexpr size_t kSmallLayer = 8u << 20;
 // size 2048 by the former 50 / 51 / 52 / 63 / 69, by the latter 75 / 75 / 75 / 78 / 79; 3072 108 / 118 / 133 / 162 / 183 and
 // 113 / 112 / 112 / 116 / 117; 4096 135 / 146 / 162 / 171 / 184 and 162 / 161 / 161 / 167 / 168; 5120 210 / 231 / 258 / 320 / 355
 // and 204 / 203 / 205 / 210 / 213; 6656 336 / 376 / 421 / 411 / 458 and 302 / 301 / 304 / 312 / 318.
-// Where rd_linear_kernel's workgroups are whole rounds of 256 it stays up to 24 rows (whole calls at 4096, 16 and 24 rows: 735 and
-// 756 so, 743 and 760 by rd_gemm_kernel).
+// Where rd_linear_kernel's workgroups of 16 columns are whole rounds of 256 it stays up to 24 rows while the activations, read
+// with every weight, cost less than the second launch: rows times weights up to 1.5 Gi.  us per call by it / by rd_gemm_kernel:
+// hidden size 4096, 16 and 24 rows 735 / 743 and 756 / 760; three MLP layers and two positions at 9 / 12 / 16 / 24 rows, 6144
+// 459 / 501 / 554 / 660 and 478 / 484 / 491 / 514, 8192 776 / 833 / 907 / 929 and 771 / 778 / 786 / 808, 10240 1144 / 1259 / 1417 / 1536
+// and 1081 / 1088 / 1100 / 1136.
 bool few_rows_gemm(int rows, int N, int K)
 {
     const size_t weights = (size_t)N * K;
-    if (rows <= 24 && N % (16 * 256) == 0) return false;
+    if (rows <= 24 && N % (16 * 256) == 0 && rows * weights <= (size_t)1536 << 20) return false;
     return (rows >= 16 && weights >= (size_t)32 << 20) || (rows >= kGemmRows && weights >= (size_t)96 << 20);
 }
 

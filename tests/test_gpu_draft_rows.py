@@ -17,7 +17,8 @@ SHAPES = [(64, 130, 1, 11, 3, 3), (64, 257, 2, 8, 8, 3), (192, 1000, 2, 5, 13, 3
           # 64 rows and fewer: layers too large for the unsplit kernel, K split, not split and in workgroups of 128 columns
           (320, 14000, 0, 5, 8, 3), (64, 66000, 0, 6, 10, 3), (192, 24000, 0, 5, 8, 3), (192, 24000, 0, 10, 8, 3),
           # 9 to 32 rows of layers large enough for it, both products of the RNN too
-          (2944, 200, 1, 4, 4, 2), (2944, 100, 1, 17, 1, 2), (5056, 100, 1, 9, 1, 2), (4160, 100, 0, 8, 2, 3), (4096, 100, 0, 1, 32, 3)]
+          (2944, 200, 1, 4, 4, 2), (2944, 100, 1, 17, 1, 2), (5056, 100, 1, 9, 1, 2), (4160, 100, 0, 8, 2, 3), (4096, 100, 0, 1, 32, 3),
+          (6144, 64, 1, 11, 1, 2), (6144, 64, 1, 10, 1, 2)]
 
 
 @pytest.mark.parametrize("tiled", [False, True])
