@@ -1324,7 +1324,13 @@ __global__ void rd_pack_weights_kernel(const uint16_t *__restrict__ src, int N, 
 // Row tiles of rd_gemm_kernel's workgroups for a launch of `rows` rows.
 int gemm_row_tiles(int rows) { return rows > 128 ? 16 : rows > 64 ? 8 : 4; }
 
-constexpr int kGemmRows = 9;            // the workspace holds rd_gemm_kernel's partial sums from this many rows on
+// From 33 rows on any layer may run on rd_gemm_kernel, with fewer those of so many weights (few_rows_gemm).
+constexpr int kGemmRows = 9, kGemmRows2 = 16;
+constexpr size_t kGemmWeights = (size_t)96 << 20, kGemmWeights2 = (size_t)32 << 20;
+bool gemm_layer(size_t rows, size_t weights)
+{
+    return rows > 32 || (rows >= kGemmRows2 && weights >= kGemmWeights2) || (rows >= kGemmRows && weights >= kGemmWeights);
+}
 
 struct Plan {
     size_t x_f32[3], x_bf[3], s_bf[2], logits, part_max, part_sum, part_cv, part_ci, row_score, row_tok, paths[2], cum[2], parent, tok, kpart, total;
@@ -1350,7 +1356,7 @@ Plan draft_plan(int B, int W, int L, int Dm, int V)
     for (int i = 0; i < 2; ++i) { p.paths[i] = take(M * L * 4); p.cum[i] = take(M * 4); }
     p.parent = take(M * 4 * (size_t)(L > 1 ? L - 1 : 1));       // parent rows of every drafted position
     p.tok = take(M * 4);
-    p.kpart = take(M >= kGemmRows ? (size_t)kSplitMaxWgs * gemm_row_tiles((int)M) * kGemmCols * 1024 : 0);      // a launch's partial tiles
+    p.kpart = take(gemm_layer(M, G * G) ? (size_t)kSplitMaxWgs * gemm_row_tiles((int)M) * kGemmCols * 1024 : 0);      // a launch's partial tiles
     p.total = off;
     return p;
 }
@@ -1480,7 +1486,7 @@ bool few_rows_gemm(int rows, int N, int K)
 {
     const size_t weights = (size_t)N * K;
     if (rows <= 24 && N % (16 * 256) == 0 && rows * weights <= (size_t)1536 << 20) return false;
-    return (rows >= 16 && weights >= (size_t)32 << 20) || (rows >= kGemmRows && weights >= (size_t)96 << 20);
+    return gemm_layer(rows, weights);
 }
 
 template <typename T, int EPI>

@@ -329,6 +329,11 @@ def test_draft_argument_errors(lib):
     assert call(ws=None) == WORKSPACE
     assert call(ws_bytes=64) == WORKSPACE
     assert lib.rd_draft_workspace(1, 4, 5, 96, 100) == 0
+    # 16 MB of partial sums from 33 rows on, and with fewer where a layer is large enough to be split
+    small = 16 << 20
+    assert lib.rd_draft_workspace(4, 4, 5, 1024, 8000) < small < lib.rd_draft_workspace(4, 4, 5, 4096, 8000)
+    assert lib.rd_draft_workspace(4, 8, 5, 1024, 8000) < small < lib.rd_draft_workspace(3, 11, 5, 1024, 8000)
+    assert lib.rd_draft_workspace(3, 3, 5, 4096, 8000) < small < lib.rd_draft_workspace(3, 3, 5, 5056, 8000)
 
 
 def test_pack_weights_argument_errors(lib):
