@@ -639,8 +639,10 @@ __device__ __forceinline__ void order_pair(float &va, int &ka, float &vb, int &k
 // of them in random rows), and those are ranked by counting how many of them are better.  A group is eight lanes; a lane owns
 // four quads of tokens, or, in a chunk of up to 1024, four tokens one by one, so that no group is empty where there are more
 // than 256 tokens.  Bound by vector instructions (256 rows of 32000 logits, eight workgroups per compute unit: 12.0 us, with
-// every lane's tokens sorted as below 19.1; 8 rows 5.6 and 8.2).  Where more than 512 logits reach the bound -- equal ones --
-// or a row holds NaN or +inf, W rounds pick the best one left.
+// every lane's tokens sorted as below 19.1; 8 rows 5.6 and 8.2).  Where more than 512 logits reach the bound, equal ones as a
+// rule, those equal to it are numbered in the order of their tokens and only as many taken as are missing (112 rows of 32000 equal
+// logits, 28 candidates, 14 us; 48 by the rounds that follow).  Where more than 512 are larger than it, or a row holds NaN or
+// +inf, W rounds pick the best one left.
 __global__ __launch_bounds__(kChunkThreads) void rd_topw_few_kernel(const float *__restrict__ logits, int V, int W, int chunks, int mstride,
                                                                     float *__restrict__ part_max, float *__restrict__ part_sum,
                                                                     float *__restrict__ part_cv, int32_t *__restrict__ part_ci)
@@ -651,7 +653,7 @@ __global__ __launch_bounds__(kChunkThreads) void rd_topw_few_kernel(const float 
     __shared__ __align__(16) uint2 s_c[kCap];               // (logit, token) of those that reach the bound
     __shared__ float s_cv[kWaves][kFewBeam];
     __shared__ int s_ci[kWaves][kFewBeam];
-    __shared__ int s_n;
+    __shared__ int s_n, s_eq[4][kWaves];
     const int c = blockIdx.x, m = blockIdx.y * mstride, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const float *z = logits + (size_t)m * V;
     // this lane's token j is t0 + (j / 4) * far + (j % 4) * near, none from V on
@@ -711,10 +713,66 @@ __global__ __launch_bounds__(kChunkThreads) void rd_topw_few_kernel(const float 
     __syncthreads();
     const size_t slot = (size_t)m * chunks + c;
     const float total = s_v[0] + s_v[1] + s_v[2] + s_v[3];
-    const int n = s_n;
+    int n = s_n;
     if (tid == 0) {
         part_max[slot] = mx;
         part_sum[slot] = total;
+    }
+    if (__builtin_expect(n > kCap && total == total, 0)) { // uniform (out of the way of the rest)
+        unsigned equal = 0, larger = 0;                     // this lane's tokens that are
+#pragma unroll
+        for (int j = 0; j < kChunkPer; ++j) {
+            equal |= (token(j) < V && x[j] == bound ? 1u : 0u) << j;
+            larger |= (token(j) < V && x[j] > bound ? 1u : 0u) << j;
+        }
+        // Tokens in their order: by quad, then lane, then place in the quad; of a short chunk by j, then lane.
+        auto is_equal = [&](int q, int u) __attribute__((always_inline)) { return (quads ? equal >> (4 * q + u) : u == 0 ? equal >> q : 0u) & 1u; };
+        int lower[4];                                       // equal ones of the lanes before this one in the wave, by quad
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            int all = 0;
+            lower[q] = 0;
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const unsigned long long b = __ballot(is_equal(q, u));
+                all += __popcll(b);
+                lower[q] += __popcll(b & ((1ull << lane) - 1));
+            }
+            if (lane == 0) s_eq[q][wave] = all;
+        }
+        __syncthreads();                                    // (all have read s_n)
+        s_c[tid] = s_c[tid + kChunkThreads] = make_uint2(__float_as_uint(-INFINITY), 0x7fffffffu);
+        if (tid == 0) s_n = 0;
+        __syncthreads();
+        int pos = larger ? atomicAdd(&s_n, __popc(larger)) : 0;
+#pragma unroll
+        for (int j = 0; j < kChunkPer; ++j) {
+            if (larger >> j & 1u) {
+                if (pos < kCap) s_c[pos] = make_uint2(__float_as_uint(x[j]), (unsigned)token(j));
+                ++pos;
+            }
+        }
+        __syncthreads();
+        const int n_larger = s_n, missing = max(W - n_larger, 0);
+        int first = 0;                                      // equal ones before this wave's in the quad
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            int at = first + lower[q];
+#pragma unroll
+            for (int w = 0; w < kWaves; ++w) {
+                at += w < wave ? s_eq[q][w] : 0;
+                first += s_eq[q][w];
+            }
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                if (is_equal(q, u)) {
+                    if (at < missing) s_c[n_larger + at] = make_uint2(__float_as_uint(bound), (unsigned)(quads ? token(4 * q + u) : token(q)));
+                    ++at;
+                }
+            }
+        }
+        __syncthreads();
+        n = n_larger + missing;
     }
     if (n <= kCap && total == total) {                      // uniform
         for (int i = tid; i < n; i += kChunkThreads) {
@@ -761,9 +819,12 @@ __global__ __launch_bounds__(kChunkThreads) void rd_topw_few_kernel(const float 
         const int w = i / W, r = i - w * W, tok = s_ci[w][r];
         const float v = s_cv[w][r];
         int place = 0;
-        for (int k = 0; k < kWaves * W; ++k) {
-            const int kw = k / W, kr = k - kw * W, ot = s_ci[kw][kr];
-            place += better(s_cv[kw][kr], ot, v, tok) || (ot == tok && k < i) ? 1 : 0;
+#pragma unroll
+        for (int kw = 0; kw < kWaves; ++kw) {
+            for (int kr = 0; kr < W; ++kr) {
+                const int ot = s_ci[kw][kr];
+                place += better(s_cv[kw][kr], ot, v, tok) || (ot == tok && kw * W + kr < i) ? 1 : 0;
+            }
         }
         if (place < W) {
             part_cv[slot * W + place] = v;
@@ -1242,9 +1303,12 @@ __global__ __launch_bounds__(kSelThreads) void rd_row_beam_kernel(
     for (int i = tid; i < n; i += kSelThreads) {
         const Entry e = s_e[i];
         int rank = 0;
-        for (int k = 0; k < n; k += 4) {                              // four reads in flight
+        for (int k = 0; k < n; k += 4) {                              // (reads in flight; past the last, what lies there, not counted)
+            Entry o[4];
 #pragma unroll
-            for (int u = 0; u < 4; ++u) rank += (k + u < n && precedes(s_e[min(k + u, n - 1)], e)) ? 1 : 0;
+            for (int u = 0; u < 4; ++u) o[u] = s_e[k + u];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) rank += ((k + u < n) & precedes(o[u], e)) ? 1 : 0;
         }
         if (rank < W) {
             s_win[rank] = e.row;

@@ -96,3 +96,25 @@ def test_rows_without_a_score(rd, what, B, W, V):
             want = [path + [tok] for tok in order]
             path.append(order[0])
         assert beams[b].tolist() == want
+
+
+@pytest.mark.parametrize("V,W", [(9000, 28), (9000, 5), (4996, 28), (4296, 28), (4100, 3), (20000, 16)])
+@pytest.mark.parametrize("what", ["equal", "10 larger", "500 larger", "600 larger", "falling", "rising", "two values"])
+def test_many_logits_at_the_bound(rd, what, V, W):  # noqa: F811
+    """Vocabularies of few distinct logits: more of them than are kept reach the bound of a chunk's best."""
+    announce(f"draft selection {what} V={V} W={W}")
+    v = np.arange(V)
+    rng = np.random.default_rng(V + W)
+    z = {"equal": 0 * v, "10 larger": np.isin(v, rng.permutation(V)[:10]) * (v % 3 + 1), "500 larger": (v % 4096 < 500) * 1, "600 larger": (v % 4096 < 600) * 1,
+         "falling": 255 - v % 4096 // 16, "rising": v % 4096 // 16, "two values": rng.integers(0, 2, V)}[what].astype(np.float32)
+    p = make_params(V, 64, 0, 5)
+    p["head_w"][:] = 0
+    p["head_w"][:, 64] = synth.f32_to_bf16_bits(z)                  # logits z in every row (integers up to 255 are exact)
+    h = synth.f32_to_bf16_bits(np.ones((2, 64), np.float32))
+    got = rd.rd_draft(dev_params(p), dev(h), dev(np.array([2, 3], np.int32)), W, 2)
+    torch.cuda.synchronize()
+    order = np.argsort(-z, kind="stable")[:W]
+    want = z[order].astype(np.float64) - np.log(np.exp((z - z.max()).astype(np.float64)).sum()) - z.max()
+    for b, last in enumerate((2, 3)):
+        assert host(got["beams"])[b].tolist() == [[last, int(t)] for t in order]
+    assert np.allclose(host(got["beam_logp"]), want[None], atol=1e-4)
