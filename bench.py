@@ -40,7 +40,7 @@ if ROOT not in sys.path:
 
 HBM_PEAK_GBS = 8000.0
 TRAFFIC_TABLE = os.path.join(ROOT, "profiles", "rd_tree_attn_hbm_traffic.md")
-ATTENTION_SOURCES = tuple(os.path.join(ROOT, "paper_2403_09919_amd", "csrc", f) for f in ("rd_tree_attn_mfma.h", "rd_attn_common.h"))
+ATTENTION_SOURCES = tuple(os.path.join(ROOT, "paper_2403_09919_amd", "csrc", f) for f in ("rd_tree_attn.hip", "rd_tree_attn_bf16.hip", "rd_tree_attn_mfma.h", "rd_attn_common.h", "rd_internal.h"))
 LAYERS_BY_HEADS = {32: 32, 40: 40, 52: 60}      # decoder layers of the 7B / 13B / 33B models the shapes come from
 FLUSH_BYTES = 1 << 30                           # larger than the 256 MB infinity cache plus every L2
 

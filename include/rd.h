@@ -398,8 +398,9 @@ int rd_commit_paged(const void *k_new, const void *v_new, const int32_t *accepte
  *   step_row int32 [B][W][L-1]: the row of matrix t-1 that produced token t of final candidate w.  workspace: rd_draft_workspace(...) bytes, 256-byte aligned, no
  * initial contents required, not shared by concurrent calls.
  * Limits: Dm a multiple of 64; W <= 128, W <= V; B*W <= 512; V <= 262144; L <= 384.
- * The call enqueues at most 4 + n_mlp launches per drafted position (5 + n_mlp after the first; one
- * fewer for W <= 8 and V <= 32768) while B*W <= 128; every further 128 rows add at most one launch per linear layer.
+ * The call enqueues at most two launches per linear layer (n_mlp + 1 of them, one more after the first position) and 256
+ * rows, and three for the selection, per drafted position (two where W <= 28 and W times the power of two from
+ * ceil(V / 4096) up is at most 256), beside one at the start and, with step_row, one at the end.
  */
 typedef struct {
     const void *emb, *rnn_u, *rnn_w;

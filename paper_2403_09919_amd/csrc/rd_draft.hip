@@ -7,13 +7,14 @@
 //     go from memory straight into the A operand of v_mfma_f32_16x16x32_bf16 (lane = one output
 //     column x 8 consecutive k), the activations (a few hundred KB, L2 resident) into the B
 //     operand, and the partial sums meet in LDS.  Bias, SiLU, skip connection and the bf16
-//     copy that the next layer reads are fused into the epilogue.  At more than 32 rows a kernel
-//     of 256-column workgroups with K split over them, fed through LDS, takes over (rd_gemm_kernel), and
-//     a second one adds the partial tiles;
-//   * three selection launches, all merges of sorted lists: per chunk of 4096 logits and row, the
-//     pieces of the log-sum-exp and the W best tokens; per row, its log-sum-exp and the W best
-//     tokens of its chunks as cumulative scores; per sequence, the best W of the (candidate, token)
-//     pairs by cumulative log probability, ties to the smaller candidate, then the smaller token
+//     copy that the next layer reads are fused into the epilogue.  Layers of many rows, and large ones
+//     from 9 rows on, run on a kernel of 256-column workgroups with K split over them, fed through LDS
+//     (rd_gemm_kernel), and a second one adds the partial tiles (launch_linear has the rules);
+//   * selection: per chunk of 4096 logits and row, the pieces of the log-sum-exp and the W best tokens;
+//     per row, its log-sum-exp and the W best tokens of its chunks as cumulative scores; per sequence,
+//     the best W of the (candidate, token) pairs by cumulative log probability, ties to the smaller
+//     candidate, then the smaller token.  Up to 28 candidates by counting, the last two in one launch
+//     where a sequence's lists have a thread each; beyond that three launches, merges of sorted lists
 //     (W <= 128; beyond 64 candidates a lane of the last merge holds two lists).
 // The RNN update reads its two inputs in place: the parent's state through a row map and the
 // chosen token's embedding straight from the table, so no gather pass exists.
@@ -42,7 +43,6 @@ template <> struct Elem16<_Float16> {
 };
 
 constexpr int kMaxRows = 512;          // B*W
-constexpr int kRowsPerLaunch = 128;    // rows of one linear-layer launch (8 MFMA row tiles)
 constexpr int kMaxBeam = 128;          // W
 constexpr int kNarrowBeam = 64;        // up to here the selection kernels keep their lists in static LDS, one candidate per lane
 // Up to here candidates are ranked by counting, us per call so and by merges (three sequences, hidden size 512, 32000 tokens):
@@ -586,7 +586,7 @@ __global__ void rd_draft_init_kernel(const T *__restrict__ emb, const T *__restr
 
 __device__ __forceinline__ bool better(float v, int i, float bv, int bi) { return v > bv || (v == bv && i < bi); }
 
-// Selection here is always a merge of sorted lists, one list per lane: every round the lanes offer
+// Selection beyond kFewBeam candidates is a merge of sorted lists, one list per lane: every round the lanes offer
 // the heads of their lists, the largest value wins and, among equal values, the lowest lane (lists are
 // laid out so that a lower lane means a smaller candidate or smaller tokens, which is the tie rule).
 // A round is a maximum over lanes by data-parallel primitives, a ballot and a find-first-set; only the

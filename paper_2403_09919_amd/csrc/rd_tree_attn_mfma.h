@@ -17,8 +17,8 @@
 // C=1024, 2.3 of arithmetic, the store of a partial result and its arrival 1.4, the merge 2.3).  Against the kernel it
 // replaced, whose waves shared every block of tiles at two barriers and fetched K and V through registers, us per launch, K
 // and V from memory: H=32, C=1024 12.1 -> 10.8; B=4, H=32, C=1024 23.9 -> 19.6; H=32, C=1777, 61 rows 22.3 -> 16.7 and 147
-// rows 30.0 -> 22.0; B=10, H=52, C=63-92, 207 tokens 49.4 -> 33.2; B=4, H=40, C=4096 74.5 -> 68.8; B=16, H=52, C=2048 183.5 ->
-// 180.2; B=24, H=32, C=101-1500 79.2 -> 68.1; nothing at B=9, H=26, C=5384 (106.7 -> 106.3).
+// rows 30.0 -> 22.0; B=10, H=52, C=63-92, 207 tokens 49.4 -> 33.2; B=4, H=40, C=4096 74.5 -> 66.5; B=16, H=52, C=2048 183.5 ->
+// 178; B=24, H=32, C=101-1500, 25 tokens, bf16 in a dense cache 78.3 -> 69.3; nothing at B=9, H=26, C=5384 (106.7 -> 106.3).
 #pragma once
 #include "rd_attn_common.h"
 #include <type_traits>
@@ -67,22 +67,6 @@ template <int D> __device__ __forceinline__ int vswz(int row, int c)
 }
 
 __device__ __forceinline__ uint4 ldg16(const void *p) { return *reinterpret_cast<const uint4 *>(p); }
-
-// Synchronisation that orders LDS traffic only.  __syncthreads() also waits for every global
-// load in flight, which would drain the K/V prefetch at each of the barriers per block.
-__device__ __forceinline__ void lds_barrier()
-{
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
-    __builtin_amdgcn_s_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
-}
-// Orders this wave's own LDS writes before its own later LDS reads (tiles private to a wave).
-__device__ __forceinline__ void wave_lds_sync()
-{
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
-}
 
 // Rotary embedding of eight elements ("rotate half": element i pairs with element i + D/2), in the
 // arithmetic of rd_rope: fp32, the partner's product rounded, then one fused multiply-add, one rounding to
@@ -397,7 +381,7 @@ __global__ __launch_bounds__(NW * 64, 2) void rd_tree_attn_mfma_kernel(AttnArgs 
         else wait_vm<0>();
     }
     RD_TR(9);
-    lds_barrier();                            // Q visible to all waves
+    rd_lds_barrier();                            // Q visible to all waves
     RD_TR(1);
 
     const float c_abs = fabsf(a.scale_log2e);
@@ -592,7 +576,7 @@ __global__ __launch_bounds__(NW * 64, 2) void rd_tree_attn_mfma_kernel(AttnArgs 
                 }
             }
             wait_vm<0>();                     // this wave's V tile
-            lds_barrier();                    // probabilities, statistics and V of all waves visible
+            rd_lds_barrier();                    // probabilities, statistics and V of all waves visible
             RD_TR(8);
             float fac[NQA][NW];               // 2^(reference of a tile - reference of the row)
 #pragma unroll
@@ -714,7 +698,7 @@ __global__ __launch_bounds__(NW * 64, 2) void rd_tree_attn_mfma_kernel(AttnArgs 
                 sL[(qt * 16 + r16) * kStat + wave] = l_own[qt][0];
             }
         }
-        lds_barrier();                        // states of all waves visible, all tiles read
+        rd_lds_barrier();                        // states of all waves visible, all tiles read
 #pragma unroll
         for (int qt = 0; qt < NQA; ++qt) {
             float x[NW], y[NW];
@@ -734,13 +718,13 @@ __global__ __launch_bounds__(NW * 64, 2) void rd_tree_attn_mfma_kernel(AttnArgs 
         }
 #pragma unroll
         for (int r = 0; r < kRoundsA; ++r) {
-            if (r > 0) lds_barrier();
+            if (r > 0) rd_lds_barrier();
 #pragma unroll
             for (int ql = 0; ql < 2; ++ql)
 #pragma unroll
                 for (int dt = 0; dt < DT; ++dt)
                     if (2 * r + ql < NQA) *reinterpret_cast<f32x4 *>(sK + ((wave * 2 * DT + ql * DT + dt) * 64 + lane) * 16) = oacc[2 * r + ql < NQA ? 2 * r + ql : 0][dt];
-            lds_barrier();
+            rd_lds_barrier();
 #pragma unroll
             for (int j = 0; j < kOwn; ++j) {
                 const int f = j * NW + wave;
@@ -873,7 +857,7 @@ __global__ __launch_bounds__(NW * 64, 2) void rd_tree_attn_mfma_kernel(AttnArgs 
     if (NQ > 1 && nqt <= kHalf) walk(std::integral_constant<int, kHalf>{});
     else walk(std::integral_constant<int, NQ>{});
     if (!ALL || ++rg >= n_act) return;
-    lds_barrier();                            // all waves have read what the next group's copies overwrite
+    rd_lds_barrier();                            // all waves have read what the next group's copies overwrite
     }
 }
 

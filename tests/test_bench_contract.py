@@ -44,3 +44,17 @@ def test_traffic_is_reported_only_for_the_kernel_it_was_measured_on(tmp_path):
     assert bench.read_traffic_table(table, bench.attention_digest([src])) == {}
     table.write_text("| 2 | 1.0 | 2.0 | 1 | 1 | 4096 |\n")
     assert bench.read_traffic_table(table, measured) == {}
+
+
+def test_traffic_depends_on_every_file_of_the_attention_kernel():
+    """What the 16-bit kernel and its entry points are made of, header by header, is what the counter summary is tied to."""
+    import bench
+    csrc = os.path.join(ROOT, "paper_2403_09919_amd", "csrc")
+    todo, files = ["rd_tree_attn.hip", "rd_tree_attn_bf16.hip"], set()
+    while todo:
+        name = todo.pop()
+        if name in files or not os.path.exists(os.path.join(csrc, name)):
+            continue
+        files.add(name)
+        todo += re.findall(r'#include "([^"]+)"', open(os.path.join(csrc, name)).read())
+    assert sorted(os.path.basename(p) for p in bench.ATTENTION_SOURCES) == sorted(files)
