@@ -158,11 +158,14 @@ static inline AttnPlan attn_plan_make(int B, int H, int N, int D, int Cmax, bool
     // The kernel finds how many row groups hold packed rows and takes the ranges of that number: those of the guess unless the
     // estimate promises 7 % (it is not exact to less: 30 x 5 tokens, H=32, C=2048, 120 packed rows 23.2 us with the guess's four,
     // 24.0 with five, where it promises 4 %).  us with the guess's ranges for all -> these, H=32: 70 x 5 tokens, C=1777, 30
-    // packed rows 18.6 -> 15.0, 96 20.8 -> 17.4, 200 29.9 -> 25.8; C=4096, 200 47.6 -> 39.2; B=2, 50 x 5, C=3000, 40 41.1 -> 29.7;
-    // B=4, H=40, 16 x 5, C=4096, 60 94.6 -> 84.7.
+    // packed rows 18.6 -> 15.0, 96 20.8 -> 17.4, 200 29.9 -> 25.8; C=4096, 200 47.6 -> 39.2.
+    // Several sequences keep the guess's: each has its own number of packed rows, and ranges that suit a launch whose heads are
+    // all alike put workgroups of one sequence on the compute units that the walks of another hold (us with the guess's / these:
+    // B=4, H=40, 16 x 5, C=4096, 27 to 60 packed rows 65.8 / 88.5, all 60 95.2 / 83.9; B=2, H=32, 70 x 5, C=3000, 40 and 300
+    // 42.8 / 55.9, all 40 42.5 / 30.5; B=8, H=8, 70 x 5, C=4000, 20 to 300 50.4 / 83.1).
     int most = 1;
     for (int n = 1; n <= n_rg; ++n) {
-        const int R = n == n_guess ? best.R : choose(plan.waves, n, (n - 0.5) * 16 * nq, best.R, 0.93).R;
+        const int R = n == n_guess || B > 1 ? best.R : choose(plan.waves, n, (n - 0.5) * 16 * nq, best.R, 0.93).R;
         plan.ranges |= (uint64_t)R << (8 * (n - 1));
         plan.S = R * n > plan.S ? R * n : plan.S;
         most = R > most ? R : most;

@@ -89,8 +89,8 @@ def test_config2_vicuna7b_full(rd):
 @pytest.mark.parametrize("idx", [3, 4, 5])
 def test_full_size_configs_whole_tensor(rd, idx):
     """Full-size tensors in the launches the benchmark uses (four-wave workgroups with three row tiles; config 3: one key range
-    per head; config 4: two row groups, three ranges where both hold packed rows; config 5: two row groups, longest
-    sequences first), every head and every row against the oracle."""
+    per head; config 4: two row groups of one range each; config 5: two row groups, longest sequences first), every head and every
+    row against the oracle."""
     cfg = synth.CONFIGS[idx]
     announce("attn config %d (bf16, full size, whole tensor)" % idx)
     t = synth.make_attn_inputs(cfg)

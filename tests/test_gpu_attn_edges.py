@@ -83,8 +83,8 @@ def test_rotary_tables_at_any_multiple_of_four_bytes(rd, D, W, L, ctx, shift):
 @pytest.mark.parametrize("H,W,L,ctx,vocabs", [(4, 70, 5, [1777], [1]), (4, 70, 5, [1777], [2]), (4, 70, 5, [4096], [3]), (3, 16, 5, [4096, 700, 3000], [2, 32000, 5]),
                                               (5, 30, 5, [2048, 2048], [2, 32000]), (2, 128, 3, [0, 3000, 31, 1500], [1, 4, 8, 32000])])
 def test_few_packed_rows_in_a_wide_beam(rd, dtype, D, H, W, L, ctx, vocabs):
-    """Candidates that share most of their prefixes (small vocabularies) beside ones that do not: the key ranges of a head go
-    by how many of its row groups hold packed rows, and the sequences of a batch differ in that."""
+    """Candidates that share most of their prefixes (small vocabularies) beside ones that do not: a lone sequence's key ranges
+    go by how many of its row groups hold packed rows; the sequences of a batch have the same ranges and differ in their groups."""
     announce(f"few packed rows {dtype} D={D} H={H} W={W} L={L} ctx={ctx} vocabs={vocabs}")
     B = len(ctx)
     ctx, _, q, kn, vn, kc, vc, _ = _case(B, H, W, L, ctx, D, dtype, W + H)
