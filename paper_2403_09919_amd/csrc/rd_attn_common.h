@@ -23,6 +23,7 @@ struct AttnPlan {
     int rg_tiles;      // 16-row tiles of packed rows per workgroup (a row group)
     int n_rg;          // row groups per (sequence, head); 1 unless N is large
     uint64_t ranges;   // key ranges per row group at most, by the number of row groups that hold packed rows (attn_ranges)
+    int usual;         // ... where the sequences of a batch differ in that number
     int sorted;        // long sequences first: more workgroups than the chip holds, of eight tiles per wave and more, and
                        // at most kOneStep sequences (us, ranked in steps of 64 / not at all: 8 x 5 tokens, H=4, 100 to 1500 keys,
                        // B=512 205 / 180; H=32, 100 to 1000 keys 1231 / 926)
@@ -159,17 +160,23 @@ static inline AttnPlan attn_plan_make(int B, int H, int N, int D, int Cmax, bool
     // estimate promises 7 % (it is not exact to less: 30 x 5 tokens, H=32, C=2048, 120 packed rows 23.2 us with the guess's four,
     // 24.0 with five, where it promises 4 %).  us with the guess's ranges for all -> these, H=32: 70 x 5 tokens, C=1777, 30
     // packed rows 18.6 -> 15.0, 96 20.8 -> 17.4, 200 29.9 -> 25.8; C=4096, 200 47.6 -> 39.2.
-    // Several sequences keep the guess's: each has its own number of packed rows, and ranges that suit a launch whose heads are
-    // all alike put workgroups of one sequence on the compute units that the walks of another hold (us with the guess's / these:
-    // B=4, H=40, 16 x 5, C=4096, 27 to 60 packed rows 65.8 / 88.5, all 60 95.2 / 83.9; B=2, H=32, 70 x 5, C=3000, 40 and 300
-    // 42.8 / 55.9, all 40 42.5 / 30.5; B=8, H=8, 70 x 5, C=4000, 20 to 300 50.4 / 83.1).
+    // Sequences that differ in the number of their groups take the guess's (`usual`), and so do more than kOneStep of them: ranges that
+    // suit a launch whose heads are all alike put workgroups of one sequence on the compute units that the walks of another hold
+    // (us with the guess's / each sequence's own: B=4, H=40, 16 x 5, C=4096, 27 to 60 packed rows 65.8 / 88.5; B=2, H=32, 70 x 5,
+    // C=3000, 40 and 300 42.5 / 55.9; B=8, H=8, 70 x 5, C=4000, 20 to 300 50.4 / 83.1).  Where all have as many groups the gain is as
+    // for one (B=2, H=32, 50 x 5, C=3000, 40 packed rows each 41.1 -> 29.4, contexts of 1000 to 3000 36.8 -> 26.0; B=4, H=40, 30 x 5, C=4000,
+    // 130 each 114 -> 92.5), but for more ranges in a launch that does not fit the chip at once, which pay only where the
+    // contexts are alike too (B=4, H=40, 16 x 5, 60 each, C=4096 94.8 -> 84.0, C=1000 to 4096 56.1 -> 60.0): not taken.
     int most = 1;
     for (int n = 1; n <= n_rg; ++n) {
-        const int R = n == n_guess || B > 1 ? best.R : choose(plan.waves, n, (n - 0.5) * 16 * nq, best.R, 0.93).R;
+        int R = n == n_guess || B > kOneStep ? best.R : choose(plan.waves, n, (n - 0.5) * 16 * nq, best.R, 0.93).R;
+        if (B > 1 && R > best.R && (BH + 7) / 8 * 8 * n * R > (plan.waves == 8 ? 256 : 512)) R = best.R;
         plan.ranges |= (uint64_t)R << (8 * (n - 1));
-        plan.S = R * n > plan.S ? R * n : plan.S;
-        most = R > most ? R : most;
+        const int either = R > best.R ? R : best.R;
+        plan.S = either * n > plan.S ? either * n : plan.S;
+        most = either > most ? either : most;
     }
+    plan.usual = best.R;
     plan.sorted = best.sorted;
     // Hundreds of sequences: finding a workgroup's place in the batch (0.5 us per 256 sequences and workgroup, also of those
     // that then have nothing to do) costs more than reading K and V once per row group where contexts are short beside the batch.
@@ -252,7 +259,9 @@ struct AttnArgs {
     float *partials;
     int B, H, N, Cmax, S, words;
     int n_rg;      // row groups per (sequence, head) (each is NQ*16 rows of the kernel's template)
-    uint64_t ranges;   // key ranges per row group at most, by the number of groups with packed rows (attn_ranges)
+    // (`usual` fills a gap of the layout: behind `ranges` the arguments took one load more, and a launch with rotation 0.25 us)
+    int usual;     // key ranges per row group at most where sequences differ in the number of groups with packed rows
+    uint64_t ranges;   // ... by that number where they do not (attn_ranges)
     int sorted;    // workgroups of long sequences first
     float scale_log2e;
     // rotary embedding fused into the call (rd_tree_attn_rope); unused (null) otherwise

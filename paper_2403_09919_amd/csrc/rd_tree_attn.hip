@@ -53,7 +53,7 @@ static int tree_attn_dense(const void *q, const void *k_cache, const void *v_cac
     a.partials = reinterpret_cast<float *>(static_cast<unsigned char *>(workspace) + plan.counters_bytes);
     a.B = B; a.H = H; a.N = N; a.Cmax = Cmax; a.S = plan.S; a.words = (N + 63) / 64;
     a.scale_log2e = scale * 1.44269504088896340736f;
-    a.n_rg = plan.n_rg; a.ranges = plan.ranges; a.sorted = plan.sorted;
+    a.n_rg = plan.n_rg; a.ranges = plan.ranges; a.usual = plan.usual; a.sorted = plan.sorted;
     a.block_table = nullptr; a.page_size = 0; a.max_pages = 0; a.n_pages = 0;
     a.position_ids = nullptr; a.cos_tab = nullptr; a.sin_tab = nullptr; a.max_pos = 0; a.k_rot = nullptr;
     if (dt == RD_BF16) return rd::tree_attn_bf16(a, D, plan.waves, plan.rg_tiles, (hipStream_t)stream);
@@ -124,7 +124,7 @@ extern "C" int rd_tree_attn_paged(const void *q, const void *k_pages, const void
     a.partials = reinterpret_cast<float *>(static_cast<unsigned char *>(workspace) + plan.counters_bytes);
     a.B = B; a.H = H; a.N = N; a.Cmax = Cmax; a.S = plan.S; a.words = (N + 63) / 64;
     a.scale_log2e = scale * 1.44269504088896340736f;
-    a.n_rg = plan.n_rg; a.ranges = plan.ranges; a.sorted = plan.sorted;
+    a.n_rg = plan.n_rg; a.ranges = plan.ranges; a.usual = plan.usual; a.sorted = plan.sorted;
     a.position_ids = nullptr; a.cos_tab = nullptr; a.sin_tab = nullptr; a.max_pos = 0; a.k_rot = nullptr;
     return rd::tree_attn_paged(a, D, plan.waves, plan.rg_tiles, dt == RD_F16, (hipStream_t)stream);
 }
@@ -159,7 +159,7 @@ extern "C" int rd_tree_attn_rope(const void *q, const void *k_cache, const void 
     a.partials = reinterpret_cast<float *>(static_cast<unsigned char *>(workspace) + plan.counters_bytes);
     a.B = B; a.H = H; a.N = N; a.Cmax = Cmax; a.S = plan.S; a.words = (N + 63) / 64;
     a.scale_log2e = scale * 1.44269504088896340736f;
-    a.n_rg = plan.n_rg; a.ranges = plan.ranges; a.sorted = plan.sorted;
+    a.n_rg = plan.n_rg; a.ranges = plan.ranges; a.usual = plan.usual; a.sorted = plan.sorted;
     a.block_table = nullptr; a.page_size = 0; a.max_pages = 0; a.n_pages = 0;
     a.position_ids = position_ids; a.cos_tab = cos_tab; a.sin_tab = sin_tab; a.max_pos = max_pos; a.k_rot = k_new_rot;
     if (dt == RD_BF16) return rd::tree_attn_rope_bf16(a, D, plan.waves, plan.rg_tiles, (hipStream_t)stream);

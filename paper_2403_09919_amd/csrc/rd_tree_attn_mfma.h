@@ -133,7 +133,7 @@ __global__ __launch_bounds__(NW * 64, 2) void rd_tree_attn_mfma_kernel(AttnArgs 
     RD_TR(0);
     // All arguments are fetched here, together: as the compiler places the loads they are a chain of four, 0.3 us each.
     asm volatile("" : : "s"(a.q), "s"(a.k_cache), "s"(a.v_cache), "s"(a.k_new), "s"(a.v_new), "s"(a.ctx_len), "s"(a.n_packed), "s"(a.mask_bits),
-                 "s"(a.B), "s"(a.H), "s"(a.N), "s"(a.Cmax), "s"(a.S), "s"(a.words), "s"(a.n_rg), "s"(a.ranges), "s"(a.sorted));
+                 "s"(a.B), "s"(a.H), "s"(a.N), "s"(a.Cmax), "s"(a.S), "s"(a.words), "s"(a.n_rg), "s"(a.ranges), "s"(a.usual), "s"(a.sorted));
     if constexpr (ROPE) asm volatile("" : : "s"(a.position_ids), "s"(a.cos_tab), "s"(a.sin_tab), "s"(a.max_pos));
     if constexpr (PAGED) asm volatile("" : : "s"(a.block_table), "s"(a.page_size), "s"(a.max_pages), "s"(a.n_pages));
 
@@ -148,7 +148,7 @@ __global__ __launch_bounds__(NW * 64, 2) void rd_tree_attn_mfma_kernel(AttnArgs 
     int bh, b, r_wg, n_act = 1, ranges = attn_ranges(a.ranges, 1);      // n_act row groups times ranges: the head's workgroups
     auto groups_of = [&](int rows) __attribute__((always_inline)) { return max((clampi(rows, 0, a.N) + kRows - 1) / kRows, 1); };
     auto heads_before = [&](int s) __attribute__((always_inline)) { return (s * a.H + 7 - xcd) >> 3; };         // this XCD's, of sequences before s
-    auto wgs_of = [&](int s, int act) __attribute__((always_inline)) { return (heads_before(s + 1) - heads_before(s)) * act * attn_ranges(a.ranges, act); };
+    auto wgs_of = [&](int s, int act) __attribute__((always_inline)) { return (heads_before(s + 1) - heads_before(s)) * act * ranges; };
     auto running = [&](int x) __attribute__((always_inline)) {             // sum over the lanes up to this one
 #pragma unroll
         for (int o = 1; o < 64; o <<= 1) {
@@ -182,6 +182,7 @@ __global__ __launch_bounds__(NW * 64, 2) void rd_tree_attn_mfma_kernel(AttnArgs 
         // one sequence's heads on this XCD, of four in large batches (a step of 64 costs 0.4 us: 512 sequences, H=32, 20 to 300
         // keys, 80 tokens 680 us by steps of 64, 614 by 256), and a running sum finds the workgroup's place.  (Workgroups without work in between
         // leave compute units idle beside others that have two: 29 us for 22 at H=32, C=1777, 147 of 350 rows.)
+        ranges = a.usual;
         int own = (int)(blockIdx.x >> 3);     // in the end: the workgroup's number among its sequence's
         if (a.B <= kOneStep) {                // a sequence to a lane
             int seq = min(lane, a.B - 1), rows = a.n_packed[seq];
@@ -196,7 +197,9 @@ __global__ __launch_bounds__(NW * 64, 2) void rd_tree_attn_mfma_kernel(AttnArgs 
                 seq = __builtin_amdgcn_ds_permute(place * 4, seq);
                 rows = __builtin_amdgcn_ds_permute(place * 4, rows);
             }
-            const int act = groups_of(rows), need = lane < a.B ? wgs_of(seq, act) : 0, sum = running(need);
+            const int act = groups_of(rows), act0 = __builtin_amdgcn_readlane(act, 0);
+            if (__builtin_amdgcn_ballot_w64(act != act0) == 0) ranges = attn_ranges(a.ranges, act0);      // (all sequences alike)
+            const int need = lane < a.B ? wgs_of(seq, act) : 0, sum = running(need);
             const uint64_t past = __builtin_amdgcn_ballot_w64(sum > own);
             if (past == 0) return;
             const int at = __builtin_ctzll(past);
@@ -238,7 +241,6 @@ __global__ __launch_bounds__(NW * 64, 2) void rd_tree_attn_mfma_kernel(AttnArgs 
                 }
             }
         }
-        ranges = attn_ranges(a.ranges, n_act);
         const int n_wg = n_act * ranges, hl = own / n_wg;
         r_wg = own - hl * n_wg;
         bh = (heads_before(b) + hl) * 8 + xcd;

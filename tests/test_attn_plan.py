@@ -43,9 +43,10 @@ int main(int argc, char **argv)
                         if (p.counters_bytes < (size_t)BH * p.n_rg * sizeof(unsigned long long)) bad("counters overlap the partial results");
                         int most = 1;              // key ranges; one is written out directly
                         for (int g = 1; !f32 && g <= p.n_rg; ++g) {
-                            const int R = attn_ranges(p.ranges, g);
+                            const int own = attn_ranges(p.ranges, g), R = own > p.usual ? own : p.usual;
                             most = R > most ? R : most;
-                            if (s[0] > 1 && R != attn_ranges(p.ranges, 1)) bad("sequences of a batch split their keys by their packed rows");
+                            if (own < 1 || p.usual < 1 || (s[0] > kOneStep && own != p.usual)) bad("key ranges");
+                            if (s[0] > 1 && own > p.usual && (BH + 7) / 8 * 8 * g * own > (p.waves == 8 ? 256 : 512)) bad("ranges that wait for a place");
                             if (R < 1 || (p.S > 1 ? R * g > p.S : R > 1)) bad("key ranges without workgroups");
                         }
                         const bool partials = f32 ? p.S > 1 : most > 1;
@@ -64,14 +65,14 @@ int main(int argc, char **argv)
                         ++n;
                     }
                 }
-    // A beam whose candidates share most of their prefixes: the rows of one or two groups out of many still get
+    // Beams whose candidates share most of their prefixes: the rows of one or two groups out of many still get
     // workgroups for about half of the chip's 256 compute units and more, as their keys allow (33 tiles of them and more here).
-    const int shared[][3] = {{32, 350, 1777}, {32, 350, 4096}, {32, 150, 2048}, {4, 384, 6000}};
+    const int shared[][4] = {{1, 32, 350, 1777}, {1, 32, 350, 4096}, {1, 32, 150, 2048}, {2, 32, 250, 3000}, {4, 40, 80, 4096}, {1, 4, 384, 6000}};
     for (auto &s : shared)
         for (int g = 1; g <= 2; ++g) {
-            const AttnPlan p = attn_plan_make(1, s[0], s[1], 128, s[2]);
-            const int wgs = s[0] * g * attn_ranges(p.ranges, g), least = s[0] * 10 < 120 ? s[0] * 10 : 120;
-            if (wgs < least) printf("H=%d N=%d C=%d: %d workgroups for %d groups of packed rows\n", s[0], s[1], s[2], wgs, g);
+            const AttnPlan p = attn_plan_make(s[0], s[1], s[2], 128, s[3]);
+            const int wgs = s[0] * s[1] * g * attn_ranges(p.ranges, g), least = s[0] * s[1] * 10 < 120 ? s[0] * s[1] * 10 : 120;
+            if (wgs < least) printf("B=%d H=%d N=%d C=%d: %d workgroups for %d groups of packed rows\n", s[0], s[1], s[2], s[3], wgs, g);
         }
     printf("plans %ld\n", n);
 }

@@ -81,14 +81,17 @@ def test_rotary_tables_at_any_multiple_of_four_bytes(rd, D, W, L, ctx, shift):
 
 @pytest.mark.parametrize("dtype,D", [("bf16", 128), ("f16", 64)])
 @pytest.mark.parametrize("H,W,L,ctx,vocabs", [(4, 70, 5, [1777], [1]), (4, 70, 5, [1777], [2]), (4, 70, 5, [4096], [3]), (3, 16, 5, [4096, 700, 3000], [2, 32000, 5]),
-                                              (5, 30, 5, [2048, 2048], [2, 32000]), (2, 128, 3, [0, 3000, 31, 1500], [1, 4, 8, 32000])])
+                                              (5, 30, 5, [2048, 2048], [2, 32000]), (2, 128, 3, [0, 3000, 31, 1500], [1, 4, 8, 32000]),
+                                              (8, 50, 5, [3000, 2700], [2, 2]), (8, 50, 5, [3000, 2700], [2, 32000]), (3, 70, 5, [700, 650], [32000, 32000]),
+                                              (4, 70, 5, [4000 - 37 * (7 * i % 20) for i in range(20)], [5] * 20)])
 def test_few_packed_rows_in_a_wide_beam(rd, dtype, D, H, W, L, ctx, vocabs):
-    """Candidates that share most of their prefixes (small vocabularies) beside ones that do not: a lone sequence's key ranges
-    go by how many of its row groups hold packed rows; the sequences of a batch have the same ranges and differ in their groups."""
+    """Candidates that share most of their prefixes (small vocabularies) beside ones that do not: the key ranges of a head go
+    by how many of its row groups hold packed rows where all sequences agree in that (by the plan 8 and not 5 for 50 x 5 tokens, 4
+    and not 7 for D=128, C=700, 2 and not 3 for the 20 sequences, longest first) and are the plan's usual ones where they differ."""
     announce(f"few packed rows {dtype} D={D} H={H} W={W} L={L} ctx={ctx} vocabs={vocabs}")
     B = len(ctx)
     ctx, _, q, kn, vn, kc, vc, _ = _case(B, H, W, L, ctx, D, dtype, W + H)
-    beams = np.concatenate([synth.make_beams(1, W, L, v, 7 + i, "uniform") for i, v in enumerate(vocabs)])
+    beams = np.concatenate([synth.make_beams(1, W, L, v, 7 + i % 4, "uniform") for i, v in enumerate(vocabs)])
     d = oracle.dedup(beams, ctx)
     scale = float(1.0 / np.sqrt(D))
     ref = oracle.tree_attn(q, kc, vc, ctx, kn, vn, d["n_packed"], d["tree_mask"], dtype, scale)
