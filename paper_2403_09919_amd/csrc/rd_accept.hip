@@ -7,9 +7,13 @@
 // final key is its arg max with the smallest-index tie rule.  This phase is a pure HBM stream
 // over the valid logits.
 // Phase 2 (the workgroup that completes a sequence, found with a per-row and then a
-// per-sequence counter): decodes the row keys, writes the arg maxes, and wave 0 runs the
-// per-candidate prefix match with lane w = candidate w, picks the best candidate with a
-// wave-wide max on (length, -w) and writes the accepted slots and the next token.
+// per-sequence counter): decodes the row keys, writes the arg maxes, compares every candidate token with the
+// prediction at its parent (a bit each), takes a candidate's accepted prefix as the run of ones from its first
+// token, picks the best candidate with a wave-wide max on (length, -w) and writes the accepted slots and the next token.
+// Up to 64 tokens one wave does all of phase 2 in registers: beside the round trips to memory it is bound by the
+// number of its instructions (1.7 ns each in a lone wave).  us per launch, phase 2 through LDS, barriers that waited for
+// stores and a walk over every candidate's tokens -> now: 4 x 4 tokens, V = 1000 4.65 -> 3.60; 8 x 5, 32000
+// 6.5 -> 5.9; 70 x 5 12.9 -> 11.4; 16 sequences of 16 x 5 22.0 -> 21.3.
 // Two counter levels keep the number of atomics that hit one address small (chunks per row,
 // rows per sequence); hundreds of increments of a single word would serialise and cost more
 // than the stream itself.
@@ -66,6 +70,7 @@ __device__ __forceinline__ bool better(float v, int i, float bv, int bi)
 
 // Order-preserving 64-bit key of (value, index): larger value first, then smaller index.
 // Every key of a real element is greater than 0, the cleared state of the workspace.
+// (The index is -1 where the upper half is 0: no element compared.)
 // -0.0 and +0.0 are one value to the comparison that defines the arg max, so both get +0.0's key.
 __device__ __forceinline__ unsigned long long encode_key(float v, int i)
 {
@@ -73,16 +78,15 @@ __device__ __forceinline__ unsigned long long encode_key(float v, int i)
     const uint32_t mono = (u & 0x80000000u) ? ~u : (u | 0x80000000u);
     return ((unsigned long long)mono << 32) | (uint32_t)~(uint32_t)i;
 }
-__device__ __forceinline__ int key_index(unsigned long long k) { return (int)~(uint32_t)k; }
+__device__ __forceinline__ int key_index(unsigned long long k) { return k >> 32 ? (int)~(uint32_t)k : -1; }
 
-// Device-scope arrival: true for the thread whose increment brought the counter to `expected`.
-// The thread's earlier device-scope atomics (the row key's max, a lower-level counter) and stores must
-// have been performed before the counter moves: they go to other addresses and could otherwise
-// complete after it, and the workgroup that sees the full count would read a key that lacks this
-// workgroup's chunk.  wait_dev_stores() waits for their acknowledgement.
+// Device-scope arrival: true for the thread whose increment brought the counter to `expected`.  What a thread has sent
+// to other addresses could otherwise complete after its increment: a key that several chunks share (atomic max) and a
+// lower-level counter have been waited for (wait_dev_stores; the returned value), or the workgroup that sees the full count
+// would read a key that lacks a chunk.  A key that one workgroup alone stores need not be: it is never 0, the cleared state,
+// and whoever sees the full count reads it until it is there (it was issued before the increment).
 __device__ __forceinline__ bool arrive(uint32_t *counter, uint32_t expected)
 {
-    rd::wait_dev_stores();
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
     const uint32_t prev = __hip_atomic_fetch_add(counter, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
@@ -98,7 +102,7 @@ template <int U, bool SPEC>
 __global__ __launch_bounds__(kAccThreads) __attribute__((amdgpu_waves_per_eu(1, U == 8 ? 7 : 8))) void rd_accept_kernel(
     const float *__restrict__ logits, const int32_t *__restrict__ beams,
     const int32_t *__restrict__ unpack_index, const int32_t *__restrict__ n_packed,
-    const int32_t *__restrict__ root_token, int W, int L, int V, int chunks, int chunk_len,
+    const int32_t *__restrict__ root_token, int W, int L, int V, int chunks, int chunk_len, uint32_t inv_l,
     int32_t *__restrict__ argmax_out, int32_t *__restrict__ n_accept, int32_t *__restrict__ best_beam,
     int32_t *__restrict__ best_len, int32_t *__restrict__ next_token, int32_t *__restrict__ accepted_idx,
     uint32_t *seq_counters, uint32_t *row_counters, unsigned long long *row_keys)
@@ -106,9 +110,10 @@ __global__ __launch_bounds__(kAccThreads) __attribute__((amdgpu_waves_per_eu(1, 
     __shared__ float s_val[kAccThreads / 64];
     __shared__ int s_idx[kAccThreads / 64];
     __shared__ int s_am[RD_MAX_N];
-    __shared__ int s_beam[RD_MAX_N], s_slot[RD_MAX_N];
+    __shared__ int s_slot[RD_MAX_N];
     __shared__ uint32_t s_seq_last;
-    __shared__ int s_best;
+    __shared__ unsigned long long s_ok[2 * kAccThreads / 64];
+    __shared__ int s_best[2];
 
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int chunk = blockIdx.x, p = blockIdx.y, b = blockIdx.z;
@@ -132,13 +137,17 @@ __global__ __launch_bounds__(kAccThreads) __attribute__((amdgpu_waves_per_eu(1, 
     // hundred bytes, overlapped with the logit stream) instead of paying two dependent round
     // trips to memory per accepted token at the very end.
     constexpr int kPre = (RD_MAX_N + kAccThreads - 1) / kAccThreads;     // tokens per thread
-    int my_beam[kPre], my_slot[kPre], my_root = 0;
+    int my_beam[kPre], my_slot[kPre], my_parent = 0, my_root = 0;        // (the parent is the token before)
+    bool first[kPre];
 #pragma unroll
     for (int u = 0; u < kPre; ++u) {
         const int e = min(u * kAccThreads + tid, N - 1);
         my_beam[u] = beams[(size_t)b * N + e];
         my_slot[u] = unpack_index[(size_t)b * N + e];
+        first[u] = (int)((uint32_t)e * inv_l >> 20) * L == e;
     }
+    const bool one_wave = N <= 64;                        // uniform: the first wave finishes the sequence
+    if (one_wave) my_parent = unpack_index[(size_t)b * N + min(max(tid - 1, 0), N - 1)];
     if (root_token != nullptr) my_root = root_token[b];
 
     // ---- phase 1: this chunk's (max, first index) -> the row's key ---------------------------------
@@ -155,13 +164,21 @@ __global__ __launch_bounds__(kAccThreads) __attribute__((amdgpu_waves_per_eu(1, 
                 if (SPEC && base == v0) { x[u] = x0[u]; v[u] = i0[u]; }
                 else x[u] = rd::row4_at(row, base + (u * kAccThreads + tid) * 4, V, &v[u]);
             }
+            // the largest value, then the first entry that holds it (v ascends with u)
+            float m = -INFINITY;
 #pragma unroll
-            for (int u = 0; u < U; ++u) {                              // ascending v per thread
-                if (better(x[u].x, v[u], bv, bi)) { bv = x[u].x; bi = v[u]; }
-                if (better(x[u].y, v[u] + 1, bv, bi)) { bv = x[u].y; bi = v[u] + 1; }
-                if (better(x[u].z, v[u] + 2, bv, bi)) { bv = x[u].z; bi = v[u] + 2; }
-                if (better(x[u].w, v[u] + 3, bv, bi)) { bv = x[u].w; bi = v[u] + 3; }
+            for (int u = 0; u < U; ++u) m = fmaxf(fmaxf(fmaxf(m, x[u].x), fmaxf(x[u].y, x[u].z)), x[u].w);
+            int first_m = 0x7fffffff;
+#pragma unroll
+            for (int u = U - 1; u >= 0; --u) {
+                int c = -1;
+                c = x[u].w == m ? 3 : c;
+                c = x[u].z == m ? 2 : c;
+                c = x[u].y == m ? 1 : c;
+                c = x[u].x == m ? 0 : c;
+                first_m = c >= 0 ? v[u] + c : first_m;
             }
+            if (better(m, first_m, bv, bi)) { bv = m; bi = first_m; }
         }
     } else {
         for (int v = v0 + tid; v < v1; v += kAccThreads) {
@@ -177,70 +194,117 @@ __global__ __launch_bounds__(kAccThreads) __attribute__((amdgpu_waves_per_eu(1, 
     }
     RD_TR(1);
     if (lane == 0) { s_val[wave] = bv; s_idx[wave] = bi; }
-    __syncthreads();
+    rd_lds_barrier();
+    if (one_wave && wave != 0) return;
     const size_t rowid = (size_t)b * N + p;
+    uint32_t last = 0;
     if (tid == 0) {
         for (int w = 1; w < kAccThreads / 64; ++w)
             if (better(s_val[w], s_idx[w], bv, bi)) { bv = s_val[w]; bi = s_idx[w]; }
-        uint32_t last = 0;
-        if (bi != 0x7fffffff)                               // (an empty chunk cannot occur, but would add nothing)
-            __hip_atomic_fetch_max(row_keys + rowid, encode_key(bv, bi), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        // (a chunk without any value that compares, all NaN, leaves the lowest key)
+        const unsigned long long key = bi != 0x7fffffff ? encode_key(bv, bi) : 1ull;
         if (chunks == 1) {                                             // the row is this workgroup's alone
+            __hip_atomic_store(row_keys + rowid, key, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             last = arrive(seq_counters + b, (uint32_t)P) ? 1u : 0u;
-        } else if (arrive(row_counters + rowid, (uint32_t)chunks)) {   // this row is complete
-            row_counters[rowid] = 0;                                   // ready for the next call
-            last = arrive(seq_counters + b, (uint32_t)P) ? 1u : 0u;    // ... and so is the sequence
+        } else {
+            __hip_atomic_fetch_max(row_keys + rowid, key, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            rd::wait_dev_stores();
+            if (arrive(row_counters + rowid, (uint32_t)chunks)) {      // this row is complete
+                row_counters[rowid] = 0;                               // ready for the next call
+                last = arrive(seq_counters + b, (uint32_t)P) ? 1u : 0u;    // ... and so is the sequence
+            }
         }
-        s_seq_last = last;
     }
     RD_TR(2);
-    __syncthreads();
-    if (!s_seq_last) return;
-    RD_TR(3);
+    unsigned long long *seq_keys = row_keys + (size_t)b * N;
+    auto row_argmax = [&](int r) __attribute__((always_inline)) {
+        unsigned long long key;
+        do key = __hip_atomic_load(seq_keys + r, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        while (key == 0);                                 // (its store is on its way: see arrive)
+        return key_index(key);
+    };
+    auto best_of = [](int x) __attribute__((always_inline)) {      // over the wave; x >= 0
+        return __float_as_int(rd::wave_reduce(__int_as_float(x), [](float y, float z) __attribute__((always_inline)) { return __int_as_float(max(__float_as_int(y), __float_as_int(z))); }));
+    };
+    static_assert(RD_MAX_W <= 128 && RD_MAX_N < (1 << 15), "candidates: two waves, index in 8 bits");
 
     // ---- phase 2 (last workgroup of the sequence): arg maxes, then token matching -----------------------
-    for (int r = tid; r < N; r += kAccThreads) {
-        int am = -1;
-        if (r < P) {
-            const unsigned long long *kp = row_keys + (size_t)b * N + r;
-            am = key_index(__hip_atomic_load(kp, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+    if (one_wave) {
+        // Lane = row, then token, then candidate; nothing goes through LDS.  A wave issues an instruction every 1.7 ns, so
+        // that this part is as long as its code.
+        if (!__builtin_amdgcn_readfirstlane(last)) return;
+        RD_TR(3);
+        const int am = lane < P ? row_argmax(lane) : -1;
+        RD_TR(4);
+        if (lane < N) argmax_out[(size_t)b * N + lane] = am;
+        if (lane < P) seq_keys[lane] = 0;     // ready for the next call
+        if (lane == 0) seq_counters[b] = 0;
+        const int predicted = __builtin_amdgcn_ds_bpermute(min(max(my_parent, 0), N - 1) * 4, am);
+        const bool ok = lane < N && (first[0] ? root_token == nullptr || my_beam[0] == my_root : predicted == my_beam[0]);
+        const unsigned long long agree = __ballot(ok);
+        // a candidate's accepted prefix is the run of ones from its first bit
+        int len = 0;
+        if (lane < W) {
+            const unsigned long long zeros = ~(agree >> (lane * L));
+            len = min(zeros ? __builtin_ctzll(zeros) : 64, L);
+            n_accept[(size_t)b * W + lane] = len;
         }
+        const int key = best_of(lane < W ? (len << 8) | (255 - lane) : 0);     // longest, smallest index among equals
+        const int bl = key >> 8, bw = 255 - (key & 255);
+        const int slot = __builtin_amdgcn_ds_bpermute((bw * L + min(lane, L - 1)) * 4, min(max(my_slot[0], 0), N - 1));
+        if (lane < L) accepted_idx[(size_t)b * L + lane] = lane < bl ? slot : -1;
+        const int next = __builtin_amdgcn_ds_bpermute(slot * 4, am);
+        if (lane == max(bl - 1, 0)) {
+            best_beam[b] = bw;
+            best_len[b] = bl;
+            next_token[b] = bl > 0 ? next : my_root;
+        }
+        RD_TR(5);
+        return;
+    }
+    if (tid == 0) s_seq_last = last;
+    rd_lds_barrier();
+    if (!s_seq_last) return;
+    RD_TR(3);
+    for (int r = tid; r < N; r += kAccThreads) {
+        const int am = r < P ? row_argmax(r) : -1;
         s_am[r] = am;
         argmax_out[(size_t)b * N + r] = am;
     }
 #pragma unroll
     for (int u = 0; u < kPre; ++u) {
         const int e = u * kAccThreads + tid;
-        if (e < N) {
-            s_beam[e] = my_beam[u];
-            s_slot[e] = min(max(my_slot[u], 0), N - 1);
-        }
+        if (e < N) s_slot[e] = min(max(my_slot[u], 0), N - 1);
     }
-    if (tid == 0) s_best = -1;
-    __syncthreads();                                      // every key has been read
+    rd_lds_barrier();                                      // every key has been read
     RD_TR(4);
-    for (int r = tid; r < P; r += kAccThreads) row_keys[(size_t)b * N + r] = 0;   // ready for the next call
+    for (int r = tid; r < P; r += kAccThreads) seq_keys[r] = 0;     // ready for the next call
     if (tid == 0) seq_counters[b] = 0;
-
-    // one thread per candidate (W <= RD_MAX_W <= kAccThreads)
-    static_assert(RD_MAX_W <= kAccThreads && RD_MAX_W <= 256, "one thread per candidate, index in 8 bits");
-    const int w = tid;
-    if (w < W) {
-        const int *bm = s_beam + w * L;
-        const int *ui = s_slot + w * L;
-        int len = 0;
-        bool ok = (root_token == nullptr) || (bm[0] == my_root);
-        while (ok) {
-            ++len;
-            if (len == L) break;
-            ok = (s_am[ui[len - 1]] == bm[len]);
-        }
-        n_accept[(size_t)b * W + w] = len;
-        // best candidate: longest accepted prefix, smallest index among equals
-        atomicMax(&s_best, (len << 8) | (255 - w));
+    // one thread per candidate token: does the LLM agree with it; a bit each
+#pragma unroll
+    for (int u = 0; u < kPre; ++u) {
+        const bool ok = u * kAccThreads + tid < N &&
+                        (first[u] ? root_token == nullptr || my_beam[u] == my_root : s_am[s_slot[u * kAccThreads + tid - 1]] == my_beam[u]);
+        const unsigned long long bits = __ballot(ok);
+        if (lane == 0) s_ok[u * (kAccThreads / 64) + wave] = bits;
     }
-    __syncthreads();
-    const int key = s_best;
+    rd_lds_barrier();
+    int len = 0;                                           // one thread per candidate
+    if (tid < W) {
+        for (int run = 64; run > 0 && len < L; len += run) {
+            const int pos = tid * L + len, left = min(64 - (pos & 63), L - len);
+            const unsigned long long zeros = ~(s_ok[pos >> 6] >> (pos & 63));
+            run = min(zeros ? __builtin_ctzll(zeros) : 64, left);
+            if (run < left) { len += run; break; }
+        }
+        n_accept[(size_t)b * W + tid] = len;
+    }
+    if (wave < 2) {
+        const int most = best_of(tid < W ? (len << 8) | (255 - tid) : 0);
+        if (lane == 0) s_best[wave] = most;
+    }
+    rd_lds_barrier();
+    const int key = max(s_best[0], s_best[1]);
     const int bl = key >> 8;
     const int bw = 255 - (key & 255);
     const int *bui = s_slot + bw * L;
@@ -290,9 +354,11 @@ static int accept_launch(const AccPlan &plan, const float *logits, const int32_t
     uint32_t *seq_counters = reinterpret_cast<uint32_t *>(ws);
     uint32_t *row_counters = reinterpret_cast<uint32_t *>(ws + plan.row_counters_off);
     unsigned long long *row_keys = reinterpret_cast<unsigned long long *>(ws + plan.keys_off);
+    const uint32_t inv_l = ((1u << 20) + (uint32_t)L - 1) / (uint32_t)L;      // e / L = e * inv_l >> 20 for e < RD_MAX_N
+    static_assert(RD_MAX_N * RD_MAX_N <= 1 << 20, "error of the reciprocal times e below 1 / L");
 #define RD_ACCEPT_LAUNCH_(U, SPEC)                                                                            \
     hipLaunchKernelGGL((rd_accept_kernel<U, SPEC>), grid, block, 0, stream, logits, beams, unpack_index,       \
-                       n_packed, root_token, W, L, V, plan.chunks, plan.chunk_len, argmax_out, n_accept,       \
+                       n_packed, root_token, W, L, V, plan.chunks, plan.chunk_len, inv_l, argmax_out, n_accept,       \
                        best_beam, best_len, next_token, accepted_idx, seq_counters, row_counters, row_keys)
 #define RD_ACCEPT_LAUNCH(U)                                 \
     do {                                                    \

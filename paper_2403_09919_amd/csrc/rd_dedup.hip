@@ -1,5 +1,6 @@
 // rd_dedup: dynamic tree attention construction (Sec. 3.3, App. A.1) for gfx950.
 //
+// Up to 64 tokens: rd_dedup_wave_kernel below.  More:
 // One workgroup per sequence (more where the dense mask is asked for), everything in LDS, data-parallel phases
 // separated by barriers (the whole input is a few hundred bytes; what costs time is dependent latency, so no phase
 // is a serial walk over positions):
@@ -25,7 +26,7 @@ constexpr int kDedupThreads = 384;                 // the fewest: one thread per
 // More than 16 candidates: their pairs are what takes time (us, 384 / 1024 threads: 16 candidates 3.82 / 3.86, 20 4.34 / 3.90,
 // 30 5.20 / 4.38, 70 12.8 / 8.8).
 constexpr int kWideThreads = 1024;
-// Rows of the dense mask per workgroup (us, all rows in one / 32 / 16: N = 40 3.95 / 3.82 / 3.83; N = 80, 16 sequences 4.94 /
+// Rows of the dense mask per workgroup (us, all rows in one / 32 / 16: N = 80, 16 sequences 4.94 /
 // 4.56 / 4.42; N = 150 8.6 / 5.4 / 5.0; N = 350 31.8 / 10.9 / 9.9).  Every workgroup repeats the construction, so fewer rows cost
 // where there are more workgroups than compute units: 24 sequences of N = 350 take 34.3 / 19.3 / 23.3 (14.2 with 48 rows).
 constexpr int kMaskRows = 32;
@@ -189,6 +190,81 @@ __global__ __launch_bounds__(kWideThreads) void rd_dedup_kernel(
     RD_TR(5);
 }
 
+// Up to 64 tokens: a wave holds a token per lane and sets of tokens are ballots, so that nothing waits at a barrier.  All four
+// waves do the same, each writes its part of the results.  Beside the launch and one round trip to memory it is bound by the
+// number of its instructions (1.7 ns each in a lone wave).  us per launch in a graph, by the phases above / so: N = 16
+// 3.70 / 2.05, 40 4.0 / 2.6 (without the dense mask 3.8 / 2.3), 24 sequences of 25 4.2 / 2.65; an empty launch takes 1.9.
+__global__ __launch_bounds__(256) void rd_dedup_wave_kernel(
+    const int32_t *__restrict__ beams, const int32_t *__restrict__ ctx_len, int W, int L, uint32_t inv_l, uint32_t inv_n,
+    int32_t *__restrict__ prefix_tree, int32_t *__restrict__ packed_tokens,
+    int32_t *__restrict__ n_packed, int32_t *__restrict__ unpack_index,
+    int32_t *__restrict__ parent, int32_t *__restrict__ position_ids,
+    uint8_t *__restrict__ tree_mask, uint64_t *__restrict__ tree_mask_bits)
+{
+    const int b = blockIdx.x, e = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), N = W * L;
+    const size_t seq = (size_t)b * N;
+    const bool tok = e < N;
+    const int token = beams[seq + min(e, N - 1)];
+    const int ctx = ctx_len ? ctx_len[b] : 0;
+    const int i = (int)((uint32_t)e * inv_l >> 20), j = e - i * L;      // e = (candidate, position)
+    auto from = [](int lane, int x) __attribute__((always_inline)) { return __builtin_amdgcn_ds_bpermute(lane * 4, x); };
+    auto from64 = [&](int lane, uint64_t x) __attribute__((always_inline)) { return (uint64_t)(uint32_t)from(lane, (int)(uint32_t)x) | (uint64_t)(uint32_t)from(lane, (int)(x >> 32)) << 32; };
+
+    // owner: the smallest candidate whose first j + 1 tokens are this one's, i.e. prefix_tree
+    const uint64_t mine = ((2ull << j) - 1) << (i * L & 63);            // tokens 0 .. j of this candidate
+    int owner = i;
+#pragma unroll 4
+    for (int k = W - 1; k >= 0; --k) {
+        const uint64_t same = __ballot(token == from(k * L + j, token));
+        owner = k < i && (same & mine) == mine ? k : owner;
+    }
+    const uint64_t kept = __ballot(tok && owner == i);                  // in the order of their slots
+    const int P = __popcll(kept), slot = __popcll(kept & ((1ull << (owner * L + j)) - 1));
+    if (wave == 0) {
+        if (tok) {
+            unpack_index[seq + e] = slot;
+            if (prefix_tree) prefix_tree[seq + e] = owner;
+        }
+        if (e == 0) n_packed[b] = P;
+    }
+    // What belongs to a slot goes to the lane of that number; copies, and lanes without a token, to the first lane without a slot.
+    const int to = tok && owner == i ? slot : P, before = from(e - 1, slot);
+    auto place = [&](int x) __attribute__((always_inline)) { return __builtin_amdgcn_ds_permute(to * 4, x); };
+    if (wave == 1) {
+        const int t = place(token), up = place(j ? before : -1), pos = place(ctx + j);
+        if (tok) {
+            packed_tokens[seq + e] = e < P ? t : -1;
+            parent[seq + e] = e < P ? up : -1;
+            position_ids[seq + e] = e < P ? pos : -1;
+        }
+    }
+    if (tree_mask == nullptr && (wave != 2 || tree_mask_bits == nullptr)) return;
+    uint64_t path = 1ull << slot;                                       // slots from the root to (i, j)
+    for (int d = 1; d < L; d <<= 1) {
+        const uint64_t up = from64(e - d, path);
+        path |= j >= d ? up : 0;
+    }
+    uint64_t row = (uint64_t)(uint32_t)place((int)(uint32_t)path) | (uint64_t)(uint32_t)place((int)(path >> 32)) << 32;
+    row = e < P ? row : 0;                                              // of slot e
+    if (wave == 2 && tok && tree_mask_bits) tree_mask_bits[seq + e] = row;
+    if (tree_mask == nullptr) return;
+    uint8_t *dst = tree_mask + seq * N;
+    if ((N & 3) == 0) {                                                 // N*N and seq*N are multiples of 4: 32-bit stores
+        const int n4 = N >> 2, all = N * n4;
+        for (int t0 = wave * 64; t0 < all; t0 += 256) {
+            const int t = t0 + e, p = (int)((uint32_t)t * inv_n >> 20), q = t - p * n4;
+            const uint32_t w = (uint32_t)(from64(p, row) >> (q * 4 & 63)) & 15u;
+            if (t < all) reinterpret_cast<uint32_t *>(dst)[t] = (w * 0x00204081u) & 0x01010101u;      // a bit to a byte
+        }
+    } else {
+        for (int t0 = wave * 64; t0 < N * N; t0 += 256) {
+            const int t = t0 + e, p = (int)((uint32_t)t * inv_n >> 20), q = t - p * N;
+            const uint64_t w = from64(p, row) >> (q & 63);
+            if (t < N * N) dst[t] = (uint8_t)(w & 1);
+        }
+    }
+}
+
 }  // namespace
 
 extern "C" int rd_dedup(const int32_t *beams, const int32_t *ctx_len, int B, int W, int L,
@@ -201,6 +277,15 @@ extern "C" int rd_dedup(const int32_t *beams, const int32_t *ctx_len, int B, int
     if (!beams || !packed_tokens || !n_packed || !unpack_index || !parent || !position_ids)
         return RD_ERR_INVALID_ARG;
     if (!rd_aligned(tree_mask, 4) || !rd_aligned(tree_mask_bits, 8)) return RD_ERR_INVALID_ARG;
+    const int N = W * L;
+    if (N <= 64) {
+        // x / d = x * inv >> 20 for x below 4096 and d up to 64 (x * (d - 1) < 2^20)
+        auto inverse = [](int d) { return ((1u << 20) + (uint32_t)d - 1) / (uint32_t)d; };
+        hipLaunchKernelGGL(rd_dedup_wave_kernel, dim3(B), dim3(256), 0, (hipStream_t)stream, beams, ctx_len, W, L, inverse(L),
+                           inverse((N & 3) == 0 ? N >> 2 : N), prefix_tree, packed_tokens, n_packed, unpack_index, parent, position_ids,
+                           tree_mask, tree_mask_bits);
+        return rd_check_launch();
+    }
     const int slices = tree_mask ? (W * L + kMaskRows - 1) / kMaskRows : 1;
     hipLaunchKernelGGL(rd_dedup_kernel, dim3(B, slices), dim3(W > 16 ? kWideThreads : kDedupThreads), 0, (hipStream_t)stream,
                        beams, ctx_len, W, L, prefix_tree, packed_tokens, n_packed, unpack_index,
