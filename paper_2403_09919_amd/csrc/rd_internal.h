@@ -92,12 +92,13 @@ __device__ __forceinline__ float2 ld_dev2(const float *p)
     return make_float2(__uint_as_float((unsigned)u), __uint_as_float((unsigned)(u >> 32)));
 }
 
-// 16 bytes as two 8-byte device-scope stores (write-through).  Both are ordinary atomic stores the
-// compiler sees, so it inserts whatever wait states the data registers need before they are reused.
+// 16 bytes, written through like the others: one store of whole lines, where two of 8 bytes each leave every second piece of
+// a line to the other.  Nothing may rely on the 16 bytes arriving together.  The compiler does not know this store: the
+// empty slot behind it is what the data registers need before they are written again.
 __device__ __forceinline__ void st_dev4(float *p, float a, float b, float c, float d)
 {
-    st_dev2(p, a, b);
-    st_dev2(p + 2, c, d);
+    typedef float f4 __attribute__((ext_vector_type(4)));
+    asm volatile("global_store_dwordx4 %0, %1, off sc1\n\ts_nop 0" : : "v"(p), "v"(f4{a, b, c, d}) : "memory");
 }
 // Returns once every vector memory operation this wave has issued -- loads, stores and atomics without
 // a return value alike, they share one counter -- has been acknowledged.  A device-scope store or atomic

@@ -14,7 +14,10 @@
 //
 // What bounds it.  Long contexts in large batches: HBM; the same copies without any arithmetic take as long (B=16, H=64,
 // C=2048 192 us, 5.6 TB/s; 191 without arithmetic).  Few heads: a chain of latencies (counts, Q, K and V in 4.4 us at H=32,
-// C=1024, 2.3 of arithmetic, the store of a partial result and its arrival 1.4, the merge 2.3).  Against the kernel it
+// C=1024, 2.3 of arithmetic, the store of a partial result and its arrival 1.4, the merge 2.3), in which a branch per tile, a
+// half-written line and a load that only fills a chunk all count: the sum over the tiles without branches, partial results
+// stored 16 bytes at a time and merged by chunks of 4, 6 or 8 take H=32, C=1024 from 11.6 to 11.0 us, with rotation from 12.5 to
+// 12.0, H=32, C=1777, 209 rows of 350 from 26.2 to 24.8.  Against the kernel it
 // replaced, whose waves shared every block of tiles at two barriers and fetched K and V through registers, us per launch, K
 // and V from memory: H=32, C=1024 12.1 -> 10.8; B=4, H=32, C=1024 23.9 -> 19.6; H=32, C=1777, 61 rows 22.3 -> 16.7 and 147
 // rows 30.0 -> 22.0; B=10, H=52, C=63-92, 207 tokens 49.4 -> 33.2; B=4, H=40, C=4096 74.5 -> 66.5; B=16, H=52, C=2048 183.5 ->
@@ -560,7 +563,14 @@ __global__ __launch_bounds__(NW * 64, 2) void rd_tree_attn_mfma_kernel(AttnArgs 
             vec8 kreg[2][KS];
             f32x4 sacc[2][NQA];
             float c_fold = 1.f;
-            if (some) c_fold = scores(t_first, kreg, sacc, std::true_type{}, []() {});
+            if (some) {
+                c_fold = scores(t_first, kreg, sacc, std::true_type{}, []() {});
+            } else {                          // no tile: zeros for the sum over the tiles below
+#pragma unroll
+                for (int s = 0; s < kLoads; ++s) *reinterpret_cast<uint4 *>(sV + wave * G::kTileBytes + s * 1024 + lane * 16) = make_uint4(0, 0, 0, 0);
+#pragma unroll
+                for (int qt = 0; qt < NQA; ++qt) *reinterpret_cast<uint4 *>(sK + wave * G::kTileBytes + (qt * 64 + lane) * 16) = make_uint4(0, 0, 0, 0);
+            }
             RD_TR(2);
 #pragma unroll
             for (int qt = 0; qt < NQA; ++qt) {
@@ -601,26 +611,29 @@ __global__ __launch_bounds__(NW * 64, 2) void rd_tree_attn_mfma_kernel(AttnArgs 
             for (int r = 0; r < kRoundsA; ++r)
 #pragma unroll
                 for (int j = 0; j < kOwn; ++j) own[r][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-            const int n_tiles = tile_end - tile_begin;
             constexpr int kD = DT >= NW ? DT / NW : 1;          // d-tiles of a wave's fragments: those of j = 0 .. kD-1
+            // NW / 2 tiles (with more than one range a workgroup has more than that), without branches: the reads run ahead
+            auto half = [&](auto first) __attribute__((always_inline)) {
 #pragma unroll
-            for (int kt = 0; kt < NW; ++kt) {
-                if (kt >= n_tiles) break;
-                float f[NQA];
+                for (int kt = decltype(first)::value; kt < decltype(first)::value + NW / 2; ++kt) {
+                    float f[NQA];
 #pragma unroll
-                for (int qt = 0; qt < NQA; ++qt) f[qt] = fac[qt][kt];
-                vec8 vf[kD];
+                    for (int qt = 0; qt < NQA; ++qt) f[qt] = fac[qt][kt];
+                    vec8 vf[kD];
 #pragma unroll
-                for (int j = 0; j < kD; ++j) vf[j] = v_frag(kt, d_tile(j));
+                    for (int j = 0; j < kD; ++j) vf[j] = v_frag(kt, d_tile(j));
 #pragma unroll
-                for (int r = 0; r < kRoundsA; ++r)
+                    for (int r = 0; r < kRoundsA; ++r)
 #pragma unroll
-                    for (int j = 0; j < kOwn; ++j) {
-                        if (DT >= NW && 2 * r + j / kD >= NQA) continue;
-                        const vec8 pb = *reinterpret_cast<const vec8 *>(sK + kt * G::kTileBytes + (min(row_tile(r, j), NQA - 1) * 64 + lane) * 16);
-                        own[r][j] += pick(f, r, j) * Elem<T>::mfma(vf[j % kD], pb, f32x4{0.f, 0.f, 0.f, 0.f});
-                    }
-            }
+                        for (int j = 0; j < kOwn; ++j) {
+                            if (DT >= NW && 2 * r + j / kD >= NQA) continue;
+                            const vec8 pb = *reinterpret_cast<const vec8 *>(sK + kt * G::kTileBytes + (min(row_tile(r, j), NQA - 1) * 64 + lane) * 16);
+                            own[r][j] += pick(f, r, j) * Elem<T>::mfma(vf[j % kD], pb, f32x4{0.f, 0.f, 0.f, 0.f});
+                        }
+                }
+            };
+            half(std::integral_constant<int, 0>{});
+            if (tile_end - tile_begin > NW / 2) half(std::integral_constant<int, NW / 2>{});
             if constexpr (ROPE) {             // (not before V is waited for: that would be a wait for these stores)
                 if (some && t_first >= nA) store_rot(t_first, kreg);
             }
@@ -768,10 +781,10 @@ __global__ __launch_bounds__(NW * 64, 2) void rd_tree_attn_mfma_kernel(AttnArgs 
         RD_TR(5);
         if (last == kNotLast) return;
         // All loads of a chunk of partials are in flight together; no branch stands before one (partials past the end
-        // are the last one again with weight zero, rows that hold nothing are never written).
+        // are the last one again with weight zero, rows that hold nothing are never written), so the chunk follows their number.
         const float *hp = a.partials + ((size_t)bh * a.S + rg) * kPF;
-        auto merge = [&](auto clean) __attribute__((always_inline)) {
-            constexpr int kChunk = kRoundsA * kOwn * 8 <= 24 ? 8 : 4;
+        auto merge = [&](auto clean, auto chunk) __attribute__((always_inline)) {
+            constexpr int kChunk = decltype(chunk)::value;
             f32x4 acc[kRoundsA][kOwn];
             float M[NQA], den[NQA];
 #pragma unroll
@@ -850,8 +863,11 @@ __global__ __launch_bounds__(NW * 64, 2) void rd_tree_attn_mfma_kernel(AttnArgs 
                 for (int j = 0; j < kOwn; ++j)
                     if (row_tile(r, j) < NQ) put(row_tile(r, j), d_tile(j), acc[r < kRoundsA ? r : 0][j], r < kRoundsA ? pick(den, r < kRoundsA ? r : 0, j) : 1.f);
         };
-        if (last == kLastClean) merge(std::true_type{});
-        else merge(std::false_type{});
+        using std::integral_constant;
+        if (last != kLastClean) merge(std::false_type{}, integral_constant<int, 2>{});       // (not seen where workgroups are dealt to the XCDs in turn)
+        else if (n_part <= 4 || kRoundsA * kOwn * 8 > 24) merge(std::true_type{}, integral_constant<int, 4>{});
+        else if (n_part <= 6) merge(std::true_type{}, integral_constant<int, 6>{});
+        else merge(std::true_type{}, integral_constant<int, 8>{});
         if (tid == 0) a.counters[unit] = 0;   // leave the workspace ready for the next call
         RD_TR(6);
     };

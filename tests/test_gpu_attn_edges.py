@@ -131,3 +131,23 @@ def test_fp16_tiles_far_below_the_largest_score(rd, D, W, L, C):
     # one rounding of the probabilities and one of the result to 11 bits, and the result lies among fp16's subnormals in part
     assert np.abs(ref[0, :, :P].astype(np.float64) - want).max() <= 2 ** -11 * want.max() + 2 ** -25
     assert (np.abs(got[0, :, :P].astype(np.float64) - want) <= 2 ** -10 * want + 2 ** -25).all()
+
+
+@pytest.mark.parametrize("dtype,D", [("bf16", 128), ("f16", 64)])
+@pytest.mark.parametrize("W,L", [(3, 4), (8, 5), (12, 8)])
+@pytest.mark.parametrize("C", [1, 40, 100, 290, 560, 820, 1100, 1400, 1700, 2300])
+def test_waves_without_a_tile_and_numbers_of_partials(rd, dtype, D, W, L, C):
+    """One tile per wave at most: waves without one add nothing, whatever the launch before left in their LDS (here NaN), and
+    heads of two to nine ranges are merged from as many partial results."""
+    announce(f"idle waves {dtype} D={D} W={W} L={L} C={C}")
+    H = 4
+    ctx, beams, q, kn, vn, kc, vc, d = _case(1, H, W, L, [C], D, dtype, C + W)
+    scale = float(1.0 / np.sqrt(D))
+    ref = oracle.tree_attn(q, kc, vc, ctx, kn, vn, d["n_packed"], d["tree_mask"], dtype, scale)
+    npk, bits = dev(d["n_packed"]), dev(d["tree_mask_bits"])
+    nan = torch.full((1, H, 4000, D), float("nan"), dtype=dev(kc).dtype, device="cuda")
+    rd.rd_tree_attn(dev(q), nan, nan, dev(np.array([4000], np.int32)), dev(kn), dev(vn), npk, bits, scale)
+    out = rd.rd_tree_attn(dev(q), dev(kc), dev(vc), dev(ctx), dev(kn), dev(vn), npk, bits, scale)
+    torch.cuda.synchronize()
+    got, want = synth.to_f64(host(out), dtype), synth.to_f64(ref, dtype)
+    assert np.isfinite(got).all() and np.abs(got - want).max() <= TOL[dtype]
