@@ -223,9 +223,6 @@ __global__ __launch_bounds__(kAccThreads) __attribute__((amdgpu_waves_per_eu(1, 
         while (key == 0);                                 // (its store is on its way: see arrive)
         return key_index(key);
     };
-    auto best_of = [](int x) __attribute__((always_inline)) {      // over the wave; x >= 0
-        return __float_as_int(rd::wave_reduce(__int_as_float(x), [](float y, float z) __attribute__((always_inline)) { return __int_as_float(max(__float_as_int(y), __float_as_int(z))); }));
-    };
     static_assert(RD_MAX_W <= 128 && RD_MAX_N < (1 << 15), "candidates: two waves, index in 8 bits");
 
     // ---- phase 2 (last workgroup of the sequence): arg maxes, then token matching -----------------------
@@ -245,11 +242,10 @@ __global__ __launch_bounds__(kAccThreads) __attribute__((amdgpu_waves_per_eu(1, 
         // a candidate's accepted prefix is the run of ones from its first bit
         int len = 0;
         if (lane < W) {
-            const unsigned long long zeros = ~(agree >> (lane * L));
-            len = min(zeros ? __builtin_ctzll(zeros) : 64, L);
+            len = rd::accepted_run(agree, lane * L, L);
             n_accept[(size_t)b * W + lane] = len;
         }
-        const int key = best_of(lane < W ? (len << 8) | (255 - lane) : 0);     // longest, smallest index among equals
+        const int key = rd::wave_reduce_max_i(lane < W ? (len << 8) | (255 - lane) : 0);     // longest, smallest index among equals
         const int bl = key >> 8, bw = 255 - (key & 255);
         const int slot = __builtin_amdgcn_ds_bpermute((bw * L + min(lane, L - 1)) * 4, min(max(my_slot[0], 0), N - 1));
         if (lane < L) accepted_idx[(size_t)b * L + lane] = lane < bl ? slot : -1;
@@ -291,16 +287,11 @@ __global__ __launch_bounds__(kAccThreads) __attribute__((amdgpu_waves_per_eu(1, 
     rd_lds_barrier();
     int len = 0;                                           // one thread per candidate
     if (tid < W) {
-        for (int run = 64; run > 0 && len < L; len += run) {
-            const int pos = tid * L + len, left = min(64 - (pos & 63), L - len);
-            const unsigned long long zeros = ~(s_ok[pos >> 6] >> (pos & 63));
-            run = min(zeros ? __builtin_ctzll(zeros) : 64, left);
-            if (run < left) { len += run; break; }
-        }
+        len = rd::accepted_run(s_ok, tid * L, L);
         n_accept[(size_t)b * W + tid] = len;
     }
     if (wave < 2) {
-        const int most = best_of(tid < W ? (len << 8) | (255 - tid) : 0);
+        const int most = rd::wave_reduce_max_i(tid < W ? (len << 8) | (255 - tid) : 0);
         if (lane == 0) s_best[wave] = most;
     }
     rd_lds_barrier();

@@ -36,6 +36,7 @@ constexpr int kSelPer = 16;                  // consecutive entries per thread o
 constexpr int kSelChunk = kSelPer * kSelThreads;
 constexpr int kSelWaves = kSelThreads / 64;
 constexpr int kMaxSelChunks = 256;           // V <= 1 Mi entries
+constexpr int kTokens = (RD_MAX_N + kSelThreads - 1) / kSelThreads;      // per thread
 static_assert(kSelChunk == kLseChunk, "launch 2 takes the chunk totals of p from launch 1's partials");
 
 // Entries v .. v+3 of a row, -inf past the end (weight 0, neutral for the maximum).  VEC: rows of four entries and
@@ -173,9 +174,9 @@ __device__ __forceinline__ float block_exclusive_scan(float x, float *s_wave, fl
         const float o = __shfl_up(incl, off, 64);
         if (lane >= off) incl += o;
     }
-    __syncthreads();                                        // s_wave free again
+    rd_lds_barrier();                                        // s_wave free again
     if (lane == 63) s_wave[wave] = incl;
-    __syncthreads();
+    rd_lds_barrier();
     float before = 0.f, all = 0.f;
 #pragma unroll
     for (int w = 0; w < kSelWaves; ++w) {
@@ -217,15 +218,15 @@ __global__ __launch_bounds__(kSelThreads) void rd_accept_sample_kernel(
     int rows_per_step, const int32_t *__restrict__ beams,
     const int32_t *__restrict__ unpack_index, const int32_t *__restrict__ n_packed,
     const int32_t *__restrict__ root_token, const float *__restrict__ u_accept, const float *__restrict__ u_next,
-    int W, int L, int V, int chunks, float inv_t, const float4 *__restrict__ part,
+    int W, int L, uint32_t inv_l /* e / L = e * inv_l >> 20 */, int V, int chunks, float inv_t, const float4 *__restrict__ part,
     float *chunk_totals /*[B][chunks]*/, uint32_t *counters /*[B]*/,
     int32_t *__restrict__ n_accept, int32_t *__restrict__ best_beam, int32_t *__restrict__ best_len,
     int32_t *__restrict__ next_token, int32_t *__restrict__ accepted_idx)
 {
     __shared__ float s_lse_p[RD_MAX_N], s_lse_q[RD_MAX_N];
     __shared__ int s_slot[RD_MAX_N];
-    __shared__ unsigned char s_ok[RD_MAX_N];
-    __shared__ int s_best, s_pick, s_lastpos;
+    __shared__ unsigned long long s_ok[kTokens * kSelWaves];
+    __shared__ int s_best[2], s_pick[kSelWaves], s_lastpos[kSelWaves];
     __shared__ uint32_t s_last;
     __shared__ float s_wave[kSelWaves];
     __shared__ int s_ci, s_residual;
@@ -243,16 +244,20 @@ __global__ __launch_bounds__(kSelThreads) void rd_accept_sample_kernel(
     // ---- every workgroup of the sequence: log-sum-exps, rejection tests, best candidate -------------------
     // candidate tokens: at most two per thread; slot of a token and of its parent, and (where it has one) the
     // draft distribution it was drawn from, all fetched before anything waits
-    constexpr int kTok = (RD_MAX_N + kSelThreads - 1) / kSelThreads;
-    int tx[kTok], ts[kTok], tc[kTok], tr[kTok];
+    constexpr int kTok = kTokens;
+    int tx[kTok], ts[kTok], tc[kTok], tr[kTok], tj[kTok];    // (tj: position in the candidate)
     const bool has_row = step_row != nullptr && L > 1;
+    // Up to 64 tokens every wave tests all of them, so that no barrier stands behind the tests.
+    const bool by_wave = N <= 64;                           // uniform
+    const int token0 = by_wave ? lane : tid;
+    auto over_l = [&](int e) __attribute__((always_inline)) { return (int)((uint32_t)e * inv_l >> 20); };     // e / L
 #pragma unroll
     for (int k = 0; k < kTok; ++k) {
-        const int e = min(k * kSelThreads + tid, N - 1), ep = max(e - 1, 0), j = e % L;
+        const int e = min(k * kSelThreads + token0, N - 1), ep = max(e - 1, 0), j = tj[k] = e - over_l(e) * L;
         tx[k] = beams[(size_t)b * N + e];
         tc[k] = unpack_index[(size_t)b * N + e];
         ts[k] = unpack_index[(size_t)b * N + ep];
-        tr[k] = *(has_row ? step_row + ((size_t)b * W + e / L) * (L - 1) + max(j - 1, 0) : n_packed);   // (no branch around a load)
+        tr[k] = *(has_row ? step_row + ((size_t)b * W + over_l(e)) * (L - 1) + max(j - 1, 0) : n_packed);   // (no branch around a load)
     }
     // Partials: a group of G lanes (a power of two) takes a row, one or more chunks per lane; up to kRowsAhead rows per
     // lane group have their loads in flight together, the first of them beside the logits gathered below.  Rows of
@@ -274,21 +279,21 @@ __global__ __launch_bounds__(kSelThreads) void rd_accept_sample_kernel(
     float zp_t[kTok], zq_t[kTok], u_t[kTok];
 #pragma unroll
     for (int k = 0; k < kTok; ++k) {
-        const int e = min(k * kSelThreads + tid, N - 1), j = max(e % L, 1);
+        const int e = min(k * kSelThreads + token0, N - 1), j = max(tj[k], 1);
         const int x = min(max(tx[k], 0), V - 1);
         tc[k] = min(max(tc[k], 0), N - 1);
         ts[k] = min(max(ts[k], 0), N - 1);
-        const int s = e % L == 0 ? 0 : ts[k];
+        const int s = tj[k] == 0 ? 0 : ts[k];
         const size_t qrow = has_row ? (size_t)(j - 1) * rows_per_step + min(max(tr[k], 0), rows_per_step - 1) : (size_t)b * N + s;
         zp_t[k] = L > 1 ? logits[((size_t)b * N + s) * V + x] : 0.f;
         zq_t[k] = L > 1 ? draft_logits[qrow * V + x] : 0.f;
         u_t[k] = u_accept[(size_t)b * N + tc[k]];
-        if (k * kSelThreads + tid < N) s_slot[e] = tc[k];
+        if (k * kSelThreads + token0 < N) s_slot[e] = tc[k];
     }
     auto larger = [](float a, float c) __attribute__((always_inline)) { return fmaxf(a, c); };
     auto plus = [](float a, float c) __attribute__((always_inline)) { return a + c; };
     auto reduce_rows = [&](int r0, const float4 *rows) __attribute__((always_inline)) {
-        constexpr int K = kRowsAhead;
+        constexpr int K = kRowsAhead / 2;
         float mp[K], mq[K], sp[K], sq[K];
         float4 x[K];
 #pragma unroll
@@ -323,43 +328,57 @@ __global__ __launch_bounds__(kSelThreads) void rd_accept_sample_kernel(
     };
     for (int r0 = 0;;) {
         reduce_rows(r0, v);
+        if (r0 + kRowsAhead / 2 * rows_per < P) reduce_rows(r0 + kRowsAhead / 2 * rows_per, v + kRowsAhead / 2);     // uniform
         r0 += kRowsAhead * rows_per;
         if (r0 >= P) break;                                 // uniform
         load_rows(r0);
     }
-    if (tid == 0) { s_best = -1; s_pick = 0x7fffffff; s_lastpos = -1; }
-    __syncthreads();
+    rd_lds_barrier();
     RD_TR(1);
 
-    // one thread per candidate token: the rejection test of token (w, j), j >= 1
+    // the rejection test of token (w, j), j >= 1, a bit each
+    uint64_t bits[kTok];
 #pragma unroll
     for (int k = 0; k < kTok; ++k) {
-        const int e = k * kSelThreads + tid;
-        if (e >= N) continue;
-        const int x = tx[k];
-        bool ok;
-        if (e % L == 0) {
-            ok = (root_token == nullptr) || (x == my_root);
-        } else {
-            const float lp = zp_t[k] * inv_t - s_lse_p[ts[k]], lq = zq_t[k] - s_lse_q[ts[k]];
-            ok = x >= 0 && x < V && u_t[k] < fminf(__expf(lp - lq), 1.0f);
+        const int e = k * kSelThreads + token0, x = tx[k];
+        bool ok = false;
+        if (e < N) {
+            if (tj[k] == 0) {
+                ok = (root_token == nullptr) || (x == my_root);
+            } else {
+                const float lp = zp_t[k] * inv_t - s_lse_p[ts[k]], lq = zq_t[k] - s_lse_q[ts[k]];
+                ok = x >= 0 && x < V && u_t[k] < fminf(__expf(lp - lq), 1.0f);
+            }
         }
-        s_ok[e] = ok ? 1 : 0;
+        bits[k] = __ballot(ok);
     }
-    __syncthreads();
     RD_TR(2);
 
     // one thread per candidate: length of the accepted prefix; best = longest, then smallest index
-    static_assert(RD_MAX_W <= kSelThreads && RD_MAX_W <= 256, "one thread per candidate, index in 8 bits");
-    if (tid < W) {
+    static_assert(RD_MAX_W <= 128 && RD_MAX_N < (1 << 15), "candidates: two waves, index in 8 bits");
+    int key;
+    if (by_wave) {
+        const int len = rd::accepted_run(bits[0], min(lane * L, 63), L);
+        if (chunk == 0 && tid < W) n_accept[(size_t)b * W + tid] = len;
+        key = rd::wave_reduce_max_i(lane < W ? (len << 8) | (255 - lane) : 0);
+    } else {
+#pragma unroll
+        for (int k = 0; k < kTok; ++k)
+            if (lane == 0) s_ok[k * kSelWaves + wave] = bits[k];
+        rd_lds_barrier();
         int len = 0;
-        while (len < L && s_ok[tid * L + len]) ++len;
-        if (chunk == 0) n_accept[(size_t)b * W + tid] = len;
-        atomicMax(&s_best, (len << 8) | (255 - tid));
+        if (tid < W) {
+            len = rd::accepted_run(s_ok, tid * L, L);
+            if (chunk == 0) n_accept[(size_t)b * W + tid] = len;
+        }
+        if (wave < 2) {
+            const int most = rd::wave_reduce_max_i(tid < W ? (len << 8) | (255 - tid) : 0);
+            if (lane == 0) s_best[wave] = most;
+        }
+        rd_lds_barrier();
+        key = max(s_best[0], s_best[1]);
     }
-    __syncthreads();
     RD_TR(3);
-    const int key = s_best;
     const int bl = key >> 8, bw = 255 - (key & 255);
     if (chunk == 0) {
         for (int t = tid; t < L; t += kSelThreads) accepted_idx[(size_t)b * L + t] = (t < bl) ? s_slot[bw * L + t] : -1;
@@ -384,14 +403,14 @@ __global__ __launch_bounds__(kSelThreads) void rd_accept_sample_kernel(
         float t = chunk_weights<VEC>(zp, zq, chunk, V, inv_t, lse_p, lse_q, true, w);
         t = rd::wave_reduce_sum(t);
         if (lane == 0) s_wave[wave] = t;
-        __syncthreads();
+        rd_lds_barrier();
         if (tid == 0) {
             rd::st_dev(chunk_totals + (size_t)b * chunks + chunk, (s_wave[0] + s_wave[1]) + (s_wave[2] + s_wave[3]));
             rd::wait_dev_stores();                                      // the total is visible before the arrival
             const uint32_t prev = __hip_atomic_fetch_add(counters + b, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             s_last = (prev + 1u == (uint32_t)chunks) ? 1u : 0u;
         }
-        __syncthreads();
+        rd_lds_barrier();
         if (!s_last) return;
         if (tid == 0) counters[b] = 0;                      // ready for the next call
     } else if (chunk != 0) {
@@ -448,7 +467,7 @@ __global__ __launch_bounds__(kSelThreads) void rd_accept_sample_kernel(
         }
         if (lane == 0) { s_ci = ci; s_base = base; s_target = target; s_residual = residual ? 1 : 0; }
     }
-    __syncthreads();
+    rd_lds_barrier();
     const int ci = s_ci;
     const float base = s_base, target = s_target;
     residual = s_residual != 0;
@@ -468,13 +487,16 @@ __global__ __launch_bounds__(kSelThreads) void rd_accept_sample_kernel(
             if (pick == 0x7fffffff && cum > target) pick = v0 + k;
         }
     }
-    if (pick != 0x7fffffff) atomicMin(&s_pick, pick);
-    if (lastpos >= 0) atomicMax(&s_lastpos, lastpos);
-    __syncthreads();
+    // (tokens ascend with the threads)
+    const uint64_t found = __ballot(pick != 0x7fffffff), held = __ballot(lastpos >= 0);
+    const int first = found ? __builtin_amdgcn_readlane(pick, __ffsll((long long)found) - 1) : 0x7fffffff;
+    const int last = held ? __builtin_amdgcn_readlane(lastpos, 63 - __clzll((long long)held)) : -1;
+    if (lane == 0) { s_pick[wave] = first; s_lastpos[wave] = last; }
+    rd_lds_barrier();
     RD_TR(5);
     if (tid == 0) {
-        int tok = s_pick;
-        if (tok == 0x7fffffff) tok = s_lastpos;             // rounding left no crossing: the last token of positive weight
+        int tok = min(min(s_pick[0], s_pick[1]), min(s_pick[2], s_pick[3]));
+        if (tok == 0x7fffffff) tok = max(max(s_lastpos[0], s_lastpos[1]), max(s_lastpos[2], s_lastpos[3]));      // rounding left no crossing: the last token of positive weight
         if (tok < 0) tok = 0;
         next_token[b] = tok;
     }
@@ -538,7 +560,7 @@ extern "C" int rd_accept_sample(const float *logits, const float *draft_logits, 
     hipLaunchKernelGGL(vec ? rd_accept_sample_kernel<true> : rd_accept_sample_kernel<false>, dim3(plan.chunks, B),
                        dim3(kSelThreads), 0, s, logits, draft_logits, draft_step_row, draft_rows_per_step, beams, unpack_index, n_packed,
                        root_token, u_accept,
-                       u_next, W, L, V, plan.chunks, inv_t, part, chunk_totals, counters, n_accept, best_beam, best_len,
+                       u_next, W, L, ((1u << 20) + (uint32_t)L - 1) / (uint32_t)L, V, plan.chunks, inv_t, part, chunk_totals, counters, n_accept, best_beam, best_len,
                        next_token, accepted_idx);
     return rd_check_launch();
 }

@@ -213,7 +213,32 @@ __device__ __forceinline__ uint32_t wave_reduce_min_u(uint32_t x)
         return __uint_as_float(min(__float_as_uint(a), __float_as_uint(b)));
     }));
 }
+// (integers from 0 on)
+__device__ __forceinline__ int wave_reduce_max_i(int x)
+{
+    return __float_as_int(wave_reduce(__int_as_float(x), [](float a, float b) __attribute__((always_inline)) {
+        return __int_as_float(max(__float_as_int(a), __float_as_int(b)));
+    }));
+}
 __device__ __forceinline__ float wave_reduce_sum(float x) { return wave_reduce(x, [](float a, float b) { return a + b; }); }
+
+// Length of the run of ones in a bit set from bit `first` on, at most L: a candidate's accepted prefix, where the candidates'
+// tokens are a bit each in row-major order.  In one word, and in several.
+__device__ __forceinline__ int accepted_run(uint64_t bits, int first, int L)
+{
+    const uint64_t zeros = ~(bits >> first);
+    return min(zeros ? __builtin_ctzll(zeros) : 64, L);
+}
+__device__ __forceinline__ int accepted_run(const unsigned long long *bits, int first, int L)
+{
+    int len = 0;
+    for (int run = 64; run > 0 && len < L; len += run) {
+        const int pos = first + len, left = min(64 - (pos & 63), L - len);
+        run = accepted_run(bits[pos >> 6], pos & 63, left);
+        if (run < left) return len + run;
+    }
+    return len;
+}
 
 }  // namespace rd
 
