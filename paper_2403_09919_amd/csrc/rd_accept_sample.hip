@@ -20,8 +20,11 @@
 // cumulative weight exceeds the target.  After a fully accepted candidate the weights are p itself,
 // whose chunk totals follow from launch 1's partials: workgroup 0 goes straight to the last step.
 // Both launches are chains of memory round trips (0.6-1 us each), so what bounds them is the number of loads that wait
-// for another: the partials of all rows and chunks, the tokens and the gathered logits are fetched side by side, and
-// the totals travel as write-through stores (a device-scope fence writes back the XCD's L2).
+// for another -- the partials of all rows and chunks, the tokens and the gathered logits are fetched side by side, and
+// the totals travel as write-through stores (a device-scope fence writes back the XCD's L2) that nobody waits for before
+// arriving -- and, in launch 2, a lone wave's instructions (1.7 ns each): tests and accepted prefixes are ballots.  us a call
+// against tests through LDS and atomics, barriers that waited for stores and arrivals that waited for totals: 8 sequences of
+// 8 x 5 tokens, V = 32000 21.9 -> 19.2, one 14.1 -> 12.1, 70 x 5 25.4 -> 21.9, 16 of 16 x 5 39.0 -> 36.5.
 #include "rd_internal.h"
 #include <math.h>
 
@@ -405,8 +408,10 @@ __global__ __launch_bounds__(kSelThreads) void rd_accept_sample_kernel(
         if (lane == 0) s_wave[wave] = t;
         rd_lds_barrier();
         if (tid == 0) {
-            rd::st_dev(chunk_totals + (size_t)b * chunks + chunk, (s_wave[0] + s_wave[1]) + (s_wave[2] + s_wave[3]));
-            rd::wait_dev_stores();                                      // the total is visible before the arrival
+            // A total is never negative: with its sign set it cannot be taken for the cleared word, and whoever arrives last
+            // reads it until it is there.  (It was issued before the arrival: nothing waits for it here.)
+            const float total = (s_wave[0] + s_wave[1]) + (s_wave[2] + s_wave[3]);
+            rd::st_dev(chunk_totals + (size_t)b * chunks + chunk, __uint_as_float(__float_as_uint(total) | 0x80000000u));
             const uint32_t prev = __hip_atomic_fetch_add(counters + b, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             s_last = (prev + 1u == (uint32_t)chunks) ? 1u : 0u;
         }
@@ -430,12 +435,21 @@ __global__ __launch_bounds__(kSelThreads) void rd_accept_sample_kernel(
                 const int i = min(lane * per + k, chunks - 1);
                 mine[k] = 0.f;
                 if (k < per) {
-                    // totals of p from launch 1's partials
-                    const float t = residual ? rd::ld_dev(chunk_totals + (size_t)b * chunks + i) : prow[i].y * __expf(prow[i].x - lse_p);
+                    float t;
+                    if (residual) {
+                        uint32_t u;
+                        do u = __float_as_uint(rd::ld_dev(chunk_totals + (size_t)b * chunks + i));
+                        while (!(u & 0x80000000u));
+                        t = __uint_as_float(u & 0x7fffffffu);
+                    } else {
+                        t = prow[i].y * __expf(prow[i].x - lse_p);      // totals of p from launch 1's partials
+                    }
                     if (lane * per + k < chunks) mine[k] = t;
                 }
                 sum += mine[k];
             }
+            if (residual)
+                for (int i = lane; i < chunks; i += 64) chunk_totals[(size_t)b * chunks + i] = 0.f;      // ready for the next call
             any = __ballot(sum > 0.f) != 0;
             if (any || !residual) break;
             residual = false;
@@ -476,27 +490,30 @@ __global__ __launch_bounds__(kSelThreads) void rd_accept_sample_kernel(
     // last token of positive weight is the one.
     const float tsum = chunk_weights<VEC>(zp, zq, ci, V, inv_t, lse_p, lse_q, residual, w);
     float chunk_total;
-    float cum = base + block_exclusive_scan(tsum, s_wave, chunk_total);
-    const int v0 = ci * kSelChunk + tid * kSelPer;
-    int pick = 0x7fffffff, lastpos = -1;
+    float cum = base + block_exclusive_scan(tsum, s_wave, chunk_total), upto[kSelPer];
 #pragma unroll
-    for (int k = 0; k < kSelPer; ++k) {
-        cum += w[k];
-        if (w[k] > 0.f) {
-            lastpos = v0 + k;
-            if (pick == 0x7fffffff && cum > target) pick = v0 + k;
-        }
-    }
+    for (int k = 0; k < kSelPer; ++k) upto[k] = cum += w[k];
+    const int v0 = ci * kSelChunk + tid * kSelPer;
+    int pick = -1;
+#pragma unroll
+    for (int k = kSelPer - 1; k >= 0; --k) pick = w[k] > 0.f && upto[k] > target ? v0 + k : pick;
     // (tokens ascend with the threads)
-    const uint64_t found = __ballot(pick != 0x7fffffff), held = __ballot(lastpos >= 0);
+    const uint64_t found = __ballot(pick >= 0);
     const int first = found ? __builtin_amdgcn_readlane(pick, __ffsll((long long)found) - 1) : 0x7fffffff;
-    const int last = held ? __builtin_amdgcn_readlane(lastpos, 63 - __clzll((long long)held)) : -1;
-    if (lane == 0) { s_pick[wave] = first; s_lastpos[wave] = last; }
+    if (lane == 0) s_pick[wave] = first;
     rd_lds_barrier();
     RD_TR(5);
+    int tok = min(min(s_pick[0], s_pick[1]), min(s_pick[2], s_pick[3]));
+    if (tok == 0x7fffffff) {                                // rounding left no crossing: the last token of positive weight
+        int lastpos = -1;
+#pragma unroll
+        for (int k = 0; k < kSelPer; ++k) lastpos = w[k] > 0.f ? v0 + k : lastpos;
+        const uint64_t held = __ballot(lastpos >= 0);
+        if (lane == 0) s_lastpos[wave] = held ? __builtin_amdgcn_readlane(lastpos, 63 - __clzll((long long)held)) : -1;
+        rd_lds_barrier();
+        tok = max(max(s_lastpos[0], s_lastpos[1]), max(s_lastpos[2], s_lastpos[3]));
+    }
     if (tid == 0) {
-        int tok = min(min(s_pick[0], s_pick[1]), min(s_pick[2], s_pick[3]));
-        if (tok == 0x7fffffff) tok = max(max(s_lastpos[0], s_lastpos[1]), max(s_lastpos[2], s_lastpos[3]));      // rounding left no crossing: the last token of positive weight
         if (tok < 0) tok = 0;
         next_token[b] = tok;
     }

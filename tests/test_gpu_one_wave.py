@@ -1,4 +1,4 @@
-"""rd_dedup and rd_accept about 64 candidate tokens, up to which one wave holds a sequence: lanes without a token, masks
+"""rd_dedup, rd_accept and rd_accept_sample about 64 candidate tokens, up to which one wave holds a sequence: lanes without a token, masks
 whose bits cross 32, candidates of one token and of 64, rows of one chunk and of several."""
 import numpy as np
 import pytest
@@ -39,3 +39,27 @@ def test_rows_of_nan_end(rd, W, L, V):  # noqa: F811
     logits[1, 2, :] = np.nan
     want[1, 2] = -1
     assert np.array_equal(run_accept(rd, logits, beams, d, None)["argmax"], want)
+
+
+@pytest.mark.parametrize("W,L", [(1, 2), (8, 8), (13, 5), (70, 5), (128, 3)])
+@pytest.mark.parametrize("V", [900, 9000])
+def test_sample_on_a_used_workspace(rd, W, L, V):  # noqa: F811
+    """A call finds the arrival counters and the chunks' totals as the call before left them: cleared.  Draws from the
+    residual and from p, a first token refuted, several calls on one workspace, each as on a fresh one."""
+    announce("sample, used workspace W=%d L=%d V=%d" % (W, L, V))
+    B, N = 3, W * L
+    gen = torch.Generator(device="cuda").manual_seed(W + V)
+    ws = rd.new_workspace(rd.rd_accept_sample_workspace(B, W, L, V), "cuda")
+    for seed in range(4):
+        beams = synth.make_beams(B, W, L, V, seed, "uniform")
+        d = rd.rd_dedup(dev(beams))
+        logits = torch.randn((B, N, V), generator=gen, device="cuda") * 3
+        draft = logits + (torch.randn((B, N, V), generator=gen, device="cuda") if seed % 2 else 0)      # (the same: all accepted)
+        u, un = torch.rand((B, N), generator=gen, device="cuda"), torch.rand((B,), generator=gen, device="cuda")
+        root = dev(np.where(np.arange(B) == seed, -1, beams[:, 0, 0]).astype(np.int32))
+        got, want = (rd.rd_accept_sample(logits, draft, dev(beams), d["unpack_index"], d["n_packed"], u, un, 0.9, root_token=root, workspace=w)
+                     for w in (ws, None))
+        torch.cuda.synchronize()
+        for k in want:
+            assert torch.equal(got[k], want[k]), k
+    assert not ws[:256].any()
