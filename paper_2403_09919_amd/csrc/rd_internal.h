@@ -132,8 +132,8 @@ __device__ __forceinline__ void dma4(uintptr_t base, uint32_t off, uint32_t lds)
 }
 // Returns when at most N of the wave's vector memory operations are outstanding.
 template <int N> __device__ __forceinline__ void wait_vm() { asm volatile("s_waitcnt vmcnt(%0)" : : "n"(N) : "memory"); }
-// Returns when the wave's LDS reads are in registers.
-__device__ __forceinline__ void wait_lds() { asm volatile("s_waitcnt lgkmcnt(0)" : : : "memory"); }
+// Returns when the wave's LDS reads but the last N are in registers (they return in order; scalar loads in flight only make the wait longer).
+template <int N = 0> __device__ __forceinline__ void wait_lds() { asm volatile("s_waitcnt lgkmcnt(%0)" : : "n"(N) : "memory"); }
 
 // ---- rows of any length in 16-byte loads --------------------------------------------------------------
 // Rows of V floats start at multiples of 4 bytes only, unless V is a multiple of 4; global memory instructions of any

@@ -17,7 +17,10 @@
 // C=1024, 2.3 of arithmetic, the store of a partial result and its arrival 1.4, the merge 2.3), in which a branch per tile, a
 // half-written line and a load that only fills a chunk all count: the sum over the tiles without branches, partial results
 // stored 16 bytes at a time and merged by chunks of 4, 6 or 8 take H=32, C=1024 from 11.6 to 11.0 us, with rotation from 12.5 to
-// 12.0, H=32, C=1777, 209 rows of 350 from 26.2 to 24.8.  Against the kernel it
+// 12.0, H=32, C=1777, 209 rows of 350 from 26.2 to 24.8.  Several row groups: the copies, of which a compute unit has some 48 KB
+// under way at most, 21 bytes a clock from beyond L2, and every group of a range waits for the same ones (taking the tiles in
+// another order in each group, so that most are in L2, is slower: 23.2 us against 21.4).  A wave's own chain of a tile, beside that:
+// Q's operands read ahead and V's before the exponents shorten it (scores 1280 -> 500 clocks of 3380), H=32, C=1024 by 1 %.  Against the kernel it
 // replaced, whose waves shared every block of tiles at two barriers and fetched K and V through registers, us per launch, K
 // and V from memory: H=32, C=1024 12.1 -> 10.8; B=4, H=32, C=1024 23.9 -> 19.6; H=32, C=1777, 61 rows 22.3 -> 16.7 and 147
 // rows 30.0 -> 22.0; B=10, H=52, C=63-92, 207 tokens 49.4 -> 33.2; B=4, H=40, C=4096 74.5 -> 66.5; B=16, H=52, C=2048 183.5 ->
@@ -472,7 +475,19 @@ __global__ __launch_bounds__(NW * 64, 2) void rd_tree_attn_mfma_kernel(AttnArgs 
                 for (int t = 0; t < KS; ++t) kreg[mt][t] = op(myK, mt, t);
 #pragma unroll
             for (int qt = 0; qt < NQA; ++qt) vis[qt] = *reinterpret_cast<const uint32_t *>(sMask + wave * 256 + (qt * 16 + r16) * 4);
-            wait_lds();
+            // Q's operands are read kAhead k-steps before they are multiplied: read when needed, a lone wave waits for LDS at each
+            // of them.  LDS answers in order: with theirs outstanding K's reads are done.
+            constexpr int kAhead = ROPE && NQA == 3 ? 1 : 2;      // (with the angles the registers for two are not there)
+            vec8 bq[KS][NQA];
+            auto read_q = [&](int t) __attribute__((always_inline)) {
+#pragma unroll
+                for (int qt = 0; qt < NQA; ++qt) bq[t][qt] = op(sQ, qt, t);
+            };
+            asm volatile("" : : : "memory");
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int t = 0; t < kAhead; ++t) read_q(t);
+            wait_lds<kAhead * NQA>();
             prefetch();
             if constexpr (ROPE) {
                 if (tree) {
@@ -494,13 +509,15 @@ __global__ __launch_bounds__(NW * 64, 2) void rd_tree_attn_mfma_kernel(AttnArgs 
 #pragma unroll
             for (int qt = 0; qt < NQA; ++qt) sacc[0][qt] = sacc[1][qt] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-            for (int t = 0; t < KS; ++t)
+            for (int t = 0; t < KS; ++t) {
+                if (t + kAhead < KS) read_q(t + kAhead);
+                __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
                 for (int qt = 0; qt < NQA; ++qt) {
-                    const vec8 bq = op(sQ, qt, t);
-                    sacc[0][qt] = Elem<T>::mfma(kreg[0][t], bq, sacc[0][qt]);
-                    sacc[1][qt] = Elem<T>::mfma(kreg[1][t], bq, sacc[1][qt]);
+                    sacc[0][qt] = Elem<T>::mfma(kreg[0][t], bq[t][qt], sacc[0][qt]);
+                    sacc[1][qt] = Elem<T>::mfma(kreg[1][t], bq[t][qt], sacc[1][qt]);
                 }
+            }
 
             // softmax in log2 units.  An interior context tile keeps the raw scores (the scale is folded into
             // the exponent); a tile with masked or missing keys is scaled here and its dead entries set to -inf.
@@ -663,6 +680,11 @@ __global__ __launch_bounds__(NW * 64, 2) void rd_tree_attn_mfma_kernel(AttnArgs 
                 }
                 page = page_of(next + NW);
             });
+            if (more) wait_vm<kLoads + 1>();  // V of this tile (the next K and mask are younger)
+            else wait_vm<0>();
+            vec8 vreg[DT];                    // read while the exponents are taken
+#pragma unroll
+            for (int dt = 0; dt < DT; ++dt) vreg[dt] = v_frag(wave, dt);
             // Reference of the exponents: the running one, or this tile's maximum in rows where it lies more than
             // 2^kSlack above that.  Rows seldom move once the first tile is in, and while none does the products add
             // up without a factor.
@@ -691,11 +713,6 @@ __global__ __launch_bounds__(NW * 64, 2) void rd_tree_attn_mfma_kernel(AttnArgs 
                 pb[qt] = weights(sacc, qt, c_fold, m_ref[qt] == -INFINITY ? 0.f : m_ref[qt]);
                 l_own[qt] = Elem<T>::mfma(ones, pb[qt], l_own[qt]);
             }
-            if (more) wait_vm<kLoads + 1>();  // V of this tile (the next K and mask are younger)
-            else wait_vm<0>();
-            vec8 vreg[DT];
-#pragma unroll
-            for (int dt = 0; dt < DT; ++dt) vreg[dt] = v_frag(wave, dt);
             wait_lds();
             if (more) copy_v((next >= nA ? Vn : Vc) + off_next, keys_next);
 #pragma unroll
