@@ -1,6 +1,7 @@
 """The 16-bit attention kernel where its tiles, row groups and key ranges end, against the oracle: contexts around multiples
 of a tile (32 keys) and of a workgroup's tiles (4 or 8 of them), rows around row tiles (16) and row groups (48), one tile per
-wave and several, and rotary tables that do not start at a multiple of 16 bytes."""
+wave and several, and rotary tables that do not start at a multiple of 16 bytes; the fp32 kernel where its ranges
+grow past two tiles per wave."""
 import numpy as np
 import pytest
 import torch
@@ -151,3 +152,21 @@ def test_waves_without_a_tile_and_numbers_of_partials(rd, dtype, D, W, L, C):
     torch.cuda.synchronize()
     got, want = synth.to_f64(host(out), dtype), synth.to_f64(ref, dtype)
     assert np.isfinite(got).all() and np.abs(got - want).max() <= TOL[dtype]
+
+
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("W,L", [(1, 2), (4, 4), (8, 5), (20, 4)])
+@pytest.mark.parametrize("ctx", [(0, 1), (15, 17), (111, 113), (127, 128), (225, 256), (370, 20), (604, 3), (1700, 900)])
+def test_fp32_ranges_of_one_two_and_more_tiles_per_wave(rd, D, W, L, ctx):
+    """Tiles of 16 keys, eight waves: ranges of at most two tiles per wave have a kernel of their own.  Bound: the fp32 target."""
+    announce(f"fp32 edges D={D} W={W} L={L} ctx={ctx}")
+    ctx, beams, q, kn, vn, kc, vc, d = _case(2, 3, W, L, ctx, D, "f32", W + L)
+    scale = float(1.0 / np.sqrt(D))
+    ref = oracle.tree_attn(q, kc, vc, ctx, kn, vn, d["n_packed"], d["tree_mask"], "f32", scale)
+    dd = rd.rd_dedup(dev(beams), dev(ctx))
+    out = rd.rd_tree_attn(dev(q), dev(kc), dev(vc), dev(ctx), dev(kn), dev(vn), dd["n_packed"], dd["tree_mask_bits"], scale)
+    torch.cuda.synchronize()
+    got = host(out)
+    assert np.isfinite(got).all() and np.abs(got - ref).max() <= 1e-5 * np.abs(ref).max()
+    for b in range(2):
+        assert not got[b, :, int(d["n_packed"][b]):].any()
