@@ -22,9 +22,15 @@ __global__ __launch_bounds__(kCommitThreads) void rd_commit_kernel(
     const int32_t *__restrict__ block_table /* NULL: dense cache */, int page_size, int max_pages, int n_pages)
 {
     const int b = blockIdx.y, h = blockIdx.x, tid = threadIdx.x;
+    // All arguments in one round trip, then the slot, the accepted length and the context in another: as the compiler places the
+    // loads each waits for the one before, six in a row.
+    asm volatile("" : : "s"(k_new), "s"(v_new), "s"(accepted_idx), "s"(best_len), "s"(ctx_len), "s"(H), "s"(N), "s"(Cmax), "s"(L), "s"(row_shift),
+                 "s"(k_cache), "s"(v_cache), "s"(ctx_len_out), "s"(n_committed), "s"(block_table), "s"(page_size), "s"(max_pages), "s"(n_pages));
     const int my_slot = accepted_idx[(size_t)b * L + min(tid >> row_shift, L - 1)];
-    const int bl = clamp_i(best_len[b], 0, L);
-    const int c = clamp_i(ctx_len[b], 0, Cmax);
+    const int best = best_len[b], ctx = ctx_len[b];
+    asm volatile("" : : "v"(my_slot), "s"(best), "s"(ctx));
+    const int bl = clamp_i(best, 0, L);
+    const int c = clamp_i(ctx, 0, Cmax);
     const int n = min(bl, Cmax - c);
     if (h == H) {
         if (tid == 0) {
