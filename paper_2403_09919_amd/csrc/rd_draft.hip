@@ -83,8 +83,22 @@ __device__ __forceinline__ float silu(float x) { return x / (1.0f + __expf(-x));
 // One output tile (16 rows x 16 columns) leaves the kernel: bias, activation, skip connection and the
 // bf16 copy that the next layer reads.  Accumulator layout: element i of lane (r16, g) is output
 // column n_tile + 4g + i of logical row m_tile + r16.
+struct EpilogueIn { f32x4 bias, res; };
 template <typename T, int EPI>
-__device__ __forceinline__ void linear_epilogue(const LinArgs<T> &a, f32x4 v, int m_tile, int n_tile, int r16, int g)
+__device__ __forceinline__ EpilogueIn linear_epilogue_in(const LinArgs<T> &a, int m_tile, int n_tile, int r16, int g)
+{
+    EpilogueIn in = {f32x4{0.f, 0.f, 0.f, 0.f}, f32x4{0.f, 0.f, 0.f, 0.f}};
+    if (EPI == EPI_HEAD) return in;
+    const int n0 = min(n_tile + 4 * g, a.N - 4);                // (N is a multiple of 64 here)
+    if (a.bias) {
+        const rd::f4_any bias = *reinterpret_cast<const rd::f4_any *>(a.bias + n0);
+        in.bias = f32x4{bias[0], bias[1], bias[2], bias[3]};
+    }
+    if (EPI == EPI_MLP) in.res = *reinterpret_cast<const f32x4 *>(a.res + (size_t)(a.m0 + min(m_tile + r16, a.M - 1)) * a.mstride * a.ldy + n0);
+    return in;
+}
+template <typename T, int EPI>
+__device__ __forceinline__ void linear_epilogue(const LinArgs<T> &a, f32x4 v, int m_tile, int n_tile, int r16, int g, const EpilogueIn &in)
 {
     const int m = m_tile + r16;
     if (m >= a.M) return;
@@ -104,21 +118,23 @@ __device__ __forceinline__ void linear_epilogue(const LinArgs<T> &a, f32x4 v, in
     if (n0 >= a.N) return;                                      // (N is a multiple of 64 here)
     typedef __attribute__((ext_vector_type(4))) T vec4;
     const size_t o = prow * a.ldy + n0;
-    rd::f4_any bias = {0.f, 0.f, 0.f, 0.f};
-    if (a.bias) bias = *reinterpret_cast<const rd::f4_any *>(a.bias + n0);
-    const f32x4 res = EPI == EPI_MLP ? *reinterpret_cast<const f32x4 *>(a.res + o) : f32x4{0.f, 0.f, 0.f, 0.f};
     f32x4 y;
     vec4 yb;
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-        float t = silu(v[i] + bias[i]);
-        if (EPI == EPI_MLP) t += res[i];
+        float t = silu(v[i] + in.bias[i]);
+        if (EPI == EPI_MLP) t += in.res[i];
         y[i] = t;
         yb[i] = (T)t;
     }
     *reinterpret_cast<f32x4 *>(a.y_f32 + o) = y;
     *reinterpret_cast<vec4 *>(a.y_bf + o) = yb;
     if (EPI == EPI_RNN) *reinterpret_cast<vec4 *>(a.s_bf + prow * a.N + n0) = yb;
+}
+template <typename T, int EPI>
+__device__ __forceinline__ void linear_epilogue(const LinArgs<T> &a, f32x4 v, int m_tile, int n_tile, int r16, int g)
+{
+    if (m_tile + r16 < a.M) linear_epilogue<T, EPI>(a, v, m_tile, n_tile, r16, g, linear_epilogue_in<T, EPI>(a, m_tile, n_tile, r16, g));
 }
 
 // A workgroup owns NT*16 output columns for all M = MT*16 rows; its NWV waves split K.  The host
@@ -528,14 +544,18 @@ __global__ __launch_bounds__(WR * WC * 64, 1) void rd_gemm_kernel(LinArgs<T> a)
             if ((wr * MT + mt) * 16 < a.M) *reinterpret_cast<f32x4 *>(out + ((wr * MT + mt) * CT + wc * NT + nt) * 256) = acc[mt][nt];
 }
 
-// Adds the partial tiles of rd_gemm_kernel in split order and finishes the layer, a wave per tile.
+// Adds the partial tiles of rd_gemm_kernel in split order and finishes the layer, a wave per tile.  Short layers are bound by
+// their round trips: the arguments are fetched together, skip input and bias beside the partial sums.
 template <typename T, int RT, int CT, int EPI>
 __global__ __launch_bounds__(256) void rd_linear_finish_kernel(LinArgs<T> a)
 {
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    asm volatile("" : : "s"(a.kpart), "s"(a.ksplit), "s"(a.M), "s"(a.N), "s"(a.m0), "s"(a.mstride), "s"(a.bias), "s"(a.res), "s"(a.ldy),
+                 "s"(a.y_f32), "s"(a.y_bf), "s"(a.s_bf));
     const int nts = (a.N + 15) / 16, id = blockIdx.x * 4 + wave;
     const int mt = id / nts, n_tile = id - mt * nts;
     if (mt * 16 >= a.M) return;
+    const EpilogueIn in = linear_epilogue_in<T, EPI>(a, mt * 16, n_tile * 16, lane & 15, lane >> 4);
     const float *src = a.kpart + (((size_t)(n_tile / CT) * a.ksplit * RT + mt) * CT + n_tile % CT) * 256 + lane * 4;
     f32x4 v = {0.f, 0.f, 0.f, 0.f};
     for (int s0 = 0; s0 < a.ksplit; s0 += 8) {
@@ -546,7 +566,7 @@ __global__ __launch_bounds__(256) void rd_linear_finish_kernel(LinArgs<T> a)
         for (int i = 0; i < 8; ++i)
             if (s0 + i < a.ksplit) v += p[i];
     }
-    linear_epilogue<T, EPI>(a, v, mt * 16, n_tile * 16, lane & 15, lane >> 4);
+    linear_epilogue<T, EPI>(a, v, mt * 16, n_tile * 16, lane & 15, lane >> 4, in);
 }
 
 // rows m = b*W + w: X0 = [e(last token), h] (fp32 and bf16), state = e(last token), path = [last token].  The first position
