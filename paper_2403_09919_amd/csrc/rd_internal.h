@@ -93,12 +93,14 @@ __device__ __forceinline__ float2 ld_dev2(const float *p)
 }
 
 // 16 bytes, written through like the others: one store of whole lines, where two of 8 bytes each leave every second piece of
-// a line to the other.  Nothing may rely on the 16 bytes arriving together.  The compiler does not know this store: the
-// empty slot behind it is what the data registers need before they are written again.
+// a line to the other.  Nothing may rely on the 16 bytes arriving together.  A store that the compiler knows, not assembly:
+// gfx950 needs two wait states between a store of more than 8 bytes and a vector write to its data registers, and up to eight
+// in front of one whose data a matrix instruction wrote, and only the compiler sees what stands around it.
 __device__ __forceinline__ void st_dev4(float *p, float a, float b, float c, float d)
 {
-    typedef float f4 __attribute__((ext_vector_type(4)));
-    asm volatile("global_store_dwordx4 %0, %1, off sc1\n\ts_nop 0" : : "v"(p), "v"(f4{a, b, c, d}) : "memory");
+    typedef uint32_t u4 __attribute__((ext_vector_type(4)));
+    const u4 v = {__float_as_uint(a), __float_as_uint(b), __float_as_uint(c), __float_as_uint(d)};
+    __builtin_amdgcn_global_store_b128((u4 __attribute__((address_space(1))) *)p, v, "agent");
 }
 // Returns once every vector memory operation this wave has issued -- loads, stores and atomics without
 // a return value alike, they share one counter -- has been acknowledged.  A device-scope store or atomic
