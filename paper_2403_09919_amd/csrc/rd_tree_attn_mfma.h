@@ -151,7 +151,8 @@ __global__ __launch_bounds__(NW * 64, 2) void rd_tree_attn_mfma_kernel(AttnArgs 
     typedef const __attribute__((address_space(4))) int32_t cint32;
     cint32 *ctx_len = (cint32 *)(uintptr_t)a.ctx_len, *packed = (cint32 *)(uintptr_t)a.n_packed;
     const int xcd = (int)(blockIdx.x & 7), n_rg = a.n_rg;
-    int bh, b, r_wg, n_act = 1, ranges = attn_ranges(a.ranges, 1);      // n_act row groups times ranges: the head's workgroups
+    // (ALL has one range, so that its instances hold no merge and its registers: B=1024, H=4, 16 x 5 tokens, C=60 78.5 -> 75.9 us)
+    int bh, b, r_wg, n_act = 1, ranges = ALL ? 1 : attn_ranges(a.ranges, 1);      // n_act row groups times ranges: the head's workgroups
     auto groups_of = [&](int rows) __attribute__((always_inline)) { return max((clampi(rows, 0, a.N) + kRows - 1) / kRows, 1); };
     auto heads_before = [&](int s) __attribute__((always_inline)) { return (s * a.H + 7 - xcd) >> 3; };         // this XCD's, of sequences before s
     auto wgs_of = [&](int s, int act) __attribute__((always_inline)) { return (heads_before(s + 1) - heads_before(s)) * act * ranges; };
@@ -477,7 +478,10 @@ __global__ __launch_bounds__(NW * 64, 2) void rd_tree_attn_mfma_kernel(AttnArgs 
             for (int qt = 0; qt < NQA; ++qt) vis[qt] = *reinterpret_cast<const uint32_t *>(sMask + wave * 256 + (qt * 16 + r16) * 4);
             // Q's operands are read kAhead k-steps before they are multiplied: read when needed, a lone wave waits for LDS at each
             // of them.  LDS answers in order: with theirs outstanding K's reads are done.
-            constexpr int kAhead = ROPE && NQA == 3 ? 1 : 2;      // (with the angles the registers for two are not there)
+            // (With three row tiles and the angles the registers for two are not there, and at D = 64 four waves of more than 168
+            // leave two workgroups to a compute unit instead of three: us when needed / one ahead, H=32, B=16, 70 x 5 tokens, C=300
+            // 44.8 / 53.2, B=64, 16 x 5, C=200 39.3 / 44.9.  Eight waves are alone on it either way: H=32, C=2000 10.3 / 9.9.)
+            constexpr int kAhead = ROPE && NQA == 3 ? (D == 64 && NW == 4 ? 0 : 1) : 2;
             vec8 bq[KS][NQA];
             auto read_q = [&](int t) __attribute__((always_inline)) {
 #pragma unroll
