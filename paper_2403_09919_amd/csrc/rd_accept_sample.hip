@@ -6,7 +6,8 @@
 // (maximum, sum of exp(x - maximum)) each and stores the two pairs in the workspace.  Every wave finds by itself which
 // draft row belongs to the slot, the 16-byte loads of a row are in flight together, and the waves meet
 // once.  Rows of slots at the last position carry no draft distribution and their draft half is skipped.  No
-// atomics, no counters: the partials are combined in a fixed order by launch 2, so results do not depend on timing.
+// atomics, no counters: the partials are combined in a fixed order by launch 2, so results do not depend on timing.  It also
+// clears the words in which launch 2 hands over its chunks' totals.
 // Launch 2 (grid: chunks of 4096 vocabulary entries x sequences, 256 threads).  Every workgroup of a
 // sequence repeats the small part: log-sum-exps of the rows from the partials; one thread per
 // candidate token gathers the two logits of its token under its parent slot and decides
@@ -91,7 +92,8 @@ template <bool VEC>
 __global__ __launch_bounds__(kLseThreads) void rd_lse_chunk_kernel(
     const float *__restrict__ logits, const float *__restrict__ draft_logits, const int32_t *__restrict__ step_row,
     int rows_per_step, const int32_t *__restrict__ unpack_index,
-    const int32_t *__restrict__ n_packed, int W, int L, int V, int chunks, float inv_t, float4 *__restrict__ part)
+    const int32_t *__restrict__ n_packed, int W, int L, int V, int chunks, float inv_t, float4 *__restrict__ part,
+    float *__restrict__ chunk_totals /*[B][chunks]*/)
 {
     constexpr int kWaves = kLseThreads / 64;
     __shared__ float4 s_red[kWaves];
@@ -155,6 +157,7 @@ __global__ __launch_bounds__(kLseThreads) void rd_lse_chunk_kernel(
             c = merge_max_sum(c, make_float2(s_red[w].z, s_red[w].w));
         }
         part[rowid * chunks + chunk] = make_float4(a.x, a.y, c.x, c.y);
+        if (p == 0) chunk_totals[(size_t)b * chunks + chunk] = 0.f;      // launch 2 waits until it is not
     }
 }
 
@@ -408,8 +411,8 @@ __global__ __launch_bounds__(kSelThreads) void rd_accept_sample_kernel(
         if (lane == 0) s_wave[wave] = t;
         rd_lds_barrier();
         if (tid == 0) {
-            // A total is never negative: with its sign set it cannot be taken for the cleared word, and whoever arrives last
-            // reads it until it is there.  (It was issued before the arrival: nothing waits for it here.)
+            // A total is never negative: with its sign set it cannot be taken for the word that launch 1 cleared, and whoever
+            // arrives last reads it until it is there.  (It was issued before the arrival: nothing waits for it here.)
             const float total = (s_wave[0] + s_wave[1]) + (s_wave[2] + s_wave[3]);
             rd::st_dev(chunk_totals + (size_t)b * chunks + chunk, __uint_as_float(__float_as_uint(total) | 0x80000000u));
             const uint32_t prev = __hip_atomic_fetch_add(counters + b, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -448,8 +451,6 @@ __global__ __launch_bounds__(kSelThreads) void rd_accept_sample_kernel(
                 }
                 sum += mine[k];
             }
-            if (residual)
-                for (int i = lane; i < chunks; i += 64) chunk_totals[(size_t)b * chunks + i] = 0.f;      // ready for the next call
             any = __ballot(sum > 0.f) != 0;
             if (any || !residual) break;
             residual = false;
@@ -572,7 +573,7 @@ extern "C" int rd_accept_sample(const float *logits, const float *draft_logits, 
     const bool vec = V >= 4;
     hipLaunchKernelGGL(vec ? rd_lse_chunk_kernel<true> : rd_lse_chunk_kernel<false>, dim3(plan.chunks, N, B),
                        dim3(kLseThreads), 0, s, logits, draft_logits, draft_step_row, draft_rows_per_step, unpack_index, n_packed, W, L, V,
-                       plan.chunks, inv_t, part);
+                       plan.chunks, inv_t, part, chunk_totals);
     if (rd_check_launch() != RD_OK) return RD_ERR_HIP;
     hipLaunchKernelGGL(vec ? rd_accept_sample_kernel<true> : rd_accept_sample_kernel<false>, dim3(plan.chunks, B),
                        dim3(kSelThreads), 0, s, logits, draft_logits, draft_step_row, draft_rows_per_step, beams, unpack_index, n_packed,

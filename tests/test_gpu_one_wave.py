@@ -44,22 +44,29 @@ def test_rows_of_nan_end(rd, W, L, V):  # noqa: F811
 @pytest.mark.parametrize("W,L", [(1, 2), (8, 8), (13, 5), (70, 5), (128, 3)])
 @pytest.mark.parametrize("V", [900, 9000])
 def test_sample_on_a_used_workspace(rd, W, L, V):  # noqa: F811
-    """A call finds the arrival counters and the chunks' totals as the call before left them: cleared.  Draws from the
-    residual and from p, a first token refuted, several calls on one workspace, each as on a fresh one."""
+    """A call finds the arrival counters as the call before left them, cleared, and needs nothing of what else is in the workspace:
+    here every other bit is set before a call.  Draws from the residual and from p, a first token refuted, several calls on one
+    workspace, each as on a fresh one; after a call that draws from p alone the chunks' totals are as launch 1 cleared them."""
     announce("sample, used workspace W=%d L=%d V=%d" % (W, L, V))
     B, N = 3, W * L
     gen = torch.Generator(device="cuda").manual_seed(W + V)
     ws = rd.new_workspace(rd.rd_accept_sample_workspace(B, W, L, V), "cuda")
+    totals = ws[256:256 + 4 * B * ((V + 4095) // 4096)]            # behind the counters
     for seed in range(4):
+        ws[256:] = 255
         beams = synth.make_beams(B, W, L, V, seed, "uniform")
         d = rd.rd_dedup(dev(beams))
         logits = torch.randn((B, N, V), generator=gen, device="cuda") * 3
-        draft = logits + (torch.randn((B, N, V), generator=gen, device="cuda") if seed % 2 else 0)      # (the same: all accepted)
-        u, un = torch.rand((B, N), generator=gen, device="cuda"), torch.rand((B,), generator=gen, device="cuda")
-        root = dev(np.where(np.arange(B) == seed, -1, beams[:, 0, 0]).astype(np.int32))
+        draft = logits * (1 / 0.9) + (torch.randn((B, N, V), generator=gen, device="cuda") if seed % 2 else 0)      # (the same: all accepted)
+        u, un = torch.rand((B, N), generator=gen, device="cuda") * 0.999, torch.rand((B,), generator=gen, device="cuda")
+        root = dev(np.where(np.arange(B) == seed - 1, -1, beams[:, 0, 0]).astype(np.int32))
         got, want = (rd.rd_accept_sample(logits, draft, dev(beams), d["unpack_index"], d["n_packed"], u, un, 0.9, root_token=root, workspace=w)
                      for w in (ws, None))
         torch.cuda.synchronize()
         for k in want:
             assert torch.equal(got[k], want[k]), k
-    assert not ws[:256].any()
+        assert not ws[:4 * B].any()
+        if seed == 0:
+            assert (got["best_len"] == L).all() and not totals.any()
+        if seed == 3 and L > 2:
+            assert (got["best_len"] < L).any()                     # (the residual is drawn from)
