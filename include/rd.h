@@ -220,8 +220,9 @@ int rd_tree_attn_paged(const void *q, const void *k_pages, const void *v_pages,
  * accepted_idx [B,L].  logits must be 16-byte aligned.
  *
  * workspace: as for rd_tree_attn (at least rd_accept_workspace(...) bytes, 256-byte
- * aligned, all zero before first use, counters left zero by every call, tied to the
- * shape arguments).
+ * aligned, all zero before first use, tied to the shape arguments; it holds counters and
+ * row keys, and every call leaves all of it zero).  Calls that share a workspace must not
+ * overlap: their results would be wrong (the kernels still end).
  */
 size_t rd_accept_workspace(int B, int W, int L, int V);
 
@@ -244,9 +245,9 @@ int rd_accept(const float *logits, const int32_t *beams, const int32_t *unpack_i
  *
  * Sizes with rd_accept_workspace(B, W, L, V) > RD_ACCEPT_STATIC_BYTES (about B*W*L > 87000 packed rows)
  * are rejected with RD_ERR_SCRATCH_LIMIT before anything is launched; the other argument errors are
- * rd_accept's.  All calls on one GPU share that GPU's array: calls that may overlap on one GPU (two
- * streams, two threads) race and must be serialised by the caller, or use rd_accept with separate
- * workspaces.
+ * rd_accept's.  All calls on one GPU share that GPU's array, so calls on one GPU must not overlap (two
+ * streams, two threads): their results would be wrong, as for a shared workspace.  The caller
+ * serialises them or uses rd_accept with separate workspaces.
  */
 #define RD_ACCEPT_STATIC_BYTES (1 << 20)
 
@@ -289,7 +290,8 @@ int rd_accept_static(const float *logits, const int32_t *beams, const int32_t *u
  * u_accept : float [B,N] in [0,1);  u_next : float [B] in [0,1);  temperature > 0.
  * beams, unpack_index, n_packed, root_token and the int32 outputs as for rd_accept (no argmax_out).
  * workspace: as for rd_accept (at least rd_accept_sample_workspace(...) bytes, 256-byte aligned, all
- * zero before first use, counters left zero by every call, not shared by concurrent calls).
+ * zero before first use, counters left zero by every call and nothing else in it kept between calls,
+ * not shared by overlapping calls).
  * V <= 1048576.  Two launches on `stream`.
  */
 size_t rd_accept_sample_workspace(int B, int W, int L, int V);

@@ -218,9 +218,8 @@ __global__ __launch_bounds__(kAccThreads) __attribute__((amdgpu_waves_per_eu(1, 
     RD_TR(2);
     unsigned long long *seq_keys = row_keys + (size_t)b * N;
     auto row_argmax = [&](int r) __attribute__((always_inline)) {
-        unsigned long long key;
-        do key = __hip_atomic_load(seq_keys + r, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        while (key == 0);                                 // (its store is on its way: see arrive)
+        const unsigned long long key = rd::poll([&]() { return __hip_atomic_load(seq_keys + r, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); },
+                                                [](unsigned long long k) { return k != 0; });      // (its store is on its way: see arrive)
         return key_index(key);
     };
     static_assert(RD_MAX_W <= 128 && RD_MAX_N < (1 << 15), "candidates: two waves, index in 8 bits");

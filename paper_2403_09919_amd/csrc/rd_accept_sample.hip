@@ -412,7 +412,7 @@ __global__ __launch_bounds__(kSelThreads) void rd_accept_sample_kernel(
         rd_lds_barrier();
         if (tid == 0) {
             // A total is never negative: with its sign set it cannot be taken for the word that launch 1 cleared, and whoever
-            // arrives last reads it until it is there.  (It was issued before the arrival: nothing waits for it here.)
+            // arrives last reads it until it is there (rd::poll).  (It was issued before the arrival: nothing waits for it here.)
             const float total = (s_wave[0] + s_wave[1]) + (s_wave[2] + s_wave[3]);
             rd::st_dev(chunk_totals + (size_t)b * chunks + chunk, __uint_as_float(__float_as_uint(total) | 0x80000000u));
             const uint32_t prev = __hip_atomic_fetch_add(counters + b, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -440,9 +440,8 @@ __global__ __launch_bounds__(kSelThreads) void rd_accept_sample_kernel(
                 if (k < per) {
                     float t;
                     if (residual) {
-                        uint32_t u;
-                        do u = __float_as_uint(rd::ld_dev(chunk_totals + (size_t)b * chunks + i));
-                        while (!(u & 0x80000000u));
+                        const uint32_t u = rd::poll([&]() { return __float_as_uint(rd::ld_dev(chunk_totals + (size_t)b * chunks + i)); },
+                                                    [](uint32_t x) { return (x & 0x80000000u) != 0; });
                         t = __uint_as_float(u & 0x7fffffffu);
                     } else {
                         t = prow[i].y * __expf(prow[i].x - lse_p);      // totals of p from launch 1's partials

@@ -109,6 +109,18 @@ __device__ __forceinline__ void st_dev4(float *p, float a, float b, float c, flo
 // L2, which is what the exchange avoids.
 __device__ __forceinline__ void wait_dev_stores() { asm volatile("s_waitcnt vmcnt(0)" : : : "memory"); }
 
+// Where nobody waits for a store before the counter is bumped, whoever sees the full count reads the word, which is 0 until the
+// store arrives, until it is there.  The store has been issued by then and arrives within microseconds, so that the first read
+// nearly always finds it.  The wait has an end all the same (some 50 ms): calls that overlap on one workspace may clear
+// each other's words, and must end with wrong results, not hang.  Returns the last value read.
+constexpr int kPolls = 1 << 16;
+template <typename Read, typename There> __host__ __device__ __forceinline__ auto poll(Read read, There there)
+{
+    auto x = read();
+    for (int i = 1; i < kPolls && !there(x); ++i) x = read();
+    return x;
+}
+
 // ---- memory straight into LDS -------------------------------------------------------------------------
 // Copies 1 KB of memory into LDS, 16 bytes per lane, without passing through registers: lane l's bytes come from
 // base + off and land at lds + 16 l.  Complete when the wave's count of vector memory operations says so (wait_vm);
