@@ -1,11 +1,13 @@
 """rd_dedup, rd_accept and rd_accept_sample about 64 candidate tokens, up to which one wave holds a sequence: lanes without a token, masks
 whose bits cross 32, candidates of one token and of 64, rows of one chunk and of several."""
+import itertools
+
 import numpy as np
 import pytest
 import torch
 
 import oracle
-from gpu_util import announce, dev, host
+from gpu_util import announce, dev, host, mask_bits_u64
 from paper_2403_09919_amd import synth
 from test_gpu_dedup_accept import check_accept, check_dedup, rd, run_accept  # noqa: F401  (rd: the fixture)
 
@@ -25,6 +27,26 @@ def test_edges_of_a_wave(rd, W, L):  # noqa: F811
         logits = synth.make_logits(3, W * L, V, seed, d["packed_tokens"], d["parent"], d["n_packed"], 0.9)
         for root in (None, beams[:, W - 1, 0].copy(), np.array([-1, beams[1, 0, 0], -1], np.int32)):
             check_accept(rd, logits, beams, root)
+
+
+@pytest.mark.parametrize("W,L", SHAPES)
+def test_edges_of_a_wave_with_and_without_masks(rd, W, L):  # noqa: F811
+    """The dense mask, the bit mask and prefix_tree are optional: every combination writes the rest, and nothing else."""
+    announce("one wave, optional outputs W=%d L=%d" % (W, L))
+    beams, ctx = synth.make_beams(3, W, L, 7, W + L, "high"), np.array([0, 9, 4000], np.int32)
+    ref = oracle.dedup(beams, ctx)
+    shapes = {k: ref[k].shape for k in ("prefix_tree", "packed_tokens", "n_packed", "unpack_index", "parent", "position_ids")}
+    for dense, bits, prefix in itertools.product((False, True), repeat=3):
+        out = {k: torch.full(s, -7, dtype=torch.int32, device="cuda") for k, s in shapes.items()}
+        out["tree_mask"] = torch.full(ref["tree_mask"].shape, 9, dtype=torch.uint8, device="cuda") if dense else None
+        out["tree_mask_bits"] = torch.full(ref["tree_mask_bits"].shape, -7, dtype=torch.int64, device="cuda") if bits else None
+        if not prefix:
+            out["prefix_tree"] = None
+        rd.rd_dedup(dev(beams), dev(ctx), out=out)
+        torch.cuda.synchronize()
+        for k, v in out.items():
+            if v is not None:
+                assert np.array_equal(mask_bits_u64(v) if k == "tree_mask_bits" else host(v), ref[k]), (k, dense, bits, prefix)
 
 
 @pytest.mark.parametrize("W,L", [(4, 4), (16, 5)])
