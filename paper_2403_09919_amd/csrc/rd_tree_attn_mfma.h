@@ -885,7 +885,10 @@ __global__ __launch_bounds__(NW * 64, 2) void rd_tree_attn_mfma_kernel(AttnArgs 
                     if (row_tile(r, j) < NQ) put(row_tile(r, j), d_tile(j), acc[r < kRoundsA ? r : 0][j], r < kRoundsA ? pick(den, r < kRoundsA ? r : 0, j) : 1.f);
         };
         using std::integral_constant;
-        if (last != kLastClean) merge(std::false_type{}, integral_constant<int, 2>{});       // (not seen where workgroups are dealt to the XCDs in turn)
+        // Partials of several XCDs are not seen where workgroups are dealt to them in turn; their reads, 8 bytes each past the L2,
+        // take chunks of two (us by 2 / 4: H=32, C=1024, 8 x 5 tokens 12.1 / 13.3, C=2048, 16 x 5 22.5 / 23.4; H=8, C=6000, 3 x 5,
+        // many small partials, 14.3 / 13.6).
+        if (last != kLastClean) merge(std::false_type{}, integral_constant<int, 2>{});
         else if (n_part <= 4 || kRoundsA * kOwn * 8 > 24) merge(std::true_type{}, integral_constant<int, 4>{});
         else if (n_part <= 6) merge(std::true_type{}, integral_constant<int, 6>{});
         else merge(std::true_type{}, integral_constant<int, 8>{});
