@@ -23,11 +23,7 @@ namespace rd {
 constexpr int kF32Waves = 8;
 
 // A workgroup takes one row tile (16 packed rows); more rows are row groups.
-// TWO: no range holds more than two tiles per wave (launch_f32); both are on their way at once and there is no loop.  us before /
-// now: H=4, D=64, C=128 5.67 / 5.45, C=600 7.06 / 6.65; H=32, D=64, C=100 5.0 / 4.55; H=4, D=128, C=900 10.8 / 10.1; B=6, H=10,
-// D=128, C=120 10.3 / 9.5.  Longer ranges keep one tile ahead: two take the registers of a second workgroup on the compute unit
-// (D = 64, C=1000 9.0 -> 10.0; D = 128, B=4, H=40, C=2000 90 -> 97).
-template <int D, bool TWO>
+template <int D>
 __global__ __launch_bounds__(kF32Waves * 64, 2) void rd_tree_attn_f32_kernel(AttnArgs a)
 {
     constexpr int NW = kF32Waves;
@@ -90,14 +86,22 @@ __global__ __launch_bounds__(kF32Waves * 64, 2) void rd_tree_attn_f32_kernel(Att
     const uintptr_t Vn = reinterpret_cast<uintptr_t>(a.v_new) + (size_t)bh * a.N * D * 4 - Vc;
     typedef const __attribute__((address_space(1))) f32x4 gvec;
 
-    const int q_frag = min(wave, KC - 1);
-    const f32x4 qreg = *reinterpret_cast<const f32x4 *>(Qb + (size_t)min(r16, Ng - 1) * D + q_frag * 16 + g * 4);
+    // Q is asked for before K and V: loads return in order, and a wave that asks for it last, as the compiler would by the use
+    // below, meets the others at the barrier only when all of its first tile has come.  us by Q last / Q first: H=8, D=128,
+    // C=55 7.60 / 6.67; B=53, H=40, C=147, 24 x 4 tokens 569 / 490; B=7, H=52, C=214 30.7 / 28.7; D=64, B=6, H=32, C=101 5.27 /
+    // 4.91; B=11, H=52, C=200 21.4 / 21.0; over 200 launches of 17 to 4400 keys 5 % less in the mean, none longer.
+    // (The first two tiles of a wave asked for together, without a loop: as fast where the second is not there, slower
+    // where it is: 32.8 and 23.7 us at the third and the last of these.)
+    f32x4 qreg;
+    const bool q_wave = KC >= NW || wave < KC;
+    if (q_wave) qreg = *reinterpret_cast<const f32x4 *>(Qb + (size_t)min(r16, Ng - 1) * D + wave * 16 + g * 4);
+    __builtin_amdgcn_sched_barrier(0);
 
     // K, V and visibility words of a tile.  A wave whose turn falls past the end takes the last tile again (masked), a
     // workgroup without tiles the first there is: no branch around the loads.  Rows past a tile's keys are its last key.
     f32x4 kreg[KC], vreg[4][JJ];
     uint64_t mword;
-    auto fetch = [&](f32x4 (&kreg)[KC], f32x4 (&vreg)[4][JJ], uint64_t &mword, int tile, auto which_k, auto which_v) __attribute__((always_inline)) {
+    auto fetch = [&](int tile, auto which_k, auto which_v) __attribute__((always_inline)) {
         const int tl = max(min(tile, tile_end - 1), 0);
         const bool tree = tl >= nA;
         const int first = (tl - (tree ? nA : 0)) * 16;
@@ -120,14 +124,9 @@ __global__ __launch_bounds__(kF32Waves * 64, 2) void rd_tree_attn_f32_kernel(Att
     using yes = std::true_type;
     using no = std::false_type;
     const int t_first = tile_begin + wave;
-    fetch(kreg, vreg, mword, t_first, yes{}, yes{});
-    struct {
-        f32x4 k[KC], v[4][JJ];
-        uint64_t mask;
-    } two;                                      // TWO: the second tile
-    if (TWO && t_first + NW < tile_end) fetch(two.k, two.v, two.mask, t_first + NW, yes{}, yes{});
+    fetch(t_first, yes{}, yes{});
 
-    if (wave < KC) sQ[wave * 64 + lane] = r16 < P ? qreg : f32x4{0.f, 0.f, 0.f, 0.f};
+    if (q_wave) sQ[wave * 64 + lane] = r16 < P ? qreg : f32x4{0.f, 0.f, 0.f, 0.f};
     float m_run = -INFINITY, l_run = 0.f;
     f32x4 oacc[JJ][4];
 #pragma unroll
@@ -136,7 +135,7 @@ __global__ __launch_bounds__(kF32Waves * 64, 2) void rd_tree_attn_f32_kernel(Att
         for (int e = 0; e < 4; ++e) oacc[jj][e] = f32x4{0.f, 0.f, 0.f, 0.f};
     rd_lds_barrier();         // Q visible to all waves
 
-    auto tile_step = [&](f32x4 (&kreg)[KC], f32x4 (&vreg)[4][JJ], uint64_t &mword, int tile, auto more) __attribute__((always_inline)) {
+    auto tile_step = [&](int tile, auto more) __attribute__((always_inline)) {
         const bool tree = tile >= nA;
         const int first = (tile - (tree ? nA : 0)) * 16;
         const int rem = (tree ? tree_end : C) - first;          // keys of the tile inside the range
@@ -151,7 +150,7 @@ __global__ __launch_bounds__(kF32Waves * 64, 2) void rd_tree_attn_f32_kernel(Att
 #pragma unroll
             for (int e = 0; e < 4; ++e) sacc = __builtin_amdgcn_mfma_f32_16x16x4f32(kreg[c][e], q[e], sacc, 0, 0, 0);
         }
-        if (decltype(more)::value) fetch(kreg, vreg, mword, tile + NW, yes{}, no{});
+        if (decltype(more)::value) fetch(tile + NW, yes{}, no{});
         float s[4], p[4], mx = -INFINITY;
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
@@ -181,17 +180,12 @@ __global__ __launch_bounds__(kF32Waves * 64, 2) void rd_tree_attn_f32_kernel(Att
             for (int jj = 0; jj < JJ; ++jj)
 #pragma unroll
                 for (int e = 0; e < 4; ++e) oacc[jj][e] = __builtin_amdgcn_mfma_f32_16x16x4f32(vreg[i][jj][e], p[i], oacc[jj][e], 0, 0, 0);
-        if (decltype(more)::value) fetch(kreg, vreg, mword, tile + NW, no{}, yes{});
+        if (decltype(more)::value) fetch(tile + NW, no{}, yes{});
     };
     if (t_first < tile_end) {
         int tile = t_first;
-        if constexpr (TWO) {
-            tile_step(kreg, vreg, mword, tile, no{});
-            if (tile + NW < tile_end) tile_step(two.k, two.v, two.mask, tile + NW, no{});
-        } else {
-            for (; tile + NW < tile_end; tile += NW) tile_step(kreg, vreg, mword, tile, yes{});
-            tile_step(kreg, vreg, mword, tile, no{});
-        }
+        for (; tile + NW < tile_end; tile += NW) tile_step(tile, yes{});
+        tile_step(tile, no{});
     }
 
     // ---- the waves' states meet in LDS; fragment (jj, i) holds, per lane, d = 64jj + 16g + 4i .. +3 of row r16
@@ -291,27 +285,23 @@ __global__ __launch_bounds__(kF32Waves * 64, 2) void rd_tree_attn_f32_kernel(Att
     if (tid == 0) a.counters[unit] = 0;       // leave the workspace ready for the next call
 }
 
-template <int D, bool TWO>
+template <int D>
 static int launch_f32(const AttnArgs &a, hipStream_t stream)
 {
     constexpr size_t smem = (size_t)(D / 16) * 1024 + (size_t)kF32Waves * (D / 16) * 1024 + (size_t)16 * (kF32Waves * 2 + 4) * sizeof(float);
     static_assert(smem <= 160 * 1024, "LDS of a compute unit");
     static std::atomic<unsigned long long> configured{0};
-    const int st = ensure_dynamic_lds(reinterpret_cast<const void *>(&rd_tree_attn_f32_kernel<D, TWO>), smem, configured);
+    const int st = ensure_dynamic_lds(reinterpret_cast<const void *>(&rd_tree_attn_f32_kernel<D>), smem, configured);
     if (st != RD_OK) return st;
     const size_t wgs = ((size_t)a.B * a.H + 7) / 8 * 8 * a.S;
     if (wgs > 0x7fffffffull) return RD_ERR_UNSUPPORTED;
-    hipLaunchKernelGGL((rd_tree_attn_f32_kernel<D, TWO>), dim3((unsigned)wgs), dim3(kF32Waves * 64), smem, stream, a);
+    hipLaunchKernelGGL((rd_tree_attn_f32_kernel<D>), dim3((unsigned)wgs), dim3(kF32Waves * 64), smem, stream, a);
     return rd_check_launch();
 }
 
 int tree_attn_f32(const AttnArgs &a, int D, hipStream_t stream)
 {
-    // the most blocks (a tile per wave) that a range can hold, whatever the lengths are
-    const int tiles = (a.Cmax + 15) / 16 + (a.N + 15) / 16, ranges = a.S / a.n_rg > 1 ? a.S / a.n_rg : 1;
-    const bool two = ((tiles + kF32Waves - 1) / kF32Waves + ranges - 1) / ranges <= 2;
-    if (D == 128) return two ? launch_f32<128, true>(a, stream) : launch_f32<128, false>(a, stream);
-    return two ? launch_f32<64, true>(a, stream) : launch_f32<64, false>(a, stream);
+    return D == 128 ? launch_f32<128>(a, stream) : launch_f32<64>(a, stream);
 }
 
 }  // namespace rd

@@ -158,7 +158,7 @@ def test_waves_without_a_tile_and_numbers_of_partials(rd, dtype, D, W, L, C):
 @pytest.mark.parametrize("W,L", [(1, 2), (4, 4), (8, 5), (20, 4)])
 @pytest.mark.parametrize("ctx", [(0, 1), (15, 17), (111, 113), (127, 128), (225, 256), (370, 20), (604, 3), (1700, 900)])
 def test_fp32_ranges_of_one_two_and_more_tiles_per_wave(rd, D, W, L, ctx):
-    """Tiles of 16 keys, eight waves: ranges of at most two tiles per wave have a kernel of their own.  Bound: the fp32 target."""
+    """Tiles of 16 keys, eight waves: waves of no, one, two and more tiles of a range.  Bound: the fp32 target."""
     announce(f"fp32 edges D={D} W={W} L={L} ctx={ctx}")
     ctx, beams, q, kn, vn, kc, vc, d = _case(2, 3, W, L, ctx, D, "f32", W + L)
     scale = float(1.0 / np.sqrt(D))
