@@ -584,9 +584,12 @@ __global__ __launch_bounds__(NW * 64, 2) void rd_tree_attn_mfma_kernel(AttnArgs 
             vec8 kreg[2][KS];
             f32x4 sacc[2][NQA];
             float c_fold = 1.f;
+            // Tiles that are added up below.  Waves past them write nothing: zeros from every idle wave are half a tile's time
+            // (us with / without, D = 128: B=47, H=26, C=46, 6 tokens 10.2 / 9.5; B=55, H=12, C=33, 16 tokens 6.7 / 6.2).
+            const int n_tiles = tile_end - tile_begin, n_sum = n_tiles <= NW / 2 ? NW / 2 : n_tiles <= NW / 2 + NW / 4 ? NW / 2 + NW / 4 : NW;
             if (some) {
                 c_fold = scores(t_first, kreg, sacc, std::true_type{}, []() {});
-            } else {                          // no tile: zeros for the sum over the tiles below
+            } else if (wave < n_sum) {        // no tile: zeros for the sum over the tiles below
 #pragma unroll
                 for (int s = 0; s < kLoads; ++s) *reinterpret_cast<uint4 *>(sV + wave * G::kTileBytes + s * 1024 + lane * 16) = make_uint4(0, 0, 0, 0);
 #pragma unroll
@@ -633,10 +636,12 @@ __global__ __launch_bounds__(NW * 64, 2) void rd_tree_attn_mfma_kernel(AttnArgs 
 #pragma unroll
                 for (int j = 0; j < kOwn; ++j) own[r][j] = f32x4{0.f, 0.f, 0.f, 0.f};
             constexpr int kD = DT >= NW ? DT / NW : 1;          // d-tiles of a wave's fragments: those of j = 0 .. kD-1
-            // NW / 2 tiles (with more than one range a workgroup has more than that), without branches: the reads run ahead
-            auto half = [&](auto first) __attribute__((always_inline)) {
+            // NW / 2 tiles (with more than one range a workgroup has more than that) and the rest by quarters, without branches in
+            // between: the reads run ahead.  (The rest at once adds up to three tiles of zeros: us with / without, B=3, H=8, C=94, 96
+            // tokens 6.95 / 6.60, B=8, H=32, C=122, 16 tokens 4.32 / 4.17.)
+            auto add_tiles = [&](auto first, auto count) __attribute__((always_inline)) {
 #pragma unroll
-                for (int kt = decltype(first)::value; kt < decltype(first)::value + NW / 2; ++kt) {
+                for (int kt = decltype(first)::value; kt < decltype(first)::value + decltype(count)::value; ++kt) {
                     float f[NQA];
 #pragma unroll
                     for (int qt = 0; qt < NQA; ++qt) f[qt] = fac[qt][kt];
@@ -653,8 +658,14 @@ __global__ __launch_bounds__(NW * 64, 2) void rd_tree_attn_mfma_kernel(AttnArgs 
                         }
                 }
             };
-            half(std::integral_constant<int, 0>{});
-            if (tile_end - tile_begin > NW / 2) half(std::integral_constant<int, NW / 2>{});
+            using half = std::integral_constant<int, NW / 2>;
+            using three = std::integral_constant<int, NW / 2 + NW / 4>;
+            using quarter = std::integral_constant<int, NW / 4>;
+            add_tiles(std::integral_constant<int, 0>{}, half{});
+            if (n_sum > half::value) {
+                add_tiles(half{}, quarter{});
+                if (n_sum > three::value) add_tiles(three{}, quarter{});
+            }
             if constexpr (ROPE) {             // (not before V is waited for: that would be a wait for these stores)
                 if (some && t_first >= nA) store_rot(t_first, kreg);
             }

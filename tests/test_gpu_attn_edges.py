@@ -136,7 +136,7 @@ def test_fp16_tiles_far_below_the_largest_score(rd, D, W, L, C):
 
 @pytest.mark.parametrize("dtype,D", [("bf16", 128), ("f16", 64)])
 @pytest.mark.parametrize("W,L", [(3, 4), (8, 5), (12, 8)])
-@pytest.mark.parametrize("C", [1, 40, 100, 290, 560, 820, 1100, 1400, 1700, 2300])
+@pytest.mark.parametrize("C", [1, 40, 80, 100, 130, 165, 200, 230, 290, 560, 820, 1100, 1400, 1700, 2300])
 def test_waves_without_a_tile_and_numbers_of_partials(rd, dtype, D, W, L, C):
     """One tile per wave at most: waves without one add nothing, whatever the launch before left in their LDS (here NaN), and
     heads of two to nine ranges are merged from as many partial results."""
