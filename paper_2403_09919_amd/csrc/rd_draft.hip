@@ -134,7 +134,8 @@ __device__ __forceinline__ void linear_epilogue(const LinArgs<T> &a, f32x4 v, in
 template <typename T, int EPI>
 __device__ __forceinline__ void linear_epilogue(const LinArgs<T> &a, f32x4 v, int m_tile, int n_tile, int r16, int g)
 {
-    if (m_tile + r16 < a.M) linear_epilogue<T, EPI>(a, v, m_tile, n_tile, r16, g, linear_epilogue_in<T, EPI>(a, m_tile, n_tile, r16, g));
+    if (m_tile + r16 >= a.M || (EPI != EPI_HEAD && n_tile + 4 * g >= a.N)) return;      // (nothing is fetched for tiles past the end)
+    linear_epilogue<T, EPI>(a, v, m_tile, n_tile, r16, g, linear_epilogue_in<T, EPI>(a, m_tile, n_tile, r16, g));
 }
 
 // A workgroup owns NT*16 output columns for all M = MT*16 rows; its NWV waves split K.  The host
