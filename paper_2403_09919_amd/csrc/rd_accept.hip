@@ -2,10 +2,10 @@
 //
 // Phase 1 (all workgroups): the valid logit rows (p < n_packed[b]) are cut into chunks of
 // a few thousand floats; a workgroup streams one chunk with 16-byte loads, reduces it to
-// (max value, smallest index attaining it) and folds that into the row's 64-bit key in the
-// workspace with one device-scope atomic max.  The key orders (value, -index), so the row's
-// final key is its arg max with the smallest-index tie rule.  This phase is a pure HBM stream
-// over the valid logits.
+// (max value, smallest index attaining it), the row's 64-bit key in the workspace: stored where the row is
+// one chunk, folded in with one device-scope atomic max, and waited for, where it is several.  The key orders
+// (value, -index), so the row's final key is its arg max with the smallest-index tie rule.  This phase is a pure
+// HBM stream over the valid logits.
 // Phase 2 (the workgroup that completes a sequence, found with a per-row and then a
 // per-sequence counter): decodes the row keys, writes the arg maxes, compares every candidate token with the
 // prediction at its parent (a bit each), takes a candidate's accepted prefix as the run of ones from its first

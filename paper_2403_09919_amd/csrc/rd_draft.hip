@@ -370,9 +370,9 @@ __global__ __launch_bounds__(512) void rd_head_rows_kernel(LinArgs<T> a)
 // consecutive column groups of one split.
 //
 // What bounds it.  64 and 128 rows: the weights' stream, 5.2 TB/s (the MLP layer at a hidden size of 5120 40 us, and 6 of
-// adding up).  256 rows: LDS, whose reads and copies take as long as the matrix instructions (blocks of 8 x 8 tiles would
-// need less, but their accumulators spill), and the matrix rate itself: the output layer at a hidden size of 6656 208 us, 128
-// without the copies, 1.05 PFLOP/s (a library product of 8192^3 reaches 1.22).  Against the kernels it replaced, one that
+// adding up).  256 rows: a k-step takes 1750 to 1800 clocks where its matrix instructions take 1024.  The copies take a large
+// part of the rest (the output layer at a hidden size of 6656 208 us, 128 without them, 1.05 PFLOP/s; a library product of 8192^3
+// reaches 1.22), but not by their traffic in LDS: with weights straight into registers, half of it, a call is 2 % longer.  Against the kernels it replaced, one that
 // staged the activations of 128 rows through registers and one that split K over the waves, us per layer: 256 rows, hidden
 // size 6656, RNN 137 -> 52 + 14, MLP 173 -> 107 + 18, output layer 297 -> 208 + 17; 64 rows, 5120, RNN 37 -> 24 + 6, MLP 56 ->
 // 43 + 6.  A call: 256 rows 2832 -> 2124 (2072 with the selection below), 64 rows 1085 -> 1056 (1018), 80 rows, hidden size 1024 and 50000 tokens 592 -> 465; shapes that the

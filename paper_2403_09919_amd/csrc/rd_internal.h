@@ -70,8 +70,11 @@ static inline int ensure_dynamic_lds(const void *kernel, size_t bytes, std::atom
 // device-wide release/acquire fence would write back and invalidate whole L2s on every
 // workgroup, which costs far more than the kernel itself, so the
 // exchange uses device-scope (write-through / cache-bypassing) relaxed atomic accesses for the
-// data itself, made complete with a wait for outstanding memory operations before the counter
-// is bumped.  Only these few KB per workgroup travel that way; the bulk streams use plain loads.
+// data itself.  They are complete in one of two ways: the writer waits for its outstanding memory
+// operations before it bumps the counter (wait_dev_stores: partial attention states, keys that several
+// workgroups fold into), or the word itself says that it has been stored and the reader waits for it
+// (poll: keys and totals that one workgroup stores).  Only these few KB per workgroup travel that way; the
+// bulk streams use plain loads.
 __device__ __forceinline__ void st_dev(float *p, float v)
 {
     __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);

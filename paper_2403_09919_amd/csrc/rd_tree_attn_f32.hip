@@ -13,7 +13,7 @@
 // workgroup at D = 128), wide beams by the matrix unit.  One row tile per workgroup: two share a tile's loads but
 // lengthen every chain (7.6 against 5.5 us at the first shape below, 117 against 136 us at the last but one), and K/V of a
 // head's row groups come from L2.  Against vector arithmetic on LDS tiles with the packed keys as a workgroup of their
-// own, us per launch: H=4, C=128, D=64, 9 packed rows 14.4 -> 5.45; B=3, H=26, C=250 56.7 -> 13.6; H=10, C=3000 43 -> 16.5;
+// own, us per launch: H=4, C=128, D=64, 9 packed rows 14.4 -> 5.15; B=3, H=26, C=250 56.7 -> 13.6; H=10, C=3000 43 -> 16.5;
 // H=5, C=1000, 52 rows 64.7 -> 13.4; B=4, H=40, C=2000, 33 rows 453 -> 117; B=8, H=32, C=1500 487 -> 101.
 #include "rd_attn_common.h"
 #include <type_traits>
