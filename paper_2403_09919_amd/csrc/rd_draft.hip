@@ -7,7 +7,8 @@
 //     go from memory straight into the A operand of v_mfma_f32_16x16x32_bf16 (lane = one output
 //     column x 8 consecutive k), the activations (a few hundred KB, L2 resident) into the B
 //     operand, and the partial sums meet in LDS.  Bias, SiLU, skip connection and the bf16
-//     copy that the next layer reads are fused into the epilogue.  Layers of many rows, and large ones
+//     copy that the next layer reads are fused into the epilogue.  Large layers of up to 8 rows take both
+//     operands through rings in LDS (rd_stream_kernel).  Layers of many rows, and large ones
 //     from 9 rows on, run on a kernel of 256-column workgroups with K split over them, fed through LDS
 //     (rd_gemm_kernel), and a second one adds the partial tiles (launch_linear has the rules);
 //   * selection: per chunk of 4096 logits and row, the pieces of the log-sum-exp and the W best tokens;
@@ -240,6 +241,106 @@ __global__ __launch_bounds__(NWV * 64) void rd_linear_kernel(LinArgs<T> a)
             linear_epilogue<T, EPI>(a, v, (id / NT) * 16, n0 + (id % NT) * 16, r16, g);
         }
     }
+}
+
+// Layers of up to 8 rows: the stream of the weights and little else.  A workgroup owns 16 columns, its eight waves split K.  A
+// unit, two k-steps of 32, is 2 KB of weights and 1 KB of activations, the eight rows of both steps side by side; a wave has three
+// units under way, copied from memory straight into its ring in LDS, in operand order, and waits for none but the next.  No
+// barrier stands before the waves' sums meet.
+//
+// What bounds it.  A compute unit has some 64 KB of loads under way, whether they come from HBM or from L2, so activations cost
+// what weights do: with a 16-row operand per k-step, as rd_linear_kernel has it, half of all loads are activations, here a third.
+// And the memory's channels: where K is a multiple of a power of two, waves that walk their shares in step ask the same few
+// channels.  So the workgroups of an XCD start a unit after one another, those of the next XCD two units on, and all of them walk
+// around.  us per call (8 x 5 tokens, 32000 tokens, two MLP layers), rd_linear_kernel / this one without the turn / with it:
+// hidden size 4096 685 / 669 / 626, 5120 990 / 891 / 895 (another machine: 932), 3072 548 / 488 / 489 (509), 2048 330 / 318 / 316; the output
+// layer at 4096 95.8 -> 86.0 us, 6.1 TB/s, an MLP layer 27.0 -> 24.8, 2.5 of it before the first weights arrive.  Turns by the
+// plain workgroup number are no substitute (627 to 809 us by the step: workgroups alternate between XCDs).
+constexpr int kStreamRows = 8;
+constexpr int kStreamWaves = 8, kStreamUnits = 3;      // waves, units a wave has under way: 72 KB of LDS, two workgroups per compute unit
+constexpr size_t kStreamLds = (size_t)kStreamWaves * kStreamUnits * 3 * 1024;
+
+template <typename T, int EPI, bool TILED>
+__global__ __launch_bounds__(kStreamWaves * 64) void rd_stream_kernel(LinArgs<T> a)
+{
+    typedef typename Elem16<T>::vec8 vec8;
+    constexpr int NWV = kStreamWaves, R = kStreamUnits;
+    extern __shared__ __align__(16) unsigned char s_buf[];
+    typedef __attribute__((address_space(3))) unsigned char lds_byte;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int r16 = lane & 15, g = lane >> 4;
+    const int n0 = (int)blockIdx.x * 16;
+    unsigned char *ring = s_buf + wave * (R * 3 * 1024);
+    const uint32_t lds0 = (uint32_t)(uintptr_t)(lds_byte *)ring;
+
+    // this wave's n units, of one product (where there are two, half of the waves take each); the host guarantees n > 0
+    const bool two = a.K2 > 0, second = two && wave >= NWV / 2;
+    const int of = two ? NWV / 2 : NWV, at = second ? wave - NWV / 2 : wave;
+    const int K = second ? a.K2 : a.K1, units = K >> 6;
+    const int ub = units * at / of, n = units * (at + 1) / of - ub;
+    const int first = (int)(((blockIdx.x >> 3) + 2 * (blockIdx.x & 7)) % (unsigned)n);      // where it starts
+    const T *xbase = second ? a.x2 : a.x1;
+    const int32_t *map = second ? a.map2 : a.map1;
+    const int m = a.m0 + min(r16 & 7, a.M - 1);         // lanes of r16 < 8 copy the rows' first k-step, the others the second
+    const size_t row = map ? (size_t)map[m] : (size_t)m * a.mstride;
+    uintptr_t xp = reinterpret_cast<uintptr_t>(xbase + row * (second ? a.ldx2 : a.ldx1) + (size_t)(ub + first) * 64 + (r16 >> 3) * 32 + 8 * g);
+    const uintptr_t wbase = reinterpret_cast<uintptr_t>(second ? a.w2 : a.w1);
+    uintptr_t wp;
+    uint32_t woff;
+    constexpr int wstep = TILED ? 1024 : 64;            // bytes between k-steps
+    if (TILED) {
+        wp = wbase + ((size_t)blockIdx.x * (K >> 5) + (ub + first) * 2) * 1024;
+        woff = lane * 16;
+    } else {
+        wp = wbase + ((size_t)n0 * K + (size_t)(ub + first) * 64) * 2;
+        woff = (uint32_t)min(r16, a.N - 1 - n0) * (uint32_t)K * 2 + g * 16;     // rows past N read the last row; never stored
+    }
+    EpilogueIn in = {};
+    if (wave == 0) in = linear_epilogue_in<T, EPI>(a, 0, n0, r16, g);
+    int left = n - first;                               // units up to the end of the share
+    auto copy = [&](int slot) __attribute__((always_inline)) {
+        const uint32_t dst = lds0 + slot * 3072;
+        rd::dma16(wp, woff, dst);
+        rd::dma16(wp + wstep, woff, dst + 1024);
+        rd::dma16(xp, dst + 2048);
+        const int next = left == 1 ? 1 - n : 1;
+        left = left == 1 ? n : left - 1;
+        wp += next * (2 * wstep);
+        xp += next * 128;
+    };
+#pragma unroll
+    for (int u = 0; u < R; ++u)
+        if (u < n) copy(u);
+    const int x_rd = (g * 16 + (r16 & 7)) * 16;
+    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+    int slot = 0;
+    for (int u = 0; u < n; ++u) {
+        if (u + R <= n) rd::wait_vm<(R - 1) * 3>();
+        else rd::wait_vm<0>();
+        const unsigned char *p = ring + slot * 3072;
+        vec8 w[2], x[2];
+#pragma unroll
+        for (int s = 0; s < 2; ++s) {
+            w[s] = *reinterpret_cast<const vec8 *>(p + s * 1024 + lane * 16);
+            x[s] = *reinterpret_cast<const vec8 *>(p + 2048 + x_rd + s * 128);
+        }
+        rd::wait_lds();
+        if (u + R < n) copy(slot);
+        slot = slot + 1 == R ? 0 : slot + 1;
+        acc = Elem16<T>::mfma(w[0], x[0], acc);
+        acc = Elem16<T>::mfma(w[1], x[1], acc);
+    }
+    // the waves' sums meet in LDS (nothing is under way into it any more) and are added in wave order
+    f32x4 *s_part = reinterpret_cast<f32x4 *>(s_buf);
+    rd_lds_barrier();
+    s_part[wave * 64 + lane] = acc;
+    rd_lds_barrier();
+    if (wave != 0) return;
+    f32x4 v = s_part[lane];
+#pragma unroll
+    for (int w = 1; w < NWV; ++w) v += s_part[w * 64 + lane];
+    linear_epilogue<T, EPI>(a, v, 0, n0, r16, g, in);
 }
 
 // The output layer at more than a few rows: with K split over the waves, the accumulators of 128 rows leave
@@ -1574,6 +1675,24 @@ bool few_rows_gemm(int rows, int N, int K)
     return gemm_layer(rows, weights);
 }
 
+// Up to 8 rows, where the layer is more than kSmallLayer and every wave has a few units of K: below that the rings only add to
+// the launch (hidden size 512, 8000 tokens 99.6 us per call by rd_linear_kernel, 101.8 by this; 1024, 32000 177.4 and 178.0 with
+// all layers, the output layer alone is above the line).
+bool stream_layer(int rows, int N, int K) { return rows <= kStreamRows && (size_t)N * K > kSmallLayer && K >= 2048; }
+
+template <typename T, int EPI>
+int launch_stream(const LinArgs<T> &a, hipStream_t stream)
+{
+    static std::atomic<unsigned long long> conf_t{0}, conf_r{0};
+    const void *fn = a.tiled ? reinterpret_cast<const void *>(&rd_stream_kernel<T, EPI, true>)
+                             : reinterpret_cast<const void *>(&rd_stream_kernel<T, EPI, false>);
+    if (rd::ensure_dynamic_lds(fn, kStreamLds, a.tiled ? conf_t : conf_r) != RD_OK) return RD_ERR_HIP;
+    const dim3 grid((a.N + 15) / 16);
+    if (a.tiled) hipLaunchKernelGGL((rd_stream_kernel<T, EPI, true>), grid, dim3(kStreamWaves * 64), kStreamLds, stream, a);
+    else hipLaunchKernelGGL((rd_stream_kernel<T, EPI, false>), grid, dim3(kStreamWaves * 64), kStreamLds, stream, a);
+    return rd_check_launch();
+}
+
 template <typename T, int EPI>
 int launch_linear(const LinArgs<T> &all, hipStream_t stream)
 {
@@ -1585,7 +1704,10 @@ int launch_linear(const LinArgs<T> &all, hipStream_t stream)
         const int mt = (rows + 15) / 16;
         int st = RD_OK;
         bool done = false;
-        if constexpr (EPI == EPI_HEAD) {
+        if (stream_layer(rows, a.N, a.K1 + a.K2)) {
+            st = launch_stream<T, EPI>(a, stream);
+            done = true;
+        } else if constexpr (EPI == EPI_HEAD) {
             if (mt <= 1) done = launch_head_rows<T, 1, EPI>(a, stream, &st);
             else if (mt <= 2) done = launch_head_rows<T, 2, EPI>(a, stream, &st);
             else if (mt <= 4) done = launch_head_rows<T, 4, EPI>(a, stream, &st);

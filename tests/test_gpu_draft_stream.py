@@ -1,0 +1,27 @@
+"""The drafter's layers of up to 8 rows (rd_stream_kernel) at the edges of its tiles, against the oracle: one row to eight, rows of
+a sequence's own and of its candidates, columns that are no multiple of 16, shares of K that differ by a unit between waves and
+the fewest units, one product and two, both weight layouts."""
+import pytest
+import torch
+
+from draft_tolerance import inputs_small
+from gpu_util import announce, dev
+from test_gpu_draft import dev_params, rd, validate  # noqa: F401  (rd: the fixture)
+
+pytestmark = pytest.mark.gpu
+
+# The deviation of a plain fp32 evaluation from the oracle (draft_tolerance.fp32_deviation) is at most 1.8e-3 over these
+# shapes, so the tolerance of test_gpu_draft (1e-2, derived from that deviation over its own shapes) covers them.
+SHAPES = [(1024, 4099, 0, 1, 8, 3), (1024, 4111, 0, 8, 1, 3), (1088, 4001, 0, 2, 4, 3), (1536, 333, 1, 1, 5, 3), (1600, 96, 1, 7, 1, 3),
+          (2112, 130, 1, 1, 8, 4), (2112, 130, 1, 3, 2, 3), (2176, 100, 0, 1, 1, 3)]
+
+
+@pytest.mark.parametrize("tiled", [False, True])
+@pytest.mark.parametrize("Dm,V,K,B,W,L", SHAPES)
+def test_up_to_eight_rows(rd, tiled, Dm, V, K, B, W, L):  # noqa: F811
+    announce(f"draft stream Dm={Dm} V={V} K={K} B={B} W={W} L={L} tiled={tiled}")
+    p, h, last = inputs_small(Dm, V, K, B, W, L)
+    params = rd.rd_draft_pack(dev_params(p)) if tiled else dev_params(p)
+    got = rd.rd_draft(params, dev(h), dev(last), W, L)
+    torch.cuda.synchronize()
+    validate(p, h, last, W, L, got, "draft")
