@@ -343,6 +343,14 @@ __global__ __launch_bounds__(kStreamWaves * 64) void rd_stream_kernel(LinArgs<T>
     linear_epilogue<T, EPI>(a, v, 0, n0, r16, g, in);
 }
 
+// Column tiles of weights lie 32 K bytes apart.  Where that is a multiple of 64 KB, workgroups that walk K in step ask the same few
+// memory channels, so those of an XCD start one after another and walk around (us per call of 5 positions and two MLP layers
+// without / with it, in turn on one machine: 64 rows, hidden size 4096 828 / 781, row-major 900 / 835, 2048 425 / 415, 5120
+// 1037 / 1033; 128 rows, 4096 951 / 923; 16 rows, 4096 741 / 719; 80 rows, 1024, 50000 tokens 385 / 362).  Elsewhere the channels
+// take turns by themselves, and workgroups that start apart share fewer activations (60 rows, 1536 285 / 294; 32 rows, 6656
+// 1346 / 1353), and at 256 rows activations are half of the loads (6656 2060 / 2090).
+__device__ __forceinline__ bool in_phase(int K) { return K % 2048 == 0; }
+
 // The output layer at more than a few rows: with K split over the waves, the accumulators of 128 rows leave
 // a workgroup room for only 64 columns, and every workgroup then pulls two activation bytes through the
 // caches per weight byte (one per weight byte already at 16 rows, with 16-column workgroups).  Here the waves split the columns instead: a wave owns 32 columns for
@@ -351,7 +359,7 @@ __global__ __launch_bounds__(kStreamWaves * 64) void rd_stream_kernel(LinArgs<T>
 // waves walk K together in chunks of 256, and the activations of a chunk are staged once per
 // workgroup in LDS (row stride 528 bytes: the 16 rows a B-operand read touches fall in distinct banks),
 // double-buffered, one barrier per chunk.  Weights still go from memory straight into the A operand, one
-// chunk ahead.  An output is the sum of two accumulators, each over its k-steps in order, for either
+// chunk ahead.  An output is the sum of two accumulators, each over its k-steps in the same order for either
 // weight layout.
 constexpr int kRowsKC = 256;                       // k per chunk
 constexpr int kRowsStride = kRowsKC * 2 + 16;      // bytes per staged activation row
@@ -372,6 +380,7 @@ __global__ __launch_bounds__(512) void rd_head_rows_kernel(LinArgs<T> a)
     const int group = (int)blockIdx.x;
     const int n_tile = (group * 8 + cp * 2) * 16;                      // this wave's 32 columns: tiles n_tile, n_tile + 16
     const int nchunks = a.K1 / kRowsKC;
+    const int turn = in_phase(a.K1) ? (int)(((blockIdx.x >> 3) + 3 * (blockIdx.x & 7)) % (unsigned)nchunks) : 0;      // the chunk it starts with
 
     const T *wp[2];                                                    // this lane's first weight vector of either tile
     constexpr int wstep = TILED ? 512 : 32;
@@ -399,14 +408,14 @@ __global__ __launch_bounds__(512) void rd_head_rows_kernel(LinArgs<T> a)
 
     // (staged values are kept as native vectors: arrays of those stay in registers)
     vec8 wa0[2][kMine], wa1[2][kMine];
-    {   // chunk 0: activations -> buffer 0, weights -> wa0
+    {   // the first chunk: activations -> buffer 0, weights -> wa0
         vec8 x0[kPieces];
 #pragma unroll
-        for (int i = 0; i < kPieces; ++i) x0[i] = *reinterpret_cast<const vec8 *>(xsrc[i]);
+        for (int i = 0; i < kPieces; ++i) x0[i] = *reinterpret_cast<const vec8 *>(xsrc[i] + turn * kRowsKC);
 #pragma unroll
         for (int t = 0; t < 2; ++t)
 #pragma unroll
-            for (int s = 0; s < kMine; ++s) wa0[t][s] = *reinterpret_cast<const vec8 *>(wp[t] + s * wstep);
+            for (int s = 0; s < kMine; ++s) wa0[t][s] = *reinterpret_cast<const vec8 *>(wp[t] + (turn * kSteps + s) * wstep);
 #pragma unroll
         for (int i = 0; i < kPieces; ++i) *reinterpret_cast<vec8 *>(s_x + xdst[i]) = x0[i];
     }
@@ -414,7 +423,7 @@ __global__ __launch_bounds__(512) void rd_head_rows_kernel(LinArgs<T> a)
     const int b_off = r16 * kRowsStride + g * 16 + kh * kMine * 64;    // B operand: row r16 of a tile, k group g, own k-steps
     auto chunk = [&](int c, vec8 (&cur)[2][kMine], vec8 (&nxt)[2][kMine]) __attribute__((always_inline)) {
         // the next chunk's activations and weights (after the last chunk: the last chunk again, ignored)
-        const int cn = min(c + 1, nchunks - 1);
+        const int next = min(c + 1, nchunks - 1) + turn, cn = next >= nchunks ? next - nchunks : next;
         vec8 xs[kPieces];
 #pragma unroll
         for (int i = 0; i < kPieces; ++i) xs[i] = *reinterpret_cast<const vec8 *>(xsrc[i] + cn * kRowsKC);
@@ -505,6 +514,8 @@ __global__ __launch_bounds__(WR * WC * 64, 1) void rd_gemm_kernel(LinArgs<T> a)
     // this workgroup's k-steps: [kb, ke) of those of the first product and, behind them, of the second
     const int ks1 = a.K1 >> 5, ks = ks1 + (a.K2 >> 5);
     const int kb = (int)((long long)ks * split / a.ksplit), steps = (int)((long long)ks * (split + 1) / a.ksplit) - kb;
+    const int turn = RT < 16 && in_phase(a.K1) && steps > 0 ? (int)((blockIdx.x >> 3) * 3 % (unsigned)steps) : 0;      // where it starts
+    auto kstep = [&](int s) __attribute__((always_inline)) { return kb + (s + turn >= steps ? s + turn - steps : s + turn); };
 
     // A wave's pieces: the first four waves copy row tiles wave, wave + 4, .. of the activations (past the last: that one
     // again, to the same place), the others column tiles of the weights.  (Loads return in order: a wave that copied both would
@@ -543,14 +554,14 @@ __global__ __launch_bounds__(WR * WC * 64, 1) void rd_gemm_kernel(LinArgs<T> a)
     }
     const uintptr_t w1 = reinterpret_cast<uintptr_t>(a.w1), w2 = reinterpret_cast<uintptr_t>(a.w2);
     auto copy_x = [&](int s) __attribute__((always_inline)) {
-        const int k = kb + s;
+        const int k = kstep(s);
         const bool second = k >= ks1;
         const size_t at = (size_t)(second ? k - ks1 : k) * 64;
 #pragma unroll
         for (int i = 0; i < PX; ++i) rd::dma16((second ? row_at2[i] : row_at1[i]) + at, lds0 + ((uint32_t)(s % NX) * RT + min(wq + 4 * i, RT - 1)) * 1024);
     };
     auto copy_w = [&](int s) __attribute__((always_inline)) {
-        const int k = kb + s;
+        const int k = kstep(s);
         const bool second = k >= ks1;
         const int k1 = second ? k - ks1 : k, K = second ? a.K2 : a.K1;
         const uintptr_t wb = second ? w2 : w1;
