@@ -473,8 +473,8 @@ __global__ __launch_bounds__(512) void rd_head_rows_kernel(LinArgs<T> a)
 
 // Layers of many rows.  A workgroup of eight waves owns RT row tiles x CT column tiles of the output and a share of K;
 // wave (wr, wc) of WR x WC owns a block of RT/WR x CT/WC tiles.  Per k-step of 32 the operands of all its tiles, (RT + CT) KB,
-// are copied from memory straight into buffers in LDS, three k-steps ahead for the activations (from L2), as many as LDS holds
-// for the weights (5 at RT = 16, 8 at RT = 4), with one LDS-only barrier a step; operands are read into registers two row tiles
+// are copied from memory straight into buffers in LDS, three k-steps ahead for the activations (from L2), for the weights one less
+// than gemm_w_buffers, with one LDS-only barrier a step; operands are read into registers two row tiles
 // ahead, across that barrier.  K is split over a.ksplit workgroups; each leaves its tiles in the workspace and
 // rd_linear_finish_kernel adds them up in split order.  Workgroups of one split read the same activations: an XCD gets
 // consecutive column groups of one split.
@@ -488,7 +488,10 @@ __global__ __launch_bounds__(512) void rd_head_rows_kernel(LinArgs<T> a)
 // 43 + 6.  A call: 256 rows 2832 -> 2124 (2072 with the selection below), 64 rows 1085 -> 1056 (1018), 80 rows, hidden size 1024 and 50000 tokens 592 -> 465; shapes that the
 // old kernels' rules fitted badly gain most (80 rows, hidden size 4160, 12000 tokens 1377 -> 677).
 constexpr int kGemmX = 4;              // buffers for the activations' k-steps
-template <int RT, int CT> constexpr int gemm_w_buffers() { return (160 - kGemmX * RT) / CT < 12 ? (160 - kGemmX * RT) / CT : 12; }      // ... and for the weights'
+// ... and for the weights': as many as fit at 128 rows and more.  At 64 some 64 KB of them: a compute unit has no more under way, and what
+// is asked for beyond that only queues (us per call, 64 rows, 9 buffers of 16 KB / 5: hidden size 5120 1003 / 999, 3072 624 / 615,
+// 2048 414 / 409; 12 of 8 KB / 8: 5120 1006 / 994, 3072 607 / 597; fewer are slower again at 8 KB: 6 995, 5 999, 4 1049).
+template <int RT, int CT> constexpr int gemm_w_buffers() { return RT == 4 ? (CT == 8 ? 8 : 5) : (160 - kGemmX * RT) / CT < 12 ? (160 - kGemmX * RT) / CT : 12; }
 template <int RT, int CT> constexpr size_t gemm_lds() { return (size_t)(kGemmX * RT + gemm_w_buffers<RT, CT>() * CT) * 1024; }
 
 template <typename T, int RT, int CT, int WR, int WC, int EPI, bool TILED>
@@ -1605,7 +1608,7 @@ template <typename T, int RT, int CT, int WR, int WC, int EPI>
 int launch_gemm(LinArgs<T> a, hipStream_t stream)
 {
     const int groups = (a.N + 16 * CT - 1) / (16 * CT), ks = (a.K1 + a.K2) / 32;
-    a.ksplit = CT == kGemmCols && groups < kSplitMaxWgs ? kSplitMaxWgs / groups : 1;
+    a.ksplit = groups < kSplitMaxWgs ? kSplitMaxWgs / groups : 1;
     if (a.ksplit > ks / 8) a.ksplit = ks >= 8 ? ks / 8 : 1;
     constexpr size_t smem = gemm_lds<RT, CT>();
     static std::atomic<unsigned long long> conf_t{0}, conf_r{0};
@@ -1704,6 +1707,16 @@ int launch_stream(const LinArgs<T> &a, hipStream_t stream)
     return rd_check_launch();
 }
 
+// Layers of up to 64 rows take workgroups of half as many columns also where half the splits of K then fill the chip, three or more:
+// half the partial sums to write and read.  With two the activations, read twice as often, cost more.  us per call, 64 rows of hidden
+// size 4096 797 / 780, 3072 615 / 597, 5120 999 / 995, 36 rows of 1536 257 / 250; two splits, 50 rows of 7680 1685 / 1731; a chip
+// filled to four fifths, 64 rows of 6656 1440 / 1509, 4608 929 / 940.
+bool gemm_halves(int N)
+{
+    const int groups = (N + 127) / 128, splits = kSplitMaxWgs / groups;
+    return splits >= 3 && groups * splits >= kSplitMaxWgs * 15 / 16;
+}
+
 template <typename T, int EPI>
 int launch_linear(const LinArgs<T> &all, hipStream_t stream)
 {
@@ -1731,7 +1744,7 @@ int launch_linear(const LinArgs<T> &all, hipStream_t stream)
         if (!done) {
             if (all.M > 32 || (EPI != EPI_HEAD && few_rows_gemm(rows, a.N, a.K1 + a.K2))) {
                 const int rt = gemm_row_tiles(rows), groups = (a.N + 16 * kGemmCols - 1) / (16 * kGemmCols);
-                const bool narrow = groups > 64 && groups <= 128 && a.K1 + a.K2 <= 4096;
+                const bool narrow = (groups > 64 && groups <= 128 && a.K1 + a.K2 <= 4096) || (rt == 4 && gemm_halves(a.N));
                 if (rt == 16) st = launch_gemm<T, 16, 16, 2, 4, EPI>(a, stream);
                 else if (rt == 8) st = narrow ? launch_gemm<T, 8, 8, 2, 4, EPI>(a, stream) : launch_gemm<T, 8, 16, 2, 4, EPI>(a, stream);
                 else st = narrow ? launch_gemm<T, 4, 8, 2, 4, EPI>(a, stream) : launch_gemm<T, 4, 16, 1, 8, EPI>(a, stream);

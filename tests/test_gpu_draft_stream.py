@@ -1,7 +1,7 @@
 """The drafter's layers whose workgroups start apart in K, against the oracle: those of up to 8 rows (rd_stream_kernel) at the
 edges of its tiles, one row to eight, rows of a sequence's own and of its candidates, columns that are no multiple of 16, shares of
 K that differ by a unit between waves and the fewest units, one product and two; and those of more rows where K is a multiple of
-2048 (rd_head_rows_kernel, rd_gemm_kernel); both weight layouts."""
+2048 (rd_head_rows_kernel, rd_gemm_kernel), or their workgroups have half the columns; both weight layouts."""
 import pytest
 import torch
 
@@ -16,7 +16,9 @@ pytestmark = pytest.mark.gpu
 SHAPES = [(1024, 4099, 0, 1, 8, 3), (1024, 4111, 0, 8, 1, 3), (1088, 4001, 0, 2, 4, 3), (1536, 333, 1, 1, 5, 3), (1600, 96, 1, 7, 1, 3),
           (2112, 130, 1, 1, 8, 4), (2112, 130, 1, 3, 2, 3), (2176, 100, 0, 1, 1, 3),
           # 16, 40, 72 and 120 rows
-          (1024, 16500, 0, 2, 8, 3), (1024, 16399, 0, 5, 8, 3), (2048, 130, 1, 5, 8, 3), (2048, 130, 1, 9, 8, 3), (1024, 16385, 1, 15, 8, 3)]
+          (1024, 16500, 0, 2, 8, 3), (1024, 16399, 0, 5, 8, 3), (2048, 130, 1, 5, 8, 3), (2048, 130, 1, 9, 8, 3), (1024, 16385, 1, 15, 8, 3),
+          # up to 64 rows, 128 columns to a workgroup and K split: the last group whole, and half empty (the RNN's)
+          (2624, 130, 1, 5, 8, 3), (2624, 130, 1, 8, 8, 2)]
 
 
 @pytest.mark.parametrize("tiled", [False, True])
