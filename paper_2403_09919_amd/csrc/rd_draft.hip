@@ -473,8 +473,8 @@ __global__ __launch_bounds__(512) void rd_head_rows_kernel(LinArgs<T> a)
 
 // Layers of many rows.  A workgroup of eight waves owns RT row tiles x CT column tiles of the output and a share of K;
 // wave (wr, wc) of WR x WC owns a block of RT/WR x CT/WC tiles.  Per k-step of 32 the operands of all its tiles, (RT + CT) KB,
-// are copied from memory straight into buffers in LDS, three k-steps ahead for the activations (from L2), for the weights one less
-// than gemm_w_buffers, with one LDS-only barrier a step; operands are read into registers two row tiles
+// are copied from memory straight into buffers in LDS, up to one k-step less ahead than there are buffers, with one LDS-only barrier
+// a step or two; operands are read into registers two row tiles
 // ahead, across that barrier.  K is split over a.ksplit workgroups; each leaves its tiles in the workspace and
 // rd_linear_finish_kernel adds them up in split order.  Workgroups of one split read the same activations: an XCD gets
 // consecutive column groups of one split.
@@ -487,21 +487,31 @@ __global__ __launch_bounds__(512) void rd_head_rows_kernel(LinArgs<T> a)
 // size 6656, RNN 137 -> 52 + 14, MLP 173 -> 107 + 18, output layer 297 -> 208 + 17; 64 rows, 5120, RNN 37 -> 24 + 6, MLP 56 ->
 // 43 + 6.  A call: 256 rows 2832 -> 2124 (2072 with the selection below), 64 rows 1085 -> 1056 (1018), 80 rows, hidden size 1024 and 50000 tokens 592 -> 465; shapes that the
 // old kernels' rules fitted badly gain most (80 rows, hidden size 4160, 12000 tokens 1377 -> 677).
-constexpr int kGemmX = 4;              // buffers for the activations' k-steps
-// ... and for the weights': as many as fit at 128 rows and more.  At 64 some 64 KB of them: a compute unit has no more under way, and what
-// is asked for beyond that only queues (us per call, 64 rows, 9 buffers of 16 KB / 5: hidden size 5120 1003 / 999, 3072 624 / 615,
-// 2048 414 / 409; 12 of 8 KB / 8: 5120 1006 / 994, 3072 607 / 597; fewer are slower again at 8 KB: 6 995, 5 999, 4 1049).
-template <int RT, int CT> constexpr int gemm_w_buffers() { return RT == 4 ? (CT == 8 ? 8 : 5) : (160 - kGemmX * RT) / CT < 12 ? (160 - kGemmX * RT) / CT : 12; }
-template <int RT, int CT> constexpr size_t gemm_lds() { return (size_t)(kGemmX * RT + gemm_w_buffers<RT, CT>() * CT) * 1024; }
+//
+// Buffers and rounds.  At 64 rows and fewer the weights that may be under way are kept to what a compute unit has under way, some
+// 64 KB; more only queue.  256 columns: two k-steps between barriers, of which there are else so many that the loop takes half the
+// time even without its copies.  128 columns: one, and activations seven steps ahead.  us per call, 64 rows of hidden size 5120 / 4096
+// / 6656: four buffers of activations, as many of weights as fit, a barrier per k-step 1003 / 802 / 1444; 5 (256 columns) and 8 (128)
+// of weights 994 / 778 / 1434; as here 979 / 772 / 1417; two k-steps a round for both 984 / 784 / 1420, four for 128 columns 1029 / 805
+// / 1418.  Their numbers are powers of two: 7, 9, 10 or 12 take 5 to 15 us more at 5120.  More rows: as many as fit (two k-steps a round
+// at 128 rows, of 5120 1203 -> 1241, of 4096 924 -> 950).
+template <int RT, int CT> constexpr int gemm_round() { return RT == 4 && CT == 16 ? 2 : 1; }       // k-steps between two barriers
+template <int RT> constexpr int gemm_x_buffers() { return RT == 4 ? 8 : 4; }       // buffers for the activations' k-steps
+template <int RT, int CT> constexpr int gemm_w_buffers()                           // ... and for the weights'
+{
+    return RT == 4 ? 8 : (160 - gemm_x_buffers<RT>() * RT) / CT < 12 ? (160 - gemm_x_buffers<RT>() * RT) / CT : 12;
+}
+template <int RT, int CT> constexpr size_t gemm_lds() { return (size_t)(gemm_x_buffers<RT>() * RT + gemm_w_buffers<RT, CT>() * CT) * 1024; }
 
 template <typename T, int RT, int CT, int WR, int WC, int EPI, bool TILED>
 __global__ __launch_bounds__(WR * WC * 64, 1) void rd_gemm_kernel(LinArgs<T> a)
 {
     typedef typename Elem16<T>::vec8 vec8;
-    constexpr int NX = kGemmX, NW = gemm_w_buffers<RT, CT>();
+    constexpr int KU = gemm_round<RT, CT>(), NX = gemm_x_buffers<RT>(), NW = gemm_w_buffers<RT, CT>(), RX = NX / KU, RW = NW / KU;
     constexpr int PX = (RT + 3) / 4, PW = CT / 4;                       // 1 KB pieces a wave copies per k-step: four waves X, four W
     constexpr int MT = RT / WR, NT = CT / WC;                           // a wave's tiles
     static_assert(WR * WC == 8 && CT % 4 == 0 && MT % 2 == 0 && NT % (MT / 2) == 0, "whole pieces, and halves of a step");
+    static_assert(NX % KU == 0 && NW % KU == 0 && RX >= 3 && RW >= 3, "whole rounds, one of them under way");
     extern __shared__ __align__(16) unsigned char s_buf[];
     typedef __attribute__((address_space(3))) unsigned char lds_byte;
     const uint32_t lds0 = (uint32_t)(uintptr_t)(lds_byte *)s_buf;
@@ -518,7 +528,10 @@ __global__ __launch_bounds__(WR * WC * 64, 1) void rd_gemm_kernel(LinArgs<T> a)
     const int ks1 = a.K1 >> 5, ks = ks1 + (a.K2 >> 5);
     const int kb = (int)((long long)ks * split / a.ksplit), steps = (int)((long long)ks * (split + 1) / a.ksplit) - kb;
     const int turn = RT < 16 && in_phase(a.K1) && steps > 0 ? (int)((blockIdx.x >> 3) * 3 % (unsigned)steps) : 0;      // where it starts
-    auto kstep = [&](int s) __attribute__((always_inline)) { return kb + (s + turn >= steps ? s + turn - steps : s + turn); };
+    auto kstep = [&](int s) __attribute__((always_inline)) {
+        const int t = min(s, steps - 1) + turn;
+        return kb + (t >= steps ? t - steps : t);
+    };
 
     // A wave's pieces: the first four waves copy row tiles wave, wave + 4, .. of the activations (past the last: that one
     // again, to the same place), the others column tiles of the weights.  (Loads return in order: a wave that copied both would
@@ -587,18 +600,23 @@ __global__ __launch_bounds__(WR * WC * 64, 1) void rd_gemm_kernel(LinArgs<T> a)
 #pragma unroll
         for (int nt = 0; nt < NT; ++nt) acc[mt][nt] = f32x4{0.f, 0.f, 0.f, 0.f};
 
-    if (is_x) {
-        for (int s = 0; s < min(steps, NX - 1); ++s) copy_x(s);
-    } else {
-        for (int s = 0; s < min(steps, NW - 1); ++s) copy_w(s);
-    }
-    // k-step s, behind which at most NX - 3 (NW - 3) more are asked for, is in LDS when all waves have waited for their pieces of it
-    auto arrive = [&](int s) __attribute__((always_inline)) {
+    // Rounds of KU k-steps (where the last one is not whole, its last k-step again).
+    const int rounds = (steps + KU - 1) / KU;
+    auto copy_round = [&](int r) __attribute__((always_inline)) {
+#pragma unroll
+        for (int u = 0; u < KU; ++u) {
+            if (is_x) copy_x(r * KU + u);
+            else copy_w(r * KU + u);
+        }
+    };
+    for (int r = 0; r < min(rounds, (is_x ? RX : RW) - 1); ++r) copy_round(r);
+    // round r, behind which at most RX - 3 (RW - 3) more are asked for, is in LDS when all waves have waited for their pieces of it
+    auto arrive = [&](int r) __attribute__((always_inline)) {
         if (is_x) {
-            if (s + NX - 3 < steps) rd::wait_vm<(NX - 3) * PX>();
+            if (r + RX - 3 < rounds) rd::wait_vm<(RX - 3) * KU * PX>();
             else rd::wait_vm<0>();
         } else {
-            if (s + NW - 3 < steps) rd::wait_vm<(NW - 3) * PW>();
+            if (r + RW - 3 < rounds) rd::wait_vm<(RW - 3) * KU * PW>();
             else rd::wait_vm<0>();
         }
         rd_lds_barrier();
@@ -610,13 +628,10 @@ __global__ __launch_bounds__(WR * WC * 64, 1) void rd_gemm_kernel(LinArgs<T> a)
 #pragma unroll
         for (int mt = 0; mt < MT; ++mt) {
             constexpr int kHalf = MT / 2;
-            if (mt == kHalf - 1 && s + 1 < steps) {
-                arrive(s + 1);                // (all waves have read the step before this one to its end: its buffer is free)
-                if (is_x) {
-                    if (s + NX - 1 < steps) copy_x(s + NX - 1);
-                } else {
-                    if (s + NW - 1 < steps) copy_w(s + NW - 1);
-                }
+            if (mt == kHalf - 1 && s + 1 < steps && (s + 1) % KU == 0) {
+                const int r = (s + 1) / KU, ahead = r + (is_x ? RX : RW) - 2;
+                arrive(r);                    // (all waves have read the round before the one that ends here: its buffers are free)
+                if (ahead < rounds) copy_round(ahead);
             }
             const vec8 xm = x[mt];
             x[(mt + 2) % MT] = mt + 2 < MT ? read_x(s, mt + 2) : read_x(s + 1, mt + 2 - MT);
