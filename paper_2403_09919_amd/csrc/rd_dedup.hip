@@ -1,6 +1,6 @@
 // rd_dedup: dynamic tree attention construction (Sec. 3.3, App. A.1) for gfx950.
 //
-// Up to 64 tokens: rd_dedup_wave_kernel below.  More:
+// Up to 64 tokens: rd_dedup_wave_kernel below; more, in candidates of up to 64: rd_dedup_waves_kernel.  Longer ones (five at most):
 // One workgroup per sequence (more where the dense mask is asked for), everything in LDS, data-parallel phases
 // separated by barriers (the whole input is a few hundred bytes; what costs time is dependent latency, so no phase
 // is a serial walk over positions):
@@ -22,17 +22,16 @@ RD_TRACE_DEFINE(rd_debug_set_trace_dedup)
 
 namespace {
 
-constexpr int kDedupThreads = 384;                 // the fewest: one thread per token
-// More than 16 candidates: their pairs are what takes time (us, 384 / 1024 threads: 16 candidates 3.82 / 3.86, 20 4.34 / 3.90,
-// 30 5.20 / 4.38, 70 12.8 / 8.8).
-constexpr int kWideThreads = 1024;
-// Rows of the dense mask per workgroup (us, all rows in one / 32 / 16: N = 80, 16 sequences 4.94 /
-// 4.56 / 4.42; N = 150 8.6 / 5.4 / 5.0; N = 350 31.8 / 10.9 / 9.9).  Every workgroup repeats the construction, so fewer rows cost
-// where there are more workgroups than compute units: 24 sequences of N = 350 take 34.3 / 19.3 / 23.3 (14.2 with 48 rows).
+constexpr int kDedupThreads = 384;                 // of rd_dedup_kernel: one thread per token
+// Rows of the dense mask per workgroup; every workgroup repeats the construction.  us by 16 / 32 / 48 / 64 rows: N = 80, 16 sequences
+// 3.81 / 3.77 / 3.77 / 3.85, N = 150 4.43 / 4.59 / 4.83 / 4.99, N = 350 7.25 / 7.62 / 8.04 / 8.45 and 24 sequences of it 9.39 / 8.82 / 8.73 / 9.09,
+// 60 sequences of N = 240 10.25 / 6.52 / 6.71 / 6.60.
 constexpr int kMaskRows = 32;
 constexpr int kMaskWords = (RD_MAX_N + 63) / 64;
+constexpr int kMaskWaves = 8;                      // at least, where the dense mask is written
+constexpr int kMaxTokenWaves = 11;                 // of rd_dedup_waves_kernel: 33 positions, one candidate to a wave
 
-__global__ __launch_bounds__(kWideThreads) void rd_dedup_kernel(
+__global__ __launch_bounds__(kDedupThreads) void rd_dedup_kernel(
     const int32_t *__restrict__ beams, const int32_t *__restrict__ ctx_len, int W, int L,
     int32_t *__restrict__ prefix_tree, int32_t *__restrict__ packed_tokens,
     int32_t *__restrict__ n_packed, int32_t *__restrict__ unpack_index,
@@ -265,6 +264,111 @@ __global__ __launch_bounds__(256) void rd_dedup_wave_kernel(
     }
 }
 
+// More than 64 tokens, up to 64 to a candidate: a token per lane, whole candidates per wave (64 / L of them), and sets of a wave's
+// tokens are ballots.  A wave compares its candidates with every one before them, whose tokens all lanes of a position read from
+// one place in LDS (unrolled, so that the reads run ahead); three barriers in all.  Bound by that loop, some 45 clocks a candidate,
+// beside the launch and one round trip to memory.  The phases of rd_dedup_kernel, with the pairs of candidates shared out to 1024
+// threads and the owners lowered by atomics, took longer, above all for the serial sums over candidates and positions.  us per launch
+// in a graph, those phases / this: N = 80 3.8 / 3.2, 16 sequences of it with the dense mask 4.5 / 3.85, N = 150 4.7 / 4.1, 350 8.9 / 6.8,
+// with the mask 11.1 / 7.6, 24 sequences of it 16.7 / 8.85; 128 candidates of 3 tokens 18.0 / 9.7; 2 of 64 11.5 / 6.0.  (Prefixes
+// compared by 32-bit halves, without the order of candidates outside the wave: 350 7.65.)
+__global__ __launch_bounds__(kMaxTokenWaves * 64) void rd_dedup_waves_kernel(
+    const int32_t *__restrict__ beams, const int32_t *__restrict__ ctx_len, int W, int L, int per_wave, int token_waves, uint32_t inv_l, uint32_t inv_w, uint32_t inv_n4, uint32_t inv_n2,
+    int32_t *__restrict__ prefix_tree, int32_t *__restrict__ packed_tokens,
+    int32_t *__restrict__ n_packed, int32_t *__restrict__ unpack_index,
+    int32_t *__restrict__ parent, int32_t *__restrict__ position_ids,
+    uint8_t *__restrict__ tree_mask, uint64_t *__restrict__ tree_mask_bits)
+{
+    __shared__ int32_t s_beam[RD_MAX_N];
+    __shared__ __align__(8) uint32_t s_bits[RD_MAX_N * kMaskWords * 2];      // mask row of each packed slot
+    __shared__ uint64_t s_kept[kMaxTokenWaves];
+    const int b = blockIdx.x, slice = blockIdx.y;
+    const bool main_wg = slice == 0;               // (further ones: rows of the dense mask, as in rd_dedup_kernel)
+    const int tid = threadIdx.x, threads = blockDim.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int N = W * L, words = (N + 63) >> 6;
+    const size_t seq = (size_t)b * N;
+    const int own = (int)((uint32_t)lane * inv_l >> 20), j = lane - own * L;      // candidate in the wave, position
+    const int i = wave * per_wave + own, e = i * L + j;
+    const bool tok = own < per_wave && i < W;
+    const int token = beams[seq + min(e, N - 1)];
+    const int ctx = ctx_len ? ctx_len[b] : 0;
+    if (tok) s_beam[e] = token;
+    for (int t = tid; t < N * words * 2; t += threads) s_bits[t] = 0;
+    rd_lds_barrier();
+
+    // owner: the smallest candidate whose first j + 1 tokens are this one's, i.e. prefix_tree
+    const uint64_t mine = ((2ull << j) - 1) << (own * L & 63);          // tokens 0 .. j of this candidate
+    int owner = i;
+    if (wave < token_waves) {
+#pragma unroll 8
+        for (int k = min((wave + 1) * per_wave, W) - 2; k >= 0; --k) {
+            const uint64_t same = __ballot(token == s_beam[k * L + j]);
+            owner = k < i && (same & mine) == mine ? k : owner;
+        }
+        const uint64_t kept = __ballot(tok && owner == i);              // in the order of their slots
+        if (lane == 0) s_kept[wave] = kept;
+    }
+    rd_lds_barrier();
+    const int there = (int)((uint32_t)owner * inv_w >> 20);             // the owner's wave
+    int slot = __popcll(s_kept[tok ? there : 0] & ((1ull << (((owner - there * per_wave) * L + j) & 63)) - 1)), P = 0;
+    for (int w = 0; w < token_waves; ++w) {
+        const int n = __popcll(s_kept[w]);
+        slot += w < there ? n : 0;
+        P += n;
+    }
+    const bool keep = tok && owner == i;          // (waves beyond the tokens only help to write)
+    const int up = __builtin_amdgcn_ds_bpermute((lane - 1) * 4, slot);
+    if (main_wg) {
+        if (tid == 0) n_packed[b] = P;
+        if (tok) {
+            unpack_index[seq + e] = slot;
+            if (prefix_tree) prefix_tree[seq + e] = owner;
+        }
+        if (keep) {
+            packed_tokens[seq + slot] = token;
+            parent[seq + slot] = j ? up : -1;
+            position_ids[seq + slot] = ctx + j;
+        }
+        for (int p = P + tid; p < N; p += threads) packed_tokens[seq + p] = parent[seq + p] = position_ids[seq + p] = -1;
+    }
+    // the slots from the root to (i, j)
+    for (int t = 0; t < L; ++t) {
+        const int q = __builtin_amdgcn_ds_bpermute((own * L + t) * 4, slot);
+        if (keep && t <= j) atomicOr(&s_bits[slot * words * 2 + (q >> 5)], 1u << (q & 31));
+    }
+    rd_lds_barrier();
+    if (main_wg && tree_mask_bits) {
+        uint64_t *dst = tree_mask_bits + seq * words;
+        for (int t = tid; t < N * words; t += threads) dst[t] = reinterpret_cast<const uint64_t *>(s_bits)[t];
+    }
+    if (tree_mask) {
+        uint8_t *dst = tree_mask + seq * N;
+        const int p0 = slice * kMaskRows, rows = min(kMaskRows, N - p0);
+        if ((N & 3) == 0) {                          // N*N and seq*N are multiples of 4: 32-bit stores
+            uint32_t *dst4 = reinterpret_cast<uint32_t *>(dst);
+            const int n4 = N >> 2;
+            for (int t = tid; t < rows * n4; t += threads) {
+                const int r = (int)((uint32_t)t * inv_n4 >> 20), p = p0 + r, q = (t - r * n4) * 4;
+                const uint32_t w = s_bits[p * words * 2 + (q >> 5)] >> (q & 31) & 15u;
+                dst4[p * n4 + (q >> 2)] = (w * 0x00204081u) & 0x01010101u;      // a bit to a byte
+            }
+        } else if ((N & 1) == 0) {                   // the same, by pairs, which lie in one row each: N*N is a multiple of 4, the rows are even in number
+            uint32_t *dst4 = reinterpret_cast<uint32_t *>(dst + p0 * N);
+            const int n2 = N >> 1, pairs = rows * n2;
+            auto pair = [&](int t) __attribute__((always_inline)) {
+                const int r = (int)((uint64_t)(uint32_t)t * inv_n2 >> 24), p = p0 + r, q = (t - r * n2) * 2;
+                return s_bits[p * words * 2 + (q >> 5)] >> (q & 31) & 3u;
+            };
+            for (int t = tid * 2; t < pairs; t += threads * 2) dst4[t >> 1] = (pair(t) * 0x81u & 0x101u) | (pair(t + 1) * 0x810000u & 0x1010000u);
+        } else {
+            for (int t = tid; t < rows * N; t += threads) {
+                const int p = p0 + t / N, q = t % N;
+                dst[p * N + q] = (uint8_t)(s_bits[p * words * 2 + (q >> 5)] >> (q & 31) & 1);
+            }
+        }
+    }
+}
+
 }  // namespace
 
 extern "C" int rd_dedup(const int32_t *beams, const int32_t *ctx_len, int B, int W, int L,
@@ -287,7 +391,17 @@ extern "C" int rd_dedup(const int32_t *beams, const int32_t *ctx_len, int B, int
         return rd_check_launch();
     }
     const int slices = tree_mask ? (W * L + kMaskRows - 1) / kMaskRows : 1;
-    hipLaunchKernelGGL(rd_dedup_kernel, dim3(B, slices), dim3(W > 16 ? kWideThreads : kDedupThreads), 0, (hipStream_t)stream,
+    if (L <= 64) {
+        // as above; candidates below 128 by up to 32 in a wave, words of kMaskRows rows by up to 96
+        auto inverse = [](int d) { return ((1u << 20) + (uint32_t)d - 1) / (uint32_t)d; };
+        const int per_wave = 64 / L, waves = (W + per_wave - 1) / per_wave;
+        hipLaunchKernelGGL(rd_dedup_waves_kernel, dim3(B, slices), dim3((tree_mask && waves < kMaskWaves ? kMaskWaves : waves) * 64), 0,
+                           (hipStream_t)stream, beams, ctx_len, W, L, per_wave, waves, inverse(L), inverse(per_wave), inverse(N >> 2),
+                           ((1u << 24) + (uint32_t)(N >> 1) - 1) / (uint32_t)(N >> 1), prefix_tree, packed_tokens, n_packed, unpack_index, parent,
+                           position_ids, tree_mask, tree_mask_bits);
+        return rd_check_launch();
+    }
+    hipLaunchKernelGGL(rd_dedup_kernel, dim3(B, slices), dim3(kDedupThreads), 0, (hipStream_t)stream,
                        beams, ctx_len, W, L, prefix_tree, packed_tokens, n_packed, unpack_index,
                        parent, position_ids, tree_mask, tree_mask_bits);
     return rd_check_launch();
