@@ -348,8 +348,12 @@ __global__ __launch_bounds__(kStreamWaves * 64) void rd_stream_kernel(LinArgs<T>
 // without / with it, in turn on one machine: 64 rows, hidden size 4096 828 / 781, row-major 900 / 835, 2048 425 / 415, 5120
 // 1037 / 1033; 128 rows, 4096 951 / 923; 16 rows, 4096 741 / 719; 80 rows, 1024, 50000 tokens 385 / 362).  Elsewhere the channels
 // take turns by themselves, and workgroups that start apart share fewer activations (60 rows, 1536 285 / 294; 32 rows, 6656
-// 1346 / 1353), and at 256 rows activations are half of the loads (6656 2060 / 2090).
+// 1346 / 1353), and at 256 rows activations are half of the loads (6656 2060 / 2090).  65 to 128 rows lie between: where K
+// is 4096 or less the layers that split K are not turned, the output layer within each XCD only (us per call, no turns / turned as
+// fewer rows are / so: 72 rows, 2048 467 / 471 / 461; 1024, 50000 tokens 370 / 342 / 341; larger K as fewer rows: 72 rows, 4096 873 /
+// 847, 128 rows, 3072 751 / 742, 5120 1228 / 1212).
 __device__ __forceinline__ bool in_phase(int K) { return K % 2048 == 0; }
+constexpr int kFarK = 6144;
 
 // The output layer at more than a few rows: with K split over the waves, the accumulators of 128 rows leave
 // a workgroup room for only 64 columns, and every workgroup then pulls two activation bytes through the
@@ -380,7 +384,8 @@ __global__ __launch_bounds__(512) void rd_head_rows_kernel(LinArgs<T> a)
     const int group = (int)blockIdx.x;
     const int n_tile = (group * 8 + cp * 2) * 16;                      // this wave's 32 columns: tiles n_tile, n_tile + 16
     const int nchunks = a.K1 / kRowsKC;
-    const int turn = in_phase(a.K1) ? (int)(((blockIdx.x >> 3) + 3 * (blockIdx.x & 7)) % (unsigned)nchunks) : 0;      // the chunk it starts with
+    const unsigned apart = MT > 4 && a.K1 < kFarK ? 0 : 3;          // chunks that an XCD's workgroups start after the last one's
+    const int turn = in_phase(a.K1) ? (int)(((blockIdx.x >> 3) + apart * (blockIdx.x & 7)) % (unsigned)nchunks) : 0;      // the chunk it starts with
 
     const T *wp[2];                                                    // this lane's first weight vector of either tile
     constexpr int wstep = TILED ? 512 : 32;
@@ -479,10 +484,12 @@ __global__ __launch_bounds__(512) void rd_head_rows_kernel(LinArgs<T> a)
 // rd_linear_finish_kernel adds them up in split order.  Workgroups of one split read the same activations: an XCD gets
 // consecutive column groups of one split.
 //
-// What bounds it.  64 and 128 rows: the weights' stream, 5.2 TB/s (the MLP layer at a hidden size of 5120 40 us, and 6 of
-// adding up).  256 rows: a k-step takes 1750 to 1800 clocks where its matrix instructions take 1024.  The copies take a large
-// part of the rest (the output layer at a hidden size of 6656 208 us, 128 without them, 1.05 PFLOP/s; a library product of 8192^3
-// reaches 1.22), but not by their traffic in LDS: with weights straight into registers, half of it, a call is 2 % longer.  Against the kernels it replaced, one that
+// What bounds it.  64 and 128 rows: what a compute unit has under way, weights and activations together, 4.7 to 5.2 TB/s of
+// weights (the MLP layer at a hidden size of 5120 40 to 45 us by the machine, and 5 of adding up).  256 rows: a k-step takes 1750 to
+// 1800 clocks where its matrix instructions take 1024.  The copies take part of the rest (the output layer at a hidden size of
+// 6656 217 us, 180 with the activations' alone, 200 with the weights', 145 with none, at a clock that the matrix cores' power
+// holds at 1.75 to 1.9 GHz; a library product of 8192^3 reaches 1.22 PFLOP/s), but not by their traffic in LDS: with weights straight
+// into registers, half of it, a call is 2 % longer.  Against the kernels it replaced, one that
 // staged the activations of 128 rows through registers and one that split K over the waves, us per layer: 256 rows, hidden
 // size 6656, RNN 137 -> 52 + 14, MLP 173 -> 107 + 18, output layer 297 -> 208 + 17; 64 rows, 5120, RNN 37 -> 24 + 6, MLP 56 ->
 // 43 + 6.  A call: 256 rows 2832 -> 2124 (2072 with the selection below), 64 rows 1085 -> 1056 (1018), 80 rows, hidden size 1024 and 50000 tokens 592 -> 465; shapes that the
@@ -527,7 +534,7 @@ __global__ __launch_bounds__(WR * WC * 64, 1) void rd_gemm_kernel(LinArgs<T> a)
     // this workgroup's k-steps: [kb, ke) of those of the first product and, behind them, of the second
     const int ks1 = a.K1 >> 5, ks = ks1 + (a.K2 >> 5);
     const int kb = (int)((long long)ks * split / a.ksplit), steps = (int)((long long)ks * (split + 1) / a.ksplit) - kb;
-    const int turn = RT < 16 && in_phase(a.K1) && steps > 0 ? (int)((blockIdx.x >> 3) * 3 % (unsigned)steps) : 0;      // where it starts
+    const int turn = (RT < 8 || (RT == 8 && a.K1 >= kFarK)) && in_phase(a.K1) && steps > 0 ? (int)((blockIdx.x >> 3) * 3 % (unsigned)steps) : 0;      // where it starts
     auto kstep = [&](int s) __attribute__((always_inline)) {
         const int t = min(s, steps - 1) + turn;
         return kb + (t >= steps ? t - steps : t);
@@ -1642,14 +1649,14 @@ int launch_gemm(LinArgs<T> a, hipStream_t stream)
 // The output layer at 9 rows and more per launch, wide enough to cover half the chip with 128-column
 // workgroups: waves split the columns, activations staged in LDS (rd_head_rows_kernel).  Measured per call
 // at a hidden size of 4096 and 32000 tokens against the K-split kernels: 16 rows 832 -> 766 us, 32 rows
-// 919 -> 835, 64 rows 1007 -> 965, 128 rows 1400 -> 1173; 8 rows 725 -> 730 (not used there).
+// 919 -> 835, 64 rows 1007 -> 965, 128 rows 1400 -> 1173 (8 rows 725 -> 730; rd_stream_kernel takes 627).
 template <typename T, int MT, int EPI>
 bool launch_head_rows(const LinArgs<T> &a, hipStream_t stream, int *status)
 {
     if constexpr (MT >= 1 && EPI == EPI_HEAD) {
         static const int on = rd::env_int("RD_DRAFT_HEAD_ROWS", 1);    // 0: the K-split kernel (for comparisons)
         if (!on || a.K2 != 0 || a.map1 != nullptr || a.K1 % kRowsKC != 0 || a.N < 128 * 128) return false;
-        if (a.M <= 8) return false;                                    // up to 8 rows the K-split kernel is as fast or faster
+        if (a.M <= 8) return false;                                    // up to 8 rows the kernels that split K are faster
         constexpr size_t smem = 2 * (size_t)MT * 16 * kRowsStride;
         static std::atomic<unsigned long long> conf_t{0}, conf_r{0};
         const void *fn = a.tiled ? reinterpret_cast<const void *>(&rd_head_rows_kernel<T, MT, true>)
