@@ -76,6 +76,7 @@ struct LinArgs {
     int ldy;
     // rd_gemm_kernel: K split over workgroups
     int ksplit;                        // splits per column group
+    int cols;                          // rd_gemm_kernel: column tiles of a workgroup
     float *kpart;                      // partial tiles [group][split][tile][64 lanes] x 4 floats
 };
 
@@ -508,9 +509,10 @@ template <int RT, int CT> constexpr int gemm_w_buffers()                        
 {
     return RT == 4 ? 8 : (160 - gemm_x_buffers<RT>() * RT) / CT < 12 ? (160 - gemm_x_buffers<RT>() * RT) / CT : 12;
 }
+template <int RT, int CT> constexpr bool gemm_trims() { return CT == 16 && RT < 16; }       // may have 13 to 15 column tiles (TRIM)
 template <int RT, int CT> constexpr size_t gemm_lds() { return (size_t)(gemm_x_buffers<RT>() * RT + gemm_w_buffers<RT, CT>() * CT) * 1024; }
 
-template <typename T, int RT, int CT, int WR, int WC, int EPI, bool TILED>
+template <typename T, int RT, int CT, int WR, int WC, int EPI, bool TILED, bool TRIM>
 __global__ __launch_bounds__(WR * WC * 64, 1) void rd_gemm_kernel(LinArgs<T> a)
 {
     typedef typename Elem16<T>::vec8 vec8;
@@ -525,11 +527,12 @@ __global__ __launch_bounds__(WR * WC * 64, 1) void rd_gemm_kernel(LinArgs<T> a)
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int r16 = lane & 15, g = lane >> 4;
-    const int groups = (a.N + 16 * CT - 1) / (16 * CT);
+    const int cols = TRIM ? a.cols : CT;                                // column tiles of the CT that are there; the others' products are ignored
+    const int groups = (a.N + 16 * cols - 1) / (16 * cols);
     const int unit = (int)(blockIdx.x & 7) * ((int)gridDim.x >> 3) + (int)(blockIdx.x >> 3);
     if (unit >= groups * a.ksplit) return;
     const int split = unit / groups, group = unit - split * groups;
-    const int n0 = group * (16 * CT);
+    const int n0 = group * (16 * cols);
 
     // this workgroup's k-steps: [kb, ke) of those of the first product and, behind them, of the second
     const int ks1 = a.K1 >> 5, ks = ks1 + (a.K2 >> 5);
@@ -545,6 +548,7 @@ __global__ __launch_bounds__(WR * WC * 64, 1) void rd_gemm_kernel(LinArgs<T> a)
     // wait for its newest weights whenever it waits for activations.)  Rows are copied four lanes to a row (64 bytes of it);
     // the 16-byte pieces of a row are swizzled so that the 16 rows of an operand read lie in distinct banks.
     const bool is_x = wave < 4;
+    const bool whole = !TRIM || (wave & 3) + 4 * (PW - 1) < cols;       // else one piece of the weights fewer
     const int wq = wave & 3, prow = lane >> 2, pch = (lane & 3) ^ (prow >> 2);
     uintptr_t row_at1[PX], row_at2[PX];         // activations: a lane's row in either product
     uint32_t woff[PW];
@@ -591,6 +595,7 @@ __global__ __launch_bounds__(WR * WC * 64, 1) void rd_gemm_kernel(LinArgs<T> a)
         const uint32_t dst = lds0 + (NX * RT + (uint32_t)(s % NW) * CT + wq) * 1024;
 #pragma unroll
         for (int i = 0; i < PW; ++i) {
+            if (i == PW - 1 && !whole) break;
             if (TILED) rd::dma16(wb + ((size_t)wtile[i] * (K >> 5) + k1) * 1024, woff[i], dst + 4 * i * 1024);
             else rd::dma16(wb + ((size_t)n0 * K + (size_t)k1 * 32) * 2, woff[i] * (uint32_t)K * 2 + pch * 16, dst + 4 * i * 1024);
         }
@@ -623,8 +628,9 @@ __global__ __launch_bounds__(WR * WC * 64, 1) void rd_gemm_kernel(LinArgs<T> a)
             if (r + RX - 3 < rounds) rd::wait_vm<(RX - 3) * KU * PX>();
             else rd::wait_vm<0>();
         } else {
-            if (r + RW - 3 < rounds) rd::wait_vm<(RW - 3) * KU * PW>();
-            else rd::wait_vm<0>();
+            if (r + RW - 3 >= rounds) rd::wait_vm<0>();
+            else if (whole) rd::wait_vm<(RW - 3) * KU * PW>();
+            else rd::wait_vm<(RW - 3) * KU * (PW - 1)>();
         }
         rd_lds_barrier();
     };
@@ -670,7 +676,7 @@ __global__ __launch_bounds__(WR * WC * 64, 1) void rd_gemm_kernel(LinArgs<T> a)
         for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
             for (int nt = 0; nt < NT; ++nt)
-                linear_epilogue<T, EPI>(a, acc[mt][nt], (wr * MT + mt) * 16, n0 + (wc * NT + nt) * 16, r16, g);
+                if (wc * NT + nt < cols) linear_epilogue<T, EPI>(a, acc[mt][nt], (wr * MT + mt) * 16, n0 + (wc * NT + nt) * 16, r16, g);
         return;
     }
     // tiles numbered as an RT x CT grid
@@ -679,22 +685,23 @@ __global__ __launch_bounds__(WR * WC * 64, 1) void rd_gemm_kernel(LinArgs<T> a)
     for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
         for (int nt = 0; nt < NT; ++nt)
-            if ((wr * MT + mt) * 16 < a.M) *reinterpret_cast<f32x4 *>(out + ((wr * MT + mt) * CT + wc * NT + nt) * 256) = acc[mt][nt];
+            if ((wr * MT + mt) * 16 < a.M && wc * NT + nt < cols) *reinterpret_cast<f32x4 *>(out + ((wr * MT + mt) * CT + wc * NT + nt) * 256) = acc[mt][nt];
 }
 
 // Adds the partial tiles of rd_gemm_kernel in split order and finishes the layer, a wave per tile.  Short layers are bound by
 // their round trips: the arguments are fetched together, skip input and bias beside the partial sums.
-template <typename T, int RT, int CT, int EPI>
+template <typename T, int RT, int CT, int EPI, bool TRIM>
 __global__ __launch_bounds__(256) void rd_linear_finish_kernel(LinArgs<T> a)
 {
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    asm volatile("" : : "s"(a.kpart), "s"(a.ksplit), "s"(a.M), "s"(a.N), "s"(a.m0), "s"(a.mstride), "s"(a.bias), "s"(a.res), "s"(a.ldy),
+    asm volatile("" : : "s"(a.kpart), "s"(a.ksplit), "s"(a.cols), "s"(a.M), "s"(a.N), "s"(a.m0), "s"(a.mstride), "s"(a.bias), "s"(a.res), "s"(a.ldy),
                  "s"(a.y_f32), "s"(a.y_bf), "s"(a.s_bf));
     const int nts = (a.N + 15) / 16, id = blockIdx.x * 4 + wave;
     const int mt = id / nts, n_tile = id - mt * nts;
     if (mt * 16 >= a.M) return;
     const EpilogueIn in = linear_epilogue_in<T, EPI>(a, mt * 16, n_tile * 16, lane & 15, lane >> 4);
-    const float *src = a.kpart + (((size_t)(n_tile / CT) * a.ksplit * RT + mt) * CT + n_tile % CT) * 256 + lane * 4;
+    const int cols = TRIM ? a.cols : CT, group = n_tile / cols;
+    const float *src = a.kpart + (((size_t)group * a.ksplit * RT + mt) * CT + (n_tile - group * cols)) * 256 + lane * 4;
     f32x4 v = {0.f, 0.f, 0.f, 0.f};
     for (int s0 = 0; s0 < a.ksplit; s0 += 8) {
         f32x4 p[8];
@@ -1626,24 +1633,59 @@ int launch_linear_nt(const LinArgs<T> &a, hipStream_t stream)
 
 // K split over as many workgroups per column group as bring the launch to about one per compute unit, with eight k-steps each
 // at least.
-template <typename T, int RT, int CT, int WR, int WC, int EPI>
-int launch_gemm(LinArgs<T> a, hipStream_t stream)
+int gemm_splits(int groups, int ks)
 {
-    const int groups = (a.N + 16 * CT - 1) / (16 * CT), ks = (a.K1 + a.K2) / 32;
-    a.ksplit = groups < kSplitMaxWgs ? kSplitMaxWgs / groups : 1;
-    if (a.ksplit > ks / 8) a.ksplit = ks >= 8 ? ks / 8 : 1;
+    const int splits = groups < kSplitMaxWgs ? kSplitMaxWgs / groups : 1, most = ks >= 8 ? ks / 8 : 1;
+    return splits < most ? splits : most;
+}
+
+// Column tiles of a workgroup, up to 128 rows: 16, or as few as 13 where they split into more workgroups of the chip's 256, so that the
+// tiles that one of them copies, k-steps times rows and columns, are fewer by a twelfth.  A workgroup computes 16 all the same, the matrix
+// cores are not the bound.  13312 columns, K = 13312: 64 groups of 13 in four splits instead of 52 of 16 (256 workgroups instead of 208).
+// us per call by 16 / so: hidden size 6656, 64 rows 1380 / 1368, 72 1504 / 1484, 96 1572 / 1542, 128 1682 / 1651, row-major 72 rows, 8000
+// tokens 1140 / 1080; 7168, 64 rows 1581 / 1569; 5632, 72 rows 1217 / 1208; 8256, 64 rows 2023 / 1990.  Short walks gain nothing
+// (72 rows, 1536 348 / 355), and where 16 are used they are a constant (as an argument 768, 72 rows take 1 % longer).
+int gemm_columns(int rt, int N, int ks)
+{
+    int best = 16, least = 0;
+    for (int cols = 16; cols >= 13; --cols) {
+        const int groups = (N + 16 * cols - 1) / (16 * cols), splits = gemm_splits(groups, ks), steps = (ks + splits - 1) / splits;
+        if (groups > kSplitMaxWgs || steps < 32) break;
+        const int copied = steps * (rt + cols);
+        if (cols == 16) least = copied - copied / 12;
+        else if (copied < least || (best == 16 && copied == least)) { best = cols; least = copied; }
+    }
+    return best;
+}
+
+template <typename T, int RT, int CT, int WR, int WC, int EPI, bool TRIM>
+int launch_gemm_cols(LinArgs<T> a, int cols, hipStream_t stream)
+{
+    const int groups = (a.N + 16 * cols - 1) / (16 * cols);
+    a.cols = cols;
+    a.ksplit = gemm_splits(groups, (a.K1 + a.K2) / 32);
     constexpr size_t smem = gemm_lds<RT, CT>();
     static std::atomic<unsigned long long> conf_t{0}, conf_r{0};
-    const void *fn = a.tiled ? reinterpret_cast<const void *>(&rd_gemm_kernel<T, RT, CT, WR, WC, EPI, true>)
-                             : reinterpret_cast<const void *>(&rd_gemm_kernel<T, RT, CT, WR, WC, EPI, false>);
+    const void *fn = a.tiled ? reinterpret_cast<const void *>(&rd_gemm_kernel<T, RT, CT, WR, WC, EPI, true, TRIM>)
+                             : reinterpret_cast<const void *>(&rd_gemm_kernel<T, RT, CT, WR, WC, EPI, false, TRIM>);
     if (rd::ensure_dynamic_lds(fn, smem, a.tiled ? conf_t : conf_r) != RD_OK) return RD_ERR_HIP;
     const dim3 grid((groups * a.ksplit + 7) / 8 * 8);
-    if (a.tiled) hipLaunchKernelGGL((rd_gemm_kernel<T, RT, CT, WR, WC, EPI, true>), grid, dim3(WR * WC * 64), smem, stream, a);
-    else hipLaunchKernelGGL((rd_gemm_kernel<T, RT, CT, WR, WC, EPI, false>), grid, dim3(WR * WC * 64), smem, stream, a);
+    if (a.tiled) hipLaunchKernelGGL((rd_gemm_kernel<T, RT, CT, WR, WC, EPI, true, TRIM>), grid, dim3(WR * WC * 64), smem, stream, a);
+    else hipLaunchKernelGGL((rd_gemm_kernel<T, RT, CT, WR, WC, EPI, false, TRIM>), grid, dim3(WR * WC * 64), smem, stream, a);
     if (a.ksplit == 1) return rd_check_launch();
     const int tiles = (a.M + 15) / 16 * ((a.N + 15) / 16);
-    hipLaunchKernelGGL((rd_linear_finish_kernel<T, RT, CT, EPI>), dim3((tiles + 3) / 4), dim3(256), 0, stream, a);
+    hipLaunchKernelGGL((rd_linear_finish_kernel<T, RT, CT, EPI, TRIM>), dim3((tiles + 3) / 4), dim3(256), 0, stream, a);
     return rd_check_launch();
+}
+
+template <typename T, int RT, int CT, int WR, int WC, int EPI>
+int launch_gemm(const LinArgs<T> &a, hipStream_t stream)
+{
+    if constexpr (gemm_trims<RT, CT>()) {
+        const int cols = gemm_columns(RT, a.N, (a.K1 + a.K2) / 32);
+        if (cols < CT) return launch_gemm_cols<T, RT, CT, WR, WC, EPI, true>(a, cols, stream);
+    }
+    return launch_gemm_cols<T, RT, CT, WR, WC, EPI, false>(a, CT, stream);
 }
 
 // The output layer at 9 rows and more per launch, wide enough to cover half the chip with 128-column
